@@ -1,132 +1,269 @@
-// Plain fp32 attention over the paged pool: one 64-lane wave per (query token, query head) row.
+// fp32 attention over the paged pool on the fp32 matrix instruction (head_dim 64 or 128), for gfx950.
 //
-// This is the fp32 path of the library (small correctness configurations, head_dim 64 or 128).
-// It follows the same definition as the MFMA kernel -- causal over absolute positions for the
-// prefix-cached prefill (Section 3.3 / Appendix B.7 of the paper), unmasked for cross-attention
-// (Section 2.1) -- with an online softmax over chunks of 64 keys: lanes own keys for the score
-// phase and channels for the value phase.  It is latency bound and makes no roofline claim.
+// This is the fp32 path of the library (small correctness configurations and fp32 models of small heads).
+// It follows the same definition as the bf16 kernels -- causal over absolute positions for the prefix-cached
+// prefill (Section 3.3 / Appendix B.7 of the paper), unmasked for cross-attention (Section 2.1).
+//
+// What bounds it: such calls are small (a few hundred rows, up to a few thousand keys), so it is the chain of
+// memory and instruction latencies from the launch to the last store, not a rate.  The work is therefore cut
+// finely: a workgroup takes 16 query rows of one (request, KV head) -- row j * G + g is head g of new token j, so
+// the heads that share a KV head are neighbours -- and its 8 waves take the keys in turn, 16 at a time (16 keys
+// lie in one page, so a chunk's K and V are one contiguous run each and its page a scalar).  Every wave keeps
+// its own online softmax; the eight results are combined through LDS.  There is no LDS in the loop: K and
+// V go straight to registers, the next chunk's K and this chunk's V while this chunk's scores are computed.
+//
+// v_mfma_f32_16x16x4_f32 takes one A and one B value per lane (row or column lane % 16, k = lane / 16 =: g) and
+// returns column lane % 16, rows 4 g .. 4 g + 3.  The sums over k may run in any order, so the operands are laid
+// out for the loads:
+//   S^T = K Q^T   lane (key i, g) reads 16-byte pieces 16 j + 4 g of row i, j = 0, 1, ...; Q likewise.  A lane then
+//                 holds the scores of row lane % 16 with keys 4 g .. 4 g + 3: the row maximum is two lane exchanges.
+//   O^T += V^T P^T  step v takes key 4 g + v from lane group g, which is where that weight already is; as the A
+//                 operand lane i stands for channels 4 i .. 4 i + 3 of the four products of a 64-channel block, so V
+//                 rows are read whole, 16 bytes per lane, and a lane ends up with 16 consecutive channels of its row.
+// Measured, scatter and attention per step, against one wave per row with lanes owning keys (no matrix instruction):
+// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 14.7 us (what two launches cost the host); the same
+// heads, 4 x (1024 + 256) tokens 254 -> 26 us; 8 heads on 2 of 128, 4096 new tokens 5.59 -> 0.44 ms (78 TFLOP/s of the
+// 154 that a large fp32 matrix product reaches).  Relative error against 64 bits 4.2e-7 -> 3.0e-7 on the first.
 #include "emm_internal.h"
 
 namespace emm {
 
 namespace {
 
-__device__ inline float wave_max(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ inline float wave_sum(float x)
+constexpr int ROWS = 16;                              // query rows per workgroup
+constexpr int KEYS = 16;                              // keys per chunk; a page holds a whole number of chunks
+constexpr int NW = 8;                                 // waves per workgroup
+
+// max or sum of a value over the four lanes that share lane % 16
+__device__ inline float group_max(float x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
+    uint32_t u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    const auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+__device__ inline float group_sum(float x)
+{
+    uint32_t u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+    const auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+__device__ inline bool is_finite(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
+
+// First row-tile slot of request r: its ceil(rows / 16) tiles fit between this and the next request's, whatever
+// cu_new_lens[r] is, so the grid needs no more than T G / 16 + B slots and no prefix sums over row tiles.
+__device__ inline long long first_slot(const BatchView& b, int G, int r)
+{
+    return (long long)max(b.cu_new_lens[r], 0) * G / ROWS + r;
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a)
+__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
 {
-    constexpr int CPL = D / 64;                       // channels per lane in the value phase
+    constexpr int QK = D / 16;                        // 16-byte pieces of a Q or K row per lane
+    constexpr int NB = D / 64;                        // 64-channel blocks of V
+    constexpr int STRIDE = D + 4;                     // floats between rows of the LDS records: spreads the banks
+    __shared__ __attribute__((aligned(16))) float o_s[NW][ROWS][STRIDE];
+    __shared__ float m_s[NW][ROWS], l_s[NW][ROWS];
     const BatchView& b = a.b;
-    const int lane = threadIdx.x & 63;
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= (long long)b.total_new_tokens * b.num_q_heads) return;   // no block barrier below
-    const int t = (int)(row / b.num_q_heads);
-    const int h = (int)(row - (long long)t * b.num_q_heads);
-    const int kvh = h / (b.num_q_heads / b.num_kv_heads);
+    const int G = b.num_q_heads / b.num_kv_heads;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kvh = blockIdx.x % b.num_kv_heads;
+    const int slot = blockIdx.x / b.num_kv_heads;
 
-    int lo = 0, hi = b.num_reqs;
+    int lo = 0, hi = b.num_reqs;                      // the request of this slot: the last one that starts at or before it
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (b.cu_new_lens[mid] <= t) lo = mid; else hi = mid;
+        if (first_slot(b, G, mid) <= slot) lo = mid; else hi = mid;
     }
     const int r = lo;
-    const int j = t - b.cu_new_lens[r];
-    const int P = b.prefix_lens[r];
-    // (forced into what the page-table row can hold, whatever the arrays say: no access leaves the caller's buffers)
-    const int len = (int)min(max(a.causal ? (long long)P + j + 1 : (long long)P, 0ll), (long long)b.max_pages * b.page_size);
-
-    const float* __restrict__ q = (const float*)a.q + ((long long)t * b.num_q_heads + h) * D;
-    const float* __restrict__ kc = (const float*)a.k_cache;
-    const float* __restrict__ vc = (const float*)a.v_cache;
-    const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
-
+    // the pages of this wave's first 64 chunks, one per lane, asked for before the lengths are known (entries past the
+    // request's pages are not used)
     const int pg_log2 = 4 + b.page_shift, ps = b.page_size;
-    float m = -INFINITY, l = 0.f;
-    float acc[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+    const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
+    auto pages_from = [&](int i0) -> int {            // of chunks wave + NW * (i0 + lane)
+        const long long key = ((long long)wave + (long long)NW * (i0 + lane)) * KEYS;
+        return pt[min(key >> pg_log2, (long long)b.max_pages - 1)];
+    };
+    int pages = pages_from(0);
 
-    for (int base = 0; base < len; base += 64) {
-        const int i = base + lane;
-        float s = -INFINITY;
-        int my_page = 0;                                 // page of key base + lane; the value phase gets it by shuffle
-        if (i < len) {
-            const long long page = my_page = min(max(pt[i >> pg_log2], 0), b.num_pages - 1);
-            const float4* k4 = (const float4*)(kc + ((page * b.num_kv_heads + kvh) * ps + (i & (ps - 1))) * D);
-            const float4* q4 = (const float4*)q;
-            float dot = 0.f;
-#pragma unroll 16
-            for (int c = 0; c < D / 4; ++c) {
-                const float4 kv = k4[c], qv = q4[c];
-                dot = fmaf(qv.x, kv.x, dot);
-                dot = fmaf(qv.y, kv.y, dot);
-                dot = fmaf(qv.z, kv.z, dot);
-                dot = fmaf(qv.w, kv.w, dot);
-            }
-            s = dot * b.softmax_scale;
+    // (lengths forced into what the page table and the packed tensors can hold: see safe_new_len)
+    const int N = safe_new_len(b, r, a.causal != 0);
+    const int n_rows = N * G;
+    const long long row0_wide = ((long long)slot - first_slot(b, G, r)) * ROWS;
+    if (row0_wide < 0 || row0_wide >= n_rows) return;                       // uniform over the workgroup
+    const int row0 = (int)row0_wide;
+    const int P = safe_prefix_len(b, r, a.causal ? N : 0);
+    const int kv_len = a.causal ? P + min(row0 + ROWS - 1, n_rows - 1) / G + 1 : P;   // keys that some row here sees
+    const int n_chunks = (kv_len + KEYS - 1) / KEYS;
+    const int min_limit = a.causal ? P + row0 / G : P - 1;                  // last key that every row here sees
+    const int row = min(row0 + l16, n_rows - 1);
+    const int tok = row / G;
+    const int limit = a.causal ? P + tok : P - 1;                           // last key of this lane's row
+    const long long first_row = safe_first_row(b, r, N);
+
+    const float* __restrict__ qp = (const float*)a.q + ((first_row + tok) * b.num_q_heads + kvh * G + (row - tok * G)) * D + 4 * g;
+    f32x4 q[QK];
+#pragma unroll
+    for (int j = 0; j < QK; ++j) q[j] = *(const f32x4*)(qp + 16 * j);
+
+    float m = -INFINITY, l = 0.f;                     // l: this lane's keys only, until the end
+    f32x4 o[4 * NB];
+#pragma unroll
+    for (int i = 0; i < 4 * NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    int page_i0 = 0;
+    auto chunk_base = [&](int i) -> long long {       // element offset of the KV head's 16 rows of chunk wave + NW i
+        if (i - page_i0 >= 64) {
+            page_i0 = i;
+            pages = pages_from(i);
         }
-        const float m_new = fmaxf(m, wave_max(s));       // finite: key `base` is always attended
-        const float p = (i < len) ? expf(s - m_new) : 0.f;
-        const float alpha = expf(m - m_new);              // 0 on the first chunk (m = -inf)
-        l = l * alpha + wave_sum(p);
+        const int page = min(max(__builtin_amdgcn_readlane(pages, i - page_i0), 0), b.num_pages - 1);
+        const int off = ((wave + NW * i) * KEYS) & (ps - 1);
+        return (((long long)page * b.num_kv_heads + kvh) * ps + off) * D;
+    };
+    f32x4 k[2][QK], v[4][NB];
+    auto load_k = [&](long long at, f32x4 (&kk)[QK]) {
+        const float* kp = (const float*)a.k_cache + at + l16 * D + 4 * g;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= alpha;
-        const int n_here = min(64, len - base);
-        // sixteen keys at a time: their V rows are all requested before the first is used (the page of key
-        // base + kk comes from lane kk by shuffle, so no load sits in the chain that leads to a row's address);
-        // keys past the chunk's end repeat its last key with weight 0
-        constexpr int GROUP = 16;
-        for (int kk0 = 0; kk0 < n_here; kk0 += GROUP) {
-            float pk[GROUP], vv[GROUP][CPL];
+        for (int j = 0; j < QK; ++j) kk[j] = *(const f32x4*)(kp + 16 * j);
+    };
+    auto load_v = [&](long long at) {
+        const float* vp = (const float*)a.v_cache + at + 4 * g * D + 4 * l16;
 #pragma unroll
-            for (int u = 0; u < GROUP; ++u) {
-                const int kk = min(kk0 + u, n_here - 1);
-                pk[u] = kk0 + u < n_here ? __shfl(p, kk) : 0.f;
-                const long long page = __shfl(my_page, kk);
-                const float* v = vc + ((page * b.num_kv_heads + kvh) * ps + ((base + kk) & (ps - 1))) * D;
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) vv[u][c] = v[lane + 64 * c];
-            }
+            for (int n = 0; n < NB; ++n) v[u][n] = *(const f32x4*)(vp + u * D + 64 * n);
+    };
+    auto compute = [&](int c, long long at, const f32x4 (&kk)[QK]) {
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < GROUP; ++u)
+        for (int j = 0; j < QK; ++j)
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = fmaf(pk[u], vv[u][c], acc[c]);
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[j][e], q[j][e], s, 0, 0, 0);
+        const bool masked = c * KEYS + KEYS - 1 > min_limit;                // some row does not see some key
+        float x[4], p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = s[u] * b.softmax_scale;
+            if (masked && c * KEYS + 4 * g + u > limit) x[u] = -INFINITY;
         }
+        const float m_new = fmaxf(m, group_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))));
+        const float ref = m_new == -INFINITY ? 0.f : m_new;                 // a row that sees none of the keys so far
+        const float alpha = expf(m - ref);                                  // 0 on the first visible chunk (m = -inf)
         m = m_new;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u] = expf(x[u] - ref);
+        l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+        for (int i = 0; i < 4 * NB; ++i) o[i] *= alpha;
+        if (masked) {
+            // keys past the tile's last are no tokens: whatever their slots hold must not count.  A key that some rows
+            // see and others do not may hold an infinity or NaN, which a weight of 0 would not remove: such a chunk
+            // is done key by key with what each row sees.
+            bool odd = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    if (c * KEYS + 4 * g + u >= kv_len) v[u][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd = odd || !is_finite(v[u][n][e]);
+                }
+            if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+                for (int kk2 = 0; kk2 < KEYS && c * KEYS + kk2 < kv_len; ++kk2) {
+                    const int u = kk2 & 3;
+                    const float mine = u == 0 ? p[0] : u == 1 ? p[1] : u == 2 ? p[2] : p[3];
+                    const float pk = __shfl(mine, l16 + 16 * (kk2 >> 2));
+                    const float* vp = (const float*)a.v_cache + at + (long long)kk2 * D + 16 * g;
+                    if (c * KEYS + kk2 <= limit)
+#pragma unroll
+                        for (int n = 0; n < NB; ++n)
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) {
+                                const f32x4 w = *(const f32x4*)(vp + 64 * n + 4 * t);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) o[4 * n + e][t] = fmaf(pk, w[e], o[4 * n + e][t]);
+                            }
+                }
+                return;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[4 * n + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][n][e], p[u], o[4 * n + e], 0, 0, 0);
+    };
+    const int n_mine = n_chunks > wave ? (n_chunks - wave + NW - 1) / NW : 0;    // chunks wave, wave + NW, ...
+    if (n_mine > 0) {
+        // this chunk's V and the next one's K are on their way while this chunk's scores are computed
+        long long at = chunk_base(0);
+        load_k(at, k[0]);
+        for (int i = 0; i < n_mine; i += 2) {
+            load_v(at);
+            const long long at1 = i + 1 < n_mine ? chunk_base(i + 1) : at;
+            load_k(at1, k[1]);
+            compute(wave + NW * i, at, k[0]);
+            if (i + 1 >= n_mine) break;
+            load_v(at1);
+            at = i + 2 < n_mine ? chunk_base(i + 2) : at1;
+            load_k(at, k[0]);
+            compute(wave + NW * (i + 1), at1, k[1]);
+        }
     }
 
-    float* __restrict__ o = (float*)a.out + ((long long)t * b.num_q_heads + h) * D;
-    const float inv = (l > 0.f) ? 1.f / l : 0.f;          // no keys (cross, empty cache): zero row
+    // ---- the eight waves' results: o[4 n + e][t] is channel 64 n + 16 g + 4 t + e of row l16
+    l = group_sum(l);
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) o[lane + 64 * c] = acc[c] * inv;
-    if (a.lse != nullptr && lane == 0)
-        a.lse[(long long)t * b.num_q_heads + h] = (l > 0.f) ? m + logf(l) : -INFINITY;
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            *(f32x4*)&o_s[wave][l16][64 * n + 16 * g + 4 * t] = f32x4{o[4 * n][t], o[4 * n + 1][t], o[4 * n + 2][t], o[4 * n + 3][t]};
+    if (g == 0) {
+        m_s[wave][l16] = m;
+        l_s[wave][l16] = l;
+    }
+    __syncthreads();
+    const int my = tid / (D / 4), c4 = tid % (D / 4) * 4;                   // 16 rows x D / 4 pieces: 256 or 512 threads
+    if (my >= ROWS || row0 + my >= n_rows) return;
+    float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, m_s[w][my]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float wgt = m_s[w][my] == -INFINITY ? 0.f : expf(m_s[w][my] - m_all);
+        l_all += wgt * l_s[w][my];
+        acc += wgt * *(const f32x4*)&o_s[w][my][c4];
+    }
+    const float inv = (l_all > 0.f) ? 1.f / l_all : 0.f;                    // no keys (cross, empty cache): zero row
+    const int o_row = row0 + my, o_tok = o_row / G;
+    const long long at = (first_row + o_tok) * b.num_q_heads + kvh * G + (o_row - o_tok * G);
+    *(f32x4*)((float*)a.out + at * D + c4) = acc * inv;
+    if (a.lse != nullptr && c4 == 0) a.lse[at] = (l_all > 0.f) ? m_all + logf(l_all) : -INFINITY;
 }
 
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream)
 {
-    const long long rows = (long long)a.b.total_new_tokens * a.b.num_q_heads;
-    if (rows == 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((rows + 3) / 4);
-    if (a.b.head_dim == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(blocks), dim3(256), 0, stream, a);
+    const BatchView& b = a.b;
+    if (b.total_new_tokens == 0 || b.num_reqs == 0) return hipSuccess;
+    const int G = b.num_q_heads / b.num_kv_heads;
+    const long long grid = ((long long)b.total_new_tokens * G / ROWS + b.num_reqs) * b.num_kv_heads;
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    if (b.head_dim == 64)
+        hipLaunchKernelGGL(attn_f32_kernel<64>, dim3((unsigned)grid), dim3(64 * NW), 0, stream, a);
     else
-        hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(blocks), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(attn_f32_kernel<128>, dim3((unsigned)grid), dim3(64 * NW), 0, stream, a);
     return hipGetLastError();
 }
 

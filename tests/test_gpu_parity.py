@@ -684,6 +684,42 @@ def test_scores_that_jump_between_tiles(name, kind, H, Hkv, prefix, new, planted
     assert B.DeviceWorkload.to_numpy_bits(dw.out).tobytes() == first
 
 
+# 16 rows and 16 keys per step, 8 waves taking the chunks in turn, 64 chunks per wave (8192 keys) between page-table reads
+F32_CASES = [
+    ("rows_and_keys_at_the_tile_edges", "causal", 4, 1, 64, 16, [0, 1, 15, 16, 17, 111, 112, 127, 128, 129], [1, 3, 4, 5, 8, 1, 16, 17, 33, 2]),
+    ("odd_group_wide_head", "causal", 6, 2, 128, 32, [33, 0, 70, 5], [17, 0, 5, 44]),
+    ("one_head_per_kv_head", "causal", 3, 3, 64, 64, [250, 0], [15, 49]),
+    ("more_heads_than_a_row_tile", "causal", 40, 2, 128, 16, [19, 0], [3, 40]),
+    ("more_than_8192_keys", "causal", 2, 1, 64, 256, [8190, 16500], [5, 2]),
+    ("cross_empty_and_ragged", "cross", 8, 2, 128, 16, [0, 1, 16, 17, 145], [3, 1, 16, 0, 9]),
+]
+
+
+@pytest.mark.parametrize("name,kind,H,Hkv,d,ps,prefix,new", F32_CASES)
+def test_f32_tile_edges(name, kind, H, Hkv, d, ps, prefix, new):
+    print("case f32", name, flush=True)
+    wl = W.build_workload("f32_" + name, kind, "f32", 720, num_q_heads=H, num_kv_heads=Hkv, head_dim=d, page_size=ps,
+                          prefix_lens=prefix, new_lens=new)
+    _compare(wl, _gpu_run(wl))
+
+
+@pytest.mark.parametrize("d,bad", [(64, np.nan), (64, np.inf), (128, np.nan)])
+def test_f32_rows_do_not_see_what_later_tokens_hold(d, bad):
+    """A value row of a later token that is no number must not reach the rows before it, which share its row tile."""
+    wl = W.build_workload("f32_later", "causal", "f32", 730, num_q_heads=4, num_kv_heads=1, head_dim=d, page_size=16,
+                          prefix_lens=[21], new_lens=[11])
+    wl.v_new[7, 0, 3] = bad
+    dw = _gpu_run(wl)
+    _, _, ref, lse_ref = oracle.run_workload(wl)
+    out = dw.out.cpu().numpy().astype(np.float64)
+    assert np.isfinite(ref[:7]).all() and np.abs(out[:7] - ref[:7]).max() <= F32_MAX_ABS
+    seen = np.zeros(d, dtype=bool)
+    seen[3] = True
+    assert not np.isfinite(out[7:][:, :, seen]).any()
+    assert np.abs(out[7:][:, :, ~seen] - ref[7:][:, :, ~seen]).max() <= F32_MAX_ABS
+    assert np.abs(dw.lse.cpu().numpy() - lse_ref).max() <= LSE_ABS
+
+
 def test_f32_head_dim_128_and_cross():
     print("case f32 d=128 causal + cross", flush=True)
     wl = W.build_workload("f32_128", "causal", "f32", 700, num_q_heads=6, num_kv_heads=2, head_dim=128,
