@@ -2,11 +2,14 @@
 // prefix (Section 2.2 of the paper: prefill yields the KV cache of every input token; the copy
 // must be exact in the sense of Appendix B.5).
 //
-// Pure data movement, HBM bound: 4 * T * Hkv * d * elt bytes (read K,V + write K,V).  One wave moves one
-// token: finding its request (a search over the batch's offsets) and its page is wave-uniform work done once
-// on the scalar unit, and the lanes move the token's K row and V row (all KV heads, Hkv * d * elt bytes each)
-// in 16-byte chunks.  The packed source [T][Hkv][d] is read fully coalesced; a (token, head) row of d*elt
-// bytes lands contiguously in its page.
+// Pure data movement: 4 * T * Hkv * d * elt bytes (read K,V + write K,V), HBM bound on a large batch and bound by its
+// chain of memory round trips on a small one.  One wave moves one token: the lanes move the token's K row and V row
+// (all KV heads, Hkv * d * elt bytes each) in 16-byte chunks.  The packed source [T][Hkv][d] is read fully
+// coalesced; a (token, head) row of d*elt bytes lands contiguously in its page.  The chain is three round trips long:
+// kernel arguments; the batch's offsets and lengths (64 of each at once, one per lane, the token's request found by a
+// ballot) together with the rows to be moved, whose place does not depend on them; the page id.
+// Measured against a binary search by scalar loads with the rows asked for last: 5.1 -> 3.9 us for 36 tokens, 48.4 ->
+// 46.2 us (6.4 TB/s) for 36336 tokens of 8 heads; a kernel that does nothing takes 1.7 us.
 #include "emm_internal.h"
 
 namespace emm {
@@ -25,29 +28,53 @@ __global__ __launch_bounds__(64 * WAVES) void kv_scatter_kernel(BatchView b, con
     if (t >= b.total_new_tokens) return;
     const int lane = threadIdx.x & 63;
 
-    // request that owns packed token t: last r with cu[r] <= t
+    // the token's rows, asked for before it is known where they go
+    const int token_chunks = b.num_kv_heads << row_shift;                 // chunks of the token's K (or V) row, all heads
+    const long long src = (long long)t * token_chunks;
+    constexpr int HELD = 2;                                               // chunks per lane and pool held in registers (8 heads of 128 bf16)
+    uint4 k_held[HELD], v_held[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+        const int c = min(lane + 64 * u, token_chunks - 1);               // past the row: its last chunk, which is not stored
+        k_held[u] = k_new[src + c];
+        v_held[u] = v_new[src + c];
+    }
+
+    // request that owns packed token t: last r with cu[r] <= t, among 64 that the lanes look at together
     int lo = 0, hi = b.num_reqs;
-    while (hi - lo > 1) {
+    while (hi - lo > 64) {
         const int mid = (lo + hi) >> 1;
         if (b.cu_new_lens[mid] <= t) lo = mid; else hi = mid;
     }
-    const int r = lo;
-    const long long pos64 = (long long)b.prefix_lens[r] + (t - b.cu_new_lens[r]);
+    const int mine = min(lo + lane, hi - 1);
+    const int cu_mine = b.cu_new_lens[mine], prefix_mine = b.prefix_lens[mine];
+    const unsigned long long not_after = __builtin_amdgcn_ballot_w64(lo + lane < hi && cu_mine <= t);
+    const int at = not_after == 0 ? 0 : 63 - __builtin_clzll(not_after);
+    const int r = lo + at;
+    const long long pos64 = (long long)__builtin_amdgcn_readlane(prefix_mine, at) + (t - __builtin_amdgcn_readlane(cu_mine, at));
     // inconsistent lengths or a corrupt table: drop the write, never stray
-    if (pos64 < 0 || pos64 >= (long long)b.max_pages * b.page_size) return;
-    const int pos = (int)pos64;
+    const int pos = (int)min(max(pos64, 0ll), (long long)b.max_pages * b.page_size - 1);
     const int page = b.page_table[(long long)r * b.max_pages + (pos >> (4 + b.page_shift))];
-    if (page < 0 || page >= b.num_pages) return;
+    // (the rows are waited for here, with the page id: left to itself the compiler asks for them where they are stored)
+#pragma unroll
+    for (int u = 0; u < HELD; ++u)
+        asm volatile("" ::"v"(k_held[u].x), "v"(k_held[u].y), "v"(k_held[u].z), "v"(k_held[u].w), "v"(v_held[u].x), "v"(v_held[u].y),
+                     "v"(v_held[u].z), "v"(v_held[u].w));
+    if (pos64 != pos || page < 0 || page >= b.num_pages) return;
 
-    const int token_chunks = b.num_kv_heads << row_shift;                 // chunks of the token's K (or V) row, all heads
-    const long long src = (long long)t * token_chunks;
     // chunk c of the token is chunk c % row of head c / row; heads are page_size rows apart in the pool
     const long long dst = ((long long)page * b.num_kv_heads * b.page_size + (pos & (b.page_size - 1))) << row_shift;
     const int head_stride = (b.page_size - 1) << row_shift;               // extra chunks between consecutive heads
-    for (int c = lane; c < token_chunks; c += 64) {
-        const long long d = dst + c + (long long)(c >> row_shift) * head_stride;
-        k_cache[d] = k_new[src + c];
-        v_cache[d] = v_new[src + c];
+    auto place = [&](int c) -> long long { return dst + c + (long long)(c >> row_shift) * head_stride; };
+#pragma unroll
+    for (int u = 0; u < HELD; ++u)
+        if (lane + 64 * u < token_chunks) {
+            k_cache[place(lane + 64 * u)] = k_held[u];
+            v_cache[place(lane + 64 * u)] = v_held[u];
+        }
+    for (int c = lane + 64 * HELD; c < token_chunks; c += 64) {
+        k_cache[place(c)] = k_new[src + c];
+        v_cache[place(c)] = v_new[src + c];
     }
 }
 

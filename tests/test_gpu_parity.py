@@ -753,6 +753,22 @@ def test_garbage_in_unused_slots_is_ignored():
     assert B.DeviceWorkload.to_numpy_bits(_gpu_run(wl3).out).tobytes() == ref.tobytes()
 
 
+@pytest.mark.parametrize("B_,Hkv,d,dtype", [(63, 1, 128, "bf16"), (64, 9, 128, "f32"), (65, 16, 128, "bf16"), (200, 3, 64, "f32")])
+def test_scatter_many_requests_and_heads(B_, Hkv, d, dtype):
+    """More requests than a wave looks at together, more chunks per token than a lane holds, requests without new tokens."""
+    rng = np.random.default_rng(B_)
+    new = [int(x) for x in rng.integers(0, 4, size=B_)]
+    new[0], new[-1] = 0, 1
+    wl = W.build_workload("scatter_many", "causal", dtype, 740 + B_, num_q_heads=Hkv, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                          prefix_lens=[int(x) for x in rng.integers(0, 40, size=B_)], new_lens=new)
+    dw = B.DeviceWorkload(wl)
+    dw.scatter()
+    torch.cuda.synchronize()
+    kc, vc = oracle.kv_scatter(wl.page_table, wl.prefix_lens, wl.new_lens, wl.cu_new_lens, wl.k_new, wl.v_new, wl.k_cache, wl.v_cache)
+    assert B.DeviceWorkload.to_numpy_bits(dw.k_cache).tobytes() == kc.tobytes()
+    assert B.DeviceWorkload.to_numpy_bits(dw.v_cache).tobytes() == vc.tobytes()
+
+
 def test_scatter_bit_exact_with_arbitrary_bit_patterns():
     """The scatter moves bytes: NaN payloads, denormals and negative zeros survive unchanged."""
     print("case scatter bit patterns", flush=True)
