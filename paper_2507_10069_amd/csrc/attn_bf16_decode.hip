@@ -369,117 +369,119 @@ __global__ __launch_bounds__(NT, 3) void attn_bf16_decode_kernel(AttnArgs a, Dec
     }
 }
 
-// merge 2: one workgroup per (pair, query row), thread = (piece number mod 8, channel); pairs with a single
-// piece were finished by the main kernel.  Few workgroups, so what counts is the length of the chain of
-// memory round trips: every piece's (m, l) is loaded once, by its own thread, the weights of a chunk of pieces
-// go through LDS, and the loop over the records has nothing but independent loads in it.  GROUPS threads share
-// a channel: 8 when a row has many pieces (a single long context: 6.8 -> 4.8 us for 129 pieces), 2 when it has
-// few (a big batch, where 1024-thread workgroups would only crowd the chip).
-constexpr int MANY_PIECES = 48;
+// merge 2: one workgroup per (pair, query row); wave w takes pieces w, w + WAVES, ..., a lane two channels of each.
+// The kernel is a few microseconds long and bound by its chain of memory round trips, so there is one: every wave
+// asks for its first LOADS pieces (a record's 128 values and its m, l) before it knows how many the context has --
+// the workspace holds S.pieces_max of them whatever the lengths are -- and drops what turns out not to be a piece.  A
+// wave holds the m of all its pieces itself, so weights need no exchange; the waves meet in LDS once.
+// Measured against lengths first, then all (m, l), then the values, with two barriers: 4.7 -> 3.1 us for the 12 pieces of
+// one request of 1500 tokens, 6.3 -> 5.1 us for 64 requests of 3 pieces (behind a kernel that streams 1 GB).
+// 16 waves when a row has many pieces (a single long context), 4 when it has few (a big batch, where 1024-thread
+// workgroups would only crowd the chip).
+constexpr int MANY_PIECES = 32;
+constexpr int LOADS = 8;                                     // pieces of a wave in flight at a time
 
-__device__ inline float wave_max64(float x)
+template <bool CAUSAL, bool SHARED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-__device__ inline float wave_sum64(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-template <bool CAUSAL, bool SHARED, int MERGE_GROUPS>
-__global__ __launch_bounds__(MERGE_GROUPS * D) void attn_bf16_decode_merge_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
-{
-    constexpr int MERGE_THREADS = MERGE_GROUPS * D;
-    __shared__ float w_s[MERGE_THREADS], part_s[MERGE_THREADS / 64], acc_s[MERGE_GROUPS][D];
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    __shared__ f32x2 acc_s[WAVES][D / 2], ml_s[WAVES];
     const BatchView& b = a.b;
-    const int G = b.num_q_heads / b.num_kv_heads;
-    const int pair = blockIdx.x / G, row = blockIdx.x % G;
-    const int kvh = pair % b.num_kv_heads;
-    const int r = pair / b.num_kv_heads;
-    if (b.new_lens[r] <= 0) return;
-    const int P = safe_prefix_len(b, r, CAUSAL ? 1 : 0);
+    const int G = gridDim.z, row = blockIdx.z, kvh = blockIdx.y, r = blockIdx.x;
+    const int pair = r * b.num_kv_heads + kvh;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float* __restrict__ rec_own = (const float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G + row) * REC_FLOATS;
+
+    // pieces j0 + wave, j0 + wave + WAVES, ... of a list of records, `stride` floats apart, that holds `room` of them
+    f32x2 val[LOADS], ml[LOADS];
+    auto ask = [&](const float* __restrict__ rec, size_t stride, int j0, int room) {
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            const float* __restrict__ src = rec + (size_t)min(j0 + wave + u * WAVES, room - 1) * stride;
+            val[u] = *(const f32x2*)(src + 2 * lane);
+            ml[u] = *(const f32x2*)(src + D);
+        }
+    };
+    const int n_new = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
+    const int req_unit = SHARED ? sv.req_unit[r] : -1, req_shared = SHARED ? sv.req_shared_len[r] : 0;
+    ask(rec_own, MAX_G * REC_FLOATS, 0, S.pieces_max);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::"s"(n_new), "s"(cu_new));              // needed at the end only, but asked for here
+
+    const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
     // the records of this row: n_own from the request's own workgroups, then n_unit from its unit's
     // (counts and positions forced into what the workspace holds, whatever the device arrays say)
-    const int unit = SHARED ? min(max(sv.req_unit[r], -1), sv.num_units - 1) : -1;
-    const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(sv.req_shared_len[r], 0) / BK : 0, S.tiles_per_piece, unit >= 0),
+    const int unit = SHARED ? min(max(req_unit, -1), sv.num_units - 1) : -1;
+    const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(req_shared, 0) / BK : 0, S.tiles_per_piece, unit >= 0),
                           S.pieces_max);
-    if (unit < 0 && n_own == 1) return;
-    int n_unit = 0;
-    const float* __restrict__ rec_unit = nullptr;
-    if (unit >= 0) {
-        const int shared_len = (int)min((long long)max(sv.unit_shared_len[unit], 0), (long long)b.max_pages * b.page_size) / BK * BK;
-        n_unit = min((shared_len / BK + S.tiles_per_piece - 1) / S.tiles_per_piece, S.pieces_unit);
-        const int member = min(max(r - sv.unit_first_req[unit], 0), MAX_ROWS / G - 1);       // position of the request in its unit
-        rec_unit = (const float*)a.workspace + unit_records_offset(S) +
-                   ((size_t)(unit * b.num_kv_heads + kvh) * S.pieces_unit * MAX_ROWS + member * G + row) * REC_FLOATS;
-    }
-    const int n_pieces = n_own + n_unit;
+    const bool nothing = n_new <= 0 || (unit < 0 && n_own == 1);          // no query token, or finished by the main kernel
+    // (left only where the result would be stored: a branch here would have the loads wait behind it)
+
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
-    const int tid = threadIdx.x, ch = tid % D, grp = tid / D, wave = tid >> 6;
-    const float* __restrict__ rec_own =
-        (const float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G + row) * REC_FLOATS;
-    auto record = [&](int j) -> const float* {               // this row in record j
-        return j < n_own ? rec_own + (size_t)j * (MAX_G * REC_FLOATS) : rec_unit + (size_t)(j - n_own) * (MAX_ROWS * REC_FLOATS);   // consecutive pieces of the unit
-    };
-
-    // the maximum over all pieces (every piece of a context that needs several has a visible key); the (m, l)
-    // of piece `tid` stay in registers for the weights below
-    float m_mine = -INFINITY, l_mine = 0.f;
-    if (tid < n_pieces) {
-        const float* src = record(tid);
-        m_mine = src[D];
-        l_mine = src[D + 1];
-    }
-    float m_all = m_mine;
-    for (int j = tid + MERGE_THREADS; j < n_pieces; j += MERGE_THREADS) m_all = fmaxf(m_all, record(j)[D]);
-    m_all = wave_max64(m_all);
-    if ((tid & 63) == 0) part_s[wave] = m_all;
-    __syncthreads();
-    m_all = part_s[0];
+    float m = -INFINITY, l = 0.f;                            // of this wave's pieces (every piece has a visible key)
+    f32x2 acc = {0.f, 0.f};
+    auto add = [&](int j0, int n) {                          // the pieces asked for, those below n
+        float m_new = m;
 #pragma unroll
-    for (int i = 1; i < MERGE_THREADS / 64; ++i) m_all = fmaxf(m_all, part_s[i]);
-
-    float acc = 0.f, l_tot = 0.f;
-    for (int c0 = 0; c0 < n_pieces; c0 += MERGE_THREADS) {
-        __syncthreads();                                     // the weights of the chunk before have been used
-        if (c0 + tid < n_pieces) {
-            float m_j = m_mine, l_j = l_mine;
-            if (c0 > 0) {
-                const float* src = record(c0 + tid);
-                m_j = src[D];
-                l_j = src[D + 1];
-            }
-            const float wgt = __builtin_amdgcn_exp2f((m_j - m_all) * c_log2);
-            w_s[tid] = wgt;
-            l_tot += wgt * l_j;
+        for (int u = 0; u < LOADS; ++u) {
+            ml[u][0] = j0 + wave + u * WAVES < n ? ml[u][0] : -INFINITY;
+            m_new = fmaxf(m_new, ml[u][0]);
         }
-        __syncthreads();
-        const int n = min(MERGE_THREADS, n_pieces - c0);
-#pragma unroll 8
-        for (int j = grp; j < n; j += MERGE_GROUPS) acc += w_s[j] * record(c0 + j)[ch];
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // no piece of this wave so far: all weights are 0
+        const float alpha = __builtin_amdgcn_exp2f((m - ref) * c_log2);
+        l *= alpha;
+        acc *= alpha;
+        m = m_new;
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            const bool in = j0 + wave + u * WAVES < n;       // what is no piece may hold anything, infinities and NaN included
+            const float wgt = __builtin_amdgcn_exp2f((ml[u][0] - ref) * c_log2);
+            l += wgt * (in ? ml[u][1] : 0.f);
+            acc[0] += wgt * (in ? val[u][0] : 0.f);
+            acc[1] += wgt * (in ? val[u][1] : 0.f);
+        }
+    };
+    add(0, n_own);
+    for (int j0 = LOADS * WAVES; j0 < n_own; j0 += LOADS * WAVES) {
+        ask(rec_own, MAX_G * REC_FLOATS, j0, S.pieces_max);
+        add(j0, n_own);
     }
-    l_tot = wave_sum64(l_tot);
-    __syncthreads();                                         // part_s is read above
-    if ((tid & 63) == 0) part_s[wave] = l_tot;
-    acc_s[grp][ch] = acc;
+    if (SHARED && unit >= 0) {
+        const int shared_len = (int)min((long long)max(sv.unit_shared_len[unit], 0), (long long)b.max_pages * b.page_size) / BK * BK;
+        const int n_unit = min((shared_len / BK + S.tiles_per_piece - 1) / S.tiles_per_piece, S.pieces_unit);
+        const int member = min(max(r - sv.unit_first_req[unit], 0), MAX_ROWS / G - 1);       // position of the request in its unit
+        const float* __restrict__ rec_unit = (const float*)a.workspace + unit_records_offset(S) +
+                   ((size_t)(unit * b.num_kv_heads + kvh) * S.pieces_unit * MAX_ROWS + member * G + row) * REC_FLOATS;
+        for (int j0 = 0; j0 < n_unit; j0 += LOADS * WAVES) {
+            ask(rec_unit, MAX_ROWS * REC_FLOATS, j0, S.pieces_unit);
+            add(j0, n_unit);
+        }
+    }
+    acc_s[wave][lane] = acc;
+    if (lane == 0) ml_s[wave] = f32x2{m, l};
     __syncthreads();
-    if (grp == 0) {
-        acc = 0.f;
-        l_tot = 0.f;
+    if (wave > 0 || nothing) return;
+    float m_all = -INFINITY;
 #pragma unroll
-        for (int g = 0; g < MERGE_GROUPS; ++g) acc += acc_s[g][ch];
+    for (int w = 0; w < WAVES; ++w) m_all = fmaxf(m_all, ml_s[w][0]);
+    float l_tot = 0.f;
+    acc = f32x2{0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < MERGE_THREADS / 64; ++i) l_tot += part_s[i];
-        const long long q_row = safe_first_row(b, r, 1);
-        const int head = kvh * G + row;
-        ((__bf16*)a.out)[(q_row * b.num_q_heads + head) * D + ch] = (__bf16)(l_tot > 0.f ? acc / l_tot : 0.f);
-        if (ch == 0 && a.lse != nullptr)
-            a.lse[q_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
+    for (int w = 0; w < WAVES; ++w) {
+        const f32x2 x = ml_s[w];
+        const float wgt = x[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x[0] - m_all) * c_log2);
+        l_tot += wgt * x[1];
+        acc += wgt * acc_s[w][lane];
     }
+    const long long q_row = clamp_first_row(b, cu_new, 1);
+    const int head = kvh * G + row;
+    bf16x2 o;
+    o[0] = (__bf16)(l_tot > 0.f ? acc[0] / l_tot : 0.f);
+    o[1] = (__bf16)(l_tot > 0.f ? acc[1] / l_tot : 0.f);
+    *(bf16x2*)((__bf16*)a.out + (q_row * b.num_q_heads + head) * D + 2 * lane) = o;
+    if (lane == 0 && a.lse != nullptr)
+        a.lse[q_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
 }
 
 // How a decode batch is cut.  Workgroups run in rounds of WORKGROUPS_PER_ROUND, a round lasts as long as its
@@ -570,17 +572,16 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, hipStrea
         return hipErrorInvalidValue;
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || (!SHARED && S.pieces_max == 1)) return err;   // one piece each: already written
-    const int G = b.num_q_heads / b.num_kv_heads;
-    const dim3 mgrid((unsigned)(S.n_pairs * G));
+    const dim3 mgrid((unsigned)b.num_reqs, (unsigned)b.num_kv_heads, (unsigned)(b.num_q_heads / b.num_kv_heads));
     const bool many = S.pieces_max + (SHARED ? S.pieces_unit : 0) > MANY_PIECES;
     if (a.causal && many)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 8>), mgrid, dim3(8 * D), 0, stream, a, S, sv);
+        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 16>), mgrid, dim3(16 * 64), 0, stream, a, S, sv);
     else if (a.causal)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 2>), mgrid, dim3(2 * D), 0, stream, a, S, sv);
+        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 4>), mgrid, dim3(4 * 64), 0, stream, a, S, sv);
     else if (many)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 8>), mgrid, dim3(8 * D), 0, stream, a, S, sv);
+        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 16>), mgrid, dim3(16 * 64), 0, stream, a, S, sv);
     else
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 2>), mgrid, dim3(2 * D), 0, stream, a, S, sv);
+        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 4>), mgrid, dim3(4 * 64), 0, stream, a, S, sv);
     return hipGetLastError();
 }
 

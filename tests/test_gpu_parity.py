@@ -467,6 +467,24 @@ def test_page_sizes_prefill_and_cross(ps):
     print("   errors (max, mean, lse):", _compare(wl, dw), flush=True)
 
 
+# piece counts around what a merge workgroup asks for at once: 4 waves x 8 pieces up to 32, 16 waves x 8 above, more in turns
+# (one request is cut in pieces of 4 tiles of 32 keys up to about 96 of them per KV head; the page table's width is the context's)
+@pytest.mark.parametrize("kind,H,Hkv,ctx", [("causal", 28, 4, [127]), ("causal", 28, 4, [128]), ("causal", 4, 1, [1023 + 64]), ("causal", 4, 1, [4095]),
+                                            ("causal", 4, 1, [4096]), ("causal", 2, 1, [16384]), ("causal", 2, 1, [16900]), ("causal", 2, 1, [40000]),
+                                            ("cross", 16, 1, [4096]), ("cross", 4, 1, [16512]), ("causal", 4, 2, [9000, 0, 31, 4100, 64])])
+def test_decode_merge_piece_counts(kind, H, Hkv, ctx):
+    print("case merge", kind, ctx, flush=True)
+    wl = W.build_workload("merge_pieces", kind, "bf16", 760, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=ctx, new_lens=[1] * len(ctx))
+    dw = B.DeviceWorkload(wl)
+    if dw.workspace is not None:
+        dw.workspace.fill_(0xff)                             # NaN wherever no record is written
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+
+
 @pytest.mark.parametrize("ps", PAGE_SIZES)
 def test_page_sizes_decode(ps):
     """The decode step on pages of 32 .. 256 tokens: plain, with shared-prefix units, and fused with the scatter."""
