@@ -4,16 +4,19 @@
 // Same operation as the prefill kernel restricted to one row tile of G = H / Hkv rows per (request,
 // KV head) pair; what differs is where the parallelism comes from: the K/V bytes of a pair are read
 // exactly once, so the work is cut along the KEY axis, first into pieces of `tiles_per_piece` 32-key
-// tiles (one workgroup each, several times more of them than the chip holds), then, inside a
-// workgroup, tile by tile over its 4 waves.
+// tiles (one workgroup each), then, inside a workgroup, block by block of 16 keys over its 4 waves.
 //
-//   workgroup = one piece of one pair, 4 waves, 48 KB of LDS: three workgroups share a CU, so that two
-//               stream while the third starts up or writes its result.  All waves fetch the piece's
-//               tiles into LDS rings of 3 tiles (LDS-DMA, the prefill kernel's swizzled layout, a tile
-//               asked for two iterations before it is computed, every fetch landed at the iteration's
-//               one barrier: see the loop); wave w COMPUTES tiles w, w+4, ... of the piece, all
-//               waves holding the same G query rows (padded to the 32 columns of the MFMA).  The matrix
-//               pipe is mostly idle; the kernel is bound by the rate at which tiles arrive from HBM.
+//   workgroup = one piece of one pair, 4 waves, 64 KB of LDS, two on a compute unit.  Wave w takes blocks w, w+4, ... of
+//               the piece and does everything for them by itself: it fetches them by LDS-DMA into a ring of its
+//               own (two blocks of K and V: one is computed while the other is on its way), waits for its own
+//               fetches only, and keeps its own online softmax.  There is no barrier before the end.  (With
+//               tiles that all waves fetch and one of them computes, a barrier per tile, the waves' computing was
+//               one chain: 0.6 us per 32 keys, which bound every batch too small to fill the chip: one context
+//               of 1500 tokens 10.6 -> 7.2 us for both kernels, of 16384 17.1 -> 12.5.)
+//   matrix    = v_mfma_f32_16x16x32 for S^T = K Q^T and 16x16x16 for O^T += V^T P^T: 16 query rows, the most a KV head
+//               has here, so half the accumulators and half the exponentials of the 32-column shape, and a lane's
+//               four scores are the four keys that the value product expects from it.  The matrix pipe is mostly
+//               idle; the kernel is bound by the rate at which blocks arrive from HBM.
 //   merge 1   = the 4 waves' (maximum, row sum, accumulator) are combined through LDS;
 //   merge 2   = a pair with several pieces leaves one record per piece in the workspace and
 //               attn_bf16_decode_merge_kernel combines them; a pair with one piece writes its output
@@ -23,17 +26,19 @@
 // are the same physical pages can be given as a UNIT: up to 32 / G consecutive requests and the length they
 // share.  The shared keys are then read once per unit instead of once per request: extra workgroups at the
 // end of the grid take the shared part, with the query rows of all the unit's requests side by side in the
-// 32 columns of the MFMA, while the requests' own workgroups start behind the shared part; the merge
+// two groups of 16 rows, while the requests' own workgroups start behind the shared part; the merge
 // kernel adds the records of both.  Built as a second instantiation (SHARED) so that the plain path pays
 // nothing for it.
 //
 // Fused step (FUSED instantiation, emm_decode_step): the query token's own K/V row need not be in the pool
-// beforehand.  The workgroup whose piece holds the token's slot copies the row from k_new / v_new into the
-// LDS tile once the tile has landed (into the swizzled places the loads would have put it) and stores it in
+// beforehand.  The wave whose block holds the token's slot copies the row from k_new / v_new into the
+// LDS block once the block has landed (into the swizzled places the loads would have put it) and stores it in
 // the pool when it is done, so a decode step is one launch less than scatter + attention.
 #include "attn_bf16_common.h"
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace emm {
 
@@ -45,17 +50,19 @@ constexpr int MAX_G = 16;                        // query heads per KV head this
 constexpr int REC_FLOATS = D + 2;                // per row of a record: 128 accumulator values, m, l
 constexpr int NW = 4;                            // waves per workgroup
 constexpr int NT = NW * 64;
-constexpr int BK = 32;                           // keys per tile: two 16-key blocks (a page holds 1 to 16 blocks)
-constexpr int TILE_BYTES = BK * D * 2;           // one K or V tile in LDS: 32 rows of 256 bytes
-constexpr int NSLOT = 3;                         // ring depth; tile i of a piece lives in slot i % NSLOT
-constexpr int AHEAD = 2;                         // a tile is asked for this many iterations before it is computed
-constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // 124 + AHEAD page ids fit two registers of 64 lanes
-constexpr int WORKGROUPS_PER_ROUND = 3 * 256;     // three workgroups on each of 256 CUs
+constexpr int BK = 32;                           // keys per tile, the unit in which pieces are measured
+constexpr int BLK = 16;                          // keys per block, what a wave fetches and computes at a time (a page holds 1 to 16)
+constexpr int BLOCKS_PER_TILE = BK / BLK;
+constexpr int BLOCK_BYTES = BLK * D * 2;         // one K or V block in LDS: 16 rows of 256 bytes
+constexpr int NSLOT = 2;                         // blocks a wave's ring holds; block i of a wave lives in slot i % NSLOT
+constexpr int RING_BYTES = NSLOT * 2 * BLOCK_BYTES;      // of one wave: slots of a K block and a V block
+constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // a wave's blocks of a piece: at most 62, one page id per lane
+constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 256 CUs
 constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see decode_shape
 constexpr int OVERHEAD_TILES = 4;                // start and finish of a workgroup, in tile times
-constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit: the MFMA's columns
-static_assert(NW * MAX_G * REC_FLOATS * 4 <= 2 * NSLOT * TILE_BYTES, "the merge across waves reuses the tile rings");
-static_assert(AHEAD == NSLOT - 1, "the slot refilled in iteration i is the one read in iteration i-1");
+constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
+static_assert(NW * MAX_G * REC_FLOATS * 4 <= NW * RING_BYTES, "the merge across waves reuses the rings");
+static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
 
 struct DecodeShape {
     int n_pairs;            // (request, KV head) pairs
@@ -77,18 +84,41 @@ __device__ inline int own_pieces_of(int kv_len, int t_off, int tiles_per_piece, 
     const int n_tiles = (kv_len + BK - 1) / BK - t_off;
     return n_tiles <= 0 ? 0 : (n_tiles + tiles_per_piece - 1) / tiles_per_piece;
 }
+// max or sum over the four lanes that hold a query row (lane % 16)
+__device__ inline float quad_max(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float quad_sum(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
 // workspace: the requests' own records first, [pair][piece][MAX_G rows], then the units', [unit][KV head][piece][MAX_ROWS]
 __device__ __host__ inline size_t unit_records_offset(const DecodeShape& S)
 {
     return (size_t)S.n_pairs * S.pieces_max * MAX_G * REC_FLOATS;
 }
 
+// The waits of the block loop, written out because the compiler does not see the LDS-DMA fetches: all but the newest
+// PENDING of this wave's fetches have landed.  The clobber keeps reads of LDS behind it.
+template <int PENDING>
+__device__ inline void wait_fetches()
+{
+    static_assert(PENDING < 16, "the low four bits of the count");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(PENDING) : "memory");
+}
+
 template <bool CAUSAL, bool SHARED, bool FUSED>
-__global__ __launch_bounds__(NT, 3) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
+__global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
 {
     static_assert(CAUSAL || !FUSED, "only a causal step has a new token to store");
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NSLOT * TILE_BYTES];   // K ring, then V ring
-    constexpr int V_SM = NSLOT * TILE_BYTES;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * RING_BYTES];
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
 
     const BatchView& b = a.b;
     const int G = b.num_q_heads / b.num_kv_heads;
@@ -106,26 +136,27 @@ __global__ __launch_bounds__(NT, 3) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
-    const int t_off = (SHARED && !unit_mode) ? max(sv.req_shared_len[r], 0) / BK : 0;   // tiles a unit computes for this request
+    const int l16 = lane & 15, g = lane >> 4;
+    // everything that is needed of the lengths, asked for together (and before any of it decides on a branch)
+    const int new_len = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
+    const int req_unit = SHARED ? sv.req_unit[r] : -1, req_shared = SHARED ? sv.req_shared_len[r] : 0;
+    const int t_off = (SHARED && !unit_mode) ? max(req_shared, 0) / BK : 0;   // tiles a unit computes for this request
     const int t_begin = t_off + piece * S.tiles_per_piece;
-    // lane k of a wave holds where in the pool the 16-key block lies that this wave fetches for tile t_begin + k
-    // and in a second register for tile t_begin + 64 + k (a piece has at most 124 tiles and fetches run two tiles
-    // ahead, so two registers cover it).  Asked for before the lengths are
-    // known, so that the two loads overlap: entries past the request's pages are read (the row has
-    // max_pages of them) and whatever they hold is forced into the pool; those keys are masked.
+    // Wave w does blocks w, w + 4, ... of the piece; lane k holds where in the pool its k-th one lies.  Asked for before
+    // the lengths are known, so that the two loads overlap: entries past the request's pages are read (the row
+    // has max_pages of them) and forced into the pool, but never fetched from.
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
-    const int blk16 = (t_begin + lane) * 2 + (wave >> 1);                 // logical 16-key block of the request
-    const int pg_raw = b.max_pages > 0 ? pt[min(blk16 >> b.page_shift, b.max_pages - 1)] : 0;
-    const bool long_piece = S.tiles_per_piece + AHEAD > 64;  // the same for the whole grid
-    const int blk16_hi = blk16 + 128;
-    const int pg_raw_hi = (long_piece && b.max_pages > 0) ? pt[min(blk16_hi >> b.page_shift, b.max_pages - 1)] : 0;
+    const int blk16 = t_begin * BLOCKS_PER_TILE + wave + NW * lane;       // logical 16-key block of the request
+    const int pg_raw = pt[min(blk16 >> b.page_shift, b.max_pages - 1)];   // (max_pages > 0: checked on the host)
+    asm volatile("" ::"s"(new_len), "s"(prefix_len), "s"(cu_new));
+    __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
     bool direct;                                             // one piece and no unit: this workgroup writes the output
     if (!unit_mode) {
-        if (b.new_lens[r] <= 0) return;                      // no query token
-        const int P = safe_prefix_len(b, r, CAUSAL ? 1 : 0);
+        if (new_len <= 0) return;                            // no query token
+        const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
         kv_len = CAUSAL ? P + 1 : P;                         // keys the query sees = slots that hold tokens
-        const bool in_unit = SHARED && sv.req_unit[r] >= 0;
+        const bool in_unit = SHARED && req_unit >= 0;
         n_pieces = own_pieces_of(kv_len, t_off, S.tiles_per_piece, in_unit);
         n_rows = G;
         direct = n_pieces == 1 && !in_unit;
@@ -137,236 +168,230 @@ __global__ __launch_bounds__(NT, 3) void attn_bf16_decode_kernel(AttnArgs a, Dec
         direct = false;
     }
     if (piece >= n_pieces) return;
-    const int n_tiles_all = (kv_len + BK - 1) / BK;
-    const int n_tiles = min(S.tiles_per_piece, n_tiles_all - t_begin);     // 0 only for an empty context
+    const int n_blocks = min(S.tiles_per_piece * BLOCKS_PER_TILE, (kv_len + BLK - 1) / BLK - t_begin * BLOCKS_PER_TILE);    // of the piece; 0 only for an empty context
+    const int n_mine = n_blocks > wave ? (n_blocks - wave + NW - 1) / NW : 0;
     // in units of 4096 bytes (one block of one KV head): (page, KV head, block within the page)
     const int pg_vec = ((min(max(pg_raw, 0), b.num_pages - 1) * b.num_kv_heads + kvh) << b.page_shift) +
                        (blk16 & ((1 << b.page_shift) - 1));
-    const int pg_vec_hi = ((min(max(pg_raw_hi, 0), b.num_pages - 1) * b.num_kv_heads + kvh) << b.page_shift) +
-                          (blk16_hi & ((1 << b.page_shift) - 1));
-    const int l32 = lane & 31, h32 = lane >> 5;
-    const int limit = kv_len - 1;                            // last visible key (the query's own slot if causal)
-    const int n_clear = kv_len / BK;                         // tiles 0 .. n_clear-1 need no mask
 
-    // every wave holds the same query rows: the G heads of the request, or in unit mode the G heads of each
-    // of the unit's requests; the remaining columns of the MFMA repeat the last row and are discarded
-    const int my_row = min(l32, n_rows - 1);
-    const int my_req = unit_mode ? min(r + my_row / G, b.num_reqs - 1) : r;
-    const int hq = kvh * G + (unit_mode ? my_row % G : my_row);
-    const long long q_row = safe_first_row(b, my_req, 1);
-    const __bf16* __restrict__ qp = (const __bf16*)a.q + (q_row * b.num_q_heads + hq) * D + 8 * h32;
-    bf16x8 qf[8];
+    // ---- global -> LDS by LDS-DMA (lane i lands at base + 16 i), four rows of 256 bytes per instruction, rows = keys,
+    //      16-byte chunks XOR-swizzled; the hardware fixes where a lane's bytes land, so the swizzle is on the source
+    //      side: the lane that lands on (row, physical chunk p) fetches logical chunk p ^ f(row).
+    //        K: f(row) = row          read with ds_read_b128, 16 rows of one chunk at a time
+    //        V: f(row) = (row & 3) << 2   read with ds_read_tr16_b64, four rows of two chunks
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem + wave * RING_BYTES;
+    unsigned char* my_ring = smem + wave * RING_BYTES;
+    int k_goff[4];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *(const bf16x8*)(qp + 16 * s);
-
-    // ---- global -> LDS, the prefill kernel's scheme at half the tile height: wave w brings rows 8w .. 8w+7
-    //      of the K tile and of the V tile (logical 16-key block 2 kt + w/2), K rows permuted by swap23 and both
-    //      with their 16-byte chunks XOR-swizzled on the source side.
-    const int ld_row = lane >> 4, ld_p = lane & 15;
-    const int r16 = 8 * (wave & 1) + ld_row;
-    const int k_goff0 = swap23(r16) * 256 + ((ld_p ^ r16) << 4);
-    const int v_goff0 = r16 * 256 + ((ld_p ^ ((r16 & 3) << 2)) << 4);
+    for (int j = 0; j < 4; ++j) k_goff[j] = (4 * j + g) * 256 + ((l16 ^ (4 * j + g)) << 4);
+    const int v_goff = g * 256 + ((l16 ^ (g << 2)) << 4);
     const unsigned char* __restrict__ kcb = (const unsigned char*)a.k_cache;
     const unsigned char* __restrict__ vcb = (const unsigned char*)a.v_cache;
-    const int ld_lds = wave * 8 * 256;
-    const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
-    auto load_tile = [&](int i, int slot) {                  // tile t_begin + i into ring slot `slot`
-        const long long off = (long long)__builtin_amdgcn_readlane(i < 64 ? pg_vec : pg_vec_hi, i & 63) * 4096;
-        lds_dma16(kcb + off, k_goff0, smem_base + slot * TILE_BYTES + ld_lds);
-        lds_dma16(kcb + off, (k_goff0 ^ 64) + 2048, smem_base + slot * TILE_BYTES + ld_lds + 1024);
-        lds_dma16(vcb + off, v_goff0, smem_base + V_SM + slot * TILE_BYTES + ld_lds);
-        lds_dma16(vcb + off, v_goff0 + 1024, smem_base + V_SM + slot * TILE_BYTES + ld_lds + 1024);
+    constexpr int FETCHES = 8;                               // instructions per block
+    auto fetch = [&](int i, int slot) {                      // this wave's block i into its ring
+        const long long off = (long long)__builtin_amdgcn_readlane(pg_vec, i) * BLOCK_BYTES;
+        const uint32_t to = __builtin_amdgcn_readfirstlane(ring + slot * (2 * BLOCK_BYTES));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds_dma16(kcb + off, k_goff[j], to + j * 1024);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds_dma16(vcb + off, v_goff + j * 1024, to + BLOCK_BYTES + j * 1024);
     };
-    // V rows (keys) past the context are zeroed in LDS by the wave that fetched them: 0 * NaN would poison
-    // the output; K rows past it only give scores that the mask removes
+    const int limit = kv_len - 1;                            // last visible key (the query's own slot if causal)
+    auto first_key = [&](int i) { return t_begin * BK + (wave + NW * i) * BLK; };
+    // V rows (keys) past the context are zeroed in LDS: 0 * NaN would poison the output; K rows past it only give
+    // scores that the mask removes
     auto zero_v_tail = [&](int i, int slot) {
-        if ((t_begin + i + 1) * BK > kv_len) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int key = (t_begin + i) * BK + wave * 8 + 4 * j + ld_row;
-                if (key >= kv_len)
-                    *(uint4*)(smem + V_SM + slot * TILE_BYTES + ld_lds + j * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
-            }
-        }
+        for (int j = 0; j < 4; ++j)
+            if (first_key(i) + 4 * j + g >= kv_len)
+                *(uint4*)(my_ring + slot * (2 * BLOCK_BYTES) + BLOCK_BYTES + j * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
     };
-
-    // FUSED: the tile of this piece that holds the query token's own slot (none in most workgroups); its K/V
-    // row comes from k_new / v_new, written by the waves that fetched the rows it replaces
-    const int new_tile = (FUSED && !unit_mode) ? (kv_len - 1) / BK - t_begin : -1;
-    const long long new_row_bytes = ((long long)safe_first_row(b, r, 1) * b.num_kv_heads + kvh) * (D * 2);
+    // FUSED: the query token's own K/V row comes from k_new / v_new into the places the fetches would have put it
+    const long long first_row = clamp_first_row(b, cu_new, 1);
+    const long long new_row_bytes = (first_row * b.num_kv_heads + kvh) * (D * 2);
+    auto holds_new_row = [&](int i) { return FUSED && !unit_mode && first_key(i) <= limit && limit < first_key(i) + BLK; };
     auto patch_new_row = [&](int i, int slot) {
-        if (FUSED && i == new_tile) {
-            const int kk = (kv_len - 1) % BK;                                  // key within the tile
-            const int rho = (kk & 16) + swap23(kk & 15);                       // LDS row of that key in the K tile
-            if (wave == (rho >> 3) && lane < 16)
-                *(uint4*)(smem + slot * TILE_BYTES + rho * 256 + ((lane ^ (rho & 15)) << 4)) =
-                    *(const uint4*)((const unsigned char*)a.k_new + new_row_bytes + lane * 16);
-            if (wave == (kk >> 3) && lane < 16)
-                *(uint4*)(smem + V_SM + slot * TILE_BYTES + kk * 256 + ((lane ^ ((kk & 3) << 2)) << 4)) =
-                    *(const uint4*)((const unsigned char*)a.v_new + new_row_bytes + lane * 16);
+        const int row = limit - first_key(i);
+        if (lane < 32) {
+            const unsigned char* src = (const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + new_row_bytes + l16 * 16;
+            const int chunk = l16 ^ (lane < 16 ? row : (row & 3) << 2);
+            *(uint4*)(my_ring + slot * (2 * BLOCK_BYTES) + (lane < 16 ? 0 : BLOCK_BYTES) + row * 256 + (chunk << 4)) = *(const uint4*)src;
         }
     };
 
-    const int k_rd0 = l32 * 256 + ((h32 ^ (l32 & 15)) << 4);
-    const int v_rd0 = V_SM + (8 * h32 + ((lane & 15) >> 2)) * 256 +
-                      ((4 * ((lane & 15) >> 2) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) << 4) + (lane & 1) * 8;
-
-    f32x16 o_acc[4];
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o_acc[nb][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    // ---- LDS read addresses.  K: lane (key l16, g) reads chunk 4 st + g; V: lane j of a 16-lane group points at four
+    //      channels of key 4 g + j / 4 and receives the group's four keys of channel 16 nb + j.
+    const int k_rd0 = l16 * 256 + ((g ^ l16) << 4);
+    const int v_rd0 = BLOCK_BYTES + (4 * g + (l16 >> 2)) * 256 + ((((l16 >> 1) & 1) ^ ((l16 >> 2) << 2)) << 4) + (l16 & 1) * 8;
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
     const float slack = RESCALE_LOG2 / c_log2;
 
-    // one tile, start to finish, by one wave: S^T = K Q^T, mask, online softmax, O^T += V^T P^T
-    auto compute_tile = [&](int i, int slot) {
-        f32x16 s;
+    float* __restrict__ red = (float*)smem;                  // [NW waves][16 rows][130], after the loop
+    // The piece with NR groups of 16 query rows: the G heads of the request or, in unit mode, the G heads of each of
+    // the unit's requests; columns of the MFMA past them repeat the last row and are discarded.
+    auto attend = [&](auto nr_c) {
+        constexpr int NR = decltype(nr_c)::value;
+        bf16x8 qf[NR][4];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int q = 0; q < NR; ++q) {
+            const int my_row = min(16 * q + l16, n_rows - 1);
+            const int hq = kvh * G + (unit_mode ? my_row % G : my_row);
+            const long long q_row = unit_mode ? safe_first_row(b, min(r + my_row / G, b.num_reqs - 1), 1) : first_row;
+            const __bf16* __restrict__ qp = (const __bf16*)a.q + (q_row * b.num_q_heads + hq) * D + 8 * g;
 #pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            const bf16x8 kf = *(const bf16x8*)(smem + slot * TILE_BYTES + (k_rd0 ^ (st << 5)));
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[st], s, 0, 0, 0);
+            for (int st = 0; st < 4; ++st) qf[q][st] = *(const bf16x8*)(qp + 32 * st);
         }
-        const int kt = t_begin + i;
-        if (kt >= n_clear) {
+        f32x4 o_acc[NR][8];
+        float m_run[NR], l_run[NR];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int key = kt * BK + 16 * (v >> 3) + 8 * h32 + (v & 7);
-                s[v] = (key > limit) ? -INFINITY : s[v];
+        for (int q = 0; q < NR; ++q) {
+            m_run[q] = -INFINITY;
+            l_run[q] = 0.f;
+#pragma unroll
+            for (int nb = 0; nb < 8; ++nb) o_acc[q][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        // one block, start to finish: S^T = K Q^T, mask, online softmax, O^T += V^T P^T
+        auto compute = [&](int i, int slot) {
+            const unsigned char* at = my_ring + slot * (2 * BLOCK_BYTES);
+            bf16x8 kf[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) kf[st] = *(const bf16x8*)(at + (k_rd0 ^ (st << 6)));
+            s16x4 vf[8];
+#pragma unroll
+            for (int nb = 0; nb < 8; ++nb)
+                vf[nb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + (v_rd0 ^ (nb << 5))));
+            f32x4 s[NR];
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                s[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int st = 0; st < 4; ++st) s[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[st], qf[q][st], s[q], 0, 0, 0);
+            }
+            const int key0 = first_key(i);
+            if (key0 + BLK > kv_len) {
+#pragma unroll
+                for (int q = 0; q < NR; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s[q][v] = (key0 + 4 * g + v > limit) ? -INFINITY : s[q][v];
+            }
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                // the reference of a row (the same in its four lanes) is raised only when a score passes it by the slack
+                const float mx = fmaxf(fmaxf(s[q][0], s[q][1]), fmaxf(s[q][2], s[q][3]));
+                if (__builtin_amdgcn_ballot_w64(mx > m_run[q] + slack) != 0) {
+                    const float mx_row = quad_max(mx);       // finite: every block has a visible key
+                    const float m_new = mx_row > m_run[q] + slack ? mx_row : m_run[q];
+                    const float alpha = m_run[q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[q] - m_new) * c_log2);
+                    m_run[q] = m_new;
+                    l_run[q] *= alpha;
+#pragma unroll
+                    for (int nb = 0; nb < 8; ++nb) o_acc[q][nb] *= alpha;
+                }
+                const float mc = m_run[q] * c_log2;
+                bf16x4 p;
+                float psum = 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    p[v] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[q][v], c_log2, -mc));
+                    psum += (float)p[v];                     // the rounded value, as in the numerator
+                }
+                l_run[q] += psum;
+#pragma unroll
+                for (int nb = 0; nb < 8; ++nb)
+                    o_acc[q][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[nb], __builtin_bit_cast(s16x4, p), o_acc[q][nb], 0, 0, 0);
+            }
+        };
+        if (n_mine > 0) {
+            fetch(0, 0);
+            if (n_mine > 1) fetch(1, 1);
+            for (int i = 0; i < n_mine; ++i) {
+                const int slot = i & 1;
+                if (i + 1 < n_mine) wait_fetches<FETCHES>(); // the next block's stay on their way
+                else wait_fetches<0>();
+                // (the query rows, asked for first, have landed as well; used here so that the compiler, which does not
+                // count the fetches, has no wait of its own to place inside the loop)
+                if (i == 0)
+#pragma unroll
+                    for (int q = 0; q < NR; ++q)
+#pragma unroll
+                        for (int st = 0; st < 4; ++st) asm volatile("" ::"v"(qf[q][st]));
+                if (first_key(i) + BLK > kv_len) zero_v_tail(i, slot);
+                if (holds_new_row(i)) patch_new_row(i, slot);
+                compute(i, slot);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // every read of the slot is done before it is filled again
+                if (i + NSLOT < n_mine) fetch(i + NSLOT, slot);
             }
         }
-        float mx = s[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        mx = pair_max(mx);                                   // finite: a tile below kv_len has a visible key
-        if (mx > m_run + slack || m_run == -INFINITY) {      // per row; both lanes of a row decide alike
-            const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c_log2);   // 0 the first time
-            l_run *= alpha;
-            m_run = mx;
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o_acc[nb][v] *= alpha;
-        }
-        const float mc = m_run * c_log2;
-        bf16x8 p[2];
-        float psum = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const __bf16 pr = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[v], c_log2, -mc));
-            p[v >> 3][v & 7] = pr;
-            psum += (float)pr;                               // the rounded value, as in the numerator
-        }
-        l_run += psum;
-        typedef short s16x4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const unsigned char* src = smem + slot * TILE_BYTES + 16 * sb * 256 + (v_rd0 ^ (nb << 6));
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + 4 * 256));
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                o_acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[sb], o_acc[nb], 0, 0, 0);
-            }
-    };
+        __syncthreads();                                     // every wave is past its rings
 
-    if (n_tiles > 0) {
-        for (int i = 0; i < AHEAD; ++i) load_tile(i, i);     // past the piece's end: a clamped page, never read
-        __builtin_amdgcn_s_waitcnt(0x0f70 | 4 * (AHEAD - 1));    // tile 0 has landed
-        // The query rows were asked for before the tiles and have landed with tile 0, but the compiler, which does
-        // not count the tile fetches, takes half of them to be still on their way and would wait for them where
-        // they are first used: inside the loop, in the middle of every tile this wave computes, with a wait that
-        // also covers every tile fetch in flight.  Using them here puts that wait in front of the loop, once, and
-        // leaves the waits of the loop to the one written there.
+        // ---- merge 1: the waves' partial results, 16 rows at a time, through LDS
+        float* __restrict__ rec =
+            unit_mode ? (float*)a.workspace + unit_records_offset(S) + (size_t)(pair * S.pieces_unit + piece) * MAX_ROWS * REC_FLOATS
+                      : (float*)a.workspace + (size_t)(pair * S.pieces_max + piece) * MAX_G * REC_FLOATS;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) asm volatile("" ::"v"(qf[s]));
-        zero_v_tail(0, 0);
-        patch_new_row(0, 0);
-        __syncthreads();
-        int slot = 0;                                        // of tile i
-        for (int i = 0; i < n_tiles; ++i) {
-            const int slot_next = slot == NSLOT - 1 ? 0 : slot + 1, slot_last = slot == 0 ? NSLOT - 1 : slot - 1;
-            load_tile(i + AHEAD, slot_last);                 // the slot last read in iteration i-1
-            if ((i & (NW - 1)) == wave) compute_tile(i, slot);
-            // Every fetch of this wave has landed before the barrier, tile i+2 as well as tile i+1: a workgroup
-            // thus has one tile on its way at a time, asked for at the start of an iteration and waited for at its
-            // end, three workgroups of a CU 48 KB between them.  Waiting for tile i+1 only (two tiles in flight,
-            // 96 KB per CU) is slower on everything that streams from HBM (decode_b64_8k 205 against 193 us; a
-            // fetch-only kernel shows the same: the rate falls as more is in flight), and so is waiting earlier,
-            // before or inside this wave's tile (decode_mixed_b32 49 and 53 against 44 us).
-            __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0)
-            zero_v_tail(i + 1, slot_next);
-            patch_new_row(i + 1, slot_next);
+        for (int q = 0; q < NR; ++q) {
+            if (q > 0) __syncthreads();                      // the pass before has been read
+            const int row0 = 16 * q, rows_here = min(MAX_G, n_rows - row0);
+            const float l_row = quad_sum(l_run[q]);
+            if (l16 < rows_here) {
+                float* dst = red + (wave * MAX_G + l16) * REC_FLOATS;
+#pragma unroll
+                for (int nb = 0; nb < 8; ++nb) {
+                    *(f32x2*)(dst + 16 * nb + 4 * g) = f32x2{o_acc[q][nb][0], o_acc[q][nb][1]};
+                    *(f32x2*)(dst + 16 * nb + 4 * g + 2) = f32x2{o_acc[q][nb][2], o_acc[q][nb][3]};
+                }
+                if (g == 0) *(f32x2*)(dst + D) = f32x2{m_run[q], l_row};
+            }
             __syncthreads();
-            slot = slot_next;
-        }
-        __builtin_amdgcn_s_waitcnt(0x0f70);                  // the last fetches too, before LDS is reused
-    }
-    __syncthreads();                                         // every wave's fetches have landed, every read is done
-
-    if (FUSED && new_tile >= 0 && new_tile < n_tiles && wave == 0 && lane < 32) {
-        // the token's row goes to its slot in the pool (K by lanes 0..15, V by 16..31), for the steps to come
-        const int pos = kv_len - 1;
-        const int page = min(max(pt[pos >> (4 + b.page_shift)], 0), b.num_pages - 1);
-        const long long dst = (((long long)page * b.num_kv_heads + kvh) * b.page_size + (pos & (b.page_size - 1))) * 256 + (lane & 15) * 16;
-        const unsigned char* src = (const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + new_row_bytes + (lane & 15) * 16;
-        unsigned char* pool = (unsigned char*)const_cast<void*>(lane < 16 ? a.k_cache : a.v_cache);
-        *(uint4*)(pool + dst) = *(const uint4*)src;
-    }
-
-    // ---- merge 1: the waves' partial results, 16 rows at a time, through LDS (the rings are free now)
-    float* __restrict__ red = (float*)smem;                  // [NW waves][16 rows][130]
-    const float l_pair = pair_sum(l_run);
-    float* __restrict__ rec =
-        unit_mode ? (float*)a.workspace + unit_records_offset(S) + (size_t)(pair * S.pieces_unit + piece) * MAX_ROWS * REC_FLOATS
-                  : (float*)a.workspace + (size_t)(pair * S.pieces_max + piece) * MAX_G * REC_FLOATS;
-    for (int row0 = 0; row0 < n_rows; row0 += MAX_G) {
-        if (row0 > 0) __syncthreads();                       // the pass before has been read
-        const int rows_here = min(MAX_G, n_rows - row0);
-        if (l32 >= row0 && l32 < row0 + rows_here) {
-            float* dst = red + (wave * MAX_G + l32 - row0) * REC_FLOATS;
+            for (int idx = tid; idx < rows_here * (D / 2); idx += NT) {
+                const int lrow = idx / (D / 2), ch = idx % (D / 2) * 2, row = row0 + lrow;
+                f32x2 ml[NW], x[NW];
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
+                for (int w = 0; w < NW; ++w) {
+                    const float* src = red + (w * MAX_G + lrow) * REC_FLOATS;
+                    ml[w] = *(const f32x2*)(src + D);
+                    x[w] = *(const f32x2*)(src + ch);
+                }
+                float m_all = -INFINITY;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) dst[32 * nb + 8 * (v >> 2) + 4 * h32 + (v & 3)] = o_acc[nb][v];
-            if (h32 == 0) {
-                dst[D] = m_run;
-                dst[D + 1] = l_pair;
-            }
-        }
-        __syncthreads();
-        for (int idx = tid; idx < rows_here * D; idx += NT) {
-            const int lrow = idx / D, ch = idx % D, row = row0 + lrow;
-            float m_all = -INFINITY;
+                for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml[w][0]);
+                f32x2 acc = {0.f, 0.f};
+                float l_tot = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, red[(w * MAX_G + lrow) * REC_FLOATS + D]);
-            float acc = 0.f, l_tot = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float* src = red + (w * MAX_G + lrow) * REC_FLOATS;
-                const float wgt = (src[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((src[D] - m_all) * c_log2);
-                acc += wgt * src[ch];
-                l_tot += wgt * src[D + 1];
-            }
-            if (direct) {
-                const int head = kvh * G + row;
-                const long long q_own = safe_first_row(b, r, 1);
-                ((__bf16*)a.out)[(q_own * b.num_q_heads + head) * D + ch] = (__bf16)(l_tot > 0.f ? acc / l_tot : 0.f);
-                if (ch == 0 && a.lse != nullptr)
-                    a.lse[q_own * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
-            } else {
-                rec[row * REC_FLOATS + ch] = acc;
-                if (ch == 0) {
-                    rec[row * REC_FLOATS + D] = m_all;
-                    rec[row * REC_FLOATS + D + 1] = l_tot;
+                for (int w = 0; w < NW; ++w) {
+                    const float wgt = (ml[w][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((ml[w][0] - m_all) * c_log2);
+                    acc[0] += wgt * x[w][0];
+                    acc[1] += wgt * x[w][1];
+                    l_tot += wgt * ml[w][1];
+                }
+                if (direct) {
+                    const int head = kvh * G + row;
+                    bf16x2 o;
+                    o[0] = (__bf16)(l_tot > 0.f ? acc[0] / l_tot : 0.f);
+                    o[1] = (__bf16)(l_tot > 0.f ? acc[1] / l_tot : 0.f);
+                    *(bf16x2*)((__bf16*)a.out + (first_row * b.num_q_heads + head) * D + ch) = o;
+                    if (ch == 0 && a.lse != nullptr)
+                        a.lse[first_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
+                } else {
+                    *(f32x2*)(rec + row * REC_FLOATS + ch) = acc;
+                    if (ch == 0) *(f32x2*)(rec + row * REC_FLOATS + D) = f32x2{m_all, l_tot};
                 }
             }
         }
+    };
+
+    if (FUSED && n_mine > 0 && !unit_mode && limit >= first_key(0) && (limit - first_key(0)) % (NW * BLK) < BLK && (limit - first_key(0)) / (NW * BLK) < n_mine &&
+        lane < 32) {
+        // the token's row goes to its slot in the pool (K by lanes 0..15, V by 16..31), for the steps to come; the
+        // block fetched from there is patched, so the order of the two does not matter
+        const int page = min(max(pt[limit >> (4 + b.page_shift)], 0), b.num_pages - 1);
+        const long long dst = (((long long)page * b.num_kv_heads + kvh) * b.page_size + (limit & (b.page_size - 1))) * 256 + l16 * 16;
+        const unsigned char* src = (const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + new_row_bytes + l16 * 16;
+        unsigned char* pool = (unsigned char*)const_cast<void*>(lane < 16 ? a.k_cache : a.v_cache);
+        *(uint4*)(pool + dst) = *(const uint4*)src;
     }
+    if (SHARED && unit_mode && n_rows > 16) attend(std::integral_constant<int, 2>{});
+    else attend(std::integral_constant<int, 1>{});
 }
 
 // merge 2: one workgroup per (pair, query row); wave w takes pieces w, w + WAVES, ..., a lane two channels of each.

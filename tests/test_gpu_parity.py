@@ -485,6 +485,44 @@ def test_decode_merge_piece_counts(kind, H, Hkv, ctx):
     _compare(wl, dw)
 
 
+# a wave does blocks of 16 keys, every fourth of a piece; two blocks in its ring; pieces of 4 tiles of 32 keys and more
+DECODE_EDGE_LENS = [0, 1, 14, 15, 16, 17, 30, 31, 32, 47, 48, 49, 62, 63, 64, 65, 79, 80, 95, 111, 112, 126, 127, 128, 129, 143, 191, 255, 256, 300]
+
+
+@pytest.mark.parametrize("kind,H,Hkv,ps", [("causal", 28, 4, 16), ("causal", 16, 1, 64), ("causal", 3, 3, 256), ("cross", 32, 8, 32)])
+def test_decode_block_edges(kind, H, Hkv, ps):
+    print("case decode block edges", kind, H, Hkv, ps, flush=True)
+    wl = W.build_workload("decode_edges", kind, "bf16", 770, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=ps,
+                          prefix_lens=DECODE_EDGE_LENS, new_lens=[1] * len(DECODE_EDGE_LENS))
+    dw = _gpu_run(wl)
+    _compare(wl, dw)
+    if kind == "causal":                                     # the fused step stores the rows itself, and gives the same bits
+        fused = B.DeviceWorkload(wl)
+        fused.decode_step()
+        torch.cuda.synchronize()
+        assert torch.equal(fused.out, dw.out) and torch.equal(fused.lse, dw.lse)
+        assert torch.equal(fused.k_cache, dw.k_cache) and torch.equal(fused.v_cache, dw.v_cache)
+
+
+@pytest.mark.parametrize("name,group,shared,planned", [("private", [0, 1, 2], 0, False), ("shared_apart", [0, 1, 0], 12800, False),
+                                                       ("units", [0, 0, 1], 12800, True), ("units_and_apart", [0, 0, 0], 12801, True)])
+def test_decode_large_enough_to_stream(name, group, shared, planned):
+    """More than 96 MiB of K and V: fetched past the caches, except what another request of the batch holds as well."""
+    print("case decode streams", name, flush=True)
+    wl = W.build_workload("decode_stream_" + name, "causal", "bf16", 780, num_q_heads=28, num_kv_heads=4, head_dim=128, page_size=16,
+                          prefix_lens=[17000, 18011, 17500], new_lens=[1, 1, 1], share_group=group, shared_len=[shared] * 3)
+    dw = B.DeviceWorkload(wl)
+    if planned:
+        plan = dw.plan_shared()
+        assert plan["num_units"] == 1
+        dw.scatter()
+        dw.attention_shared()
+    else:
+        dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+
+
 @pytest.mark.parametrize("ps", PAGE_SIZES)
 def test_page_sizes_decode(ps):
     """The decode step on pages of 32 .. 256 tokens: plain, with shared-prefix units, and fused with the scatter."""
