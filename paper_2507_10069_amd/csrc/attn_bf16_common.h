@@ -64,6 +64,13 @@ __device__ inline void lds_dma16(const void* base, uint32_t byte_offset, uint32_
                  :: "s"(lds_byte_offset), "v"(byte_offset), "s"(base) : "memory");
 }
 
+// the same with the non-temporal hint: lines that nobody will ask for again do not displace others in the caches
+__device__ inline void lds_dma16_streamed(const void* base, uint32_t byte_offset, uint32_t lds_byte_offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :: "s"(lds_byte_offset), "v"(byte_offset), "s"(base) : "memory");
+}
+
 // in-page LDS row of a key: swap bits 2 and 3 of its index within the 16-key page.  With K rows placed
 // that way, accumulator registers 8s..8s+7 of a lane of the transposed score block are exactly the 8
 // consecutive keys the B operand of the value product expects from it.

@@ -70,6 +70,7 @@ struct DecodeShape {
     int tiles_per_piece;    // 32-key tiles per workgroup
     int pieces_max;         // workgroups per pair in the grid (a pair uses as many as its context needs)
     int pieces_unit;        // workgroups per (unit, KV head) pair in the grid
+    int stream;             // 1: K and V that one workgroup alone reads are fetched past the caches (see STREAM_BYTES)
 };
 
 __device__ inline int pieces_of(int kv_len, int tiles_per_piece)
@@ -101,6 +102,20 @@ __device__ inline float quad_sum(float x)
 __device__ __host__ inline size_t unit_records_offset(const DecodeShape& S)
 {
     return (size_t)S.n_pairs * S.pieces_max * MAX_G * REC_FLOATS;
+}
+
+// Does a request other than r .. r + n - 1 hold page `id` at entry `at` of its row of the page table?  (Shared pages are
+// leading pages, so a shared one stands at the same entry everywhere.)  The whole wave asks, 64 requests at a time; with
+// more than SHARE_LOOKUP of them the answer is yes, unasked.  What is found decides how the page is fetched and nothing
+// else, so entries past a request's own pages do no harm.
+constexpr int SHARE_LOOKUP = 512;
+__device__ inline bool holds_page(const BatchView& b, int at, int id, int r, int n)
+{
+    if (b.num_reqs > SHARE_LOOKUP) return true;
+    bool found = false;
+    for (int k = threadIdx.x & 63; k < b.num_reqs; k += 64)
+        found = found || (b.page_table[(long long)k * b.max_pages + at] == id && (k < r || k >= r + n));
+    return __builtin_amdgcn_ballot_w64(found) != 0;
 }
 
 // The waits of the block loop, written out because the compiler does not see the LDS-DMA fetches: all but the newest
@@ -148,6 +163,8 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
     const int blk16 = t_begin * BLOCKS_PER_TILE + wave + NW * lane;       // logical 16-key block of the request
     const int pg_raw = pt[min(blk16 >> b.page_shift, b.max_pages - 1)];   // (max_pages > 0: checked on the host)
+    const int pg_first = min((t_begin * BLOCKS_PER_TILE) >> b.page_shift, b.max_pages - 1);
+    const bool shared_elsewhere = S.stream && holds_page(b, pg_first, pt[pg_first], r, unit_mode ? sv.unit_num_reqs[unit] : 1);
     asm volatile("" ::"s"(new_len), "s"(prefix_len), "s"(cu_new));
     __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
@@ -188,13 +205,21 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const unsigned char* __restrict__ kcb = (const unsigned char*)a.k_cache;
     const unsigned char* __restrict__ vcb = (const unsigned char*)a.v_cache;
     constexpr int FETCHES = 8;                               // instructions per block
+    const bool streamed = S.stream && !shared_elsewhere;
     auto fetch = [&](int i, int slot) {                      // this wave's block i into its ring
         const long long off = (long long)__builtin_amdgcn_readlane(pg_vec, i) * BLOCK_BYTES;
         const uint32_t to = __builtin_amdgcn_readfirstlane(ring + slot * (2 * BLOCK_BYTES));
+        if (streamed) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lds_dma16(kcb + off, k_goff[j], to + j * 1024);
+            for (int j = 0; j < 4; ++j) lds_dma16_streamed(kcb + off, k_goff[j], to + j * 1024);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lds_dma16(vcb + off, v_goff + j * 1024, to + BLOCK_BYTES + j * 1024);
+            for (int j = 0; j < 4; ++j) lds_dma16_streamed(vcb + off, v_goff + j * 1024, to + BLOCK_BYTES + j * 1024);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) lds_dma16(kcb + off, k_goff[j], to + j * 1024);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) lds_dma16(vcb + off, v_goff + j * 1024, to + BLOCK_BYTES + j * 1024);
+        }
     };
     const int limit = kv_len - 1;                            // last visible key (the query's own slot if causal)
     auto first_key = [&](int i) { return t_begin * BK + (wave + NW * i) * BLK; };
@@ -509,6 +534,13 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
         a.lse[q_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
 }
 
+// K and V are fetched past the caches (non-temporal) when a call reads more of them than the last-level cache would keep
+// until they are read again: 6.6 instead of 5.7 TB/s (64 x 8192 tokens 196 -> 173 us, 262 MB ragged 56 -> 48, 102 MB in
+// one context 25.5 -> 23.6); below, where a repeated call finds them there, it costs up to 12 % (66 MB: 15.7 -> 17.7).
+// The line lies between.  Pages that several requests read would lose what the first of them brought into the L2 (32
+// requests on 8 videos without units: 115 -> 154 us): each wave looks whether another request holds its first page.
+constexpr long long STREAM_BYTES = 96ll << 20;
+
 // How a decode batch is cut.  Workgroups run in rounds of WORKGROUPS_PER_ROUND, a round lasts as long as its
 // longest piece plus the fixed cost of starting and finishing a workgroup (about OVERHEAD_TILES tiles'
 // worth), every workgroup of the grid, also one that finds nothing to do, costs the dispatcher about 1/128 of a
@@ -556,6 +588,8 @@ DecodeShape decode_shape(const BatchView& b, const SharedPrefixView& sv = Shared
     S.tiles_per_piece = best;
     S.pieces_max = (int)pieces(own_tiles, best);
     S.pieces_unit = (int)pieces(unit_tiles, best);
+    const long long total = sv.planned_tiles > 0 ? (long long)sv.planned_tiles * b.num_kv_heads : (long long)S.n_pairs * own_tiles + (long long)S.n_unit_pairs * unit_tiles;
+    S.stream = total * BK * D * 4 >= STREAM_BYTES ? 1 : 0;
     return S;
 }
 
