@@ -107,7 +107,7 @@ emm_status emm_kv_scatter(const emm_batch *batch, const void *k_new, const void 
  *     MB), and 0 when no context the page table can hold is long enough to be cut (under 1536 tokens);
  *     emm_prefill_plan_host shows the plan;
  *   decode batch (at most one new token per request and at most 16 query heads per KV head): every context is
- *     cut; 8320 bytes per (request, KV head, piece), a piece being 128 to 1920 keys of the longest context the
+ *     cut; 8320 bytes per (request, KV head, piece), a piece being 128 to 3968 keys of the longest context the
  *     page table can hold.
  * The contents need no initialisation and mean nothing afterwards.  Calls on different streams must not share a
  * workspace.  Host-only; reads only the scalar fields. */

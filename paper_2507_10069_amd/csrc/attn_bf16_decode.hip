@@ -59,7 +59,6 @@ constexpr int RING_BYTES = NSLOT * 2 * BLOCK_BYTES;      // of one wave: slots o
 constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // a wave's blocks of a piece: at most 62, one page id per lane
 constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 256 CUs
 constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see decode_shape
-constexpr int OVERHEAD_TILES = 4;                // start and finish of a workgroup, in tile times
 constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
 static_assert(NW * MAX_G * REC_FLOATS * 4 <= NW * RING_BYTES, "the merge across waves reuses the rings");
 static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
@@ -534,6 +533,31 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
         a.lse[q_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
 }
 
+// How a decode batch is cut: the piece length with the least time by a model of the main kernel (times in us, measured).
+//   START           from the launch to the first block and from the last block to the end
+//   TILE_HBM        one 32-key tile of one KV head (16 KB) at the rate at which the whole chip streams, 6.6 TB/s
+//   TILE_CU         the same on one compute unit that has HBM to itself: a compute unit takes no more than about 36 bytes
+//                   per ns, so the longest piece, twice where a compute unit gets two full ones, bounds the time as well
+//                   (8 x 18432 tokens: 288 workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us)
+//   two workgroups fit a compute unit, 512 the chip; what does not fit starts when others end, and a last round that is
+//   nearly empty lasts as long as a full one: half of its emptiness is charged (608 workgroups of 32 tiles: 58 us)
+//   MERGE           the second kernel, which a batch cut in single pieces does without (128 contexts of 1000 tokens: 15.7 us
+//                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds
+// What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
+// longest own part / shared part and with it the pieces per context that the grid must provide; `planned_tiles` is the
+// amount of work there is (32-key tiles per KV head, summed over contexts), by which a ragged batch is known to be one:
+// half a piece is then lost per context (32 contexts of 350 to 4600 tokens, 8 KV heads, 262 MB: pieces of 48 tiles, as for
+// a uniform batch of the longest, 56 us, of 43 48 us, of 32, which do not fit, 54 us).  Without them the host knows only
+// the longest possible context (the width of the page table) and plans for every context being that long.
+// Without the amount of work the contexts may differ and may share pages, and both do better in shorter pieces: of the
+// lengths within 3 % of the best that fit the chip at once the shortest is taken (8 requests on one video without units:
+// pieces of 45 tiles 35 us, of 36 30 us; 40 contexts of 1000 to 4000 tokens: of 63 55 us, of 43 48 us).  A batch of one request
+// is kept to 384 workgroups: its contexts cannot differ (131072 tokens: 48 us, 47 in 256 workgroups, 53 in 512).
+// Records are kept to what fits the library's own array (attn_bf16_decode_static_scratch_bytes) wherever longer pieces
+// can do that, so that batches do not outgrow it.
+constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
+constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
+
 // K and V are fetched past the caches (non-temporal) when a call reads more of them than the last-level cache would keep
 // until they are read again: 6.6 instead of 5.7 TB/s (64 x 8192 tokens 196 -> 173 us, 262 MB ragged 56 -> 48, 102 MB in
 // one context 25.5 -> 23.6); below, where a repeated call finds them there, it costs up to 12 % (66 MB: 15.7 -> 17.7).
@@ -541,23 +565,6 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 // requests on 8 videos without units: 115 -> 154 us): each wave looks whether another request holds its first page.
 constexpr long long STREAM_BYTES = 96ll << 20;
 
-// How a decode batch is cut.  Workgroups run in rounds of WORKGROUPS_PER_ROUND, a round lasts as long as its
-// longest piece plus the fixed cost of starting and finishing a workgroup (about OVERHEAD_TILES tiles'
-// worth), every workgroup of the grid, also one that finds nothing to do, costs the dispatcher about 1/128 of a
-// tile time, and the piece length with the least total is taken -- in particular one that makes the last
-// round a full one.  (Sweeps of the piece length on uniform batches put the optimum where this model puts it;
-// finer models of HBM saturation and of ragged batches were tried and predicted no better.)
-// What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
-// longest own part / shared part and with it the pieces per context that the grid must provide, and when
-// units take work away `planned_tiles` is the amount that is left (32-key tiles per KV head, summed over
-// contexts).  Without them the host knows only the longest possible context (the width of the page table) and
-// plans for every context being that long.
-// A batch of ONE request has no short contexts beside long ones: its KV heads are all as long as each other, and
-// about as long as the table is wide.  HBM is then kept busy by half as many workgroups of twice the length, which
-// start, finish and are merged half as often: measured on a single context of 131072 tokens, 350 to 410
-// workgroups take 50.6-51.5 us, 570 take 55.1, 750 take 56.3 (and 256 take 56.0: too few).  Such a batch is
-// planned for rounds of 384.  (With several requests the same would help uniform batches by 1-4 % and cost a
-// ragged one 20 %, and the host cannot tell them apart.)
 DecodeShape decode_shape(const BatchView& b, const SharedPrefixView& sv = SharedPrefixView{})
 {
     DecodeShape S;
@@ -569,26 +576,35 @@ DecodeShape decode_shape(const BatchView& b, const SharedPrefixView& sv = Shared
                                  : sv.max_unit_tiles > 0 ? std::min<long long>(sv.max_unit_tiles, table_tiles) : table_tiles;
     const long long items = (long long)S.n_pairs + S.n_unit_pairs;
     auto pieces = [](long long tiles, int tpp) { return tiles > 0 ? (tiles + tpp - 1) / tpp : 1; };
-    const int per_round = (b.num_reqs == 1 && sv.num_units == 0) ? WORKGROUPS_PER_ROUND_ONE_REQUEST : WORKGROUPS_PER_ROUND;
-    long long best_cost = -1;
+    const long long most = (long long)S.n_pairs * own_tiles + (long long)S.n_unit_pairs * unit_tiles;
+    const long long total = sv.planned_tiles > 0 ? std::min(most, (long long)sv.planned_tiles * b.num_kv_heads) : most;
+    const bool known = sv.planned_tiles > 0 && total < most;             // contexts differ
+    const long long longest = std::max(own_tiles, unit_tiles);
+    const bool one = b.num_reqs == 1 && sv.num_units == 0;
+    const int at_once = one ? WORKGROUPS_PER_ROUND_ONE_REQUEST : WORKGROUPS_PER_ROUND;
+    auto full = [](long long tiles, int tpp) { return tiles / tpp + (tiles % tpp > tpp / 4 ? 1 : 0); };      // pieces worth counting
+    double least = -1;
     int best = MIN_TILES_PER_PIECE;
-    for (int tpp = MIN_TILES_PER_PIECE; tpp <= MAX_TILES_PER_PIECE; ++tpp) {
+    const int longest_piece = (int)std::max<long long>(MIN_TILES_PER_PIECE, std::min<long long>(MAX_TILES_PER_PIECE, longest));
+    for (int tpp = longest_piece; tpp >= MIN_TILES_PER_PIECE; --tpp) {   // ties: the longer piece
         const long long grid = S.n_pairs * pieces(own_tiles, tpp) + S.n_unit_pairs * pieces(unit_tiles, tpp);
-        // known total: half a piece lost per context; else every context as long as the longest
-        const long long wgs = (sv.planned_tiles > 0 && sv.num_units > 0)
-                                  ? std::min(grid, ((long long)sv.planned_tiles * b.num_kv_heads + tpp - 1) / tpp + items / 2)
-                                  : grid;
-        const long long rounds = (wgs + per_round - 1) / per_round;
-        const long long cost = 128 * rounds * (tpp + OVERHEAD_TILES) + grid;         // in 1/128 tile times
-        if (best_cost < 0 || cost <= best_cost) {            // ties: the longer piece, fewer records to merge
-            best_cost = cost;
-            best = tpp;
-        }
+        const long long wgs = std::max<long long>(1, known ? std::min(grid, (total + tpp - 1) / tpp + items / 2) : grid);
+        if (tpp < longest_piece && ((sv.num_units == 0 && grid > STATIC_RECORDS) || (one && wgs > at_once))) break;
+        const bool doubled = (known ? wgs : S.n_pairs * full(own_tiles, tpp) + S.n_unit_pairs * full(unit_tiles, tpp)) > WORKGROUPS_PER_ROUND / 2;
+        const double piece = (double)std::min<long long>(tpp, longest);
+        double cost = START_US + std::max(total * TILE_HBM_US, piece * TILE_CU_US * (doubled ? 2 : 1));
+        const long long last_round = wgs % WORKGROUPS_PER_ROUND;
+        if (wgs > WORKGROUPS_PER_ROUND)
+            cost += START_US * 0.25 * (wgs / WORKGROUPS_PER_ROUND) +
+                    (last_round ? 0.5 * piece * TILE_CU_US * (1.0 - (double)last_round / WORKGROUPS_PER_ROUND) : 0.0);
+        if (S.n_unit_pairs > 0 || pieces(own_tiles, tpp) > 1) cost += MERGE_US;
+        cost += WORKGROUP_US * grid;
+        if (least < 0 || cost < least || (sv.planned_tiles == 0 && wgs <= at_once && cost <= 1.03 * least)) best = tpp;
+        if (least < 0 || cost < least) least = cost;
     }
     S.tiles_per_piece = best;
     S.pieces_max = (int)pieces(own_tiles, best);
     S.pieces_unit = (int)pieces(unit_tiles, best);
-    const long long total = sv.planned_tiles > 0 ? (long long)sv.planned_tiles * b.num_kv_heads : (long long)S.n_pairs * own_tiles + (long long)S.n_unit_pairs * unit_tiles;
     S.stream = total * BK * D * 4 >= STREAM_BYTES ? 1 : 0;
     return S;
 }
