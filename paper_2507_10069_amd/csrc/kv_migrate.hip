@@ -9,7 +9,15 @@
 // staging buffer).  The checksum rides along on the integer dot-product instruction: for the four bytes of a
 // word at offset i of the n-byte page, sum(d) and sum(k * d[k]) (v_dot4_u32_u8 with constants), from which
 //   A = 1 + sum over the page of d            B = n + sum over the page of (n - position) * d,  both mod 65521.
+//
+// A large move (STREAM) goes past the caches, loads and stores with the non-temporal hint: neither side is read again
+// here, and lines that wait to be written back hold up the reads.  8 requests of 18432 tokens (302 MB each way, pack +
+// unpack) 227 -> 199 us = 6.1 TB/s read + write, where the runtime's own copy of 2 GiB reaches 4.9; loads alone 203,
+// stores alone 220.  A small one is left in the caches, where the transport or the next kernel finds it (8 MB: 8.4 us, 8.6
+// with the hint); the line is drawn where pages and staging together exceed a quarter of the last-level cache.
 #include "emm_internal.h"
+
+#include <type_traits>
 
 namespace emm {
 
@@ -17,6 +25,7 @@ namespace {
 
 constexpr int THREADS = 256;
 constexpr unsigned ADLER_MOD = 65521;
+constexpr long long STREAM_BYTES = 64ll << 20;
 
 // wave sum of a 64-bit value
 __device__ inline unsigned long long wave_sum_u64(unsigned long long x)
@@ -29,8 +38,22 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long x)
     return x;
 }
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ inline u32x4 load16(const unsigned char* p)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load((const u32x4*)p);
+    else return *(const u32x4*)p;
+}
+template <bool STREAM>
+__device__ inline void store16(unsigned char* p, u32x4 w)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(w, (u32x4*)p);
+    else *(u32x4*)p = w;
+}
+
 // UNPACK = false: pools -> staging; true: staging -> pools.  page_bytes: one page of ONE pool.
-template <bool UNPACK>
+template <bool UNPACK, bool STREAM>
 __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __restrict__ k_cache,
                                                            unsigned char* __restrict__ v_cache,
                                                            unsigned char* __restrict__ staging,
@@ -49,13 +72,13 @@ __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __rest
     unsigned long long sum_d = 0, sum_w = 0;                              // sum of bytes, sum of (n - position) * byte
     constexpr int BATCH = 8;                                              // loads in flight per lane
     for (long long off0 = (long long)threadIdx.x * 16; off0 < n; off0 += (long long)BATCH * THREADS * 16) {
-        uint4 w[BATCH];
+        u32x4 w[BATCH];
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
             const long long off = off0 + (long long)u * THREADS * 16;
             if (off < n) {
                 const unsigned char* pool = off < page_bytes ? kp + off : vp + (off - page_bytes);
-                w[u] = UNPACK ? *(const uint4*)(sp + off) : *(const uint4*)pool;
+                w[u] = load16<STREAM>(UNPACK ? sp + off : pool);
             }
         }
 #pragma unroll
@@ -63,8 +86,8 @@ __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __rest
             const long long off = off0 + (long long)u * THREADS * 16;
             if (off < n) {
                 unsigned char* pool = off < page_bytes ? kp + off : vp + (off - page_bytes);
-                *(uint4*)(UNPACK ? pool : sp + off) = w[u];
-                const unsigned words[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+                store16<STREAM>(UNPACK ? pool : sp + off, w[u]);
+                const unsigned words[4] = {w[u][0], w[u][1], w[u][2], w[u][3]};
                 unsigned s_all = 0;                                       // of the 16 bytes: at most 4080
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -107,14 +130,16 @@ hipError_t launch_kv_pages(bool unpack, void* k_cache, void* v_cache, void* stag
                            uint32_t* mismatches, hipStream_t stream)
 {
     if (n == 0) return hipSuccess;
-    if (unpack)
-        hipLaunchKernelGGL(kv_pages_kernel<true>, dim3((unsigned)n), dim3(THREADS), 0, stream, (unsigned char*)k_cache,
-                           (unsigned char*)v_cache, (unsigned char*)staging, page_ids, num_pages, page_bytes, checksums,
-                           expected, mismatches);
-    else
-        hipLaunchKernelGGL(kv_pages_kernel<false>, dim3((unsigned)n), dim3(THREADS), 0, stream, (unsigned char*)k_cache,
-                           (unsigned char*)v_cache, (unsigned char*)staging, page_ids, num_pages, page_bytes, checksums,
-                           expected, mismatches);
+    auto go = [&](auto unpack_c, auto stream_c) {
+        hipLaunchKernelGGL((kv_pages_kernel<decltype(unpack_c)::value, decltype(stream_c)::value>), dim3((unsigned)n), dim3(THREADS), 0, stream,
+                           (unsigned char*)k_cache, (unsigned char*)v_cache, (unsigned char*)staging, page_ids, num_pages, page_bytes,
+                           checksums, expected, mismatches);
+    };
+    const bool streamed = 4 * page_bytes * n >= STREAM_BYTES;            // K and V pages and their staging
+    if (unpack && streamed) go(std::true_type{}, std::true_type{});
+    else if (unpack) go(std::true_type{}, std::false_type{});
+    else if (streamed) go(std::false_type{}, std::true_type{});
+    else go(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

@@ -659,6 +659,32 @@ def test_kv_page_migration_is_exact_and_checksummed():
     assert B.DeviceWorkload.to_numpy_bits(out).tobytes() == src_out
 
 
+@pytest.mark.parametrize("n,page_bytes", [(1023, 16384), (1024, 16384), (1500, 16384), (17, 1 << 20)])
+def test_kv_page_migration_past_the_caches(n, page_bytes):
+    """Either side of the size from which pages are moved with the non-temporal hint (4 n page_bytes = 64 MiB)."""
+    import zlib
+    print("case migrate", n, page_bytes, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    pools = [torch.randint(-128, 128, (n + 5, page_bytes), dtype=torch.int8, device="cuda", generator=g) for _ in range(2)]
+    ids = torch.randperm(n + 5, device="cuda", generator=g)[:n].to(torch.int32)
+    back = torch.randperm(n + 3, device="cuda", generator=g)[:n].to(torch.int32)
+    staging = torch.zeros((n, 2, page_bytes), dtype=torch.int8, device="cuda")
+    sums, sums_back = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    bad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    others = [torch.full((n + 3, page_bytes), 7, dtype=torch.int8, device="cuda") for _ in range(2)]
+    B.emm_kv_pages_pack(pools[0], pools[1], n + 5, page_bytes, ids, n, staging, sums)
+    B.emm_kv_pages_unpack(staging, back, n, others[0], others[1], n + 3, page_bytes, sums_back, sums, bad)
+    torch.cuda.synchronize()
+    assert int(bad) == 0 and torch.equal(sums, sums_back)
+    for i, (pool, other) in enumerate(zip(pools, others)):
+        assert torch.equal(staging[:, i], pool[ids.long()])
+        want = torch.full_like(other, 7)
+        want[back.long()] = pool[ids.long()]
+        assert torch.equal(other, want)
+    for p in (0, n // 2, n - 1):
+        assert zlib.adler32(staging[p].cpu().numpy().tobytes()) == int(sums[p]) & 0xffffffff
+
+
 def test_kv_page_checksum_of_the_largest_page():
     """Pages of 1 MiB per pool (the largest admitted: e.g. 16 KV heads x 256 tokens x 128 channels in bf16) filled
     with large byte values: the position-weighted sum of a 16-byte chunk alone passes 2^32 there.  Bytes and
