@@ -241,10 +241,18 @@ __device__ inline bool uneven_cuttable(int n_tiles, int k, int limit_min)
     return n_tiles - split >= MIN_TILES_PER_PART && (split + 1) * BC - 1 <= limit_min;
 }
 
-__device__ inline int wave_sum64(int x)                  // sum over the wave's 64 lanes, in every lane
+// Running sums over the wave's lanes, inclusive (the last lane holds the sum of all 64): six additions with a cross-lane
+// operand (row shifts by 1, 2, 4, 8, then the last lane of row 0 to row 1 and of row 2 to row 3, then of row 1 to rows 2 and
+// 3), about 60 cycles.  Every workgroup plans before it can ask for anything, so this is on its way to the first tile:
+// twelve exchanges through LDS for the sum and the running sums took 0.4 us of it.
+__device__ inline int wave_scan64(int x)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x += __shfl_xor(x, d, 64);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);      // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);      // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);      // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);      // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);     // row_bcast:31 into rows 2 and 3
     return x;
 }
 
@@ -279,7 +287,8 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
     const int lane_sp = xcd + NUM_XCD * pi;
     const int cnt = (pi < L.pairs_per_xcd && lane_sp < L.n_pairs)
                         ? sub_pair_tiles(safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false), G, L.fan, lane_sp) : 0;
-    const int total = __builtin_amdgcn_readfirstlane(wave_sum64(cnt));
+    const int incl = wave_scan64(cnt);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
     const int rem = total % CU_PER_XCD;
     const int parts = split_factor(rem, total / CU_PER_XCD, L.uneven);
     const int first_tail = total - rem;
@@ -297,12 +306,6 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         ordinal = first_tail + slot;
     }
     // the pair that holds this ordinal: the first one whose inclusive running count exceeds it
-    int incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d, 64);
-        if (pi >= d) incl += up;
-    }
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > ordinal);
     if (hit == 0) return u;
     const int hit_pi = __builtin_ctzll(hit);
@@ -626,9 +629,11 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         }
         load_k(t_begin, 0);
         load_v(t_begin, 0);
-        load_k(t_begin + 1, 1);
-        load_v(t_begin + 1, 1);
-        load_k(t_begin + 2, 2);
+        if (n_tiles > 1) {                                   // (a single tile, as short own parts have it, needs no others)
+            load_k(t_begin + 1, 1);
+            load_v(t_begin + 1, 1);
+            load_k(t_begin + 2, 2);
+        }
         __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0): this wave's rows have landed
         zero_v_tail(t_begin, 0);
         __syncthreads();
