@@ -139,7 +139,7 @@ constexpr int MIN_TILES_PER_PART = 16;                   // shorter pieces cost 
 constexpr int MIN_TILES_PER_PART_UNDERFILLED = 2;        // ... unless the compute units would stay idle otherwise (swept: 1 .. 12)
 constexpr int MIN_UNIT_TILES_UNDERFILLED = 24;           // ... and the unit is long enough to pay for the merge launch (measured)
 constexpr int SPLIT_MAX_PAIRS_PER_XCD = 64;              // planning scans an XCD's pairs, one per lane of a wave
-constexpr int PART_FLOATS = (64 + 2) * NTHREADS;         // per thread: 64 accumulator values, m, l
+constexpr int PART_FLOATS = (64 + 2) * NTHREADS;         // per thread: 64 accumulator values, in groups of four, then m, l
 // A build with -DEMM_TIMELINE (python -m paper_2507_10069_amd.build --timeline -> libemm_timeline.so) makes every
 // workgroup of the prefill kernel leave a 64-byte record of when and where it ran in the first TIMELINE_BYTES of
 // the workspace; bench.py --timeline reads them.  The regular build has none of it.
@@ -161,10 +161,13 @@ struct LaunchShape {
     int fan;                // sub-pairs per (request, KV head) pair: 1, 2, 4 or 8
     int uneven;             // 1: 17 .. 30 units in an XCD's last round are cut unevenly (see uneven_of)
     int ws_pieces;          // piece records per XCD that the workspace holds
+    int lent;               // 1: the fan XCDs of a pair share the units of the first of them (see plan_unit)
 };
 
 struct UnitPlan {
     int pair, tile;         // pair < 0: this workgroup has nothing to do
+    int xcd;                // where the records of its pieces lie
+    int half;               // 0, 1: rows of the first or second half only, where the unit has both; -1: all rows
     int parts, part;        // the unit's key tiles are cut into `parts` ranges; this workgroup does range `part`
     int slot;               // tail slot of the unit within its XCD (meaningful when parts > 1)
     bool rows_only;         // parts == 2 stands for a halving along the rows only (never a cut along the keys)
@@ -266,11 +269,18 @@ __device__ inline int wave_scan64(int x)
 // of the grid (sized for the longest request) has nothing to do.  All empty workgroups thus lie at the end of
 // the grid: the dispatcher hands out workgroups in order and waits when the next one does not fit anywhere,
 // so empty ones in between real ones (a batch of one long request and many short ones) would hold those up.
+// With L.lent (pairs dealt to several XCDs of which, no request having more than one row tile, only the first would have
+// anything to do) the `fan` XCDs of a pair take the units of the first one's list in turn; a single unit goes to two of
+// them by row halves, the first XCD rows 0 .. 127 of it and of all its pieces, the second rows 128 .. 255: four of a
+// workgroup's waves then work, one per SIMD, and a tile takes 60 % of the time.  Measured (28 / 4 heads): 16 requests of 4000 to 8000 cached and 2 to 30 new
+// tokens 96 -> 67 us, 30 of 2000 to 4000 and 2 to 36 92 -> 68 us (half of the XCDs had nothing to do), one request of 16384 + 36
+// 34.6 -> 32.9 us.
 // merge_idx >= 0 asks instead, whatever in_xcd is, for the plan of merge workgroup merge_idx of the XCD: the unit
 // in tail slot merge_idx / shares, with .part = merge_idx % shares, shares = parts (1 for an uneven cut).
 __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShape& L, int xcd, int in_xcd, int merge_idx = -1)
 {
     UnitPlan u;
+    u.half = -1; u.xcd = xcd;
     u.pair = -1; u.tile = 0; u.parts = 1; u.part = 0; u.slot = 0; u.rows_only = false; u.min_tiles = MIN_TILES_PER_PART; u.uneven = 0;
     if (!L.split) {
         if (merge_idx >= 0 || in_xcd >= L.pairs_per_xcd * L.n_row_tiles) return u;
@@ -282,13 +292,22 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         u.tile = sp % L.fan + L.fan * idx;
         return u;
     }
-    // lane pi looks at pair xcd + 8 pi
+    const int turn = L.lent ? xcd % L.fan : 0;               // this XCD's place among those that share a list
+    const int list_xcd = xcd - turn;                         // the one whose pairs hold the units
+    // lane pi looks at pair list_xcd + 8 pi
     const int pi = threadIdx.x & 63;
-    const int lane_sp = xcd + NUM_XCD * pi;
+    const int lane_sp = list_xcd + NUM_XCD * pi;
     const int cnt = (pi < L.pairs_per_xcd && lane_sp < L.n_pairs)
                         ? sub_pair_tiles(safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false), G, L.fan, lane_sp) : 0;
     const int incl = wave_scan64(cnt);
-    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int listed = __builtin_amdgcn_readlane(incl, 63);
+    const bool in_turns = L.lent && listed > 1;
+    if (L.lent && !in_turns) {
+        if (turn > 1 || (merge_idx >= 0 && turn == 1)) return u;
+        u.half = turn;
+        u.xcd = list_xcd;
+    }
+    const int total = in_turns ? (listed - turn + L.fan - 1) / L.fan : listed;     // units of this XCD
     const int rem = total % CU_PER_XCD;
     const int parts = split_factor(rem, total / CU_PER_XCD, L.uneven);
     const int first_tail = total - rem;
@@ -306,13 +325,14 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         ordinal = first_tail + slot;
     }
     // the pair that holds this ordinal: the first one whose inclusive running count exceeds it
-    const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > ordinal);
+    const int in_list = in_turns ? ordinal * L.fan + turn : ordinal;
+    const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > in_list);
     if (hit == 0) return u;
     const int hit_pi = __builtin_ctzll(hit);
     const int hit_incl = __builtin_amdgcn_readlane(incl, hit_pi);
-    const int hit_sp = xcd + NUM_XCD * hit_pi;
+    const int hit_sp = list_xcd + NUM_XCD * hit_pi;
     u.pair = hit_sp / L.fan;
-    u.tile = hit_sp % L.fan + L.fan * (hit_incl - 1 - ordinal);   // position = cnt - 1 - (ordinal - exclusive count)
+    u.tile = hit_sp % L.fan + L.fan * (hit_incl - 1 - in_list);   // position = cnt - 1 - (ordinal - exclusive count)
     if (parts > 1 && ordinal >= first_tail) {                // a tail unit
         u.parts = parts;
         u.part = part;
@@ -324,8 +344,9 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
     return u;
 }
 
-// Workspace: a timeline build's records, then the piece records, [xcd][tail slot x planned pieces per unit + piece]
-// [66][512] floats, ws_pieces of them per XCD.
+// Workspace: a timeline build's records, then the piece records, [xcd][tail slot x planned pieces per unit + piece],
+// ws_pieces of them per XCD.  A record is [16 groups][512 threads][4 registers], then [512 threads][m, l]: 16 and 8 bytes per
+// lane and instruction on both sides.
 __device__ inline float* part_base(void* workspace, int ws_pieces, int xcd, int slot, int parts, int part)
 {
     return (float*)((unsigned char*)workspace + TIMELINE_BYTES) + (size_t)(xcd * ws_pieces + slot * parts + part) * PART_FLOATS;
@@ -388,7 +409,11 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     // the row tile work in the regular workgroup, waves 4-7 in the workgroup of piece 1, the other four only
     // fetch.  Rows are independent, so nothing has to be merged, and with one working wave per SIMD a tile
     // takes about 60 % of the time.  (With at most half a tile of rows there is nothing to halve.)
-    int row_half = -1;                                       // -1: all eight waves work on their rows
+    int row_half = plan.half;                                // -1: all eight waves work on their rows
+    if (row_half >= 0 && n_rows - row0 <= BR / 2) {          // no rows in the second half: the first one's XCD does it all
+        if (row_half == 1) return;
+        row_half = -1;
+    }
     // into how many pieces the unit is really cut along the keys: as planned for its XCD, fewer if it is too
     // short for that, 1 if it cannot be cut at all or is only to be halved
     const int limit_first_row = CAUSAL ? P + row0 / G : P - 1;
@@ -398,7 +423,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     if (plan.uneven > 0 && cut == 1) {
         if (plan.part > 0) return;                           // too short to cut: the regular workgroup does it all
     } else if (plan.parts > 1 && cut == 1) {
-        const bool halve = n_rows - row0 > BR / 2;
+        const bool halve = row_half < 0 && n_rows - row0 > BR / 2;       // (not where another XCD does the other half)
         if (plan.part > (halve ? 1 : 0)) return;
         if (halve) row_half = plan.part;
         plan.part = 0;
@@ -943,14 +968,16 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
             // a piece of a cut unit: unnormalised accumulator, running maximum and row sum go to the
             // workspace, one coalesced row of 512 floats per register; attn_bf16_merge_kernel finishes
             if (!active) return;                             // a wave without rows has nothing to hand over
-            float* __restrict__ ws = part_base(a.workspace, L.ws_pieces, xcd, plan.slot, plan.parts, plan.part) + t2;
+            float* __restrict__ ws = part_base(a.workspace, L.ws_pieces, plan.xcd, plan.slot, plan.parts, plan.part);
             const float l_part = pair_sum(l_run);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) ws[(16 * nb + v) * NTHREADS] = o_acc[nb][v];
-            ws[64 * NTHREADS] = mc_run;
-            ws[65 * NTHREADS] = l_part;
+                for (int v4 = 0; v4 < 4; ++v4)
+                    *(f32x4*)(ws + ((4 * nb + v4) * NTHREADS + t2) * 4) =
+                        f32x4{o_acc[nb][4 * v4], o_acc[nb][4 * v4 + 1], o_acc[nb][4 * v4 + 2], o_acc[nb][4 * v4 + 3]};
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            *(f32x2*)(ws + 64 * NTHREADS + 2 * t2) = f32x2{mc_run, l_part};
             return;
         }
         // The normalised rows go to global memory through LDS, so that a store instruction writes four whole
@@ -1047,28 +1074,36 @@ __device__ inline void merge_share(const float* __restrict__ ws0, unsigned tid, 
 {
     // ws0 is the same for the whole workgroup and tid a 32-bit offset: loads with a scalar base, no address registers
     constexpr int REGS = 64 / SHARES;
-    float m_part[PARTS], l_part[PARTS], val[PARTS][REGS];
+    constexpr int W = REGS < 4 ? REGS : 4;                   // registers of a group that this share takes
+    typedef float f32xw __attribute__((ext_vector_type(W)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    f32x2 ml[PARTS];
+    f32xw val[PARTS][REGS / W];
 #pragma unroll
     for (int j = 0; j < PARTS; ++j) {
-        const float* __restrict__ wsj = ws0 + (size_t)min(j, cut - 1) * PART_FLOATS;
-        m_part[j] = (wsj + 64 * NTHREADS)[tid];
-        l_part[j] = (wsj + 65 * NTHREADS)[tid];
+        // byte offset of the record (at most 32 of 135168 bytes), added per lane: folded into the base addresses, the
+        // compiler would keep a pair of scalar registers for each of up to 32 pieces and run out of them
+        uint32_t at_ml, at_val;
+        const uint32_t rec = (uint32_t)min(j, cut - 1) * (PART_FLOATS * 4), reg = sub * REGS;
+        asm("v_add_u32_e32 %0, %1, %2" : "=v"(at_ml) : "s"(rec + 64 * NTHREADS * 4), "v"(8 * tid));
+        asm("v_add_u32_e32 %0, %1, %2" : "=v"(at_val) : "s"(rec + (reg >> 2) * (16 * NTHREADS) + (reg & 3) * 4), "v"(16 * tid));
+        ml[j] = *(const f32x2*)((const char*)ws0 + at_ml);
 #pragma unroll
-        for (int i = 0; i < REGS; ++i) val[j][i] = (wsj + (size_t)(sub * REGS + i) * NTHREADS)[tid];
+        for (int i = 0; i < REGS / W; ++i) val[j][i] = *(const f32xw*)((const char*)ws0 + at_val + i * (16 * NTHREADS));
     }
     float m_all = -INFINITY;
 #pragma unroll
     for (int j = 0; j < PARTS; ++j)
-        if (j < cut) m_all = fmaxf(m_all, m_part[j]);
+        if (j < cut) m_all = fmaxf(m_all, ml[j][0]);
     float l_tot = 0.f, acc[REGS];
 #pragma unroll
     for (int i = 0; i < REGS; ++i) acc[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < PARTS; ++j) {
-        const float w = j < cut ? __builtin_amdgcn_exp2f(m_part[j] - m_all) : 0.f;
-        l_tot += w * l_part[j];
+        const float w = j < cut ? __builtin_amdgcn_exp2f(ml[j][0] - m_all) : 0.f;
+        l_tot += w * ml[j][1];
 #pragma unroll
-        for (int i = 0; i < REGS; ++i) acc[i] += w * val[j][i];
+        for (int i = 0; i < REGS; ++i) acc[i] += w * val[j][i / W][i % W];
     }
     const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
     // register 4g + e of a thread is channel 32 (g / 4) + 8 (g % 4) + 4 h32 + e
@@ -1195,6 +1230,7 @@ static void launch_shape(const BatchView& b, bool has_workspace, LaunchShape& L,
             any = any || split_factor((int)(units[x] % CU_PER_XCD), (int)(units[x] / CU_PER_XCD), L.uneven) > 1;
         if (!any) L.split = 0;
     }
+    L.lent = (L.split && fan > 1 && n_pair_tiles == 1) ? 1 : 0;
     L.ws_pieces = 0;
     if (L.split && long_enough_to_cut(b)) {
         // Piece records of an XCD: tail slot x planned pieces + piece.  r units left over are planned for p pieces

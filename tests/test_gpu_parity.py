@@ -218,6 +218,32 @@ def test_cut_thresholds_sweep(kind, n_req):
             _compare(wl, dw)
 
 
+# requests of different lengths with one row tile each on fewer than 8 KV heads: the XCDs of a pair take the units in turns;
+# a single unit goes to two XCDs by row halves (more than 128 rows) or to one
+LENT_CASES = [
+    ("one_full", "causal", 28, 4, [16384 // 4], [36]), ("one_short", "causal", 28, 4, [3000], [5]), ("one_129_rows", "causal", 43, 1, [2500], [3]),
+    ("one_128_rows", "causal", 64, 1, [2500], [2]), ("two_heads", "causal", 14, 2, [4100, 700], [18, 3]), ("short_context", "causal", 28, 4, [60], [30]),
+    ("ragged_few", "causal", 28, 4, [1500, 3000, 40, 2222, 900], [36, 2, 17, 0, 9]), ("ragged_one_head", "causal", 7, 1, [1800] * 9, [3, 36, 20, 1, 0, 12, 30, 36, 2]),
+    ("ragged_two_heads", "cross", 16, 2, [1700, 0, 3333, 1601, 400, 2900], [32, 5, 31, 16, 8, 1]),
+    ("ragged_uneven_cut", "causal", 8, 4, [2100 + 7 * i for i in range(40)], [2 + i % 3 for i in range(40)]),
+    ("ragged_many", "causal", 8, 4, [300 + 40 * (i % 9) for i in range(90)], [1 + i % 5 for i in range(90)]),
+]
+
+
+@pytest.mark.parametrize("name,kind,H,Hkv,prefix,new", LENT_CASES)
+def test_single_row_tiles_shared_among_xcds(name, kind, H, Hkv, prefix, new):
+    print("case lent", name, flush=True)
+    wl = W.build_workload("lent_" + name, kind, "bf16", 790, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=prefix, new_lens=new)
+    dw = B.DeviceWorkload(wl)
+    if dw.workspace is not None:
+        dw.workspace.fill_(0xff)                             # NaN wherever no record is written
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+
+
 @pytest.mark.parametrize("H,Hkv,prefix,new", [(4, 1, [300], [700]), (8, 2, [0], [1500]), (6, 1, [70, 0, 513], [300, 90, 64]),
                                               (8, 4, [129], [1]), (2, 1, [5000], [1100])])
 def test_few_pairs_spread_over_xcds(H, Hkv, prefix, new):
