@@ -1064,66 +1064,98 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
     attend_unit<CAUSAL, false>(a, L, xcd, in_xcd, plan, smem);
 }
 
-// One workgroup's share of the merge of a unit planned for PARTS pieces and cut into `cut` of them: REGS = 64 / SHARES
-// consecutive ones of each thread's 64 accumulator registers (32 pieces: 32 shares of 2 registers, so that what is
-// in flight fits the register file).  Every load is issued whatever `cut` is (pieces past the last repeat it,
-// with weight 0), all of them before the first use, so that one memory latency covers them.
+// One workgroup's share of the merge of a unit planned for PARTS pieces and cut into `cut` of them: the columns (threads of
+// the main kernel, see part_base) sub * COLS .. + COLS - 1 of every piece.  Bound by memory latency and by the records'
+// bytes, which are read once: a thread takes the 16 bytes of one column and register group from each piece, 16 loads in
+// all before the first use, and (m, l) of one column and piece, from which all weights are made in LDS meanwhile.  (With shares
+// by registers every share read all (m, l): as many bytes again for 32 pieces.)  Pieces past the last repeat it, with weight 0.
 template <int PARTS, int SHARES = PARTS>
-__device__ inline void merge_share(const float* __restrict__ ws0, unsigned tid, int cut, int sub,
-                                   __bf16* __restrict__ op, int h32, float* __restrict__ lse)
+__device__ inline void merge_share(const float* __restrict__ ws0, float* lds, int cut, int sub, int row0, int n_rows, int G, int kvh,
+                                   long long first_row, const AttnArgs& a)
 {
-    // ws0 is the same for the whole workgroup and tid a 32-bit offset: loads with a scalar base, no address registers
-    constexpr int REGS = 64 / SHARES;
-    constexpr int W = REGS < 4 ? REGS : 4;                   // registers of a group that this share takes
-    typedef float f32xw __attribute__((ext_vector_type(W)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
-    f32x2 ml[PARTS];
-    f32xw val[PARTS][REGS / W];
+    constexpr int COLS = NTHREADS / SHARES;                  // columns of this share
+    constexpr int PER = PARTS > 16 ? 16 : PARTS;             // pieces a thread reads of one (column, group)
+    constexpr int SPLIT = PARTS / PER;                       // threads that share a (column, group)
+    constexpr int ITEMS = COLS * 16 * SPLIT / NTHREADS;      // (column, group)s of a thread
+    constexpr int MLS = PARTS * COLS / NTHREADS;             // (m, l)s of a thread: 1, or 2 for an uneven cut
+    static_assert(ITEMS * PER <= 32 && NTHREADS % (16 * SPLIT) == 0, "loads in flight per thread");
+    const int tid = threadIdx.x;
+    // column `col` of the unit's 512: does it hold a row?
+    auto row_of = [&](int col) { return row0 + (col >> 6) * 32 + (col & 31); };
+    float* m_s = lds;                                        // [PARTS][COLS], then the weights
+    float* wl_s = lds + PARTS * COLS;                        // [PARTS][COLS]: weight times l
+    f32x2 ml[MLS];
 #pragma unroll
-    for (int j = 0; j < PARTS; ++j) {
-        // byte offset of the record (at most 32 of 135168 bytes), added per lane: folded into the base addresses, the
-        // compiler would keep a pair of scalar registers for each of up to 32 pieces and run out of them
-        uint32_t at_ml, at_val;
-        const uint32_t rec = (uint32_t)min(j, cut - 1) * (PART_FLOATS * 4), reg = sub * REGS;
-        asm("v_add_u32_e32 %0, %1, %2" : "=v"(at_ml) : "s"(rec + 64 * NTHREADS * 4), "v"(8 * tid));
-        asm("v_add_u32_e32 %0, %1, %2" : "=v"(at_val) : "s"(rec + (reg >> 2) * (16 * NTHREADS) + (reg & 3) * 4), "v"(16 * tid));
-        ml[j] = *(const f32x2*)((const char*)ws0 + at_ml);
-#pragma unroll
-        for (int i = 0; i < REGS / W; ++i) val[j][i] = *(const f32xw*)((const char*)ws0 + at_val + i * (16 * NTHREADS));
+    for (int u = 0; u < MLS; ++u) {
+        const int idx = tid + u * NTHREADS, j = idx / COLS, col = sub * COLS + idx % COLS;
+        ml[u] = *(const f32x2*)(ws0 + (size_t)min(j, cut - 1) * PART_FLOATS + 64 * NTHREADS + 2 * col);
     }
-    float m_all = -INFINITY;
+    f32x4 val[ITEMS][PER];
 #pragma unroll
-    for (int j = 0; j < PARTS; ++j)
-        if (j < cut) m_all = fmaxf(m_all, ml[j][0]);
-    float l_tot = 0.f, acc[REGS];
+    for (int it = 0; it < ITEMS; ++it) {
+        const int idx = tid + it * NTHREADS, col = sub * COLS + idx % COLS, rest = idx / COLS, group = rest & 15, half = rest >> 4;
+        if (row_of(col) < n_rows)
 #pragma unroll
-    for (int i = 0; i < REGS; ++i) acc[i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < PARTS; ++j) {
-        const float w = j < cut ? __builtin_amdgcn_exp2f(ml[j][0] - m_all) : 0.f;
-        l_tot += w * ml[j][1];
-#pragma unroll
-        for (int i = 0; i < REGS; ++i) acc[i] += w * val[j][i / W][i % W];
+            for (int u = 0; u < PER; ++u)
+                val[it][u] = *(const f32x4*)(ws0 + (size_t)min(half * PER + u, cut - 1) * PART_FLOATS + (group * NTHREADS + col) * 4);
     }
-    const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-    // register 4g + e of a thread is channel 32 (g / 4) + 8 (g % 4) + 4 h32 + e
-    if constexpr (REGS == 2) {
-        const int g = sub >> 1;
-        bf16x2 o;
-        o[0] = (__bf16)(acc[0] * inv);
-        o[1] = (__bf16)(acc[1] * inv);
-        *(bf16x2*)(op + 32 * (g >> 2) + 8 * (g & 3) + 4 * h32 + 2 * (sub & 1)) = o;
-    } else {
 #pragma unroll
-        for (int i = 0; i < REGS / 4; ++i) {
-            const int g = sub * (REGS / 4) + i;
+    for (int u = 0; u < MLS; ++u) m_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? ml[u][0] : -INFINITY;
+    __syncthreads();
+    float w[MLS];
+#pragma unroll
+    for (int u = 0; u < MLS; ++u) {
+        const int c = (tid + u * NTHREADS) % COLS;
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < PARTS; ++j) m_all = fmaxf(m_all, m_s[j * COLS + c]);
+        w[u] = (tid + u * NTHREADS) / COLS < cut ? __builtin_amdgcn_exp2f(ml[u][0] - m_all) : 0.f;
+        if ((tid + u * NTHREADS) / COLS == 0) ml[u][0] = m_all;                   // for lse, by the threads of piece 0
+    }
+    __syncthreads();                                         // all maxima have been taken
+#pragma unroll
+    for (int u = 0; u < MLS; ++u) {
+        m_s[tid + u * NTHREADS] = w[u];
+        wl_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? w[u] * ml[u][1] : 0.f;
+    }
+    __syncthreads();
+    float* half_s = wl_s + PARTS * COLS;                     // [COLS * 16][4]: sums of the second half of 32 pieces
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int idx = tid + it * NTHREADS, c = idx % COLS, col = sub * COLS + c, rest = idx / COLS, group = rest & 15, half = rest >> 4;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const float wj = m_s[(half * PER + u) * COLS + c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += wj * val[it][u][e];
+        }
+        if constexpr (SPLIT > 1) {
+            static_assert(SPLIT <= 2 && ITEMS == 1, "two halves, one item");
+            if (half == 1) *(f32x4*)(half_s + (idx - COLS * 16) * 4) = acc;
+            __syncthreads();
+            if (half == 1) return;
+            acc += *(const f32x4*)(half_s + idx * 4);
+        }
+        const int row = row_of(col);
+        if (row < n_rows) {
+            float l_tot = 0.f;
+#pragma unroll
+            for (int j = 0; j < PARTS; ++j) l_tot += wl_s[j * COLS + c];
+            const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
+            const int tok = row / G, h32 = (col >> 5) & 1;
+            const long long at = (first_row + tok) * a.b.num_q_heads + kvh * G + (row - tok * G);
+            // register 4 group + e of a column is channel 32 (group / 4) + 8 (group % 4) + 4 h32 + e
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[4 * i + e] * inv);
-            *(bf16x4*)(op + 32 * (g >> 2) + 8 * (g & 3) + 4 * h32) = o;
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] * inv);
+            *(bf16x4*)((__bf16*)a.out + at * D + 32 * (group >> 2) + 8 * (group & 3) + 4 * h32) = o;
+            // the thread that holds m_all of this column is the one of piece 0: with group 0 and half 0 it is this one
+            if (a.lse != nullptr && group == 0 && h32 == 0)
+                a.lse[at] = (l_tot > 0.f) ? ml[it < MLS ? it : 0][0] * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
         }
     }
-    if (lse != nullptr) *lse = (l_tot > 0.f) ? m_all * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
 }
 
 // Merges the pieces of the cut units, thread for thread the layout of the main kernel's epilogue.  An XCD
@@ -1152,26 +1184,19 @@ __global__ __launch_bounds__(NTHREADS) void attn_bf16_merge_kernel(AttnArgs a, L
                                       : pieces_cut((kv_len + BC - 1) / BC, plan.parts, limit_first_row, plan.min_tiles);
     if (cut == 1) return;                                    // not cut along the keys
 
-    const int tid = threadIdx.x;
-    const int l32 = tid & 31, h32 = (tid >> 5) & 1;
-    const int row = row0 + (tid >> 6) * 32 + l32;
-    if (row >= n_rows) return;
-    const int tok = row / G;
-    const int hq = kvh * G + (row - tok * G);
-    const long long q_row = (long long)safe_first_row(b, r, N) + tok;
+    const long long first_row = safe_first_row(b, r, N);
     const float* __restrict__ ws0 = part_base(a.workspace, L.ws_pieces, xcd, plan.slot, plan.parts, 0);
-    __bf16* __restrict__ op = (__bf16*)a.out + (q_row * b.num_q_heads + hq) * D;
-    float* lse = (a.lse != nullptr && h32 == 0 && plan.part == 0) ? a.lse + q_row * b.num_q_heads + hq : nullptr;
+    __shared__ __attribute__((aligned(16))) float lds[4 * NTHREADS + 4 * NTHREADS / 2];
     if (plan.uneven > 0) {
-        merge_share<2, 1>(ws0, tid, cut, 0, op, h32, lse);
+        merge_share<2, 1>(ws0, lds, cut, 0, row0, n_rows, G, kvh, first_row, a);
         return;
     }
     switch (plan.parts) {
-        case 2: merge_share<2>(ws0, tid, cut, plan.part, op, h32, lse); break;
-        case 4: merge_share<4>(ws0, tid, cut, plan.part, op, h32, lse); break;
-        case 8: merge_share<8>(ws0, tid, cut, plan.part, op, h32, lse); break;
-        case 16: merge_share<16>(ws0, tid, cut, plan.part, op, h32, lse); break;
-        default: merge_share<32>(ws0, tid, cut, plan.part, op, h32, lse); break;
+        case 2: merge_share<2>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
+        case 4: merge_share<4>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
+        case 8: merge_share<8>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
+        case 16: merge_share<16>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
+        default: merge_share<32>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
     }
 }
 
