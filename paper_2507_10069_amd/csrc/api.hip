@@ -77,6 +77,18 @@ emm::SharedPrefixView shared_view_of(const emm_shared_prefix* sp)
                                  sp->max_unit_tiles};
 }
 
+// The plan of a decode batch with the units and hints of `sp`, if they are such as the header allows.
+emm_status plan_decode_shared(const emm_batch* b, const emm::BatchView& v, const emm_shared_prefix* sp, emm::DecodeShape* shape)
+{
+    if (sp->num_units < 0 || sp->num_units > b->num_reqs / 2 || sp->planned_tiles < 0 || sp->max_own_tiles < 0 ||
+        sp->max_unit_tiles < 0)
+        return EMM_ERR_INVALID_ARG;
+    if (b->max_new_len > 1) return EMM_ERR_INVALID_ARG;
+    if (b->dtype != EMM_BF16 || !emm::attn_bf16_decode_applies(v)) return EMM_ERR_UNSUPPORTED;
+    *shape = emm::attn_bf16_decode_shape(v, shared_view_of(sp));
+    return EMM_OK;
+}
+
 // sp: shared-prefix units of a decode batch, or nullptr
 emm_status attention(const emm_batch* b, const void* q, const void* k_cache, const void* v_cache, void* out,
                      float* lse, void* workspace, size_t workspace_bytes, void* hip_stream, int causal,
@@ -92,13 +104,21 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
         if (sp->num_units == 0 && sp->planned_tiles == 0 && sp->max_own_tiles == 0) sp = nullptr;
     }
     if (fused && sp == nullptr) sp = &no_units;              // the fused step goes through the same planner
+    const emm::BatchView view = view_of(b);
+    const bool decode = b->dtype == EMM_BF16 && emm::attn_bf16_decode_applies(view);
+    emm::DecodeShape shape = {};                             // planned here, for the workspace check and the launch alike
     size_t need = 0;
-    st = sp != nullptr ? emm_decode_attn_shared_workspace_size(b, sp, &need)
-                       : emm_prefill_attn_workspace_size(b, &need);
-    if (st != EMM_OK) return st;
+    if (sp != nullptr) {
+        st = plan_decode_shared(b, view, sp, &shape);
+        if (st != EMM_OK) return st;
+    } else if (decode) {
+        shape = emm::attn_bf16_decode_shape(view, emm::SharedPrefixView{});
+    }
+    if (sp != nullptr || decode) need = emm::attn_bf16_decode_workspace_bytes(shape);
+    else if (b->dtype == EMM_BF16) need = emm::attn_bf16_d128_workspace_bytes(view);
     if (static_scratch) {
         // the decode kernels with the library's own fixed array in place of a workspace
-        if (b->dtype != EMM_BF16 || !emm::attn_bf16_decode_applies(view_of(b))) return EMM_ERR_UNSUPPORTED;
+        if (!decode) return EMM_ERR_UNSUPPORTED;
         if (need > emm::attn_bf16_decode_static_scratch_bytes()) return EMM_ERR_WORKSPACE;
         workspace = nullptr;
         workspace_bytes = need;
@@ -122,7 +142,7 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     if (b->num_pages == 0 || b->max_pages_per_req == 0) return EMM_ERR_INVALID_ARG;
 
     emm::AttnArgs args;
-    args.b = view_of(b);
+    args.b = view;
     args.q = q;
     args.k_cache = k_cache;
     args.v_cache = v_cache;
@@ -134,14 +154,10 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     args.v_new = v_new;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t err;
-    if (static_scratch) {
-        err = emm::launch_attn_bf16_decode_static(args, stream);
-    } else if (sp != nullptr) {
-        const emm::SharedPrefixView sv = shared_view_of(sp);
-        err = fused ? emm::launch_attn_bf16_decode_step(args, sv, stream)
-                    : emm::launch_attn_bf16_decode_shared(args, sv, stream);
-    } else if (b->dtype != EMM_BF16) err = emm::launch_attn_f32(args, stream);
-    else if (emm::attn_bf16_decode_applies(args.b)) err = emm::launch_attn_bf16_decode(args, stream);
+    if (static_scratch) err = emm::launch_attn_bf16_decode_static(args, shape, stream);
+    else if (sp != nullptr) err = emm::launch_attn_bf16_decode(args, shared_view_of(sp), shape, fused, stream);
+    else if (b->dtype != EMM_BF16) err = emm::launch_attn_f32(args, stream);
+    else if (decode) err = emm::launch_attn_bf16_decode(args, emm::SharedPrefixView{}, shape, false, stream);
     else err = emm::launch_attn_bf16_d128(args, stream);
     return err == hipSuccess ? EMM_OK : EMM_ERR_LAUNCH;
 }
@@ -180,7 +196,7 @@ emm_status emm_prefill_attn_workspace_size(const emm_batch* b, size_t* bytes)
     if (st != EMM_OK) return st;
     if (b->dtype == EMM_BF16) {
         const emm::BatchView v = view_of(b);
-        *bytes = emm::attn_bf16_decode_applies(v) ? emm::attn_bf16_decode_workspace_bytes(v)
+        *bytes = emm::attn_bf16_decode_applies(v) ? emm::attn_bf16_decode_workspace_bytes(emm::attn_bf16_decode_shape(v, emm::SharedPrefixView{}))
                                                   : emm::attn_bf16_d128_workspace_bytes(v);
     }
     return EMM_OK;
@@ -217,13 +233,10 @@ emm_status emm_decode_attn_shared_workspace_size(const emm_batch* b, const emm_s
     if (st != EMM_OK) return st;
     static const emm_shared_prefix no_units = {};
     if (sp == nullptr) sp = &no_units;
-    if (sp->num_units < 0 || sp->num_units > b->num_reqs / 2 || sp->planned_tiles < 0 || sp->max_own_tiles < 0 ||
-        sp->max_unit_tiles < 0)
-        return EMM_ERR_INVALID_ARG;
-    if (b->max_new_len > 1) return EMM_ERR_INVALID_ARG;
-    const emm::BatchView v = view_of(b);
-    if (b->dtype != EMM_BF16 || !emm::attn_bf16_decode_applies(v)) return EMM_ERR_UNSUPPORTED;
-    *bytes = emm::attn_bf16_decode_shared_workspace_bytes(v, shared_view_of(sp));
+    emm::DecodeShape shape;
+    st = plan_decode_shared(b, view_of(b), sp, &shape);
+    if (st != EMM_OK) return st;
+    *bytes = emm::attn_bf16_decode_workspace_bytes(shape);
     return EMM_OK;
 }
 

@@ -58,19 +58,10 @@ constexpr int NSLOT = 2;                         // blocks a wave's ring holds; 
 constexpr int RING_BYTES = NSLOT * 2 * BLOCK_BYTES;      // of one wave: slots of a K block and a V block
 constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // a wave's blocks of a piece: at most 62, one page id per lane
 constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 256 CUs
-constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see decode_shape
+constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see attn_bf16_decode_shape
 constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
 static_assert(NW * MAX_G * REC_FLOATS * 4 <= NW * RING_BYTES, "the merge across waves reuses the rings");
 static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
-
-struct DecodeShape {
-    int n_pairs;            // (request, KV head) pairs
-    int n_unit_pairs;       // (shared-prefix unit, KV head) pairs
-    int tiles_per_piece;    // 32-key tiles per workgroup
-    int pieces_max;         // workgroups per pair in the grid (a pair uses as many as its context needs)
-    int pieces_unit;        // workgroups per (unit, KV head) pair in the grid
-    int stream;             // 1: K and V that one workgroup alone reads are fetched past the caches (see STREAM_BYTES)
-};
 
 __device__ inline int pieces_of(int kv_len, int tiles_per_piece)
 {
@@ -565,7 +556,9 @@ constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 // requests on 8 videos without units: 115 -> 154 us): each wave looks whether another request holds its first page.
 constexpr long long STREAM_BYTES = 96ll << 20;
 
-DecodeShape decode_shape(const BatchView& b, const SharedPrefixView& sv = SharedPrefixView{})
+}  // namespace
+
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
 {
     DecodeShape S;
     S.n_pairs = b.num_reqs * b.num_kv_heads;
@@ -609,33 +602,23 @@ DecodeShape decode_shape(const BatchView& b, const SharedPrefixView& sv = Shared
     return S;
 }
 
-}  // namespace
-
 bool attn_bf16_decode_applies(const BatchView& b)
 {
     return b.max_new_len <= 1 && b.num_q_heads / b.num_kv_heads <= MAX_G;
 }
 
-size_t attn_bf16_decode_workspace_bytes(const BatchView& b)
+size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S)
 {
-    const DecodeShape S = decode_shape(b);
-    return (size_t)S.n_pairs * S.pieces_max * MAX_G * REC_FLOATS * sizeof(float);
-}
-
-size_t attn_bf16_decode_shared_workspace_bytes(const BatchView& b, const SharedPrefixView& sv)
-{
-    const DecodeShape S = decode_shape(b, sv);
     return (unit_records_offset(S) + (size_t)S.n_unit_pairs * S.pieces_unit * MAX_ROWS * REC_FLOATS) * sizeof(float);
 }
 
 namespace {
 
 template <bool SHARED, bool FUSED>
-hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, hipStream_t stream)
+hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, hipStream_t stream)
 {
     const BatchView& b = a.b;
     if (b.total_new_tokens == 0 || b.num_reqs == 0) return hipSuccess;
-    const DecodeShape S = decode_shape(b, sv);
     // the requests' own workgroups first, then (SHARED) those of the units' shared parts
     const long long grid = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit;
     if (grid > 0x3fffffff) return hipErrorInvalidValue;
@@ -662,9 +645,11 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, hipStrea
 
 }  // namespace
 
-hipError_t launch_attn_bf16_decode(const AttnArgs& a, hipStream_t stream)
+hipError_t launch_attn_bf16_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, bool fused, hipStream_t stream)
 {
-    return launch_decode<false, false>(a, SharedPrefixView{}, stream);
+    // without units only the bounds matter: the plain kernels, cut by the sharper plan
+    if (sv.num_units > 0) return fused ? launch_decode<true, true>(a, sv, S, stream) : launch_decode<true, false>(a, sv, S, stream);
+    return fused ? launch_decode<false, true>(a, sv, S, stream) : launch_decode<false, false>(a, sv, S, stream);
 }
 
 // ---- The same launch for callers that cannot allocate (code under HIP graph capture, serving loops, harnesses
@@ -684,9 +669,9 @@ std::mutex scratch_lock;
 
 size_t attn_bf16_decode_static_scratch_bytes() { return STATIC_SCRATCH_BYTES; }
 
-hipError_t launch_attn_bf16_decode_static(AttnArgs a, hipStream_t stream)
+hipError_t launch_attn_bf16_decode_static(AttnArgs a, const DecodeShape& S, hipStream_t stream)
 {
-    if (attn_bf16_decode_workspace_bytes(a.b) > STATIC_SCRATCH_BYTES) return hipErrorInvalidValue;
+    if (attn_bf16_decode_workspace_bytes(S) > STATIC_SCRATCH_BYTES) return hipErrorInvalidValue;
     int dev = -1;
     hipError_t err = hipGetDevice(&dev);
     if (err != hipSuccess) return err;
@@ -705,18 +690,7 @@ hipError_t launch_attn_bf16_decode_static(AttnArgs a, hipStream_t stream)
     // The kernels write every record they later read (no counters or flags, nothing that must start at zero), so
     // what an earlier call left in the array does not matter.
     a.workspace = ptr;
-    return launch_decode<false, false>(a, SharedPrefixView{}, stream);
-}
-
-hipError_t launch_attn_bf16_decode_shared(const AttnArgs& a, const SharedPrefixView& sv, hipStream_t stream)
-{
-    // without units only the bounds matter: the plain kernels, cut by the sharper plan
-    return sv.num_units > 0 ? launch_decode<true, false>(a, sv, stream) : launch_decode<false, false>(a, sv, stream);
-}
-
-hipError_t launch_attn_bf16_decode_step(const AttnArgs& a, const SharedPrefixView& sv, hipStream_t stream)
-{
-    return sv.num_units > 0 ? launch_decode<true, true>(a, sv, stream) : launch_decode<false, true>(a, sv, stream);
+    return launch_decode<false, false>(a, SharedPrefixView{}, S, stream);
 }
 
 }  // namespace emm

@@ -81,17 +81,25 @@ void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool 
                               int32_t* units, int32_t* pieces, int32_t* uneven_k, int32_t* rows_only);
 // decode step (every request has at most one query token, at most 16 query heads per KV head)
 bool attn_bf16_decode_applies(const BatchView& b);
-size_t attn_bf16_decode_workspace_bytes(const BatchView& b);
-hipError_t launch_attn_bf16_decode(const AttnArgs& a, hipStream_t stream);
-// the same with the piece records in the library's own fixed device array (no workspace of the caller's); fails with
+// How a decode batch is cut and how many bytes its records take: made once per call, from what the host knows
+// (SharedPrefixView{}: no units, no hints).
+struct DecodeShape {
+    int n_pairs;            // (request, KV head) pairs
+    int n_unit_pairs;       // (shared-prefix unit, KV head) pairs
+    int tiles_per_piece;    // 32-key tiles per workgroup
+    int pieces_max;         // workgroups per pair in the grid (a pair uses as many as its context needs)
+    int pieces_unit;        // workgroups per (unit, KV head) pair in the grid
+    int stream;             // 1: K and V that one workgroup alone reads are fetched past the caches (see STREAM_BYTES)
+};
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv);
+size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S);
+// attention of the batch, with sv's units if it has any; fused: with the scatter of the query tokens' own K/V rows too (a.k_new,
+// a.v_new; pools writable; causal)
+hipError_t launch_attn_bf16_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, bool fused, hipStream_t stream);
+// without units, and with the piece records in the library's own fixed device array (no workspace of the caller's); fails with
 // hipErrorInvalidValue when the batch needs more than attn_bf16_decode_static_scratch_bytes()
 size_t attn_bf16_decode_static_scratch_bytes();
-hipError_t launch_attn_bf16_decode_static(AttnArgs a, hipStream_t stream);
-// the same with shared-prefix units (sv.num_units >= 1)
-size_t attn_bf16_decode_shared_workspace_bytes(const BatchView& b, const SharedPrefixView& sv);
-hipError_t launch_attn_bf16_decode_shared(const AttnArgs& a, const SharedPrefixView& sv, hipStream_t stream);
-// the same, fused with the scatter of the query tokens' own K/V rows (a.k_new, a.v_new; pools writable; causal)
-hipError_t launch_attn_bf16_decode_step(const AttnArgs& a, const SharedPrefixView& sv, hipStream_t stream);
+hipError_t launch_attn_bf16_decode_static(AttnArgs a, const DecodeShape& S, hipStream_t stream);
 
 // merge of two attention results of the same rows over disjoint key sets (prefill with shared prefixes): out and lse
 // hold the second part on entry and the merged result on return; rows of requests with req_shared_len <= 0 stay
