@@ -161,7 +161,6 @@ struct LaunchShape {
     int fan;                // sub-pairs per (request, KV head) pair: 1, 2, 4 or 8
     int uneven;             // 1: 17 .. 30 units in an XCD's last round are cut unevenly (see uneven_of)
     int ws_pieces;          // piece records per XCD that the workspace holds
-    int lent;               // 1: the fan XCDs of a pair share the units of the first of them (see plan_unit)
 };
 
 struct UnitPlan {
@@ -269,12 +268,14 @@ __device__ inline int wave_scan64(int x)
 // of the grid (sized for the longest request) has nothing to do.  All empty workgroups thus lie at the end of
 // the grid: the dispatcher hands out workgroups in order and waits when the next one does not fit anywhere,
 // so empty ones in between real ones (a batch of one long request and many short ones) would hold those up.
-// With L.lent (pairs dealt to several XCDs of which, no request having more than one row tile, only the first would have
-// anything to do) the `fan` XCDs of a pair take the units of the first one's list in turn; a single unit goes to two of
-// them by row halves, the first XCD rows 0 .. 127 of it and of all its pieces, the second rows 128 .. 255: four of a
-// workgroup's waves then work, one per SIMD, and a tile takes 60 % of the time.  Measured (28 / 4 heads): 16 requests of 4000 to 8000 cached and 2 to 30 new
-// tokens 96 -> 67 us, 30 of 2000 to 4000 and 2 to 36 92 -> 68 us (half of the XCDs had nothing to do), one request of 16384 + 36
-// 34.6 -> 32.9 us.
+// Where a pair is dealt to several XCDs (L.fan > 1) the fan XCDs that share pairs have one list between them, all row tiles
+// of those pairs, and take its units in turns: their numbers differ by at most one, which a deal of each pair's row
+// tiles by itself does not achieve (the first XCD gets the odd tile of every pair, and all there are when no request has
+// more than one).  A single unit goes to two of the XCDs by row halves, the first rows 0 .. 127 of it and of all its pieces, the
+// second rows 128 .. 255: four of a workgroup's waves then work, one per SIMD, and a tile takes 60 % of the time.
+// Measured (28 / 4 heads): 16 requests of 4000 to 8000 cached and 2 to 30 new tokens 96 -> 67 us, 30 of 2000 to 4000 and 2
+// to 36 92 -> 68 us (half of the XCDs had nothing to do), 13 of 2851
+// cached and 76 to 304 new (42 and 36 units where 39 each are possible) 142 -> 136 us, one request of 16384 + 36 34.6 -> 32.9 us.
 // merge_idx >= 0 asks instead, whatever in_xcd is, for the plan of merge workgroup merge_idx of the XCD: the unit
 // in tail slot merge_idx / shares, with .part = merge_idx % shares, shares = parts (1 for an uneven cut).
 __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShape& L, int xcd, int in_xcd, int merge_idx = -1)
@@ -292,22 +293,22 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         u.tile = sp % L.fan + L.fan * idx;
         return u;
     }
-    const int turn = L.lent ? xcd % L.fan : 0;               // this XCD's place among those that share a list
-    const int list_xcd = xcd - turn;                         // the one whose pairs hold the units
-    // lane pi looks at pair list_xcd + 8 pi
+    const int turn = xcd % L.fan;                            // this XCD's place among those that share a list
+    const int list_xcd = xcd - turn;
+    // lane pi looks at the pi-th pair of the list, pair (list_xcd + 8 pi) / fan
     const int pi = threadIdx.x & 63;
     const int lane_sp = list_xcd + NUM_XCD * pi;
     const int cnt = (pi < L.pairs_per_xcd && lane_sp < L.n_pairs)
-                        ? sub_pair_tiles(safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false), G, L.fan, lane_sp) : 0;
+                        ? (safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false) * G + BR - 1) / BR : 0;
     const int incl = wave_scan64(cnt);
     const int listed = __builtin_amdgcn_readlane(incl, 63);
-    const bool in_turns = L.lent && listed > 1;
-    if (L.lent && !in_turns) {
+    const bool halves = L.fan > 1 && listed == 1;
+    if (halves) {
         if (turn > 1 || (merge_idx >= 0 && turn == 1)) return u;
         u.half = turn;
         u.xcd = list_xcd;
     }
-    const int total = in_turns ? (listed - turn + L.fan - 1) / L.fan : listed;     // units of this XCD
+    const int total = halves ? 1 : (listed - turn + L.fan - 1) / L.fan;            // units of this XCD
     const int rem = total % CU_PER_XCD;
     const int parts = split_factor(rem, total / CU_PER_XCD, L.uneven);
     const int first_tail = total - rem;
@@ -325,14 +326,14 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         ordinal = first_tail + slot;
     }
     // the pair that holds this ordinal: the first one whose inclusive running count exceeds it
-    const int in_list = in_turns ? ordinal * L.fan + turn : ordinal;
+    const int in_list = halves ? 0 : ordinal * L.fan + turn;
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > in_list);
     if (hit == 0) return u;
     const int hit_pi = __builtin_ctzll(hit);
     const int hit_incl = __builtin_amdgcn_readlane(incl, hit_pi);
     const int hit_sp = list_xcd + NUM_XCD * hit_pi;
     u.pair = hit_sp / L.fan;
-    u.tile = hit_sp % L.fan + L.fan * (hit_incl - 1 - in_list);   // position = cnt - 1 - (ordinal - exclusive count)
+    u.tile = hit_incl - 1 - in_list;                         // = cnt - 1 - (place in the list - exclusive count): the last tile first
     if (parts > 1 && ordinal >= first_tail) {                // a tail unit
         u.parts = parts;
         u.part = part;
@@ -1255,7 +1256,6 @@ static void launch_shape(const BatchView& b, bool has_workspace, LaunchShape& L,
             any = any || split_factor((int)(units[x] % CU_PER_XCD), (int)(units[x] / CU_PER_XCD), L.uneven) > 1;
         if (!any) L.split = 0;
     }
-    L.lent = (L.split && fan > 1 && n_pair_tiles == 1) ? 1 : 0;
     L.ws_pieces = 0;
     if (L.split && long_enough_to_cut(b)) {
         // Piece records of an XCD: tail slot x planned pieces + piece.  r units left over are planned for p pieces
