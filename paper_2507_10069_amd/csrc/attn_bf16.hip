@@ -138,6 +138,12 @@ constexpr int MERGE_PER_XCD = CU_PER_XCD;                // merge workgroups: ta
 constexpr int MIN_TILES_PER_PART = 16;                   // shorter pieces cost more (prologue, merge) than they gain: measured
 constexpr int MIN_TILES_PER_PART_UNDERFILLED = 2;        // ... unless the compute units would stay idle otherwise (swept: 1 .. 12)
 constexpr int MIN_UNIT_TILES_UNDERFILLED = 24;           // ... and the unit is long enough to pay for the merge launch (measured)
+// The few units (at most 8) that are left over after up to 3 full rounds are cut in 4 from this length on, however short the
+// pieces: the alternative, row halves, lasts 60 % of a whole unit beside an almost idle XCD.  Eight questions on two images (35
+// units of 18 to 24 tiles on an XCD) 67.4 -> 63.0 us, 13 of 2851 + 76 .. 304 tokens (39 units) 137 -> 130, 12 of 2200 + 125 .. 500
+// on 8 KV heads (67 units) 181 -> 172.  With many rounds the XCDs are not in step at the end and the merge only costs (582
+// units: 0.1 to 0.6 % slower).
+constexpr int MIN_UNIT_TILES_TAIL = 16, MIN_TILES_PER_PART_TAIL = 4, MAX_ROUNDS_TAIL = 3, MAX_UNITS_TAIL = 8;
 constexpr int SPLIT_MAX_PAIRS_PER_XCD = 64;              // planning scans an XCD's pairs, one per lane of a wave
 constexpr int PART_FLOATS = (64 + 2) * NTHREADS;         // per thread: 64 accumulator values, in groups of four, then m, l
 // A build with -DEMM_TIMELINE (python -m paper_2507_10069_amd.build --timeline -> libemm_timeline.so) makes every
@@ -227,7 +233,7 @@ __device__ inline bool cuttable(int n_tiles, int parts, int limit_min, int min_t
 // that it can be cut into (1: not at all).  Every workgroup concerned with the unit finds the same number.
 __device__ inline int pieces_cut(int n_tiles, int parts, int limit_min, int min_tiles)
 {
-    if (n_tiles < MIN_UNIT_TILES_UNDERFILLED) min_tiles = MIN_TILES_PER_PART;
+    if (n_tiles < (min_tiles == MIN_TILES_PER_PART_TAIL ? MIN_UNIT_TILES_TAIL : MIN_UNIT_TILES_UNDERFILLED)) min_tiles = MIN_TILES_PER_PART;
     while (parts > 1 && !cuttable(n_tiles, parts, limit_min, min_tiles)) parts >>= 1;
     // two short pieces are no better than two row halves, which need no merge: pieces shorter than the usual
     // minimum only when there are at least four of them
@@ -339,7 +345,10 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         u.part = part;
         u.slot = slot;
         u.rows_only = rows_only_of(rem, total / CU_PER_XCD);
-        u.min_tiles = total < CU_PER_XCD ? MIN_TILES_PER_PART_UNDERFILLED : MIN_TILES_PER_PART;
+        // (without room for records, which a page table of under 24 key tiles has not, nothing may be cut along the keys: the usual
+        // minimum sees to that, two pieces of it are longer than any context there)
+        const bool short_tail = rem <= MAX_UNITS_TAIL && total / CU_PER_XCD <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
+        u.min_tiles = total < CU_PER_XCD ? MIN_TILES_PER_PART_UNDERFILLED : short_tail ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART;
         u.uneven = L.uneven ? uneven_of(rem) : 0;
     }
     return u;

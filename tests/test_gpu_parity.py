@@ -244,6 +244,29 @@ def test_single_row_tiles_shared_among_xcds(name, kind, H, Hkv, prefix, new):
     _compare(wl, dw)
 
 
+# units left over after one full round on an XCD, cut in four however short the pieces (16 key tiles and more), and contexts under
+# 24 key tiles, for which there is no room for records and nothing may be cut
+TAIL_CASES = [
+    ("images", "causal", 28, 4, [1056] * 8, [490, 350, 389, 152, 251, 243, 148, 343]), ("too_short_to_record", "causal", 28, 4, [900] * 8, [490, 350, 389, 152, 251, 243, 148, 343]),
+    ("eight_left", "causal", 32, 8, [1500] * 9, [398, 211, 358, 171, 244, 171, 148, 228, 260]), ("just_sixteen_tiles", "cross", 32, 8, [1024] * 6 + [1600], [370, 300, 420, 380, 290, 400, 60]),
+    ("not_page_aligned", "causal", 28, 4, [1101, 1330, 987, 1490, 1203, 1111], [460, 444, 498, 301, 377, 420]), ("uniform", "causal", 8, 8, [1400] * 34, [250] * 34),
+]
+
+
+@pytest.mark.parametrize("name,kind,H,Hkv,prefix,new", TAIL_CASES)
+def test_short_pieces_of_the_last_units(name, kind, H, Hkv, prefix, new):
+    print("case tail", name, flush=True)
+    wl = W.build_workload("tail_" + name, kind, "bf16", 800, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=prefix, new_lens=new)
+    dw = B.DeviceWorkload(wl)
+    if dw.workspace is not None:
+        dw.workspace.fill_(0xff)                             # NaN wherever no record is written
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+
+
 @pytest.mark.parametrize("H,Hkv,prefix,new", [(4, 1, [300], [700]), (8, 2, [0], [1500]), (6, 1, [70, 0, 513], [300, 90, 64]),
                                               (8, 4, [129], [1]), (2, 1, [5000], [1100])])
 def test_few_pairs_spread_over_xcds(H, Hkv, prefix, new):
