@@ -18,7 +18,6 @@ constexpr int BC = 64;            // keys per tile
 constexpr int KV_BYTES = BC * D * 2;   // one K or V tile in LDS: 64 rows of 256 bytes
 constexpr int NBUF = 4;             // depth of the K and of the V tile ring in LDS (tile t lives in slot t % NBUF)
 constexpr int NUM_XCD = 8;
-constexpr float RESCALE_LOG2 = 8.0f;   // slack of the lagging maximum, in powers of two
 
 // A query row lives in lanes l and l^32 (16 of a block's 32 keys each).  v_permlane32_swap with the
 // same register as both operands leaves the low half's value in every lane of the first result and
