@@ -138,12 +138,13 @@ constexpr int MERGE_PER_XCD = CU_PER_XCD;                // merge workgroups: ta
 constexpr int MIN_TILES_PER_PART = 16;                   // shorter pieces cost more (prologue, merge) than they gain: measured
 constexpr int MIN_TILES_PER_PART_UNDERFILLED = 2;        // ... unless the compute units would stay idle otherwise (swept: 1 .. 12)
 constexpr int MIN_UNIT_TILES_UNDERFILLED = 24;           // ... and the unit is long enough to pay for the merge launch (measured)
-// The few units (at most 8) that are left over after up to 3 full rounds are cut in 4 from this length on, however short the
+// The few units (at most 4) that are left over after up to 3 full rounds are cut in 4 from this length on, however short the
 // pieces: the alternative, row halves, lasts 60 % of a whole unit beside an almost idle XCD.  Eight questions on two images (35
-// units of 18 to 24 tiles on an XCD) 67.4 -> 63.0 us, 13 of 2851 + 76 .. 304 tokens (39 units) 137 -> 130, 12 of 2200 + 125 .. 500
-// on 8 KV heads (67 units) 181 -> 172.  With many rounds the XCDs are not in step at the end and the merge only costs (582
-// units: 0.1 to 0.6 % slower).
-constexpr int MIN_UNIT_TILES_TAIL = 16, MIN_TILES_PER_PART_TAIL = 4, MAX_ROUNDS_TAIL = 3, MAX_UNITS_TAIL = 8;
+// units of 18 to 24 tiles on an XCD) 67.4 -> 61.2 us, 12 of 2200 + 125 .. 500 on 8 KV heads (67 units) 181 -> 172.  5 to 8 units fill
+// half of the XCD as halves already: pieces of 8 tiles and more still pay there (13 of 2851 + 76 .. 304 tokens, 39 units of 47 tiles:
+// 137 -> 130), shorter ones do not (39 to 40 units of 18 to 25 tiles: 67.4 -> 69.4).  With many rounds the XCDs are not in step at
+// the end and the merge only costs (582 units: 0.1 to 0.6 % slower).
+constexpr int MIN_UNIT_TILES_TAIL = 16, MIN_TILES_PER_PART_TAIL = 4, MIN_TILES_PER_PART_TAIL_MORE = 8, MAX_ROUNDS_TAIL = 3;
 constexpr int SPLIT_MAX_PAIRS_PER_XCD = 64;              // planning scans an XCD's pairs, one per lane of a wave
 constexpr int PART_FLOATS = (64 + 2) * NTHREADS;         // per thread: 64 accumulator values, in groups of four, then m, l
 // A build with -DEMM_TIMELINE (python -m paper_2507_10069_amd.build --timeline -> libemm_timeline.so) makes every
@@ -347,8 +348,9 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         u.rows_only = rows_only_of(rem, total / CU_PER_XCD);
         // (without room for records, which a page table of under 24 key tiles has not, nothing may be cut along the keys: the usual
         // minimum sees to that, two pieces of it are longer than any context there)
-        const bool short_tail = rem <= MAX_UNITS_TAIL && total / CU_PER_XCD <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
-        u.min_tiles = total < CU_PER_XCD ? MIN_TILES_PER_PART_UNDERFILLED : short_tail ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART;
+        const bool short_tail = rem <= CU_PER_XCD / 4 && total / CU_PER_XCD <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
+        u.min_tiles = total < CU_PER_XCD ? MIN_TILES_PER_PART_UNDERFILLED : !short_tail ? MIN_TILES_PER_PART
+                      : rem <= CU_PER_XCD / 8 ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART_TAIL_MORE;
         u.uneven = L.uneven ? uneven_of(rem) : 0;
     }
     return u;
