@@ -295,15 +295,15 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
                 // against 64 bits is 6 % larger where a wave has two blocks.)
                 const float mx = fmaxf(fmaxf(s[q][0], s[q][1]), fmaxf(s[q][2], s[q][3]));
                 if (__builtin_amdgcn_ballot_w64(mx > m_run[q]) != 0) {
-                    const float mx_row = quad_max(mx);       // finite: every block has a visible key
-                    const float m_new = fmaxf(mx_row, m_run[q]);
+                    const float m_new = fmaxf(quad_max(mx), m_run[q]);
                     const float alpha = m_run[q] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[q] - m_new) * c_log2);
                     m_run[q] = m_new;
                     l_run[q] *= alpha;
 #pragma unroll
                     for (int nb = 0; nb < 8; ++nb) o_acc[q][nb] *= alpha;
                 }
-                const float mc = m_run[q] * c_log2;
+                // every block has a visible key, but all its scores may be -infinity (products past the largest float): weights of 0
+                const float mc = m_run[q] == -INFINITY ? 0.f : m_run[q] * c_log2;
                 bf16x4 p;
                 float psum = 0.f;
 #pragma unroll

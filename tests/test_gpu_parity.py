@@ -553,6 +553,30 @@ def test_decode_block_edges(kind, H, Hkv, ps):
         assert torch.equal(fused.k_cache, dw.k_cache) and torch.equal(fused.v_cache, dw.v_cache)
 
 
+# which 16-key blocks have only scores of -infinity: one of a tile of 32 keys, a whole tile, all of wave 1's, a whole piece
+@pytest.mark.parametrize("blocks", [[1], [2, 3], list(range(1, 94, 4)), list(range(0, 8))])
+def test_decode_block_of_scores_that_are_minus_infinity(blocks):
+    """K elements of the type's lowest value against query elements of 8: the products pass the largest float and
+    the scores are -infinity.  Such keys have weight 0, whatever else the block they stand in holds."""
+    print("case decode -inf", blocks[:3], flush=True)
+    wl = W.build_workload("decode_minus_inf", "causal", "bf16", 790, num_q_heads=14, num_kv_heads=2, head_dim=128, page_size=16,
+                          prefix_lens=[1500, 1500], new_lens=[1, 1], share_group=[0, 0], shared_len=[1504 - 32] * 2)
+    wl.q[:, :, 0] = 0x4100                                   # 8.0
+    for blk in blocks:
+        wl.k_cache[wl.page_table[:, blk], :, :, 0] = 0xFF7F  # the lowest bf16
+    dw = _gpu_run(wl)
+    _compare(wl, dw)
+    dw.plan_shared()
+    for fused in (False, True):
+        dw.out.zero_()
+        if fused:
+            dw.decode_step(True)
+        else:
+            dw.attention_shared()
+        torch.cuda.synchronize()
+        _compare(wl, dw)
+
+
 @pytest.mark.parametrize("name,group,shared,planned", [("private", [0, 1, 2], 0, False), ("shared_apart", [0, 1, 0], 12800, False),
                                                        ("units", [0, 0, 1], 12800, True), ("units_and_apart", [0, 0, 0], 12801, True)])
 def test_decode_large_enough_to_stream(name, group, shared, planned):
