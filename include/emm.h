@@ -359,10 +359,9 @@ emm_status emm_validate_batch_host(const emm_batch *batch, const int32_t *host_p
  *                   (every XCD then gets the same share of every request)
  *   cutting         1: units left over after an XCD's full rounds of 32 may be cut along the keys or halved
  *   slots_per_xcd   workgroups per XCD that may hold a unit; grid = 8 * (slots_per_xcd + 31 if cutting)
- *   units[x]        work units of XCD x by the deal of each pair's row tiles.  With cutting and fan > 1 the kernels level
- *                   what that leaves unequal: the fan XCDs that share pairs take the units of all of them in turns,
- *                   so that their numbers differ by at most one (a single one goes to two XCDs by row halves), and
- *                   plan pieces from that number by the rules that pieces, uneven_k and rows_only show
+ *   units[x]        work units of XCD x.  With cutting, the fan XCDs that share pairs take the row tiles of all of them in
+ *                   turns, so that their numbers differ by at most one; a single one, listed for the first of them, is
+ *                   done by two of these XCDs, a half of its rows each.  Without, XCD j of the fan has tiles j, j + fan, ...
  *   pieces[x]       pieces planned for each of its left-over units (1: none are cut)
  *   uneven_k[x]     > 0: those pieces are a long and a short one, the cut at k / (k + 1) of the keys
  *   rows_only[x]    1: the left-over units are halved along their rows, never cut along the keys

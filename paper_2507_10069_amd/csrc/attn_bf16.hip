@@ -265,6 +265,36 @@ __device__ inline int wave_scan64(int x)
     return x;
 }
 
+// What XCD `xcd` does of a batch with cutting, from the number of units on the list that it shares with the other XCDs of its
+// group of fan: the kernels and the host (attn_bf16_d128_plan_host) derive it here.
+// (Without room for records, which a page table of under 24 key tiles has not, nothing may be cut along the keys: the usual
+// minimum of key tiles sees to that, two pieces of it are longer than any context there.)
+struct XcdPlan {
+    int total;              // units
+    bool halves;            // it does one half of the rows of the only unit of its list
+    int rem, parts;         // units left over after full rounds of 32, and the pieces planned for each
+    bool rows_only;         // those are never cut along the keys
+    int uneven;             // see uneven_of
+    int min_tiles;          // key tiles that a piece must have
+};
+__host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int listed)
+{
+    XcdPlan p;
+    const int turn = xcd % L.fan;                            // this XCD's place among those that share the list
+    const bool single = L.fan > 1 && listed == 1;
+    p.halves = single && turn <= 1;
+    p.total = single ? (turn <= 1 ? 1 : 0) : (listed - turn + L.fan - 1) / L.fan;
+    p.rem = p.total % CU_PER_XCD;
+    const int full = p.total / CU_PER_XCD;
+    p.parts = split_factor(p.rem, full, L.uneven);
+    p.rows_only = rows_only_of(p.rem, full);
+    p.uneven = L.uneven ? uneven_of(p.rem) : 0;
+    const bool short_tail = p.rem <= CU_PER_XCD / 4 && full <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
+    p.min_tiles = full == 0 ? MIN_TILES_PER_PART_UNDERFILLED : !short_tail ? MIN_TILES_PER_PART
+                  : p.rem <= CU_PER_XCD / 8 ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART_TAIL_MORE;
+    return p;
+}
+
 // Plan of workgroup `in_xcd` of XCD `xcd`.
 // Without cutting (L.split == 0: no workspace, or more than 64 pairs on an XCD) the grid has as many slots per
 // pair as the longest request needs (pair-major, row tiles descending) and a workgroup whose slot holds no
@@ -309,15 +339,13 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
                         ? (safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false) * G + BR - 1) / BR : 0;
     const int incl = wave_scan64(cnt);
     const int listed = __builtin_amdgcn_readlane(incl, 63);
-    const bool halves = L.fan > 1 && listed == 1;
-    if (halves) {
-        if (turn > 1 || (merge_idx >= 0 && turn == 1)) return u;
+    const XcdPlan x = xcd_plan(L, xcd, listed);
+    if (x.halves) {
+        if (merge_idx >= 0 && turn == 1) return u;           // (merged once, by the first of the two)
         u.half = turn;
         u.xcd = list_xcd;
     }
-    const int total = halves ? 1 : (listed - turn + L.fan - 1) / L.fan;            // units of this XCD
-    const int rem = total % CU_PER_XCD;
-    const int parts = split_factor(rem, total / CU_PER_XCD, L.uneven);
+    const int total = x.total, rem = x.rem, parts = x.parts;
     const int first_tail = total - rem;
     int ordinal, slot = 0, part = 0;
     if (merge_idx < 0 && in_xcd < total) {
@@ -326,14 +354,14 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
     } else {
         if (parts == 1) return u;
         const int e = in_xcd - total;
-        const int shares = (L.uneven && uneven_of(rem) > 0) ? 1 : parts;     // merge workgroups per unit
+        const int shares = x.uneven > 0 ? 1 : parts;         // merge workgroups per unit
         slot = merge_idx >= 0 ? merge_idx / shares : e / (parts - 1);
         part = merge_idx >= 0 ? merge_idx % shares : 1 + e % (parts - 1);
         if (slot >= rem) return u;
         ordinal = first_tail + slot;
     }
     // the pair that holds this ordinal: the first one whose inclusive running count exceeds it
-    const int in_list = halves ? 0 : ordinal * L.fan + turn;
+    const int in_list = x.halves ? 0 : ordinal * L.fan + turn;
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > in_list);
     if (hit == 0) return u;
     const int hit_pi = __builtin_ctzll(hit);
@@ -345,13 +373,9 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         u.parts = parts;
         u.part = part;
         u.slot = slot;
-        u.rows_only = rows_only_of(rem, total / CU_PER_XCD);
-        // (without room for records, which a page table of under 24 key tiles has not, nothing may be cut along the keys: the usual
-        // minimum sees to that, two pieces of it are longer than any context there)
-        const bool short_tail = rem <= CU_PER_XCD / 4 && total / CU_PER_XCD <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
-        u.min_tiles = total < CU_PER_XCD ? MIN_TILES_PER_PART_UNDERFILLED : !short_tail ? MIN_TILES_PER_PART
-                      : rem <= CU_PER_XCD / 8 ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART_TAIL_MORE;
-        u.uneven = L.uneven ? uneven_of(rem) : 0;
+        u.rows_only = x.rows_only;
+        u.min_tiles = x.min_tiles;
+        u.uneven = x.uneven;
     }
     return u;
 }
@@ -1308,7 +1332,8 @@ size_t attn_bf16_d128_workspace_bytes(const BatchView& b)
 }
 
 // What the planner makes of a batch whose new-token counts are given as a host array: the launch shape and, per
-// XCD, the units, the pieces planned for each tail unit and the kind of cut (see emm_prefill_plan in emm.h).
+// XCD, the units, the pieces planned for each tail unit and the kind of cut (see emm_prefill_plan in emm.h), by the
+// function that the kernels use.
 void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool has_workspace, int32_t* shape6, long long* grid,
                               int32_t* units, int32_t* pieces, int32_t* uneven_k, int32_t* rows_only)
 {
@@ -1319,18 +1344,23 @@ void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool 
     shape6[0] = L.fan; shape6[1] = L.n_row_tiles; shape6[2] = L.pairs_per_xcd; shape6[3] = L.split; shape6[4] = L.uneven;
     shape6[5] = (int32_t)slots;
     *grid = NUM_XCD * (slots + (L.split ? EXTRA_PER_XCD : 0));
+    auto new_len = [&](long long sp) {
+        return std::min(std::max(new_lens[sp / L.fan / b.num_kv_heads], 0), std::min(b.max_new_len, b.total_new_tokens));
+    };
     for (int x = 0; x < NUM_XCD; ++x) {
-        long long total = 0;
-        for (long long sp = x; sp < L.n_pairs; sp += NUM_XCD) {
-            const int r = (int)(sp / L.fan / b.num_kv_heads);
-            const int n = std::min(std::max(new_lens[r], 0), std::min(b.max_new_len, b.total_new_tokens));
-            total += sub_pair_tiles(n, G, L.fan, (int)sp);
+        units[x] = 0; pieces[x] = 1; uneven_k[x] = 0; rows_only[x] = 0;
+        if (!L.split) {                                      // each sub-pair's row tiles by themselves, nothing is cut
+            for (long long sp = x; sp < L.n_pairs; sp += NUM_XCD) units[x] += sub_pair_tiles(new_len(sp), G, L.fan, (int)sp);
+            continue;
         }
-        const int rem = (int)(total % CU_PER_XCD), full = (int)(total / CU_PER_XCD);
-        units[x] = (int32_t)total;
-        pieces[x] = L.split ? split_factor(rem, full, L.uneven) : 1;
-        uneven_k[x] = (L.split && L.uneven) ? uneven_of(rem) : 0;
-        rows_only[x] = (L.split && rows_only_of(rem, full)) ? 1 : 0;
+        long long listed = 0;
+        for (long long sp = x - x % L.fan; sp < L.n_pairs; sp += NUM_XCD) listed += ((long long)new_len(sp) * G + BR - 1) / BR;
+        const XcdPlan p = xcd_plan(L, x, (int)listed);
+        if (p.halves && x % L.fan == 1) continue;            // the second half of a unit that counts for the first XCD
+        units[x] = p.total;
+        pieces[x] = p.parts;
+        uneven_k[x] = p.uneven;
+        rows_only[x] = p.rows_only ? 1 : 0;
     }
 }
 

@@ -30,15 +30,21 @@ def _model(H, Hkv, new):
     if len(set(new)) > 1:                                      # requests of different lengths: every request on every XCD
         while fan < XCDS and (Hkv * fan) % XCDS:
             fan *= 2
-    units = [0] * XCDS
-    for p in range(pairs):
-        tiles = -(-new[p // Hkv] * G // ROWS)
-        for j in range(fan):                                   # sub-pair j of pair p takes row tiles j, j + fan, ...
-            units[(p * fan + j) % XCDS] += len(range(j, tiles, fan))
-    per_xcd = -(-pairs * fan // XCDS)
+    tiles_of = [-(-new[p // Hkv] * G // ROWS) for p in range(pairs)]
     uniform = len(set(new)) == 1
-    cutting = per_xcd <= 64
-    uneven_ok = not (uniform and len(set(units)) == 1)
+    cutting = -(-pairs * fan // XCDS) <= 64
+    dealt = [0] * XCDS                                         # sub-pair j of pair p has row tiles j, j + fan, ...
+    for p in range(pairs):
+        for j in range(fan):
+            dealt[(p * fan + j) % XCDS] += len(range(j, tiles_of[p], fan))
+    units = dealt
+    if cutting:                                                # the fan XCDs that share pairs take all their row tiles in turns
+        units = []
+        for x in range(XCDS):
+            first, turn = x - x % fan, x % fan
+            listed = sum(tiles_of[sp // fan] for sp in range(first, pairs * fan, XCDS))
+            units.append(len(range(turn, listed, fan)))        # (of a single one, two XCDs do a half of the rows each)
+    uneven_ok = not (uniform and len(set(dealt)) == 1)
     pieces, ks, halves = [], [], []
     for u in units:
         rem, full = u % CUS, u // CUS
@@ -75,7 +81,7 @@ def test_named_workloads():
     cfg2 = W.config(2)                                           # requests of different lengths on 4 KV heads: each pair is
     p2 = B.emm_prefill_plan_host(_batch(28, 4, cfg2.new_lens.tolist()), cfg2.new_lens)   # dealt to 2 XCDs, so that every XCD
     assert p2["fan"] == 2                                        # gets half the row tiles of one KV head of every request
-    assert max(p2["units"]) - min(p2["units"]) <= len(cfg2.new_lens), p2["units"]
+    assert max(p2["units"]) - min(p2["units"]) <= 1, p2["units"]
     no_ws = B.emm_prefill_plan_host(_batch(28, 4, [36]), [36], with_workspace=False)
     assert no_ws["cutting"] == 0 and no_ws["pieces"] == [1] * 8 and no_ws["grid"] == 8
 
@@ -99,9 +105,13 @@ def test_random_batches_match_model_and_keep_invariants(seed):
     assert (p["pieces"], p["uneven_k"], p["rows_only"]) == (pieces, ks, halves), (new, p)
     assert sum(p["units"]) == sum(-(-n * G // ROWS) for n in new) * Hkv              # every row tile of every pair, once
     assert p["grid"] == XCDS * (p["slots_per_xcd"] + (31 if p["cutting"] else 0))
+    if cutting:                                                                        # XCDs that share a list differ by one unit
+        assert all(max(p["units"][x:x + fan]) - min(p["units"][x:x + fan]) <= 1 for x in range(0, XCDS, fan)), (new, p)
     for x in range(XCDS):
         rem = p["units"][x] % CUS
         assert p["units"][x] <= p["slots_per_xcd"]                                     # a slot for every unit
+        if cutting and fan > 1 and sum(p["units"][x - x % fan:][:fan]) == 1:           # a single unit: row halves on two XCDs
+            assert p["slots_per_xcd"] >= 1 and p["units"][x] == int(x % fan == 0)
         assert rem * (p["pieces"][x] - 1) <= 31                                        # extra workgroups for pieces 1, 2, ...
         assert rem * p["pieces"][x] <= 64                                              # workspace slots of the XCD
         shares = 1 if p["uneven_k"][x] else p["pieces"][x]
