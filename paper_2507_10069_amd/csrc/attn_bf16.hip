@@ -266,9 +266,9 @@ __device__ inline int wave_scan64(int x)
 }
 
 // What XCD `xcd` does of a batch with cutting, from the number of units on the list that it shares with the other XCDs of its
-// group of fan: the kernels and the host (attn_bf16_d128_plan_host) derive it here.
-// (Without room for records, which a page table of under 24 key tiles has not, nothing may be cut along the keys: the usual
-// minimum of key tiles sees to that, two pieces of it are longer than any context there.)
+// group of fan: the kernels and the host (attn_bf16_d128_plan_host) derive it here.  A key cut needs room for its records: a
+// plan that would write more of them than the workspace holds (a page table of under 24 key tiles has none; a batch whose
+// lengths contradict its scalar fields may need more than those let the host provide) halves the rows instead.
 struct XcdPlan {
     int total;              // units
     bool halves;            // it does one half of the rows of the only unit of its list
@@ -287,9 +287,9 @@ __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int l
     p.rem = p.total % CU_PER_XCD;
     const int full = p.total / CU_PER_XCD;
     p.parts = split_factor(p.rem, full, L.uneven);
-    p.rows_only = rows_only_of(p.rem, full);
+    p.rows_only = rows_only_of(p.rem, full) || p.rem * p.parts > L.ws_pieces;
     p.uneven = L.uneven ? uneven_of(p.rem) : 0;
-    const bool short_tail = p.rem <= CU_PER_XCD / 4 && full <= MAX_ROUNDS_TAIL && L.ws_pieces > 0;
+    const bool short_tail = p.rem <= CU_PER_XCD / 4 && full <= MAX_ROUNDS_TAIL;
     p.min_tiles = full == 0 ? MIN_TILES_PER_PART_UNDERFILLED : !short_tail ? MIN_TILES_PER_PART
                   : p.rem <= CU_PER_XCD / 8 ? MIN_TILES_PER_PART_TAIL : MIN_TILES_PER_PART_TAIL_MORE;
     return p;

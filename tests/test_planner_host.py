@@ -159,6 +159,26 @@ def test_workspace_size_covers_the_plan(seed):
     assert stride <= 64
 
 
+@pytest.mark.parametrize("seed", range(40))
+def test_lengths_that_contradict_the_scalars_leave_no_record_outside_the_workspace(seed):
+    """The workspace is sized from the scalar fields, the kernels plan from the lengths in device memory.  Whatever those
+    hold, the plan cuts along the keys only where an XCD's records fit its share of the workspace."""
+    rng = np.random.default_rng(1700 + seed)
+    Hkv = int(rng.choice([1, 2, 4, 8]))
+    G = int(rng.choice([1, 4, 7, 8]))
+    n_req = int(rng.choice([2, 3, 8, 16, 40]))
+    top = int(rng.choice([3, 40, 300, 2100]))
+    b = _batch(Hkv * G, Hkv, [top] * n_req)                   # the scalars of a uniform batch: the size is exactly its plan's
+    stride = B.emm_prefill_attn_workspace_size(b) // (XCDS * PIECE_BYTES)
+    for _ in range(20):
+        lens = [int(x) for x in rng.integers(-2, top + 40, n_req)]
+        p = B.emm_prefill_plan_host(b, lens)
+        for x in range(XCDS):
+            rem = p["units"][x] % CUS
+            if p["cutting"] and p["pieces"][x] > 1 and not p["rows_only"][x]:
+                assert rem * p["pieces"][x] <= stride, (lens, p, stride)
+
+
 def test_workspace_of_the_headline_workload_is_empty():
     cfg3 = W.config(3)
     b = _batch(28, 4, cfg3.new_lens.tolist())
