@@ -145,6 +145,9 @@ constexpr int MIN_UNIT_TILES_UNDERFILLED = 24;           // ... and the unit is 
 // 137 -> 130), shorter ones do not (39 to 40 units of 18 to 25 tiles: 67.4 -> 69.4).  With many rounds the XCDs are not in step at
 // the end and the merge only costs (582 units: 0.1 to 0.6 % slower).
 constexpr int MIN_UNIT_TILES_TAIL = 16, MIN_TILES_PER_PART_TAIL = 4, MIN_TILES_PER_PART_TAIL_MORE = 8, MAX_ROUNDS_TAIL = 3;
+// (pieces_cut tells the kinds of plan apart by the minimum that they bring)
+static_assert(MIN_TILES_PER_PART_TAIL != MIN_TILES_PER_PART && MIN_TILES_PER_PART_TAIL != MIN_TILES_PER_PART_UNDERFILLED &&
+              MIN_TILES_PER_PART_TAIL != MIN_TILES_PER_PART_TAIL_MORE, "a minimum of its own");
 constexpr int SPLIT_MAX_PAIRS_PER_XCD = 64;              // planning scans an XCD's pairs, one per lane of a wave
 constexpr int PART_FLOATS = (64 + 2) * NTHREADS;         // per thread: 64 accumulator values, in groups of four, then m, l
 // A build with -DEMM_TIMELINE (python -m paper_2507_10069_amd.build --timeline -> libemm_timeline.so) makes every
@@ -1002,7 +1005,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         asm volatile("" : "+v"(t2));
         if (cut > 1) {
             // a piece of a cut unit: unnormalised accumulator, running maximum and row sum go to the
-            // workspace, one coalesced row of 512 floats per register; attn_bf16_merge_kernel finishes
+            // workspace (see part_base for the layout); attn_bf16_merge_kernel finishes
             if (!active) return;                             // a wave without rows has nothing to hand over
             float* __restrict__ ws = part_base(a.workspace, L.ws_pieces, plan.xcd, plan.slot, plan.parts, plan.part);
             const float l_part = pair_sum(l_run);
@@ -1194,10 +1197,10 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
     }
 }
 
-// Merges the pieces of the cut units, thread for thread the layout of the main kernel's epilogue.  An XCD
-// whose tail units are planned for p pieces each gets 32 workgroups: number k works on tail slot k / p and
-// there on share k % p of the 64 accumulator registers, so every workgroup reads the same 64 rows of 2 KB
-// whatever p is (one workgroup per unit, 128 rows, for an uneven cut in two).  Workgroups whose slot holds no cut unit leave at once.
+// Merges the pieces of the cut units, column for column (thread for thread) the layout of the main kernel's epilogue.  An XCD
+// whose tail units are planned for p pieces each gets 32 workgroups: number k works on tail slot k / p and there on the
+// columns of share k % p, 512 / p of each piece's 512, so every workgroup reads as many bytes whatever p is (one
+// workgroup per unit for an uneven cut in two).  Workgroups whose slot holds no cut unit leave at once.
 __global__ __launch_bounds__(NTHREADS) void attn_bf16_merge_kernel(AttnArgs a, LaunchShape L)
 {
     const BatchView& b = a.b;
