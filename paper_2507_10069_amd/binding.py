@@ -134,19 +134,20 @@ def _bytes(t) -> int:
     return 0 if t is None else t.nbytes
 
 
-_raw_stream = _device = None                            # set by the first call on torch's current stream
+_current = None                                          # (raw stream of a device, current device): set by the first call that asks
 
 
 def _stream(stream) -> Optional[int]:
     """The handle of `stream`, or of the current stream of torch's current device, asked for at every call."""
-    global _raw_stream, _device
+    global _current
     if stream is None:
-        if _raw_stream is not None:
-            return _raw_stream(_device()) or None
+        current = _current                                   # one store and one load: other threads see both functions or none
+        if current is not None:
+            return current[0](current[1]()) or None
         import torch
         stream = torch.cuda.current_stream()                 # initialises torch's device side if nothing has yet
         # the same answer as an integer, without the Stream object that torch.cuda.current_stream() makes (2.7 us a call)
-        _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        _current = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
     handle = int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
     return handle or None
 

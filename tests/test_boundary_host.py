@@ -280,3 +280,39 @@ def test_descriptors_keep_their_tensors_alive():
     del batch, shared
     gc.collect()
     assert ref() is None
+
+
+def test_first_stream_lookup_with_other_threads_between_its_steps(monkeypatch):
+    """The first call on torch's current stream keeps the two functions that later calls ask.  Whatever step of it another
+    thread's call comes between, that call must find both of them or neither."""
+    import sys
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=7))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 40 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 2, raising=False)
+    first_lookup = [(name, getattr(B, name)) for name in ("_current", "_raw_stream", "_device") if hasattr(B, name)]
+    for name, _ in first_lookup:
+        monkeypatch.setattr(B, name, None)
+    seen = []
+
+    def between(frame, event, arg):                          # after every instruction of the first call: the same call again
+        if frame.f_code is not B._stream.__code__:
+            return None
+        frame.f_trace_opcodes = True
+        if event == "opcode":
+            sys.settrace(None)
+            kept = [(name, getattr(B, name)) for name, _ in first_lookup]
+            seen.append(B._stream(None))
+            for name, value in kept:                         # what the first call finds is what it left
+                setattr(B, name, value)
+            sys.settrace(between)
+        return between
+
+    sys.settrace(between)
+    try:
+        assert B._stream(None) == 7
+    finally:
+        sys.settrace(None)
+    assert len(seen) > 10 and set(seen) <= {7, 42}
+    assert B._stream(None) == 42
