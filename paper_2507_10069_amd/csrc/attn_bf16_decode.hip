@@ -94,16 +94,32 @@ __device__ __host__ inline size_t unit_records_offset(const DecodeShape& S)
     return (size_t)S.n_pairs * S.pieces_max * MAX_G * REC_FLOATS;
 }
 
+// K and V are fetched past the caches (non-temporal) when a call reads more of them than the last-level cache would keep
+// until they are read again: 6.6 instead of 5.7 TB/s (64 x 8192 tokens 196 -> 173 us, 262 MB ragged 56 -> 48, 102 MB in
+// one context 25.5 -> 23.6); below, where a repeated call finds them there, it costs up to 12 % (66 MB: 15.7 -> 17.7).
+// The line lies between.  Pages that several requests read would lose what the first of them brought into the L2 (32
+// requests on 8 videos without units: 115 -> 154 us): each wave looks whether another request holds its first page.
+constexpr long long STREAM_BYTES = 96ll << 20;
+constexpr int STREAM_TILES = (int)(STREAM_BYTES / (BK * D * 4));
+
 // Does a request other than r .. r + n - 1 hold page `id` at entry `at` of its row of the page table?  (Shared pages are
 // leading pages, so a shared one stands at the same entry everywhere.)  The whole wave asks, 64 requests at a time; with
 // more than SHARE_LOOKUP of them the answer is yes, unasked.  What is found decides how the page is fetched and nothing
-// else, so entries past a request's own pages do no harm.
+// else, so entries past a request's own pages do no harm.  The entries of the first 64 requests (`first`, one per lane) are
+// asked for together with the lengths, the answer is formed when the workgroups without work have left.
 constexpr int SHARE_LOOKUP = 512;
-__device__ inline bool holds_page(const BatchView& b, int at, int id, int r, int n)
+__device__ inline int first_holders(const BatchView& b, int at)
+{
+    // (an atomic load of the weakest kind, which is an ordinary one, but which the compiler leaves where it is written)
+    return __hip_atomic_load(b.page_table + (long long)min((int)threadIdx.x & 63, b.num_reqs - 1) * b.max_pages + at, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ inline bool holds_page(const BatchView& b, int first, int at, int id, int r, int n)
 {
     if (b.num_reqs > SHARE_LOOKUP) return true;
-    bool found = false;
-    for (int k = threadIdx.x & 63; k < b.num_reqs; k += 64)
+    const int lane = threadIdx.x & 63;
+    bool found = first == id && lane < b.num_reqs && (lane < r || lane >= r + n);
+    for (int k = lane + 64; k < b.num_reqs; k += 64)
         found = found || (b.page_table[(long long)k * b.max_pages + at] == id && (k < r || k >= r + n));
     return __builtin_amdgcn_ballot_w64(found) != 0;
 }
@@ -153,8 +169,8 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
     const int blk16 = t_begin * BLOCKS_PER_TILE + wave + NW * lane;       // logical 16-key block of the request
     const int pg_raw = pt[min(blk16 >> b.page_shift, b.max_pages - 1)];   // (max_pages > 0: checked on the host)
-    const int pg_first = min((t_begin * BLOCKS_PER_TILE) >> b.page_shift, b.max_pages - 1);
-    const bool shared_elsewhere = S.stream && holds_page(b, pg_first, pt[pg_first], r, unit_mode ? sv.unit_num_reqs[unit] : 1);
+    const int pg_first = __builtin_amdgcn_readfirstlane(min(blk16 >> b.page_shift, b.max_pages - 1));    // of the wave's first block
+    const int holders = S.stream != DecodeShape::STREAM_NEVER ? first_holders(b, pg_first) : 0;
     asm volatile("" ::"s"(new_len), "s"(prefix_len), "s"(cu_new));
     __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
@@ -195,7 +211,10 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const unsigned char* __restrict__ kcb = (const unsigned char*)a.k_cache;
     const unsigned char* __restrict__ vcb = (const unsigned char*)a.v_cache;
     constexpr int FETCHES = 8;                               // instructions per block
-    const bool streamed = S.stream && !shared_elsewhere;
+    // (what the host does not know it takes from this context: the others are as long)
+    const bool long_enough = S.stream == DecodeShape::STREAM_PRIVATE || (long long)(kv_len / BK - t_off) * n_items >= STREAM_TILES;
+    const bool streamed = S.stream != DecodeShape::STREAM_NEVER && long_enough &&
+                          !holds_page(b, holders, pg_first, __builtin_amdgcn_readfirstlane(pg_raw), r, unit_mode ? sv.unit_num_reqs[unit] : 1);
     auto fetch = [&](int i, int slot) {                      // this wave's block i into its ring
         const long long off = (long long)__builtin_amdgcn_readlane(pg_vec, i) * BLOCK_BYTES;
         const uint32_t to = __builtin_amdgcn_readfirstlane(ring + slot * (2 * BLOCK_BYTES));
@@ -550,13 +569,6 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
 constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 
-// K and V are fetched past the caches (non-temporal) when a call reads more of them than the last-level cache would keep
-// until they are read again: 6.6 instead of 5.7 TB/s (64 x 8192 tokens 196 -> 173 us, 262 MB ragged 56 -> 48, 102 MB in
-// one context 25.5 -> 23.6); below, where a repeated call finds them there, it costs up to 12 % (66 MB: 15.7 -> 17.7).
-// The line lies between.  Pages that several requests read would lose what the first of them brought into the L2 (32
-// requests on 8 videos without units: 115 -> 154 us): each wave looks whether another request holds its first page.
-constexpr long long STREAM_BYTES = 96ll << 20;
-
 }  // namespace
 
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
@@ -599,7 +611,8 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     S.tiles_per_piece = best;
     S.pieces_max = (int)pieces(own_tiles, best);
     S.pieces_unit = (int)pieces(unit_tiles, best);
-    S.stream = total * BK * D * 4 >= STREAM_BYTES ? 1 : 0;
+    S.stream = total < STREAM_TILES ? DecodeShape::STREAM_NEVER
+               : sv.planned_tiles > 0 ? DecodeShape::STREAM_PRIVATE : DecodeShape::STREAM_BY_LENGTHS;
     return S;
 }
 

@@ -5,6 +5,8 @@ merge workgroups suffice; the workspace size covers any plan the scalar fields a
 the rule in plain Python only guards against the C++ and the description drifting apart.  No GPU."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -187,7 +189,6 @@ def test_workspace_of_the_headline_workload_is_empty():
 
 def test_argument_errors():
     lib = B.load()
-    import ctypes
     plan = B.emm_prefill_plan()
     ok = (ctypes.c_int32 * 2)(5, 5)
     assert lib.emm_prefill_plan_host(None, ok, 1, ctypes.byref(plan)) == B.EMM_ERR_NULL
@@ -234,3 +235,40 @@ def test_decode_plan_of_a_single_request_uses_fewer_longer_pieces():
     assert 256 < 4 * one <= 384
     two = pieces(2, 4096)                                       # the same number of tiles in two requests
     assert 384 < 8 * two <= 768
+
+
+class _BatchView(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("page_table", "prefix_lens", "new_lens", "cu_new_lens")] + \
+               [(n, ctypes.c_int32) for n in ("num_reqs", "num_q_heads", "num_kv_heads", "head_dim", "page_size", "num_pages", "max_pages",
+                                              "total_new_tokens", "max_new_len", "page_shift")] + [("softmax_scale", ctypes.c_float)]
+
+
+class _SharedPrefixView(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("unit_first_req", "unit_num_reqs", "unit_shared_len", "req_unit", "req_shared_len")] + \
+               [(n, ctypes.c_int32) for n in ("num_units", "planned_tiles", "max_own_tiles", "max_unit_tiles")]
+
+
+class _DecodeShape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("n_pairs", "n_unit_pairs", "tiles_per_piece", "pieces_max", "pieces_unit", "stream")]
+
+
+def _decode_plan(n_req, H, Hkv, table_tokens, planned_tiles=0, max_own_tiles=0, num_units=0, max_unit_tiles=0):
+    """The plan of a decode batch, from the library's own planner (emm::attn_bf16_decode_shape)."""
+    plan = B.load()["_ZN3emm22attn_bf16_decode_shapeERKNS_9BatchViewERKNS_16SharedPrefixViewE"]
+    plan.restype = _DecodeShape
+    plan.argtypes = [ctypes.POINTER(_BatchView), ctypes.POINTER(_SharedPrefixView)]
+    b = _BatchView(num_reqs=n_req, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16, num_pages=1 << 20,
+                   max_pages=-(-table_tokens // 16), total_new_tokens=n_req, max_new_len=1, softmax_scale=0.1)
+    return plan(b, _SharedPrefixView(num_units=num_units, planned_tiles=planned_tiles, max_own_tiles=max_own_tiles, max_unit_tiles=max_unit_tiles))
+
+
+def test_decode_streams_by_what_is_known_of_the_work():
+    """More than 96 MiB of K and V are fetched past the caches.  The width of the page table says how long the contexts may be,
+    not how long they are: without the amount of work each workgroup decides by the length of its own context."""
+    NEVER, PRIVATE, BY_LENGTHS = 0, 1, 2
+    assert _decode_plan(1, 28, 4, 131072).stream == BY_LENGTHS                 # a chat of whatever length behind a wide row
+    assert _decode_plan(64, 28, 4, 8192).stream == BY_LENGTHS
+    assert _decode_plan(1, 28, 4, 40000).stream == NEVER                       # 82 MB at most
+    assert _decode_plan(1, 28, 4, 131072, planned_tiles=47, max_own_tiles=47).stream == NEVER
+    assert _decode_plan(64, 28, 4, 8192, planned_tiles=64 * 256, max_own_tiles=256).stream == PRIVATE
+    assert _decode_plan(64, 28, 4, 8192, planned_tiles=64 * 23, max_own_tiles=256).stream == NEVER
