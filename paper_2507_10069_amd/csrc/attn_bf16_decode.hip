@@ -430,18 +430,21 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
 }
 
 // merge 2: one workgroup per (pair, query row); wave w takes pieces w, w + WAVES, ..., a lane two channels of each.
-// The kernel is a few microseconds long and bound by its chain of memory round trips, so there is one: every wave
+// The kernel is a few microseconds long and bound by its chain of memory round trips, so there is one (AHEAD): every wave
 // asks for its first LOADS pieces (a record's 128 values and its m, l) before it knows how many the context has --
 // the workspace holds S.pieces_max of them whatever the lengths are -- and drops what turns out not to be a piece.  A
 // wave holds the m of all its pieces itself, so weights need no exchange; the waves meet in LDS once.
 // Measured against lengths first, then all (m, l), then the values, with two barriers: 4.7 -> 3.1 us for the 12 pieces of
 // one request of 1500 tokens, 6.3 -> 5.1 us for 64 requests of 3 pieces (behind a kernel that streams 1 GB).
+// Where most of those records are none (short contexts behind a page table that is wide, or of which a few are long) asking
+// for them all costs more than the round trip: see AHEAD_BYTES.  The lengths come first then.
 // 16 waves when a row has many pieces (a single long context), 4 when it has few (a big batch, where 1024-thread
 // workgroups would only crowd the chip).
-constexpr int MANY_PIECES = 32;
+constexpr int MANY_PIECES = 32, MANY_WAVES = 16, FEW_WAVES = 4;
 constexpr int LOADS = 8;                                     // pieces of a wave in flight at a time
+inline bool many_pieces(const DecodeShape& S) { return S.pieces_max + (S.n_unit_pairs > 0 ? S.pieces_unit : 0) > MANY_PIECES; }
 
-template <bool CAUSAL, bool SHARED, int WAVES>
+template <bool CAUSAL, bool SHARED, int WAVES, bool AHEAD>
 __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -465,9 +468,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
     };
     const int n_new = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
     const int req_unit = SHARED ? sv.req_unit[r] : -1, req_shared = SHARED ? sv.req_shared_len[r] : 0;
-    ask(rec_own, MAX_G * REC_FLOATS, 0, S.pieces_max);
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::"s"(n_new), "s"(cu_new));              // needed at the end only, but asked for here
+    if (AHEAD) {
+        ask(rec_own, MAX_G * REC_FLOATS, 0, S.pieces_max);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::"s"(n_new), "s"(cu_new));          // needed at the end only, but asked for here
+    }
 
     const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
     // the records of this row: n_own from the request's own workgroups, then n_unit from its unit's
@@ -476,7 +481,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
     const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(req_shared, 0) / BK : 0, S.tiles_per_piece, unit >= 0),
                           S.pieces_max);
     const bool nothing = n_new <= 0 || (unit < 0 && n_own == 1);          // no query token, or finished by the main kernel
-    // (left only where the result would be stored: a branch here would have the loads wait behind it)
+    // (with the loads on their way left only where the result would be stored: a branch here would have them wait behind it)
+    if (!AHEAD) {
+        if (nothing) return;
+        ask(rec_own, MAX_G * REC_FLOATS, 0, max(n_own, 1));
+    }
 
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
     float m = -INFINITY, l = 0.f;                            // of this wave's pieces (every piece has a visible key)
@@ -569,6 +578,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
 constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 
+// The merge kernel asks for records before it knows which of them there are when they are few in all, or when the amount of
+// work says that at least half of them are.  (28 / 4 heads, both kernels: 200 contexts of 333 to 500 tokens behind a table of
+// 131072 68 us, 89 with all records asked for; 16 of 1000 to 1500 behind a table of that length, 1.9 MB, 15.0 and 14.4.)
+constexpr long long AHEAD_BYTES = 2ll << 20;
+
 }  // namespace
 
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
@@ -611,6 +625,10 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     S.tiles_per_piece = best;
     S.pieces_max = (int)pieces(own_tiles, best);
     S.pieces_unit = (int)pieces(unit_tiles, best);
+    const long long asked = std::min<long long>(S.pieces_max, LOADS * (many_pieces(S) ? MANY_WAVES : FEW_WAVES));      // per row
+    const long long grid = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit;
+    S.ahead = (asked * S.n_pairs * (b.num_q_heads / b.num_kv_heads) * REC_FLOATS * 4 <= AHEAD_BYTES ||
+               (sv.planned_tiles > 0 && 2 * std::min(grid, (total + best - 1) / best + items / 2) >= grid)) ? 1 : 0;
     S.stream = total < STREAM_TILES ? DecodeShape::STREAM_NEVER
                : sv.planned_tiles > 0 ? DecodeShape::STREAM_PRIVATE : DecodeShape::STREAM_BY_LENGTHS;
     return S;
@@ -645,15 +663,20 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || (!SHARED && S.pieces_max == 1)) return err;   // one piece each: already written
     const dim3 mgrid((unsigned)b.num_reqs, (unsigned)b.num_kv_heads, (unsigned)(b.num_q_heads / b.num_kv_heads));
-    const bool many = S.pieces_max + (SHARED ? S.pieces_unit : 0) > MANY_PIECES;
-    if (a.causal && many)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 16>), mgrid, dim3(16 * 64), 0, stream, a, S, sv);
-    else if (a.causal)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<true, SHARED, 4>), mgrid, dim3(4 * 64), 0, stream, a, S, sv);
-    else if (many)
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 16>), mgrid, dim3(16 * 64), 0, stream, a, S, sv);
-    else
-        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<false, SHARED, 4>), mgrid, dim3(4 * 64), 0, stream, a, S, sv);
+    auto merge = [&](auto causal, auto waves, auto ahead) {
+        hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<decltype(causal)::value, SHARED, decltype(waves)::value, decltype(ahead)::value>), mgrid,
+                           dim3(64 * decltype(waves)::value), 0, stream, a, S, sv);
+    };
+    auto merge_of = [&](auto causal) {
+        using few = std::integral_constant<int, FEW_WAVES>;
+        using many = std::integral_constant<int, MANY_WAVES>;
+        if (many_pieces(S) && S.ahead) merge(causal, many{}, std::true_type{});
+        else if (many_pieces(S)) merge(causal, many{}, std::false_type{});
+        else if (S.ahead) merge(causal, few{}, std::true_type{});
+        else merge(causal, few{}, std::false_type{});
+    };
+    if (a.causal) merge_of(std::true_type{});
+    else merge_of(std::false_type{});
     return hipGetLastError();
 }
 

@@ -596,6 +596,33 @@ def test_decode_large_enough_to_stream(name, group, shared, planned):
     _compare(wl, dw)
 
 
+@pytest.mark.parametrize("reqs,ctx", [(64, [100, 1500]), (3, [17000, 18000]), (1, [1500])])
+def test_decode_behind_a_page_table_much_wider_than_the_contexts(reqs, ctx):
+    """The rows of a serving loop's page table have one width, the longest context it takes.  Most workgroups and records of the
+    plan are for nothing then; what the unused entries of a row hold does not matter."""
+    print("case decode wide table", reqs, ctx, flush=True)
+    lens = [ctx[i % len(ctx)] + i for i in range(reqs)]
+    wl = W.build_workload("decode_wide", "causal", "bf16", 795, num_q_heads=14, num_kv_heads=2, head_dim=128, page_size=16,
+                          prefix_lens=lens, new_lens=[1] * reqs)
+    narrow = _gpu_run(wl)
+    rng = np.random.default_rng(5)
+    wide = rng.integers(-5, 2 * wl.num_pages, (reqs, 8192), dtype=np.int32)
+    wide[:, : wl.page_table.shape[1]] = np.where(wl.page_table >= 0, wl.page_table, wide[:, : wl.page_table.shape[1]])
+    wl.page_table, wl.max_pages_per_req = wide, 8192
+    dw = B.DeviceWorkload(wl)
+    dw.workspace.fill_(0xff)                                 # NaN wherever no record is written
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+    assert torch.equal(dw.k_cache, narrow.k_cache) and torch.equal(dw.v_cache, narrow.v_cache)
+    fused = B.DeviceWorkload(wl)
+    fused.plan_shared(use_hint=False)
+    fused.decode_step(True)
+    torch.cuda.synchronize()
+    _compare(wl, fused)
+
+
 @pytest.mark.parametrize("ps", PAGE_SIZES)
 def test_page_sizes_decode(ps):
     """The decode step on pages of 32 .. 256 tokens: plain, with shared-prefix units, and fused with the scatter."""

@@ -249,7 +249,7 @@ class _SharedPrefixView(ctypes.Structure):
 
 
 class _DecodeShape(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("n_pairs", "n_unit_pairs", "tiles_per_piece", "pieces_max", "pieces_unit", "stream")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("n_pairs", "n_unit_pairs", "tiles_per_piece", "pieces_max", "pieces_unit", "ahead", "stream")]
 
 
 def _decode_plan(n_req, H, Hkv, table_tokens, planned_tiles=0, max_own_tiles=0, num_units=0, max_unit_tiles=0):
@@ -272,3 +272,11 @@ def test_decode_streams_by_what_is_known_of_the_work():
     assert _decode_plan(1, 28, 4, 131072, planned_tiles=47, max_own_tiles=47).stream == NEVER
     assert _decode_plan(64, 28, 4, 8192, planned_tiles=64 * 256, max_own_tiles=256).stream == PRIVATE
     assert _decode_plan(64, 28, 4, 8192, planned_tiles=64 * 23, max_own_tiles=256).stream == NEVER
+
+
+def test_decode_merge_asks_ahead_only_for_what_is_there():
+    """The merge kernel may ask for records before it knows the lengths where those are few or most of them exist."""
+    assert _decode_plan(1, 28, 4, 1504).ahead == 1                             # 28 rows of 12 records
+    assert _decode_plan(64, 28, 4, 131072).ahead == 0                          # up to 1792 rows of 32 records, who knows how many of them
+    assert _decode_plan(64, 28, 4, 131072, planned_tiles=64 * 4096, max_own_tiles=4096).ahead == 1
+    assert _decode_plan(64, 28, 4, 131072, planned_tiles=64 * 40, max_own_tiles=4096).ahead == 0      # one long context, the others short
