@@ -565,10 +565,15 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 //                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds
 // What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
 // longest own part / shared part and with it the pieces per context that the grid must provide; `planned_tiles` is the
-// amount of work there is (32-key tiles per KV head, summed over contexts), by which a ragged batch is known to be one:
-// half a piece is then lost per context (32 contexts of 350 to 4600 tokens, 8 KV heads, 262 MB: pieces of 48 tiles, as for
-// a uniform batch of the longest, 56 us, of 43 48 us, of 32, which do not fit, 54 us).  Without them the host knows only
-// the longest possible context (the width of the page table) and plans for every context being that long.
+// amount of work there is (32-key tiles per KV head, summed over contexts), by which contexts are known to DIFFER: half a piece
+// is then lost per context.  Their workgroups are dealt in the order of the grid, the empty ones among them, so as soon
+// as the grid has more than one for every compute unit some of those get two that are long.  (Told by the workgroups that have
+// work, that came too late: 25 contexts of 800 to 8000 tokens on 4 KV heads, pieces of 77 tiles, 232 workgroups of a grid of 400,
+// 59.6 us, pieces of 41 43.3; 19 of them 48.5, 34.8.  The two constants with _DIFFER are fitted to 189 such batches at 20 piece
+// lengths each: the piece taken is 3 % behind the best one, by the constants for equal contexts 8 %.)  32 contexts of 350 to
+// 4600 tokens, 8 KV heads, 262 MB: pieces of 48 tiles 48.5 us, of 45 46.7, of 40, which do not fit at once, 49.8.
+// Without them the host knows only the longest possible context (the width of the page table) and plans for every context
+// being that long.
 // Without the amount of work the contexts may differ and may share pages, and both do better in shorter pieces: of the
 // lengths within 3 % of the best that fit the chip at once the shortest is taken (8 requests on one video without units:
 // pieces of 45 tiles 35 us, of 36 30 us; 40 contexts of 1000 to 4000 tokens: of 63 55 us, of 43 48 us).  A batch of one request
@@ -576,6 +581,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 // Records are kept to what fits the library's own array (attn_bf16_decode_static_scratch_bytes) wherever longer pieces
 // can do that, so that batches do not outgrow it.
 constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
+constexpr double TILE_CU_DIFFER_US = 0.42, WORKGROUP_DIFFER_US = 0.004;
 constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 
 // The merge kernel asks for records before it knows which of them there are when they are few in all, or when the amount of
@@ -602,24 +608,45 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     const long long longest = std::max(own_tiles, unit_tiles);
     const bool one = b.num_reqs == 1 && sv.num_units == 0;
     const int at_once = one ? WORKGROUPS_PER_ROUND_ONE_REQUEST : WORKGROUPS_PER_ROUND;
-    auto full = [](long long tiles, int tpp) { return tiles / tpp + (tiles % tpp > tpp / 4 ? 1 : 0); };      // pieces worth counting
-    double least = -1;
-    int best = MIN_TILES_PER_PIECE;
+    // the cut into pieces of tpp tiles
+    struct Cut {
+        int tpp;
+        long long own, unit, grid;                           // pieces of the longest own part and of the longest shared part, workgroups
+    };
+    auto cut_of = [&](int tpp) {
+        Cut c = {tpp, pieces(own_tiles, tpp), S.n_unit_pairs > 0 ? pieces(unit_tiles, tpp) : 1, 0};
+        c.grid = S.n_pairs * c.own + S.n_unit_pairs * c.unit;
+        return c;
+    };
+    // those of n pieces of a part that are worth counting: not a last one of under a quarter
+    auto full = [](long long tiles, long long n, int tpp) { return tiles > 0 && 4 * (tiles - (n - 1) * tpp) <= tpp ? n - 1 : n; };
+    // workgroups that have work: of equal contexts all of the grid
+    auto busy_of = [&](const Cut& c) { return std::max<long long>(1, known ? std::min(c.grid, (total + c.tpp - 1) / c.tpp + items / 2) : c.grid); };
+    auto cost_of = [&](const Cut& c) {
+        const long long busy = busy_of(c);
+        const bool doubled = (known ? c.grid : S.n_pairs * full(own_tiles, c.own, c.tpp) + S.n_unit_pairs * full(unit_tiles, c.unit, c.tpp)) > WORKGROUPS_PER_ROUND / 2;
+        const double piece = std::min<long long>(c.tpp, longest) * (known ? TILE_CU_DIFFER_US : TILE_CU_US);
+        double cost = START_US + std::max(total * TILE_HBM_US, piece * (doubled ? 2 : 1));
+        const long long last_round = busy % WORKGROUPS_PER_ROUND;
+        if (busy > WORKGROUPS_PER_ROUND)
+            cost += START_US * 0.25 * (busy / WORKGROUPS_PER_ROUND) +
+                    (last_round ? 0.5 * piece * (1.0 - (double)last_round / WORKGROUPS_PER_ROUND) : 0.0);
+        if (S.n_unit_pairs > 0 || c.own > 1) cost += MERGE_US;
+        return cost + (known ? WORKGROUP_DIFFER_US : WORKGROUP_US) * c.grid;
+    };
     const int longest_piece = (int)std::max<long long>(MIN_TILES_PER_PIECE, std::min<long long>(MAX_TILES_PER_PIECE, longest));
-    for (int tpp = longest_piece; tpp >= MIN_TILES_PER_PIECE; --tpp) {   // ties: the longer piece
-        const long long grid = S.n_pairs * pieces(own_tiles, tpp) + S.n_unit_pairs * pieces(unit_tiles, tpp);
-        const long long wgs = std::max<long long>(1, known ? std::min(grid, (total + tpp - 1) / tpp + items / 2) : grid);
-        if (tpp < longest_piece && ((sv.num_units == 0 && grid > STATIC_RECORDS) || (one && wgs > at_once))) break;
-        const bool doubled = (known ? wgs : S.n_pairs * full(own_tiles, tpp) + S.n_unit_pairs * full(unit_tiles, tpp)) > WORKGROUPS_PER_ROUND / 2;
-        const double piece = (double)std::min<long long>(tpp, longest);
-        double cost = START_US + std::max(total * TILE_HBM_US, piece * TILE_CU_US * (doubled ? 2 : 1));
-        const long long last_round = wgs % WORKGROUPS_PER_ROUND;
-        if (wgs > WORKGROUPS_PER_ROUND)
-            cost += START_US * 0.25 * (wgs / WORKGROUPS_PER_ROUND) +
-                    (last_round ? 0.5 * piece * TILE_CU_US * (1.0 - (double)last_round / WORKGROUPS_PER_ROUND) : 0.0);
-        if (S.n_unit_pairs > 0 || pieces(own_tiles, tpp) > 1) cost += MERGE_US;
-        cost += WORKGROUP_US * grid;
-        if (least < 0 || cost < least || (sv.planned_tiles == 0 && wgs <= at_once && cost <= 1.03 * least)) best = tpp;
+    int best = longest_piece;
+    double least = -1;
+    Cut next = cut_of(longest_piece);
+    for (int tpp = longest_piece; tpp >= MIN_TILES_PER_PIECE; --tpp) {
+        const Cut c = next;
+        if (tpp > MIN_TILES_PER_PIECE) next = cut_of(tpp - 1);
+        if (tpp < longest_piece && ((sv.num_units == 0 && c.grid > STATIC_RECORDS) || (one && c.grid > at_once))) break;
+        const double cost = cost_of(c);
+        // ties: the longer piece, but of contexts that differ the shorter one that fits at once, by which they differ less
+        if (least < 0 || cost < least || (known && cost == least && busy_of(c) <= at_once) ||
+            (sv.planned_tiles == 0 && c.grid <= at_once && cost <= 1.03 * least))
+            best = tpp;
         if (least < 0 || cost < least) least = cost;
     }
     S.tiles_per_piece = best;

@@ -280,3 +280,15 @@ def test_decode_merge_asks_ahead_only_for_what_is_there():
     assert _decode_plan(64, 28, 4, 131072).ahead == 0                          # up to 1792 rows of 32 records, who knows how many of them
     assert _decode_plan(64, 28, 4, 131072, planned_tiles=64 * 4096, max_own_tiles=4096).ahead == 1
     assert _decode_plan(64, 28, 4, 131072, planned_tiles=64 * 40, max_own_tiles=4096).ahead == 0      # one long context, the others short
+
+
+# piece lengths (tiles of 32 keys) that measured within 10 % of the best for batches whose contexts are spread evenly
+@pytest.mark.parametrize("n_req,H,Hkv,lo,hi,shortest,longest", [(25, 28, 4, 800, 8000, 16, 45), (19, 28, 4, 800, 8000, 22, 36), (12, 28, 4, 800, 8000, 16, 28),
+                                                                (19, 32, 8, 384, 3844, 24, 36), (74, 16, 2, 401, 4019, 26, 36)])
+def test_decode_plan_of_contexts_known_to_differ(n_req, H, Hkv, lo, hi, shortest, longest):
+    """With the amount of work given, a batch whose contexts differ is not cut in pieces so long that a compute unit which gets
+    two of them ends long after the others."""
+    tiles = [-(-int(c) // 32) for c in np.linspace(lo, hi, n_req)]
+    S = _decode_plan(n_req, H, Hkv, hi, planned_tiles=sum(tiles), max_own_tiles=max(tiles))
+    assert shortest <= S.tiles_per_piece <= longest, S.tiles_per_piece
+    assert S.pieces_max == -(-max(tiles) // S.tiles_per_piece)
