@@ -561,6 +561,9 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 //                   (8 x 18432 tokens: 288 workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us)
 //   two workgroups fit a compute unit, 512 the chip; what does not fit starts when others end, and a last round that is
 //   nearly empty lasts as long as a full one: half of its emptiness is charged (608 workgroups of 32 tiles: 58 us)
+//   equal contexts are cut evenly: of the lengths that give the same number of pieces the shortest, so that no sliver takes the
+//   place of a workgroup with work (64 x 8192 tokens, 256 tiles: 85 + 85 + 85 + 1 180 us, 64 four times 176; of contexts from
+//   2048 to 8191 133 and 125)
 //   MERGE           the second kernel, which a batch cut in single pieces does without (128 contexts of 1000 tokens: 15.7 us
 //                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds
 // What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
@@ -620,11 +623,14 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     };
     // those of n pieces of a part that are worth counting: not a last one of under a quarter
     auto full = [](long long tiles, long long n, int tpp) { return tiles > 0 && 4 * (tiles - (n - 1) * tpp) <= tpp ? n - 1 : n; };
-    // workgroups that have work: of equal contexts all of the grid
-    auto busy_of = [&](const Cut& c) { return std::max<long long>(1, known ? std::min(c.grid, (total + c.tpp - 1) / c.tpp + items / 2) : c.grid); };
+    // workgroups that have work worth counting
+    auto busy_of = [&](const Cut& c) {
+        return std::max<long long>(1, known ? std::min(c.grid, (total + c.tpp - 1) / c.tpp + items / 2)
+                                            : S.n_pairs * full(own_tiles, c.own, c.tpp) + S.n_unit_pairs * full(unit_tiles, c.unit, c.tpp));
+    };
     auto cost_of = [&](const Cut& c) {
         const long long busy = busy_of(c);
-        const bool doubled = (known ? c.grid : S.n_pairs * full(own_tiles, c.own, c.tpp) + S.n_unit_pairs * full(unit_tiles, c.unit, c.tpp)) > WORKGROUPS_PER_ROUND / 2;
+        const bool doubled = (known ? c.grid : busy) > WORKGROUPS_PER_ROUND / 2;
         const double piece = std::min<long long>(c.tpp, longest) * (known ? TILE_CU_DIFFER_US : TILE_CU_US);
         double cost = START_US + std::max(total * TILE_HBM_US, piece * (doubled ? 2 : 1));
         const long long last_round = busy % WORKGROUPS_PER_ROUND;
@@ -642,6 +648,7 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
         const Cut c = next;
         if (tpp > MIN_TILES_PER_PIECE) next = cut_of(tpp - 1);
         if (tpp < longest_piece && ((sv.num_units == 0 && c.grid > STATIC_RECORDS) || (one && c.grid > at_once))) break;
+        if (!known && tpp > MIN_TILES_PER_PIECE && next.grid == c.grid) continue;           // the same number of pieces, more alike
         const double cost = cost_of(c);
         // ties: the longer piece, but of contexts that differ the shorter one that fits at once, by which they differ less
         if (least < 0 || cost < least || (known && cost == least && busy_of(c) <= at_once) ||

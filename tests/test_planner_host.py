@@ -292,3 +292,18 @@ def test_decode_plan_of_contexts_known_to_differ(n_req, H, Hkv, lo, hi, shortest
     S = _decode_plan(n_req, H, Hkv, hi, planned_tiles=sum(tiles), max_own_tiles=max(tiles))
     assert shortest <= S.tiles_per_piece <= longest, S.tiles_per_piece
     assert S.pieces_max == -(-max(tiles) // S.tiles_per_piece)
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_decode_plan_of_equal_contexts_is_cut_evenly(seed):
+    """Pieces of equal contexts are as short as their number allows: no last piece that is a sliver beside the others."""
+    rng = np.random.default_rng(2100 + seed)
+    for _ in range(20):
+        Hkv, n_req = int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 2, 5, 16, 64, 100]))
+        tiles = int(2 ** rng.uniform(3, 11))
+        if Hkv * n_req * -(-tiles // 124) > 2016:
+            continue
+        hints = dict(planned_tiles=n_req * tiles, max_own_tiles=tiles) if rng.random() < 0.5 else {}
+        S = _decode_plan(n_req, 4 * Hkv, Hkv, 32 * tiles, **hints)
+        assert S.pieces_max == -(-tiles // S.tiles_per_piece)
+        assert S.tiles_per_piece == 4 or -(-tiles // (S.tiles_per_piece - 1)) > S.pieces_max, (n_req, Hkv, tiles, S.tiles_per_piece)
