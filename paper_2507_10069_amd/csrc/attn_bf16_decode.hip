@@ -579,10 +579,13 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 // being that long.
 // Without the amount of work the contexts may differ and may share pages, and both do better in shorter pieces: of the
 // lengths within 3 % of the best that fit the chip at once the shortest is taken (8 requests on one video without units:
-// pieces of 45 tiles 35 us, of 36 30 us; 40 contexts of 1000 to 4000 tokens: of 63 55 us, of 43 48 us).  A batch of one request
+// pieces of 45 tiles 35 us, of 36 30 us; 40 contexts of 1000 to 4000 tokens: of 63 55 us, of 43 48 us).  And where the
+// longest piece bounds the time, not HBM, those of one and a half rounds count as well, up to 12 % more by the model of equal ones
+// (22 contexts of 1200 to 4900 tokens, 8 KV heads: of 77 tiles 67 us, of 39 52).  A batch of one request
 // is kept to 384 workgroups: its contexts cannot differ (131072 tokens: 48 us, 47 in 256 workgroups, 53 in 512).
 // Records are kept to what fits the library's own array (attn_bf16_decode_static_scratch_bytes) wherever longer pieces
-// can do that, so that batches do not outgrow it.
+// can do that, so that batches do not outgrow it.  A batch that needs more at any length has its pairs fill the chip several times
+// over, and is best left to the longest pieces (300 contexts of 4120 tokens on 8 KV heads, 129 tiles: 124 + 5 804 us, 65 + 64 819).
 constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
 constexpr double TILE_CU_DIFFER_US = 0.42, WORKGROUP_DIFFER_US = 0.004;
 constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
@@ -610,6 +613,7 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     const bool known = sv.planned_tiles > 0 && total < most;             // contexts differ
     const long long longest = std::max(own_tiles, unit_tiles);
     const bool one = b.num_reqs == 1 && sv.num_units == 0;
+    const bool may_differ = sv.planned_tiles == 0 && sv.num_units == 0 && !one;
     const int at_once = one ? WORKGROUPS_PER_ROUND_ONE_REQUEST : WORKGROUPS_PER_ROUND;
     // the cut into pieces of tpp tiles
     struct Cut {
@@ -643,6 +647,7 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     const int longest_piece = (int)std::max<long long>(MIN_TILES_PER_PIECE, std::min<long long>(MAX_TILES_PER_PIECE, longest));
     int best = longest_piece;
     double least = -1;
+    bool best_is_bound_by_its_longest = false;
     Cut next = cut_of(longest_piece);
     for (int tpp = longest_piece; tpp >= MIN_TILES_PER_PIECE; --tpp) {
         const Cut c = next;
@@ -650,10 +655,14 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
         if (tpp < longest_piece && ((sv.num_units == 0 && c.grid > STATIC_RECORDS) || (one && c.grid > at_once))) break;
         if (!known && tpp > MIN_TILES_PER_PIECE && next.grid == c.grid) continue;           // the same number of pieces, more alike
         const double cost = cost_of(c);
+        // what contexts that may differ are to be taken for the better one at: see above
+        const bool at_a_time = c.grid <= at_once, nearly = c.grid <= at_once + at_once / 2 && best_is_bound_by_its_longest;
         // ties: the longer piece, but of contexts that differ the shorter one that fits at once, by which they differ less
         if (least < 0 || cost < least || (known && cost == least && busy_of(c) <= at_once) ||
-            (sv.planned_tiles == 0 && c.grid <= at_once && cost <= 1.03 * least))
+            (sv.planned_tiles == 0 && ((at_a_time && cost <= 1.03 * least) || (nearly && cost <= 1.12 * least)))) {
             best = tpp;
+            best_is_bound_by_its_longest = may_differ && c.grid > WORKGROUPS_PER_ROUND / 2 && 2 * tpp * TILE_CU_US >= 0.9 * total * TILE_HBM_US;
+        }
         if (least < 0 || cost < least) least = cost;
     }
     S.tiles_per_piece = best;

@@ -307,3 +307,11 @@ def test_decode_plan_of_equal_contexts_is_cut_evenly(seed):
         S = _decode_plan(n_req, 4 * Hkv, Hkv, 32 * tiles, **hints)
         assert S.pieces_max == -(-tiles // S.tiles_per_piece)
         assert S.tiles_per_piece == 4 or -(-tiles // (S.tiles_per_piece - 1)) > S.pieces_max, (n_req, Hkv, tiles, S.tiles_per_piece)
+
+
+# piece lengths that measured within 8 % of the best for contexts spread from a quarter of this length up, and for equal ones
+@pytest.mark.parametrize("n_req,H,Hkv,longest,shortest_piece,longest_piece", [(22, 32, 8, 4880, 36, 46), (40, 28, 4, 4000, 42, 45), (64, 28, 4, 8191, 43, 86),
+                                                                              (8, 28, 4, 18000, 24, 44), (128, 28, 4, 1000, 32, 32)])
+def test_decode_plan_without_hints_suits_equal_and_different_contexts(n_req, H, Hkv, longest, shortest_piece, longest_piece):
+    S = _decode_plan(n_req, H, Hkv, longest)
+    assert shortest_piece <= S.tiles_per_piece <= longest_piece, S.tiles_per_piece
