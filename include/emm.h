@@ -108,7 +108,8 @@ emm_status emm_kv_scatter(const emm_batch *batch, const void *k_new, const void 
  *     emm_prefill_plan_host shows the plan;
  *   decode batch (at most one new token per request and at most 16 query heads per KV head): every context is
  *     cut; 8320 bytes per (request, KV head, piece), a piece being 128 to 3968 keys of the longest context the
- *     page table can hold.
+ *     page table can hold.  The size is enough for the same batch with any hints (emm_shared_prefix without units): up to
+ *     16 MiB are reserved for them where the call itself needs less.
  * The contents need no initialisation and mean nothing afterwards.  Calls on different streams must not share a
  * workspace.  Host-only; reads only the scalar fields. */
 emm_status emm_prefill_attn_workspace_size(const emm_batch *batch, size_t *bytes);
@@ -257,7 +258,7 @@ typedef struct {
 
 /* Workspace bytes of emm_decode_attn_shared / emm_decode_step for this batch and the four scalar fields of
  * `shared` (the values the call itself will be given; num_units <= num_reqs / 2; the pointers are not looked
- * at; NULL = no units and no hints).
+ * at; NULL = no units and no hints).  Without units never more than emm_prefill_attn_workspace_size of the batch.
  * EMM_ERR_UNSUPPORTED unless the batch is EMM_BF16, head_dim 128, at most 16 query heads per KV head. */
 emm_status emm_decode_attn_shared_workspace_size(const emm_batch *batch, const emm_shared_prefix *shared,
                                                  size_t *bytes);

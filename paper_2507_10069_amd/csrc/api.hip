@@ -77,15 +77,14 @@ emm::SharedPrefixView shared_view_of(const emm_shared_prefix* sp)
                                  sp->max_unit_tiles};
 }
 
-// The plan of a decode batch with the units and hints of `sp`, if they are such as the header allows.
-emm_status plan_decode_shared(const emm_batch* b, const emm::BatchView& v, const emm_shared_prefix* sp, emm::DecodeShape* shape)
+// Are the units and hints of `sp` such as the header allows for this batch?
+emm_status check_decode_shared(const emm_batch* b, const emm::BatchView& v, const emm_shared_prefix* sp)
 {
     if (sp->num_units < 0 || sp->num_units > b->num_reqs / 2 || sp->planned_tiles < 0 || sp->max_own_tiles < 0 ||
         sp->max_unit_tiles < 0)
         return EMM_ERR_INVALID_ARG;
     if (b->max_new_len > 1) return EMM_ERR_INVALID_ARG;
     if (b->dtype != EMM_BF16 || !emm::attn_bf16_decode_applies(v)) return EMM_ERR_UNSUPPORTED;
-    *shape = emm::attn_bf16_decode_shape(v, shared_view_of(sp));
     return EMM_OK;
 }
 
@@ -109,8 +108,9 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     emm::DecodeShape shape = {};                             // planned here, for the workspace check and the launch alike
     size_t need = 0;
     if (sp != nullptr) {
-        st = plan_decode_shared(b, view, sp, &shape);
+        st = check_decode_shared(b, view, sp);
         if (st != EMM_OK) return st;
+        shape = emm::attn_bf16_decode_shape(view, shared_view_of(sp));
     } else if (decode) {
         shape = emm::attn_bf16_decode_shape(view, emm::SharedPrefixView{});
     }
@@ -196,7 +196,7 @@ emm_status emm_prefill_attn_workspace_size(const emm_batch* b, size_t* bytes)
     if (st != EMM_OK) return st;
     if (b->dtype == EMM_BF16) {
         const emm::BatchView v = view_of(b);
-        *bytes = emm::attn_bf16_decode_applies(v) ? emm::attn_bf16_decode_workspace_bytes(emm::attn_bf16_decode_shape(v, emm::SharedPrefixView{}))
+        *bytes = emm::attn_bf16_decode_applies(v) ? emm::attn_bf16_decode_reserve_bytes(v, emm::SharedPrefixView{})
                                                   : emm::attn_bf16_d128_workspace_bytes(v);
     }
     return EMM_OK;
@@ -233,10 +233,9 @@ emm_status emm_decode_attn_shared_workspace_size(const emm_batch* b, const emm_s
     if (st != EMM_OK) return st;
     static const emm_shared_prefix no_units = {};
     if (sp == nullptr) sp = &no_units;
-    emm::DecodeShape shape;
-    st = plan_decode_shared(b, view_of(b), sp, &shape);
+    st = check_decode_shared(b, view_of(b), sp);
     if (st != EMM_OK) return st;
-    *bytes = emm::attn_bf16_decode_workspace_bytes(shape);
+    *bytes = emm::attn_bf16_decode_reserve_bytes(view_of(b), shared_view_of(sp));
     return EMM_OK;
 }
 

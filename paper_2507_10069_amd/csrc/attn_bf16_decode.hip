@@ -37,6 +37,7 @@
 #include "attn_bf16_common.h"
 
 #include <algorithm>
+#include <climits>
 #include <mutex>
 #include <type_traits>
 
@@ -595,14 +596,21 @@ constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 // 131072 68 us, 89 with all records asked for; 16 of 1000 to 1500 behind a table of that length, 1.9 MB, 15.0 and 14.4.)
 constexpr long long AHEAD_BYTES = 2ll << 20;
 
-}  // namespace
+// Hints never make a plan without units need more records than the same batch without hints, so that a caller may allocate once, by
+// the batch alone.  Room is therefore left for the shorter pieces of contexts that are known to differ: what a batch without
+// hints reports is at least as many records as the library's own array holds, up to RESERVED_PIECES for a context, and hints
+// are planned within that.  (Room for 768 records only: 52 of 87 such batches would get longer pieces, and 5 to 16 % slower for it.)
+constexpr int RESERVED_PIECES = 96;
 
-DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
+long long table_tiles_of(const BatchView& b) { return ((long long)b.max_pages * b.page_size + BK - 1) / BK; }
+
+// most_allowed: records (own pieces, without units) that the plan may need, unless even the longest pieces need more
+DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_allowed)
 {
     DecodeShape S;
     S.n_pairs = b.num_reqs * b.num_kv_heads;
     S.n_unit_pairs = sv.num_units * b.num_kv_heads;
-    const long long table_tiles = ((long long)b.max_pages * b.page_size + BK - 1) / BK;       // longest possible context
+    const long long table_tiles = table_tiles_of(b);         // longest possible context
     const long long own_tiles = sv.max_own_tiles > 0 ? std::min<long long>(sv.max_own_tiles, table_tiles) : table_tiles;
     const long long unit_tiles = sv.num_units == 0 ? 0
                                  : sv.max_unit_tiles > 0 ? std::min<long long>(sv.max_unit_tiles, table_tiles) : table_tiles;
@@ -652,7 +660,7 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     for (int tpp = longest_piece; tpp >= MIN_TILES_PER_PIECE; --tpp) {
         const Cut c = next;
         if (tpp > MIN_TILES_PER_PIECE) next = cut_of(tpp - 1);
-        if (tpp < longest_piece && ((sv.num_units == 0 && c.grid > STATIC_RECORDS) || (one && c.grid > at_once))) break;
+        if (tpp < longest_piece && ((sv.num_units == 0 && c.grid > STATIC_RECORDS) || (one && c.grid > at_once) || c.grid > most_allowed)) break;
         if (!known && tpp > MIN_TILES_PER_PIECE && next.grid == c.grid) continue;           // the same number of pieces, more alike
         const double cost = cost_of(c);
         // what contexts that may differ are to be taken for the better one at: see above
@@ -677,6 +685,28 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
     return S;
 }
 
+bool has_hints(const BatchView& b, const SharedPrefixView& sv)
+{
+    return sv.planned_tiles > 0 || (sv.max_own_tiles > 0 && sv.max_own_tiles < table_tiles_of(b));
+}
+
+// pieces of a context that the workspace of the batch without units and hints has room for at least
+long long pieces_reserved(const BatchView& b)
+{
+    const long long n_pairs = std::max<long long>(1, (long long)b.num_reqs * b.num_kv_heads);
+    return std::min({(long long)RESERVED_PIECES, STATIC_RECORDS / n_pairs, (table_tiles_of(b) + MIN_TILES_PER_PIECE - 1) / MIN_TILES_PER_PIECE});
+}
+
+}  // namespace
+
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
+{
+    const DecodeShape S = plan(b, sv, LLONG_MAX);
+    if (sv.num_units > 0 || !has_hints(b, sv) || S.pieces_max <= pieces_reserved(b)) return S;
+    const long long room = std::max<long long>(pieces_reserved(b), plan(b, SharedPrefixView{}, LLONG_MAX).pieces_max);
+    return S.pieces_max <= room ? S : plan(b, sv, room * S.n_pairs);
+}
+
 bool attn_bf16_decode_applies(const BatchView& b)
 {
     return b.max_new_len <= 1 && b.num_q_heads / b.num_kv_heads <= MAX_G;
@@ -685,6 +715,13 @@ bool attn_bf16_decode_applies(const BatchView& b)
 size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S)
 {
     return (unit_records_offset(S) + (size_t)S.n_unit_pairs * S.pieces_unit * MAX_ROWS * REC_FLOATS) * sizeof(float);
+}
+
+size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView& sv)
+{
+    DecodeShape S = attn_bf16_decode_shape(b, sv);
+    if (sv.num_units == 0 && !has_hints(b, sv)) S.pieces_max = (int)std::max<long long>(S.pieces_max, pieces_reserved(b));
+    return attn_bf16_decode_workspace_bytes(S);
 }
 
 namespace {

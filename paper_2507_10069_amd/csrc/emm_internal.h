@@ -95,6 +95,8 @@ struct DecodeShape {
 };
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv);
 size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S);
+// what a caller is told to bring: of a batch without units and hints enough for the same batch with any hints
+size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView& sv);
 // attention of the batch, with sv's units if it has any; fused: with the scatter of the query tokens' own K/V rows too (a.k_new,
 // a.v_new; pools writable; causal)
 hipError_t launch_attn_bf16_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, bool fused, hipStream_t stream);

@@ -223,7 +223,7 @@ def test_decode_workspace_holds_the_pieces_of_the_longest_context(n_req, Hkv, G,
 
 def test_decode_plan_of_a_single_request_uses_fewer_longer_pieces():
     """One request cannot be ragged: its contexts are cut so that about 1.5 workgroups per compute unit (at most 384)
-    stream them, where a batch of several requests is planned for rounds of 768."""
+    stream them, where a batch of several requests is planned for rounds of 512 (and reserves room for shorter pieces)."""
     per_piece = 16 * 130 * 4
     def pieces(n_req, max_pages):
         b = B.make_batch(num_reqs=n_req, num_q_heads=28, num_kv_heads=4, head_dim=128, page_size=16, num_pages=1 << 20,
@@ -315,3 +315,23 @@ def test_decode_plan_of_equal_contexts_is_cut_evenly(seed):
 def test_decode_plan_without_hints_suits_equal_and_different_contexts(n_req, H, Hkv, longest, shortest_piece, longest_piece):
     S = _decode_plan(n_req, H, Hkv, longest)
     assert shortest_piece <= S.tiles_per_piece <= longest_piece, S.tiles_per_piece
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_decode_hints_never_grow_the_workspace(seed):
+    """Whatever hints a step brings, the workspace that the batch without hints asks for is enough (no units)."""
+    rng = np.random.default_rng(2300 + seed)
+    for _ in range(50):
+        Hkv, G, n_req = int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 4, 7, 8])), int(rng.integers(1, 65))
+        top = int(2 ** rng.uniform(6, 16))
+        ctx = rng.integers(1, top + 1, n_req)
+        width = int(-(-int(ctx.max()) // 16) * rng.choice([1, 1, 2, 8]))
+        b = B.make_batch(num_reqs=n_req, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=128, page_size=16, num_pages=1 << 20,
+                         max_pages_per_req=width, total_new_tokens=n_req, max_new_len=1, dtype="bf16", softmax_scale=0.1)
+        size = B.emm_prefill_attn_workspace_size(b)
+        tiles = -(-ctx // 32)
+        for hints in ({"planned_tiles": int(tiles.sum()), "max_own_tiles": int(tiles.max())}, {"planned_tiles": int(tiles.sum())},
+                      {"max_own_tiles": int(tiles.max())}, {"planned_tiles": int(rng.integers(1, 2 * n_req * top))}):
+            assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0, **hints)) <= size, (n_req, Hkv, width, hints)
+        assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0)) == size
+        assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0, max_unit_tiles=3)) == size
