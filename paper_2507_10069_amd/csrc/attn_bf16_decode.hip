@@ -166,12 +166,17 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int t_begin = t_off + piece * S.tiles_per_piece;
     // Wave w does blocks w, w + 4, ... of the piece; lane k holds where in the pool its k-th one lies.  Asked for before
     // the lengths are known, so that the two loads overlap: entries past the request's pages are read (the row
-    // has max_pages of them) and forced into the pool, but never fetched from.
+    // has max_pages of them) and forced into the pool, but never fetched from.  (S.late: after them, so that workgroups without
+    // work do not stay for the answer.)
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
     const int blk16 = t_begin * BLOCKS_PER_TILE + wave + NW * lane;       // logical 16-key block of the request
-    const int pg_raw = pt[min(blk16 >> b.page_shift, b.max_pages - 1)];   // (max_pages > 0: checked on the host)
     const int pg_first = __builtin_amdgcn_readfirstlane(min(blk16 >> b.page_shift, b.max_pages - 1));    // of the wave's first block
-    const int holders = S.stream != DecodeShape::STREAM_NEVER ? first_holders(b, pg_first) : 0;
+    int pg_raw = 0, holders = 0;
+    auto ask_pages = [&]() {
+        pg_raw = pt[min(blk16 >> b.page_shift, b.max_pages - 1)];         // (max_pages > 0: checked on the host)
+        if (S.stream != DecodeShape::STREAM_NEVER) holders = first_holders(b, pg_first);
+    };
+    if (!S.late) ask_pages();
     asm volatile("" ::"s"(new_len), "s"(prefix_len), "s"(cu_new));
     __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
@@ -192,6 +197,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         direct = false;
     }
     if (piece >= n_pieces) return;
+    if (S.late) ask_pages();
     const int n_blocks = min(S.tiles_per_piece * BLOCKS_PER_TILE, (kv_len + BLK - 1) / BLK - t_begin * BLOCKS_PER_TILE);    // of the piece; 0 only for an empty context
     const int n_mine = n_blocks > wave ? (n_blocks - wave + NW - 1) / NW : 0;
     // in units of 4096 bytes (one block of one KV head): (page, KV head, block within the page)
@@ -595,6 +601,10 @@ constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 // work says that at least half of them are.  (28 / 4 heads, both kernels: 200 contexts of 333 to 500 tokens behind a table of
 // 131072 68 us, 89 with all records asked for; 16 of 1000 to 1500 behind a table of that length, 1.9 MB, 15.0 and 14.4.)
 constexpr long long AHEAD_BYTES = 2ll << 20;
+// Without the amount of work a grid of several rounds is mostly one of a page table wider than the contexts.  Its workgroups without
+// work leave on the lengths alone then (64 / 8 heads, 73 contexts of 50 to 500 tokens behind a table of 131072: 50 -> 43 us, 128 of 300 to
+// 900 on 32 / 8 heads 99 -> 88); a workgroup with work starts half a microsecond later for it (64 contexts that do have 8192: 177 -> 180).
+constexpr long long LATE_GRID = 4 * WORKGROUPS_PER_ROUND;
 
 // Hints never make a plan without units need more records than the same batch without hints, so that a caller may allocate once, by
 // the batch alone.  Room is therefore left for the shorter pieces of contexts that are known to differ: what a batch without
@@ -680,6 +690,7 @@ DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_
     const long long grid = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit;
     S.ahead = (asked * S.n_pairs * (b.num_q_heads / b.num_kv_heads) * REC_FLOATS * 4 <= AHEAD_BYTES ||
                (sv.planned_tiles > 0 && 2 * std::min(grid, (total + best - 1) / best + items / 2) >= grid)) ? 1 : 0;
+    S.late = sv.planned_tiles == 0 && grid > LATE_GRID ? 1 : 0;
     S.stream = total < STREAM_TILES ? DecodeShape::STREAM_NEVER
                : sv.planned_tiles > 0 ? DecodeShape::STREAM_PRIVATE : DecodeShape::STREAM_BY_LENGTHS;
     return S;

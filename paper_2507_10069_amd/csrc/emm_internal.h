@@ -90,6 +90,7 @@ struct DecodeShape {
     int pieces_max;         // workgroups per pair in the grid (a pair uses as many as its context needs)
     int pieces_unit;        // workgroups per (unit, KV head) pair in the grid
     int ahead;              // 1: the merge kernel asks for records before it knows the lengths: see AHEAD_BYTES
+    int late;               // 1: the decode kernel asks for page ids after the lengths: see LATE_GRID
     int stream;             // which K and V are fetched past the caches: see STREAM_BYTES
     enum { STREAM_NEVER, STREAM_PRIVATE /* those that no other request holds */, STREAM_BY_LENGTHS /* the same, of contexts that are long enough */ };
 };

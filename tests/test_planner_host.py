@@ -249,7 +249,7 @@ class _SharedPrefixView(ctypes.Structure):
 
 
 class _DecodeShape(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("n_pairs", "n_unit_pairs", "tiles_per_piece", "pieces_max", "pieces_unit", "ahead", "stream")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("n_pairs", "n_unit_pairs", "tiles_per_piece", "pieces_max", "pieces_unit", "ahead", "late", "stream")]
 
 
 def _decode_plan(n_req, H, Hkv, table_tokens, planned_tiles=0, max_own_tiles=0, num_units=0, max_unit_tiles=0):
@@ -335,3 +335,10 @@ def test_decode_hints_never_grow_the_workspace(seed):
             assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0, **hints)) <= size, (n_req, Hkv, width, hints)
         assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0)) == size
         assert B.emm_decode_attn_shared_workspace_size(b, B.make_shared_prefix(0, max_unit_tiles=3)) == size
+
+
+def test_decode_workgroups_leave_on_the_lengths_where_most_have_no_work():
+    """Page ids are asked for together with the lengths unless the grid is that of a table much wider than the chip needs."""
+    assert _decode_plan(64, 28, 4, 131072).late == 1 and _decode_plan(256, 32, 8, 131072).late == 1
+    assert _decode_plan(64, 28, 4, 8192).late == 0 and _decode_plan(1, 28, 4, 131072).late == 0
+    assert _decode_plan(64, 28, 4, 131072, planned_tiles=64 * 47, max_own_tiles=50).late == 0
