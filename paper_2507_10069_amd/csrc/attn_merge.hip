@@ -24,7 +24,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // the request that packed token t belongs to: the last r with cu_new_lens[r] <= t among requests that have tokens
 // (what the array holds is forced into range wherever an index depends on it).  Among up to 64 requests the lanes look at one
 // offset each and a ballot for each of the wave's four rows counts them (all lanes must be there): one round trip
-// instead of one per search step.  With the two parts asked for first, the kernel takes 4.9 instead of 5.1 us for 7168 rows of 64 requests.
+// instead of one per search step.
 __device__ inline int request_of_token(const BatchView& b, int t)
 {
     if (b.num_reqs <= 64) {
@@ -58,16 +58,17 @@ __global__ __launch_bounds__(THREADS) void attn_merge_parts_kernel(BatchView b, 
     const long long my_row = (long long)blockIdx.x * (THREADS / 16) + (threadIdx.x >> 4);
     const long long row = my_row < n_rows ? my_row : n_rows - 1;          // every lane stays for the ballots: left below
     const int t = n_rows <= 0x7fffffff ? (int)row / b.num_q_heads : (int)(row / b.num_q_heads);   // (a 64-bit division is 150 instructions)
-    // both parts, asked for before it is known whether the row has a first one (a row without holds whatever the workspace did)
-    const float lo = lse_own[row], ls = lse_shared[row];
-    const long long at = row * D + (threadIdx.x & 15) * 8;
-    const bf16x8 a = *(const bf16x8*)(out_shared + at);
-    const bf16x8 c = *(const bf16x8*)(out + at);
+    const float lo = lse_own[row];
     const int r = request_of_token(b, t);
-    const bool member = req_shared_len[r] > 0 && my_row < n_rows;
-    asm volatile("" ::"v"(a), "v"(c), "v"(lo), "v"(ls));     // waited for with the request's entry, not asked for behind it
     float merged = lo;
-    if (member) {
+    // The parts are read for members only: a batch may hold a group of short questions beside long prompts that are in no group.
+    // (Asked for in every row, before it is known, they take no time off a batch of members: 91.5 us both ways for 64 short questions on
+    // 8 videos; beside a group of 16, a prompt of 4096 tokens 202 -> 197 us, four of them 556 -> 534.)
+    if (req_shared_len[r] > 0 && my_row < n_rows) {
+        const long long at = row * D + (threadIdx.x & 15) * 8;
+        const float ls = lse_shared[row];
+        const bf16x8 a = *(const bf16x8*)(out_shared + at);
+        const bf16x8 c = *(const bf16x8*)(out + at);
         const float m = fmaxf(ls, lo);
         if (m > -INFINITY) {
             const float ws = __expf(ls - m), wo = __expf(lo - m);
