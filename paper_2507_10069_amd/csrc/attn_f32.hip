@@ -7,9 +7,9 @@
 // What bounds it: such calls are small (a few hundred rows, up to a few thousand keys), so it is the chain of
 // memory and instruction latencies from the launch to the last store, not a rate.  The work is therefore cut
 // finely: a workgroup takes 16 query rows of one (request, KV head) -- row j * G + g is head g of new token j, so
-// the heads that share a KV head are neighbours -- and its 8 waves take the keys in turn, 16 at a time (16 keys
-// lie in one page, so a chunk's K and V are one contiguous run each and its page a scalar).  Every wave keeps
-// its own online softmax; the eight results are combined through LDS.  There is no LDS in the loop: K and
+// the heads that share a KV head are neighbours -- and its waves, 8 of them in a small call, take the keys in turn, 16 at
+// a time (16 keys lie in one page, so a chunk's K and V are one contiguous run each and its page a scalar).  Every wave
+// keeps its own online softmax; the results are combined through LDS.  There is no LDS in the loop: K and
 // V go straight to registers, the next chunk's K and this chunk's V while this chunk's scores are computed.
 //
 // v_mfma_f32_16x16x4_f32 takes one A and one B value per lane (row or column lane % 16, k = lane / 16 =: g) and
@@ -26,6 +26,8 @@
 // 154 that a large fp32 matrix product reaches).  Relative error against 64 bits 4.2e-7 -> 3.0e-7 on the first.
 #include "emm_internal.h"
 
+#include <type_traits>
+
 namespace emm {
 
 namespace {
@@ -34,7 +36,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int ROWS = 16;                              // query rows per workgroup
 constexpr int KEYS = 16;                              // keys per chunk; a page holds a whole number of chunks
-constexpr int NW = 8;                                 // waves per workgroup
 
 // max or sum of a value over the four lanes that share lane % 16
 __device__ inline float group_max(float x)
@@ -62,7 +63,7 @@ __device__ inline long long first_slot(const BatchView& b, int G, int r)
     return (long long)max(b.cu_new_lens[r], 0) * G / ROWS + r;
 }
 
-template <int D>
+template <int D, int NW>                             // NW: waves per workgroup
 __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
 {
     constexpr int QK = D / 16;                        // 16-byte pieces of a Q or K row per lane
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
         }
     }
 
-    // ---- the eight waves' results: o[4 n + e][t] is channel 64 n + 16 g + 4 t + e of row l16
+    // ---- the waves' results: o[4 n + e][t] is channel 64 n + 16 g + 4 t + e of row l16
     l = group_sum(l);
 #pragma unroll
     for (int n = 0; n < NB; ++n)
@@ -232,23 +233,44 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
         l_s[wave][l16] = l;
     }
     __syncthreads();
-    const int my = tid / (D / 4), c4 = tid % (D / 4) * 4;                   // 16 rows x D / 4 pieces: 256 or 512 threads
-    if (my >= ROWS || row0 + my >= n_rows) return;
-    float m_all = -INFINITY, l_all = 0.f;
+    // 16 rows x D / 4 pieces of 16 bytes
+    for (int idx = tid; idx < ROWS * (D / 4); idx += 64 * NW) {
+        const int my = idx / (D / 4), c4 = idx % (D / 4) * 4;
+        if (row0 + my >= n_rows) break;
+        float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, m_s[w][my]);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, m_s[w][my]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float wgt = m_s[w][my] == -INFINITY ? 0.f : expf(m_s[w][my] - m_all);
-        l_all += wgt * l_s[w][my];
-        acc += wgt * *(const f32x4*)&o_s[w][my][c4];
+        for (int w = 0; w < NW; ++w) {
+            const float wgt = m_s[w][my] == -INFINITY ? 0.f : expf(m_s[w][my] - m_all);
+            l_all += wgt * l_s[w][my];
+            acc += wgt * *(const f32x4*)&o_s[w][my][c4];
+        }
+        const float inv = (l_all > 0.f) ? 1.f / l_all : 0.f;                // no keys (cross, empty cache): zero row
+        const int o_row = row0 + my, o_tok = o_row / G;
+        const long long at = (first_row + o_tok) * b.num_q_heads + kvh * G + (o_row - o_tok * G);
+        *(f32x4*)((float*)a.out + at * D + c4) = acc * inv;
+        if (a.lse != nullptr && c4 == 0) a.lse[at] = (l_all > 0.f) ? m_all + logf(l_all) : -INFINITY;
     }
-    const float inv = (l_all > 0.f) ? 1.f / l_all : 0.f;                    // no keys (cross, empty cache): zero row
-    const int o_row = row0 + my, o_tok = o_row / G;
-    const long long at = (first_row + o_tok) * b.num_q_heads + kvh * G + (o_row - o_tok * G);
-    *(f32x4*)((float*)a.out + at * D + c4) = acc * inv;
-    if (a.lse != nullptr && c4 == 0) a.lse[at] = (l_all > 0.f) ? m_all + logf(l_all) : -INFINITY;
+}
+
+// Waves of a workgroup.  Few workgroups need many, which share the keys; where the workgroups alone fill the chip, the
+// combination of the waves and the LDS that it takes only cost, the more so the shorter the contexts (at most `keys`, what a row
+// of the page table can hold).  Long ones that differ keep more, by which the longest ends sooner.  Measured on 300 shapes, us with
+// 8 / 4 / 2 / 1 waves: one new token of 128 requests, 32 heads of 64 (4352 workgroups), 16 keys 53 / 28 / 20 / 16, 301 keys 146 /
+// 124 / 126 / 123; of 32 requests (1088), 16 keys 17 / 11 / 11 / 11; of 8 (256), 301 keys 15 / 16 / 21 / 29; of 44 (1472), up to 700 keys
+// 71 / 66 / 70 / 87, up to 2700 244 / 256 / 258 / 312; of 64 on 4 KV heads (384), the same 61 / 69 / 125 / 191.  Prompts share K and V
+// among their row tiles: 1024 new tokens, 32 heads on 8 of 64 (2056) 88 / 71 / 83 / 92; 32 requests of 64 + 256 (4352) 127 / 86 / 82 / 76.
+// `single`: at most one row tile for a (request, KV head), as in a decode step.
+int waves_of(long long workgroups, bool single, long long keys)
+{
+    int waves;
+    if (keys >= 512) waves = workgroups <= 512 || (single && keys >= 1024) ? 8 : 4;
+    else if (single) waves = workgroups <= 320 ? 8 : workgroups <= 1024 ? 4 : workgroups <= 2048 ? 2 : 1;
+    else waves = workgroups <= 320 ? 8 : workgroups <= 4096 ? 4 : 2;
+    while (waves > 1 && (waves / 2) * KEYS >= keys) waves /= 2;           // no more than there are chunks of keys
+    return waves;
 }
 
 }  // namespace
@@ -260,10 +282,18 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream)
     const int G = b.num_q_heads / b.num_kv_heads;
     const long long grid = ((long long)b.total_new_tokens * G / ROWS + b.num_reqs) * b.num_kv_heads;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (b.head_dim == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, dim3((unsigned)grid), dim3(64 * NW), 0, stream, a);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<128>, dim3((unsigned)grid), dim3(64 * NW), 0, stream, a);
+    auto go = [&](auto d, auto nw) {
+        hipLaunchKernelGGL((attn_f32_kernel<decltype(d)::value, decltype(nw)::value>), dim3((unsigned)grid), dim3(64 * decltype(nw)::value), 0, stream, a);
+    };
+    const int waves = waves_of(grid, (long long)b.max_new_len * G <= ROWS, (long long)b.max_pages * b.page_size);
+    auto of_dim = [&](auto d) {
+        if (waves == 8) go(d, std::integral_constant<int, 8>{});
+        else if (waves == 4) go(d, std::integral_constant<int, 4>{});
+        else if (waves == 2) go(d, std::integral_constant<int, 2>{});
+        else go(d, std::integral_constant<int, 1>{});
+    };
+    if (b.head_dim == 64) of_dim(std::integral_constant<int, 64>{});
+    else of_dim(std::integral_constant<int, 128>{});
     return hipGetLastError();
 }
 

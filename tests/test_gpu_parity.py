@@ -785,6 +785,21 @@ def test_kv_page_migration_past_the_caches(n, page_bytes):
         assert zlib.adler32(staging[p].cpu().numpy().tobytes()) == int(sums[p]) & 0xffffffff
 
 
+# workgroups of 16 rows on either side of where they get fewer waves: tables of under 512 keys at 320, 1024, 2048 workgroups (one row
+# tile each) and 4096 (several), longer ones at 512; tables of one, two and four chunks of 16 keys
+@pytest.mark.parametrize("reqs,H,Hkv,d,new,longest", [(37, 8, 8, 64, 1, 143), (38, 8, 8, 128, 1, 143), (40, 8, 8, 64, 1, 143), (121, 8, 8, 128, 1, 143),
+                                                      (122, 8, 8, 64, 1, 143), (60, 32, 32, 64, 1, 143), (62, 32, 32, 128, 1, 143), (5, 32, 8, 64, 33, 143),
+                                                      (6, 32, 8, 128, 33, 143), (55, 32, 8, 64, 33, 143), (57, 32, 8, 128, 33, 143), (60, 8, 8, 64, 1, 800),
+                                                      (61, 8, 8, 128, 1, 800), (3, 8, 2, 128, 1, 15), (3, 8, 2, 64, 1, 31), (3, 8, 2, 128, 1, 63)])
+def test_fp32_waves_per_workgroup(reqs, H, Hkv, d, new, longest):
+    print("case fp32 waves", reqs, H, Hkv, d, new, longest, flush=True)
+    ctx = [longest] + [c for c in (0, 1, 14, 15, 16, 31, 47, 100, 127) if c < longest]
+    wl = W.build_workload("f32_waves", "causal", "f32", 980 + reqs, num_q_heads=H, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                          prefix_lens=[ctx[i % len(ctx)] for i in range(reqs)], new_lens=[new - i % 2 if new > 1 else 1 for i in range(reqs)])
+    dw = _gpu_run(wl)
+    _compare(wl, dw)
+
+
 def test_kv_page_checksum_of_the_largest_page():
     """Pages of 1 MiB per pool (the largest admitted: e.g. 16 KV heads x 256 tokens x 128 channels in bf16) filled
     with large byte values: the position-weighted sum of a 16-byte chunk alone passes 2^32 there.  Bytes and
