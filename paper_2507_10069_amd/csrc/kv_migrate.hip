@@ -12,9 +12,11 @@
 //
 // A large move (STREAM) goes past the caches, loads and stores with the non-temporal hint: neither side is read again
 // here, and lines that wait to be written back hold up the reads.  8 requests of 18432 tokens (302 MB each way, pack +
-// unpack) 227 -> 199 us = 6.1 TB/s read + write, where the runtime's own copy of 2 GiB reaches 4.9; loads alone 203,
-// stores alone 220.  A small one is left in the caches, where the transport or the next kernel finds it (8 MB: 8.4 us, 8.6
-// with the hint); the line is drawn where pages and staging together exceed a quarter of the last-level cache.
+// unpack) 239 -> 219 us = 5.5 TB/s read + write, where the runtime's own copy of 2 GiB reaches 4.9; loads alone 203 of 227, stores
+// alone 220.  What the last-level cache holds is left there, where the transport or the next kernel finds it: the line is drawn
+// where pages and staging together pass its 256 MiB (a staging buffer unpacked after it was packed: 134 MB of pages, 268 MB
+// in all, 94 us and 99 with the hint; 302 in all 114 and 110; 134 in all 42 and 49; 67 in all 23 and 25.  Pages and buffers
+// that nobody had touched before: 108 and 100, 121 and 111, 50 and 51, 31 and 28).
 #include "emm_internal.h"
 
 #include <type_traits>
@@ -25,7 +27,7 @@ namespace {
 
 constexpr int THREADS = 256;
 constexpr unsigned ADLER_MOD = 65521;
-constexpr long long STREAM_BYTES = 64ll << 20;
+constexpr long long STREAM_BYTES = 256ll << 20;
 
 // wave sum of a 64-bit value
 __device__ inline unsigned long long wave_sum_u64(unsigned long long x)
@@ -135,7 +137,7 @@ hipError_t launch_kv_pages(bool unpack, void* k_cache, void* v_cache, void* stag
                            (unsigned char*)k_cache, (unsigned char*)v_cache, (unsigned char*)staging, page_ids, num_pages, page_bytes,
                            checksums, expected, mismatches);
     };
-    const bool streamed = 4 * page_bytes * n >= STREAM_BYTES;            // K and V pages and their staging
+    const bool streamed = 4 * page_bytes * n > STREAM_BYTES;            // K and V pages and their staging
     if (unpack && streamed) go(std::true_type{}, std::true_type{});
     else if (unpack) go(std::true_type{}, std::false_type{});
     else if (streamed) go(std::false_type{}, std::true_type{});

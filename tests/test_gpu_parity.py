@@ -759,9 +759,10 @@ def test_kv_page_migration_is_exact_and_checksummed():
     assert B.DeviceWorkload.to_numpy_bits(out).tobytes() == src_out
 
 
-@pytest.mark.parametrize("n,page_bytes", [(1023, 16384), (1024, 16384), (1500, 16384), (17, 1 << 20)])
+@pytest.mark.parametrize("n,page_bytes", [(1023, 16384), (1024, 16384), (1500, 16384), (17, 1 << 20), (4096, 16384), (4097, 16384), (5000, 16384),
+                                          (64, 1 << 20), (65, 1 << 20)])
 def test_kv_page_migration_past_the_caches(n, page_bytes):
-    """Either side of the size from which pages are moved with the non-temporal hint (4 n page_bytes = 64 MiB)."""
+    """Either side of the size from which pages are moved with the non-temporal hint (4 n page_bytes = 256 MiB)."""
     import zlib
     print("case migrate", n, page_bytes, flush=True)
     g = torch.Generator(device="cuda").manual_seed(n)
