@@ -580,20 +580,29 @@ def test_decode_block_of_scores_that_are_minus_infinity(blocks):
 @pytest.mark.parametrize("name,group,shared,planned", [("private", [0, 1, 2], 0, False), ("shared_apart", [0, 1, 0], 12800, False),
                                                        ("units", [0, 0, 1], 12800, True), ("units_and_apart", [0, 0, 0], 12801, True)])
 def test_decode_large_enough_to_stream(name, group, shared, planned):
-    """More than 96 MiB of K and V: fetched past the caches, except what another request of the batch holds as well."""
+    """More than 96 MiB of K and V: fetched past the caches, except what another request of the batch holds as well.  With units
+    the amount of work counts shared keys once."""
     print("case decode streams", name, flush=True)
     wl = W.build_workload("decode_stream_" + name, "causal", "bf16", 780, num_q_heads=28, num_kv_heads=4, head_dim=128, page_size=16,
-                          prefix_lens=[17000, 18011, 17500], new_lens=[1, 1, 1], share_group=group, shared_len=[shared] * 3)
+                          prefix_lens=[27000, 28011, 27500], new_lens=[1, 1, 1], share_group=group, shared_len=[shared] * 3)
+    tile_bytes = 32 * 128 * 2 * 2
     dw = B.DeviceWorkload(wl)
+    plan = dw.plan_shared()
+    assert plan["planned_tiles"] * wl.num_kv_heads * tile_bytes > 96 << 20
+    dw.scatter()
     if planned:
-        plan = dw.plan_shared()
         assert plan["num_units"] == 1
-        dw.scatter()
         dw.attention_shared()
     else:
-        dw.step()
+        dw.attention()
     torch.cuda.synchronize()
     _compare(wl, dw)
+    fused = B.DeviceWorkload(wl)                             # the fused step stores the rows itself, and gives the same bits
+    fused.plan_shared(use_hint=planned)
+    fused.decode_step(planned)
+    torch.cuda.synchronize()
+    assert torch.equal(fused.out, dw.out) and torch.equal(fused.lse, dw.lse)
+    assert torch.equal(fused.k_cache, dw.k_cache) and torch.equal(fused.v_cache, dw.v_cache)
 
 
 @pytest.mark.parametrize("reqs,ctx", [(64, [100, 1500]), (3, [17000, 18000]), (1, [1500])])
