@@ -154,7 +154,7 @@ emm_status emm_decode_attn(const emm_batch *batch, const void *q, const void *k_
  *   bf16 decode-shaped batches only (max_new_len <= 1, H / Hkv <= 16), else EMM_ERR_INVALID_ARG /
  *   EMM_ERR_UNSUPPORTED; a batch for which emm_prefill_attn_workspace_size exceeds
  *   EMM_DECODE_STATIC_SCRATCH_BYTES is refused with EMM_ERR_WORKSPACE before anything is launched (64 requests
- *   x 4 KV heads x 8192 tokens need 12.2 MiB).
+ *   x 4 KV heads x 8192 tokens: 14.2 MiB, with the room kept for hints).
  * All calls on one GPU share that GPU's array: calls that may overlap there (different streams, several
  * threads) race on it and must be ordered by the caller.  Nothing in the array has to start at zero; a call
  * overwrites what it later reads.

@@ -12,7 +12,7 @@
 //               fetches only, and keeps its own online softmax.  There is no barrier before the end.  (With
 //               tiles that all waves fetch and one of them computes, a barrier per tile, the waves' computing was
 //               one chain: 0.6 us per 32 keys, which bound every batch too small to fill the chip: one context
-//               of 1500 tokens 10.6 -> 7.2 us for both kernels, of 16384 17.1 -> 12.5.)
+//               of 1500 tokens 10.6 -> 7.3 us for both kernels, of 16384 17.1 -> 13.6.)
 //   matrix    = v_mfma_f32_16x16x32 for S^T = K Q^T and 16x16x16 for O^T += V^T P^T: 16 query rows, the most a KV head
 //               has here, so half the accumulators and half the exponentials of the 32-column shape, and a lane's
 //               four scores are the four keys that the value product expects from it.  The matrix pipe is mostly
@@ -32,8 +32,8 @@
 //
 // Fused step (FUSED instantiation, emm_decode_step): the query token's own K/V row need not be in the pool
 // beforehand.  The wave whose block holds the token's slot copies the row from k_new / v_new into the
-// LDS block once the block has landed (into the swizzled places the loads would have put it) and stores it in
-// the pool when it is done, so a decode step is one launch less than scatter + attention.
+// LDS block once the block has landed (into the swizzled places the loads would have put it); it stores it in
+// the pool before its first block, so a decode step is one launch less than scatter + attention.
 #include "attn_bf16_common.h"
 
 #include <algorithm>
@@ -569,8 +569,8 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 //   two workgroups fit a compute unit, 512 the chip; what does not fit starts when others end, and a last round that is
 //   nearly empty lasts as long as a full one: half of its emptiness is charged (608 workgroups of 32 tiles: 58 us)
 //   equal contexts are cut evenly: of the lengths that give the same number of pieces the shortest, so that no sliver takes the
-//   place of a workgroup with work (64 x 8192 tokens, 256 tiles: 85 + 85 + 85 + 1 180 us, 64 four times 176; of contexts from
-//   2048 to 8191 133 and 125)
+//   place of a workgroup with work (64 contexts of 2048 to 8191 tokens behind a table of 256 tiles: 85 + 85 + 85 + 1 133 us, 64 four
+//   times 125; where all have 8192 tokens both take 176)
 //   MERGE           the second kernel, which a batch cut in single pieces does without (128 contexts of 1000 tokens: 15.7 us
 //                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds
 // What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the

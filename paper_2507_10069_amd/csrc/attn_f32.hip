@@ -21,7 +21,7 @@
 //                 operand lane i stands for channels 4 i .. 4 i + 3 of the four products of a 64-channel block, so V
 //                 rows are read whole, 16 bytes per lane, and a lane ends up with 16 consecutive channels of its row.
 // Measured, scatter and attention per step, against one wave per row with lanes owning keys (no matrix instruction):
-// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 14.7 us (what two launches cost the host); the same
+// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 14.7 us (11 since two launches cost the host less); the same
 // heads, 4 x (1024 + 256) tokens 254 -> 26 us; 8 heads on 2 of 128, 4096 new tokens 5.59 -> 0.44 ms (78 TFLOP/s of the
 // 154 that a large fp32 matrix product reaches).  Relative error against 64 bits 4.2e-7 -> 3.0e-7 on the first.
 #include "emm_internal.h"
