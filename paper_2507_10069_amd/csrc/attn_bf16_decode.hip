@@ -563,9 +563,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 // How a decode batch is cut: the piece length with the least time by a model of the main kernel (times in us, measured).
 //   START           from the launch to the first block and from the last block to the end
 //   TILE_HBM        one 32-key tile of one KV head (16 KB) at the rate at which the whole chip streams, 6.6 TB/s
-//   TILE_CU         the same on one compute unit that has HBM to itself: a compute unit takes no more than about 36 bytes
-//                   per ns, so the longest piece, twice where a compute unit gets two full ones, bounds the time as well
-//                   (8 x 18432 tokens: 288 workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us)
+//   TILE_CU         the same on one compute unit of a chip that has one piece on each: about 36 bytes per ns, so the longest
+//                   piece, twice where a compute unit gets two full ones, bounds the time as well (8 x 18432 tokens: 288
+//                   workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us).  Measured over 100 batches of equal contexts:
+//                   .49 us a tile of 192 to 255 workgroups, .78 to .93 of 256 to 447.  Of fewer than 64 it is .26, of 64 to
+//                   127 .34; the model has one figure for all
 //   two workgroups fit a compute unit, 512 the chip; what does not fit starts when others end, and a last round that is
 //   nearly empty lasts as long as a full one: half of its emptiness is charged (608 workgroups of 32 tiles: 58 us)
 //   equal contexts are cut evenly: of the lengths that give the same number of pieces the shortest, so that no sliver takes the
