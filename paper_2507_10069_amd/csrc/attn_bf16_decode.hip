@@ -565,7 +565,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 //   TILE_HBM        one 32-key tile of one KV head (16 KB) at the rate at which the whole chip streams, 6.6 TB/s
 //   TILE_CU         the same on one compute unit of a chip that has one piece on each: about 36 bytes per ns, so the longest
 //                   piece, twice where a compute unit gets two full ones, bounds the time as well (8 x 18432 tokens: 288
-//                   workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us).  Measured over 100 batches of equal contexts:
+//                   workgroups of 64 tiles 66 us, 448 of 43 53 us, 800 of 24 55 us).  Measured over 66 batches of equal contexts:
 //                   .49 us a tile of 192 to 255 workgroups, .78 to .93 of 256 to 447.  Of fewer than 64 it is .26, of 64 to
 //                   127 .34; the model has one figure for all
 //   two workgroups fit a compute unit, 512 the chip; what does not fit starts when others end, and a last round that is
