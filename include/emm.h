@@ -99,7 +99,7 @@ emm_status emm_kv_scatter(const emm_batch *batch, const void *k_new, const void 
 
 /* Bytes of device workspace emm_prefill_attn / emm_cross_attn / emm_decode_attn need for this batch: 0 for
  * EMM_F32.  For EMM_BF16 the kernels cut work along the key axis, park the pieces' accumulators in the workspace
- * and merge them with a second kernel on the same stream:
+ * and merge them (small decode batches in the same kernel, all others with a second one on the same stream):
  *   prefill / cross-attention: the work units an XCD has left over after its full rounds of 32 are cut in up to 32
  *     pieces; a piece record is 135168 bytes, and the size is 8 XCDs x the most records an XCD can need: exactly that
  *     of the plan when all requests have the same number of new tokens (0 when that plan cuts nothing, as for 2 x

@@ -6,7 +6,7 @@
 // exactly once, so the work is cut along the KEY axis, first into pieces of `tiles_per_piece` 32-key
 // tiles (one workgroup each), then, inside a workgroup, block by block of 16 keys over its 4 waves.
 //
-//   workgroup = one piece of one pair, 4 waves, 64 KB of LDS, two on a compute unit.  Wave w takes blocks w, w+4, ... of
+//   workgroup = one piece of one pair, 4 waves, 64 KB of LDS, two on a compute unit (or 8, 128 KB, one).  Wave w takes blocks w, w+4, ... of
 //               the piece and does everything for them by itself: it fetches them by LDS-DMA into a ring of its
 //               own (two blocks of K and V: one is computed while the other is on its way), waits for its own
 //               fetches only, and keeps its own online softmax.  There is no barrier before the end.  (With
@@ -18,9 +18,9 @@
 //               four scores are the four keys that the value product expects from it.  The matrix pipe is mostly
 //               idle; the kernel is bound by the rate at which blocks arrive from HBM.
 //   merge 1   = the 4 waves' (maximum, row sum, accumulator) are combined through LDS;
-//   merge 2   = a pair with several pieces leaves one record per piece in the workspace and
-//               attn_bf16_decode_merge_kernel combines them; a pair with one piece writes its output
-//               directly.  Both kernels derive the piece count from the lengths, nothing is exchanged.
+//   merge 2   = a pair with several pieces leaves one record per piece in the workspace, and the last of its workgroups
+//               (small batches: see FOLD_PIECES) or attn_bf16_decode_merge_kernel combines them; a pair with one piece writes
+//               its output directly.  Both kernels derive the piece count from the lengths.
 //
 // Shared prefixes (Section 3.3: requests repeat system prompts and images).  Requests whose leading pages
 // are the same physical pages can be given as a UNIT: up to 32 / G consecutive requests and the length they
@@ -31,12 +31,15 @@
 // nothing for it.
 //
 // Fused step (FUSED instantiation, emm_decode_step): the query token's own K/V row need not be in the pool
-// beforehand.  The wave whose block holds the token's slot copies the row from k_new / v_new into the
-// LDS block once the block has landed (into the swizzled places the loads would have put it); it stores it in
-// the pool before its first block, so a decode step is one launch less than scatter + attention.
+// beforehand.  The wave whose block holds the token's slot asks for the row in k_new / v_new before its first fetch and
+// puts it into the LDS block once the block has landed (into the swizzled places the loads would have put it) and into
+// the pool, so a decode step is one launch less than scatter + attention.  (Stored in the pool before the first fetch, as
+// it was, the row cost its wave two round trips: 32 contexts of 1500 tokens 20.9 -> 20.0 us, 8 of 4000 17.3 -> 16.4.)
 #include "attn_bf16_common.h"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <climits>
 #include <mutex>
 #include <type_traits>
@@ -48,9 +51,13 @@ namespace {
 using namespace bf16attn;
 
 constexpr int MAX_G = 16;                        // query heads per KV head this kernel takes
-constexpr int REC_FLOATS = D + 2;                // per row of a record: 128 accumulator values, m, l
-constexpr int NW = 4;                            // waves per workgroup
-constexpr int NT = NW * 64;
+constexpr int REC_FLOATS = D + 2;                // per row of a record: 128 accumulator values, m, l (folded: the rows' values, then their m, l)
+constexpr int RED_FLOATS = D + 4;                // per row in LDS: 128 accumulator values, m, l, and the next row 16 bytes aligned
+// Waves per workgroup.  Eight, and all of a compute unit's LDS, where a piece is no more than a block for each and a compute unit has one
+// piece anyway: a wave's two blocks in turn become one (32 / 8 heads, one context of 1500 tokens 7.2 -> 6.8 us, two of 2000 7.9 -> 7.3).  With
+// longer pieces eight are slower than four (one of 6000 10.2 and 9.8, 16 of 1000 on 28 / 4 heads 10.8 and 10.3).
+constexpr int FEW = 4, MANY = 8;
+constexpr int MANY_TILES = 4;                    // of a piece: 8 blocks
 constexpr int BK = 32;                           // keys per tile, the unit in which pieces are measured
 constexpr int BLK = 16;                          // keys per block, what a wave fetches and computes at a time (a page holds 1 to 16)
 constexpr int BLOCKS_PER_TILE = BK / BLK;
@@ -61,20 +68,37 @@ constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // a wave's b
 constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 256 CUs
 constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see attn_bf16_decode_shape
 constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
-static_assert(NW * MAX_G * REC_FLOATS * 4 <= NW * RING_BYTES, "the merge across waves reuses the rings");
-static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
+static_assert(MAX_G * RED_FLOATS * 4 <= RING_BYTES, "the merge across waves reuses the rings");
+static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= FEW * 64, "a wave's page ids sit in one register");
 
-__device__ inline int pieces_of(int kv_len, int tiles_per_piece)
+// Division of 0 .. 2^31 - 1 by a number that the host knows, 2^(shift - 1) < d <= 2^shift: n * ceil(2^(31 + shift) / d) / 2^(31 + shift),
+// exact because d times the multiplier passes 2^(31 + shift) by less than d and n < 2^31, so the quotient grows by less than 1 / d.
+struct Divisor {
+    uint32_t mul;
+    int32_t shift;
+    __device__ int quotient(int n) const { return (int)((uint32_t)(((uint64_t)(2u * (uint32_t)n) * mul) >> 32) >> shift); }
+};
+// What a launch adds to its arguments: the ticket of a folded merge (0: none) and quotients that every workgroup would have to work out
+// (a division is 25 instructions of one chain: without, and with the arguments asked for at once, every call is 0.3 us shorter).
+struct LaunchInfo {
+    unsigned long long ticket;
+    int32_t G, grid_y;
+    Divisor by_kv_heads, by_piece /* tiles_per_piece */, by_pairs, by_unit_pairs;
+};
+constexpr int MAX_GRID_Y = 32768;
+__device__ inline int up_to_pieces(int n_tiles, int tiles_per_piece) { return (n_tiles + tiles_per_piece - 1) / tiles_per_piece; }
+__device__ inline int up_to_pieces(int n_tiles, const Divisor& by_piece) { return by_piece.quotient(n_tiles - 1) + 1; }    // n_tiles > 0
+template <typename PIECE> __device__ inline int pieces_of(int kv_len, const PIECE& tiles_per_piece)
 {
     const int n_tiles = (kv_len + BK - 1) / BK;
-    return n_tiles == 0 ? 1 : (n_tiles + tiles_per_piece - 1) / tiles_per_piece;
+    return n_tiles == 0 ? 1 : up_to_pieces(n_tiles, tiles_per_piece);
 }
 // pieces of a request's own part when its first t_off tiles belong to a unit's shared part: possibly none
-__device__ inline int own_pieces_of(int kv_len, int t_off, int tiles_per_piece, bool in_unit)
+template <typename PIECE> __device__ inline int own_pieces_of(int kv_len, int t_off, const PIECE& tiles_per_piece, bool in_unit)
 {
     if (!in_unit) return pieces_of(kv_len, tiles_per_piece);
     const int n_tiles = (kv_len + BK - 1) / BK - t_off;
-    return n_tiles <= 0 ? 0 : (n_tiles + tiles_per_piece - 1) / tiles_per_piece;
+    return n_tiles <= 0 ? 0 : up_to_pieces(n_tiles, tiles_per_piece);
 }
 // max or sum over the four lanes that hold a query row (lane % 16)
 __device__ inline float quad_max(float x)
@@ -88,6 +112,26 @@ __device__ inline float quad_sum(float x)
     const uint32_t u = __float_as_uint(x);
     const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+// max or sum over the 16 lanes of a row of lanes, in every one of them
+template <int CTRL> __device__ inline float from_lane(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, false));
+}
+constexpr int ROR1 = 0x121, ROR2 = 0x122, ROR4 = 0x124, ROR8 = 0x128;       // rotate within a row of 16
+__device__ inline float max_of_16(float x)
+{
+    x = fmaxf(x, from_lane<ROR8>(x));
+    x = fmaxf(x, from_lane<ROR4>(x));
+    x = fmaxf(x, from_lane<ROR2>(x));
+    return fmaxf(x, from_lane<ROR1>(x));
+}
+__device__ inline float sum_of_16(float x)
+{
+    x += from_lane<ROR8>(x);
+    x += from_lane<ROR4>(x);
+    x += from_lane<ROR2>(x);
+    return x + from_lane<ROR1>(x);
 }
 // workspace: the requests' own records first, [pair][piece][MAX_G rows], then the units', [unit][KV head][piece][MAX_ROWS]
 __device__ __host__ inline size_t unit_records_offset(const DecodeShape& S)
@@ -134,25 +178,54 @@ __device__ inline void wait_fetches()
     asm volatile("s_waitcnt vmcnt(%0)" ::"i"(PENDING) : "memory");
 }
 
-template <bool CAUSAL, bool SHARED, bool FUSED>
-__global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
+// ---- Folded merge: where a context has few pieces (fold_applies), the last of its workgroups to finish combines them and the second
+// kernel is not launched.  Nobody waits for anybody: a workgroup stores its record, counts itself in and leaves unless it is the one that
+// completes the count.  Records and counts are stored, counted and read with agent scope (past what the XCDs do not share), a wave's
+// stores are awaited before its workgroup counts, and pieces are combined in their order, so the result does not depend on who is last.
+// The count of a (request, KV head) lies in the last row of its first record, which G < MAX_G query heads leave unused, and needs no
+// zero to start from: it is the launch's ticket (48 bits that no other launch of this process has) above the number of workgroups.
+// Each workgroup asks for it with the lengths and, unless the ticket is there, puts it there before its first fetch; whoever completes
+// the count takes the ticket away, so that a replay of a captured launch starts again.  Every workgroup that the grid has for a context
+// counts, whatever the device arrays hold, so the count is completed in every launch.
+constexpr int FOLD_PIECES = 16, FOLD_COUNT_BITS = 16;
+__device__ inline unsigned long long* fold_count(const AttnArgs& a, const DecodeShape& S, int pair)
+{
+    return (unsigned long long*)((float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G) * REC_FLOATS + (MAX_G - 1) * D);
+}
+
+typedef float f32x2_rec __attribute__((ext_vector_type(2)));
+__device__ inline void put_record(float* at, f32x2_rec x)
+{
+    __hip_atomic_store((unsigned long long*)at, __builtin_bit_cast(unsigned long long, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline f32x2_rec get_record(const float* at)
+{
+    return __builtin_bit_cast(f32x2_rec, __hip_atomic_load((const unsigned long long*)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+template <bool CAUSAL, bool SHARED, bool FUSED, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, LaunchInfo info)
 {
     static_assert(CAUSAL || !FUSED, "only a causal step has a new token to store");
+    constexpr int NT = 64 * NW;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * RING_BYTES];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
 
     const BatchView& b = a.b;
-    const int G = b.num_q_heads / b.num_kv_heads;
+    const int G = info.G;
+    const unsigned long long ticket = info.ticket;
     const int n_own_blocks = S.n_pairs * S.pieces_max;
     const bool unit_mode = SHARED && (int)blockIdx.x >= n_own_blocks;     // this workgroup: a unit's shared part
-    const int blk = unit_mode ? blockIdx.x - n_own_blocks : blockIdx.x;
     // piece-major: the first pieces of all contexts come first in the grid, the workgroups that find their
     // context too short for their piece number (they exit at once) gather at its end
     const int n_items = unit_mode ? S.n_unit_pairs : S.n_pairs;
-    const int pair = blk % n_items, piece = blk / n_items;                // unit mode: pair = (unit, KV head)
-    const int kvh = pair % b.num_kv_heads;
-    const int unit = pair / b.num_kv_heads;                               // own part: this is the request itself
+    // (without units the grid has a dimension for the pieces, which saves a division; the third is for more than MAX_GRID_Y)
+    const int blk = unit_mode ? blockIdx.x - n_own_blocks : blockIdx.x;
+    const int piece = SHARED ? (unit_mode ? info.by_unit_pairs : info.by_pairs).quotient(blk) : blockIdx.y + info.grid_y * blockIdx.z;
+    const int pair = SHARED ? blk - piece * n_items : blk;                // unit mode: (unit, KV head)
+    const int unit = info.by_kv_heads.quotient(pair);                     // own part: this is the request itself
+    const int kvh = pair - unit * b.num_kv_heads;
     // (what the device arrays hold is forced into range wherever an address depends on it: see safe_new_len)
     const int r = unit_mode ? min(max(sv.unit_first_req[unit], 0), b.num_reqs - 1) : unit;   // the request whose page table is read
     const int tid = threadIdx.x;
@@ -177,7 +250,14 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         if (S.stream != DecodeShape::STREAM_NEVER) holders = first_holders(b, pg_first);
     };
     if (!S.late) ask_pages();
+    constexpr int SPEAKER = NW - 1;                          // the wave that counts for the workgroup: see FOLD_PIECES
+    unsigned long long seen = 0;
+    if (!SHARED && ticket != 0 && wave == SPEAKER)
+        seen = __hip_atomic_load(fold_count(a, S, pair), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" ::"s"(new_len), "s"(prefix_len), "s"(cu_new));
+    // and every argument that is needed further down, which the compiler would ask for where it is first used
+    asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out), "s"(a.lse), "s"(a.workspace), "s"(info.by_piece.mul), "s"(S.n_pairs));
+    if (FUSED) asm volatile("" ::"s"(a.k_new), "s"(a.v_new));
     __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
     bool direct;                                             // one piece and no unit: this workgroup writes the output
@@ -186,18 +266,22 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
         kv_len = CAUSAL ? P + 1 : P;                         // keys the query sees = slots that hold tokens
         const bool in_unit = SHARED && req_unit >= 0;
-        n_pieces = own_pieces_of(kv_len, t_off, S.tiles_per_piece, in_unit);
+        n_pieces = own_pieces_of(kv_len, t_off, info.by_piece, in_unit);
         n_rows = G;
         direct = n_pieces == 1 && !in_unit;
     } else {
         // a multiple of the tile: no mask, no ragged tail
         kv_len = (int)min((long long)max(sv.unit_shared_len[unit], 0), (long long)b.max_pages * b.page_size) / BK * BK;
-        n_pieces = (kv_len / BK + S.tiles_per_piece - 1) / S.tiles_per_piece;
+        n_pieces = kv_len > 0 ? up_to_pieces(kv_len / BK, info.by_piece) : 0;
         n_rows = min(max(sv.unit_num_reqs[unit], 1) * G, MAX_ROWS);
         direct = false;
     }
     if (piece >= n_pieces) return;
     if (S.late) ask_pages();
+    const bool folded = !SHARED && ticket != 0 && !direct;   // see FOLD_PIECES
+    unsigned long long* const count = fold_count(a, S, pair);
+    if (folded && wave == SPEAKER && lane == 0 && ((seen ^ ticket) >> FOLD_COUNT_BITS) != 0)
+        __hip_atomic_compare_exchange_strong(count, &seen, ticket, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int n_blocks = min(S.tiles_per_piece * BLOCKS_PER_TILE, (kv_len + BLK - 1) / BLK - t_begin * BLOCKS_PER_TILE);    // of the piece; 0 only for an empty context
     const int n_mine = n_blocks > wave ? (n_blocks - wave + NW - 1) / NW : 0;
     // in units of 4096 bytes (one block of one KV head): (page, KV head, block within the page)
@@ -247,16 +331,23 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
             if (first_key(i) + 4 * j + g >= kv_len)
                 *(uint4*)(my_ring + slot * (2 * BLOCK_BYTES) + BLOCK_BYTES + j * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
     };
-    // FUSED: the query token's own K/V row comes from k_new / v_new into the places the fetches would have put it
+    // FUSED: the query token's own K/V row (K by lanes 0..15, V by 16..31) comes from k_new / v_new into the places the fetches
+    // would have put it, and into its slot in the pool for the steps to come (the block fetched from there is patched, so the order of the
+    // two does not matter).  Only its wave asks for it, before its fetches: the row is in registers when the block has landed.
     const long long first_row = clamp_first_row(b, cu_new, 1);
-    const long long new_row_bytes = (first_row * b.num_kv_heads + kvh) * (D * 2);
-    auto holds_new_row = [&](int i) { return FUSED && !unit_mode && first_key(i) <= limit && limit < first_key(i) + BLK; };
+    const bool row_is_mine = FUSED && !unit_mode && n_mine > 0 && limit >= first_key(0) && (limit - first_key(0)) % (NW * BLK) < BLK &&
+                             (limit - first_key(0)) / (NW * BLK) < n_mine;
+    const int row_block = row_is_mine ? (limit - first_key(0)) / (NW * BLK) : -1;
+    uint4 new_row = make_uint4(0, 0, 0, 0);
+    if (row_is_mine && lane < 32)
+        new_row = *(const uint4*)((const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + (first_row * b.num_kv_heads + kvh) * (D * 2) + l16 * 16);
     auto patch_new_row = [&](int i, int slot) {
         const int row = limit - first_key(i);
         if (lane < 32) {
-            const unsigned char* src = (const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + new_row_bytes + l16 * 16;
             const int chunk = l16 ^ (lane < 16 ? row : (row & 3) << 2);
-            *(uint4*)(my_ring + slot * (2 * BLOCK_BYTES) + (lane < 16 ? 0 : BLOCK_BYTES) + row * 256 + (chunk << 4)) = *(const uint4*)src;
+            *(uint4*)(my_ring + slot * (2 * BLOCK_BYTES) + (lane < 16 ? 0 : BLOCK_BYTES) + row * 256 + (chunk << 4)) = new_row;
+            unsigned char* pool = (unsigned char*)const_cast<void*>(lane < 16 ? a.k_cache : a.v_cache);
+            *(uint4*)(pool + (long long)__builtin_amdgcn_readlane(pg_vec, i) * BLOCK_BYTES + row * 256 + l16 * 16) = new_row;
         }
     };
 
@@ -266,7 +357,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int v_rd0 = BLOCK_BYTES + (4 * g + (l16 >> 2)) * 256 + ((((l16 >> 1) & 1) ^ ((l16 >> 2) << 2)) << 4) + (l16 & 1) * 8;
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
 
-    float* __restrict__ red = (float*)smem;                  // [NW waves][16 rows][130], after the loop
+    float* __restrict__ red = (float*)smem;                  // [NW waves][16 rows][132], after the loop
     // The piece with NR groups of 16 query rows: the G heads of the request or, in unit mode, the G heads of each of
     // the unit's requests; columns of the MFMA past them repeat the last row and are discarded.
     auto attend = [&](auto nr_c) {
@@ -357,8 +448,9 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
                     for (int q = 0; q < NR; ++q)
 #pragma unroll
                         for (int st = 0; st < 4; ++st) asm volatile("" ::"v"(qf[q][st]));
+                if (FUSED && i == 0) asm volatile("" ::"v"(new_row.x), "v"(new_row.y), "v"(new_row.z), "v"(new_row.w));
                 if (first_key(i) + BLK > kv_len) zero_v_tail(i, slot);
-                if (holds_new_row(i)) patch_new_row(i, slot);
+                if (i == row_block) patch_new_row(i, slot);
                 compute(i, slot);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // every read of the slot is done before it is filled again
                 if (i + NSLOT < n_mine) fetch(i + NSLOT, slot);
@@ -376,64 +468,121 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
             const int row0 = 16 * q, rows_here = min(MAX_G, n_rows - row0);
             const float l_row = quad_sum(l_run[q]);
             if (l16 < rows_here) {
-                float* dst = red + (wave * MAX_G + l16) * REC_FLOATS;
+                float* dst = red + (wave * MAX_G + l16) * RED_FLOATS;
 #pragma unroll
-                for (int nb = 0; nb < 8; ++nb) {
-                    *(f32x2*)(dst + 16 * nb + 4 * g) = f32x2{o_acc[q][nb][0], o_acc[q][nb][1]};
-                    *(f32x2*)(dst + 16 * nb + 4 * g + 2) = f32x2{o_acc[q][nb][2], o_acc[q][nb][3]};
-                }
+                for (int nb = 0; nb < 8; ++nb) *(f32x4*)(dst + 16 * nb + 4 * g) = o_acc[q][nb];
                 if (g == 0) *(f32x2*)(dst + D) = f32x2{m_run[q], l_row};
             }
             __syncthreads();
-            for (int idx = tid; idx < rows_here * (D / 2); idx += NT) {
-                const int lrow = idx / (D / 2), ch = idx % (D / 2) * 2, row = row0 + lrow;
-                f32x2 ml[NW], x[NW];
+            // half a wave takes a row, a lane four of its channels: up to 8 rows at once
+            for (int lrow = tid / (D / 4); lrow < rows_here; lrow += NT / (D / 4)) {
+                const int ch = 4 * (lane & (D / 4 - 1)), row = row0 + lrow;
+                f32x2 ml[NW];
+                f32x4 x[NW];
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
-                    const float* src = red + (w * MAX_G + lrow) * REC_FLOATS;
+                    const float* src = red + (w * MAX_G + lrow) * RED_FLOATS;
                     ml[w] = *(const f32x2*)(src + D);
-                    x[w] = *(const f32x2*)(src + ch);
+                    x[w] = *(const f32x4*)(src + ch);
                 }
                 float m_all = -INFINITY;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml[w][0]);
-                f32x2 acc = {0.f, 0.f};
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
                 float l_tot = 0.f;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
                     const float wgt = (ml[w][0] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((ml[w][0] - m_all) * c_log2);
-                    acc[0] += wgt * x[w][0];
-                    acc[1] += wgt * x[w][1];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[v] += wgt * x[w][v];
                     l_tot += wgt * ml[w][1];
                 }
                 if (direct) {
                     const int head = kvh * G + row;
-                    bf16x2 o;
-                    o[0] = (__bf16)(l_tot > 0.f ? acc[0] / l_tot : 0.f);
-                    o[1] = (__bf16)(l_tot > 0.f ? acc[1] / l_tot : 0.f);
-                    *(bf16x2*)((__bf16*)a.out + (first_row * b.num_q_heads + head) * D + ch) = o;
+                    bf16x4 o;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) o[v] = (__bf16)(l_tot > 0.f ? acc[v] / l_tot : 0.f);
+                    *(bf16x4*)((__bf16*)a.out + (first_row * b.num_q_heads + head) * D + ch) = o;
                     if (ch == 0 && a.lse != nullptr)
                         a.lse[first_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
+                } else if (folded) {
+                    put_record(rec + row * D + ch, f32x2{acc[0], acc[1]});
+                    put_record(rec + row * D + ch + 2, f32x2{acc[2], acc[3]});
+                    if (ch == 0) put_record(rec + MAX_G * D + row * 2, f32x2{m_all, l_tot});
                 } else {
-                    *(f32x2*)(rec + row * REC_FLOATS + ch) = acc;
+                    *(f32x2*)(rec + row * REC_FLOATS + ch) = f32x2{acc[0], acc[1]};
+                    *(f32x2*)(rec + row * REC_FLOATS + ch + 2) = f32x2{acc[2], acc[3]};
                     if (ch == 0) *(f32x2*)(rec + row * REC_FLOATS + D) = f32x2{m_all, l_tot};
                 }
             }
         }
     };
 
-    if (FUSED && n_mine > 0 && !unit_mode && limit >= first_key(0) && (limit - first_key(0)) % (NW * BLK) < BLK && (limit - first_key(0)) / (NW * BLK) < n_mine &&
-        lane < 32) {
-        // the token's row goes to its slot in the pool (K by lanes 0..15, V by 16..31), for the steps to come; the
-        // block fetched from there is patched, so the order of the two does not matter
-        const int page = min(max(pt[limit >> (4 + b.page_shift)], 0), b.num_pages - 1);
-        const long long dst = (((long long)page * b.num_kv_heads + kvh) * b.page_size + (limit & (b.page_size - 1))) * 256 + l16 * 16;
-        const unsigned char* src = (const unsigned char*)(lane < 16 ? a.k_new : a.v_new) + new_row_bytes + l16 * 16;
-        unsigned char* pool = (unsigned char*)const_cast<void*>(lane < 16 ? a.k_cache : a.v_cache);
-        *(uint4*)(pool + dst) = *(const uint4*)src;
-    }
     if (SHARED && unit_mode && n_rows > 16) attend(std::integral_constant<int, 2>{});
     else attend(std::integral_constant<int, 1>{});
+    if (!folded) return;
+
+    // ---- merge 2, folded
+    const int n = min(n_pieces, S.pieces_max);               // workgroups of this pair that the grid has
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's part of the record is where every XCD sees it
+    __syncthreads();
+    if (wave == SPEAKER) {
+        unsigned long long before = 0;
+        if (lane == 0) before = __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool last = lane == 0 && (int)(before & ((1 << FOLD_COUNT_BITS) - 1)) + 1 == n;
+        if (lane == 0) *(int*)smem = last ? 1 : 0;
+        // no ticket, so that the same launch replayed from a graph starts again
+        if (last) __hip_atomic_store(count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (*(volatile int*)smem == 0) return;
+    const float* rec0 = (const float*)a.workspace + (size_t)pair * S.pieces_max * MAX_G * REC_FLOATS;
+    // 8 rows at a time: a wave takes ROWS of them, a lane two channels of each; the weights are made with a lane for each record,
+    // of the first row in lanes 0 .. 15, of the second in 16 .. 31
+    constexpr int ROWS = 8 / NW;
+    static_assert(ROWS * FOLD_PIECES <= 64, "a lane for every weight");
+    for (int row0 = wave; row0 < G; row0 += ROWS * NW) {
+        const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(row0 + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
+        const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
+        f32x2 val[ROWS][FOLD_PIECES];
+#pragma unroll
+        for (int u0 = 0; u0 < FOLD_PIECES; u0 += 4)
+            if (u0 < n)
+#pragma unroll
+                for (int u = u0; u < u0 + 4; ++u)
+#pragma unroll
+                    for (int h = 0; h < ROWS; ++h)
+                        val[h][u] = get_record(rec0 + min(u, n - 1) * (MAX_G * REC_FLOATS) + min(row0 + h * NW, G - 1) * D + 2 * lane);
+        const float m = u_lane < n ? ml[0] : -INFINITY;
+        const float m_all = max_of_16(m);
+        const float wgt = u_lane < n ? __builtin_amdgcn_exp2f((m - (m_all == -INFINITY ? 0.f : m_all)) * c_log2) : 0.f;
+        const float l_tot = sum_of_16(u_lane < n ? wgt * ml[1] : 0.f);
+        f32x2 acc[ROWS] = {};
+#pragma unroll
+        for (int u0 = 0; u0 < FOLD_PIECES; u0 += 4)
+            if (u0 < n)
+#pragma unroll
+                for (int u = u0; u < u0 + 4; ++u)
+#pragma unroll
+                    for (int h = 0; h < ROWS; ++h) {         // (past the last record its value again: 0, lest it be infinite)
+                        const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u + FOLD_PIECES * h));
+                        acc[h][0] += w_u * (u < n ? val[h][u][0] : 0.f);
+                        acc[h][1] += w_u * (u < n ? val[h][u][1] : 0.f);
+                    }
+#pragma unroll
+        for (int h = 0; h < ROWS; ++h) {
+            const int row = row0 + NW * h;
+            if (row >= G) break;
+            const float l = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
+            const float m_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_all), FOLD_PIECES * h));
+            const long long at_out = first_row * b.num_q_heads + kvh * G + row;
+            bf16x2 o;
+            o[0] = (__bf16)(l > 0.f ? acc[h][0] / l : 0.f);
+            o[1] = (__bf16)(l > 0.f ? acc[h][1] / l : 0.f);
+            *(bf16x2*)((__bf16*)a.out + at_out * D + 2 * lane) = o;
+            if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l > 0.f) ? m_row * b.softmax_scale + logf(l) : -INFINITY;
+        }
+    }
 }
 
 // merge 2: one workgroup per (pair, query row); wave w takes pieces w, w + WAVES, ..., a lane two channels of each.
@@ -739,6 +888,41 @@ size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView
 
 namespace {
 
+// Folded where the batch fits the chip at once (grid of at most 512) and its pieces are short, so that the second launch is a good part
+// of the call: up to 8 pieces of 16 tiles, or 16 of FOLD_SHORT.  Of these the GPU needs the same time or less (28 / 4 heads, us, two
+// kernels and one: 32 contexts of 1000 tokens 17.0 and 15.5, 16 of 500 8.6 and 7.6, one of 1500 7.2 and 7.2), and the host a
+// launch less, which is what bounds the smallest (one of 1500, a call after the other: 9.0 and 7.1).  Not folded: more than 512
+// workgroups (32 of 2000 to 8000, 32 / 8 heads: 119.6 and 121.2) and 16 longer pieces (4 of 1500 to 6000: 13.4 and 13.9), where the round
+// trips of whoever comes last end the call.
+constexpr int FOLD_SHORT = 6;
+bool fold_applies(const BatchView& b, const DecodeShape& S)
+{
+    const int most = S.tiles_per_piece <= FOLD_SHORT ? FOLD_PIECES : S.tiles_per_piece <= 16 ? FOLD_PIECES / 2 : 0;
+    return S.n_unit_pairs == 0 && S.pieces_max > 1 && S.pieces_max <= most && (long long)S.n_pairs * S.pieces_max <= WORKGROUPS_PER_ROUND &&
+           b.num_q_heads / b.num_kv_heads < MAX_G;
+}
+
+// 48 bits that no other launch of this process has, above FOLD_COUNT_BITS bits of count.  They start from a number that is another in
+// every process, so that what an uninitialised workspace holds is a ticket with a chance of 2^-48 only.  Never 0.
+unsigned long long next_ticket()
+{
+    static std::atomic<unsigned long long> next{[] {
+        unsigned long long x = (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() ^ (unsigned long long)(uintptr_t)&next;
+        x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;         // the finaliser of splitmix64
+        x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+        return x ^ (x >> 31);
+    }()};
+    const unsigned long long t = next.fetch_add(1, std::memory_order_relaxed) << FOLD_COUNT_BITS;
+    return t != 0 ? t : next.fetch_add(1, std::memory_order_relaxed) << FOLD_COUNT_BITS;
+}
+
+Divisor divisor_of(int d)                                    // d >= 1
+{
+    int shift = 0;
+    while ((1ll << shift) < d) ++shift;
+    return {(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
+}
+
 template <bool SHARED, bool FUSED>
 hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, hipStream_t stream)
 {
@@ -747,14 +931,26 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
     // the requests' own workgroups first, then (SHARED) those of the units' shared parts
     const long long grid = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit;
     if (grid > 0x3fffffff) return hipErrorInvalidValue;
-    if (a.causal)
-        hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED>), dim3((unsigned)grid), dim3(NT), 0, stream, a, S, sv);
-    else if constexpr (!FUSED)
-        hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false>), dim3((unsigned)grid), dim3(NT), 0, stream, a, S, sv);
-    else
-        return hipErrorInvalidValue;
+    dim3 dims((unsigned)grid);
+    if (!SHARED) {
+        dims.x = (unsigned)S.n_pairs;
+        dims.z = (unsigned)((S.pieces_max + MAX_GRID_Y - 1) / MAX_GRID_Y);
+        dims.y = (unsigned)((S.pieces_max + dims.z - 1) / dims.z);
+    }
+    const LaunchInfo info = {fold_applies(b, S) ? next_ticket() : 0, b.num_q_heads / b.num_kv_heads, (int32_t)dims.y, divisor_of(b.num_kv_heads), divisor_of(S.tiles_per_piece),
+                             SHARED ? divisor_of(S.n_pairs) : Divisor{}, SHARED ? divisor_of(std::max(S.n_unit_pairs, 1)) : Divisor{}};
+    if (!a.causal && FUSED) return hipErrorInvalidValue;
+    auto attend = [&](auto waves) {
+        constexpr int NW = decltype(waves)::value;
+        if (a.causal)
+            hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED, NW>), dims, dim3(64 * NW), 0, stream, a, S, sv, info);
+        else if constexpr (!FUSED)
+            hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false, NW>), dims, dim3(64 * NW), 0, stream, a, S, sv, info);
+    };
+    if (!SHARED && S.tiles_per_piece <= MANY_TILES && grid <= WORKGROUPS_PER_ROUND / 2) attend(std::integral_constant<int, SHARED ? FEW : MANY>{});
+    else attend(std::integral_constant<int, FEW>{});
     hipError_t err = hipGetLastError();
-    if (err != hipSuccess || (!SHARED && S.pieces_max == 1)) return err;   // one piece each: already written
+    if (err != hipSuccess || info.ticket != 0 || (!SHARED && S.pieces_max == 1)) return err;    // merged, or one piece each: already written
     const dim3 mgrid((unsigned)b.num_reqs, (unsigned)b.num_kv_heads, (unsigned)(b.num_q_heads / b.num_kv_heads));
     auto merge = [&](auto causal, auto waves, auto ahead) {
         hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<decltype(causal)::value, SHARED, decltype(waves)::value, decltype(ahead)::value>), mgrid,
@@ -817,8 +1013,8 @@ hipError_t launch_attn_bf16_decode_static(AttnArgs a, const DecodeShape& S, hipS
         }
         ptr = scratch_ptr[dev];
     }
-    // The kernels write every record they later read (no counters or flags, nothing that must start at zero), so
-    // what an earlier call left in the array does not matter.
+    // The kernels write every record they later read, and a count starts from whatever is there (see FOLD_PIECES), so what an
+    // earlier call left in the array does not matter.
     a.workspace = ptr;
     return launch_decode<false, false>(a, SharedPrefixView{}, S, stream);
 }

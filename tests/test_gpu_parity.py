@@ -534,6 +534,75 @@ def test_decode_merge_piece_counts(kind, H, Hkv, ctx):
     _compare(wl, dw)
 
 
+# Batches whose last workgroup merges: 1, 2, 3, 5, 16 pieces (17: the second kernel), of 4 tiles and more, 1 to 15 of a record's 16 rows
+# (16: the second kernel), grids of 256 and 512 workgroups, contexts of fewer pieces than the longest, requests without a token
+@pytest.mark.parametrize("H,Hkv,ctx,new", [(28, 4, [127], [1]), (28, 4, [128], [1]), (8, 1, [300], [1]), (15, 1, [600], [1]), (16, 1, [600], [1]),
+                                           (4, 1, [2047], [1]), (4, 1, [2048], [1]), (3, 3, [1500, 40, 0, 700], [1, 0, 1, 1]), (28, 4, [500] * 16, [1] * 16),
+                                           (28, 4, [1000, 900, 10] * 10 + [1000, 129], [1] * 32), (32, 8, [1999, 2000], [1, 1])])
+def test_decode_merge_by_the_last_workgroup(H, Hkv, ctx, new):
+    """The count by which workgroups learn who is last starts from whatever the workspace holds, call after call and replay
+    after replay, and the result does not depend on it."""
+    print("case last workgroup", H, Hkv, len(ctx), max(ctx), flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+    wl = W.build_workload("last_workgroup", "causal", "bf16", 765, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=ctx, new_lens=new)
+    dw = B.DeviceWorkload(wl)
+    if dw.workspace is not None:
+        dw.workspace.fill_(0xff)
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+    want, want_lse = bits(dw.out).tobytes(), dw.lse.cpu().numpy().tobytes()
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert bits(dw.out).tobytes() == want and dw.lse.cpu().numpy().tobytes() == want_lse, what
+        dw.out.zero_()
+        dw.lse.zero_()
+    dw.out.zero_()
+    dw.lse.zero_()
+    for fill in (None, 0, 0x5a, None):                       # None: what the call before left
+        if dw.workspace is not None and fill is not None:
+            dw.workspace.fill_(fill)
+        dw.decode_step()
+        check(fill)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        dw.decode_step()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            dw.decode_step()
+    dw.out.zero_()
+    lens = dw.prefix_lens.clone()
+    for replay in range(4):
+        dw.prefix_lens.copy_(lens // (replay + 1))           # other contexts, other piece counts, the same captured launch
+        graph.replay()
+        torch.cuda.synchronize()
+        dw.prefix_lens.copy_(lens)
+        for tensor, source in ((dw.k_cache, wl.k_cache), (dw.v_cache, wl.v_cache)):
+            tensor.copy_(torch.from_numpy(source.view(np.int16)).view(torch.bfloat16))       # the shorter contexts' new rows went into other slots
+        graph.replay()
+        check(replay)
+
+
+def test_decode_merge_of_an_infinite_value():
+    """An infinity in V makes its channel infinite and no other, in whichever piece its key lies; of two pieces the last workgroup's
+    merge reads the second one in the places of the third and fourth too."""
+    for key in (3, 140):
+        wl = W.build_workload("infinite_value", "causal", "bf16", 766, num_q_heads=28, num_kv_heads=4, head_dim=128, page_size=16,
+                              prefix_lens=[200], new_lens=[1])
+        dw = B.DeviceWorkload(wl)
+        page = int(wl.page_table[0, key // 16])
+        dw.v_cache[page, :, key % 16, 77] = float("inf")
+        dw.step()
+        torch.cuda.synchronize()
+        out = dw.out.float()
+        assert torch.isposinf(out[..., 77]).all(), key
+        assert torch.isfinite(out[..., :77]).all() and torch.isfinite(out[..., 78:]).all(), key
+
+
 # a wave does blocks of 16 keys, every fourth of a piece; two blocks in its ring; pieces of 4 tiles of 32 keys and more
 DECODE_EDGE_LENS = [0, 1, 14, 15, 16, 17, 30, 31, 32, 47, 48, 49, 62, 63, 64, 65, 79, 80, 95, 111, 112, 126, 127, 128, 129, 143, 191, 255, 256, 300]
 
