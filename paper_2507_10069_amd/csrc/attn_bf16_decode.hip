@@ -71,15 +71,8 @@ constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefi
 static_assert(MAX_G * RED_FLOATS * 4 <= RING_BYTES, "the merge across waves reuses the rings");
 static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= FEW * 64, "a wave's page ids sit in one register");
 
-// Division of 0 .. 2^31 - 1 by a number that the host knows, 2^(shift - 1) < d <= 2^shift: n * ceil(2^(31 + shift) / d) / 2^(31 + shift),
-// exact because d times the multiplier passes 2^(31 + shift) by less than d and n < 2^31, so the quotient grows by less than 1 / d.
-struct Divisor {
-    uint32_t mul;
-    int32_t shift;
-    __device__ int quotient(int n) const { return (int)((uint32_t)(((uint64_t)(2u * (uint32_t)n) * mul) >> 32) >> shift); }
-};
 // What a launch adds to its arguments: the ticket of a folded merge (0: none) and quotients that every workgroup would have to work out
-// (a division is 25 instructions of one chain: without, and with the arguments asked for at once, every call is 0.3 us shorter).
+// (with every argument asked for at the start a call is 0.3 us shorter than with divisions).
 struct LaunchInfo {
     unsigned long long ticket;
     int32_t G, grid_y;
@@ -914,13 +907,6 @@ unsigned long long next_ticket()
     }()};
     const unsigned long long t = next.fetch_add(1, std::memory_order_relaxed) << FOLD_COUNT_BITS;
     return t != 0 ? t : next.fetch_add(1, std::memory_order_relaxed) << FOLD_COUNT_BITS;
-}
-
-Divisor divisor_of(int d)                                    // d >= 1
-{
-    int shift = 0;
-    while ((1ll << shift) < d) ++shift;
-    return {(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
 }
 
 template <bool SHARED, bool FUSED>

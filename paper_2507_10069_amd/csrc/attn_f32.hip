@@ -21,7 +21,8 @@
 //                 operand lane i stands for channels 4 i .. 4 i + 3 of the four products of a 64-channel block, so V
 //                 rows are read whole, 16 bytes per lane, and a lane ends up with 16 consecutive channels of its row.
 // Measured, scatter and attention per step, against one wave per row with lanes owning keys (no matrix instruction):
-// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 14.7 us (11 since two launches cost the host less); the same
+// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 9.3 us (11.1 before the loads overlapped, the lengths came in one
+// round trip and the channels were split: see SPLIT_WORKGROUPS); the same
 // heads, 4 x (1024 + 256) tokens 254 -> 26 us; 8 heads on 2 of 128, 4096 new tokens 5.59 -> 0.44 ms (78 TFLOP/s of the
 // 154 that a large fp32 matrix product reaches).  Relative error against 64 bits 4.2e-7 -> 3.0e-7 on the first.
 #include "emm_internal.h"
@@ -58,56 +59,61 @@ __device__ inline bool is_finite(float x) { return (__float_as_uint(x) & 0x7f800
 
 // First row-tile slot of request r: its ceil(rows / 16) tiles fit between this and the next request's, whatever
 // cu_new_lens[r] is, so the grid needs no more than T G / 16 + B slots and no prefix sums over row tiles.
-__device__ inline long long first_slot(const BatchView& b, int G, int r)
-{
-    return (long long)max(b.cu_new_lens[r], 0) * G / ROWS + r;
-}
+__device__ inline long long first_slot(int cu_new, int G, int r) { return (long long)max(cu_new, 0) * G / ROWS + r; }
 
-template <int D, int NW>                             // NW: waves per workgroup
-__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
+// NW: waves per workgroup; SPLIT: workgroups that share a row tile's channels; ALONE: no two workgroups on a compute unit
+template <int D, int NW, int SPLIT, bool ALONE>
+__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a, int G, Divisor by_G, Divisor by_kv_heads)
 {
     constexpr int QK = D / 16;                        // 16-byte pieces of a Q or K row per lane
-    constexpr int NB = D / 64;                        // 64-channel blocks of V
-    constexpr int STRIDE = D + 4;                     // floats between rows of the LDS records: spreads the banks
+    constexpr int CH = D / SPLIT;                     // channels of the output that this workgroup makes
+    constexpr int NB = CH < 64 ? 1 : CH / 64;         // blocks of V
+    constexpr int VE = CH / NB / 16;                  // channels of a block that a lane reads: VE l16 .. VE l16 + VE - 1
+    constexpr int STRIDE = ALONE ? 164 : CH + 4;      // floats between rows of the LDS records: spreads the banks (ALONE: and takes half the LDS)
+    static_assert(!ALONE || (NW == 8 && CH <= 160 && NW * ROWS * STRIDE * 4 > 80 << 10), "more than half of 160 KB");
+    typedef float vec __attribute__((ext_vector_type(VE)));
     __shared__ __attribute__((aligned(16))) float o_s[NW][ROWS][STRIDE];
     __shared__ float m_s[NW][ROWS], l_s[NW][ROWS];
     const BatchView& b = a.b;
-    const int G = b.num_q_heads / b.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kvh = blockIdx.x % b.num_kv_heads;
-    const int slot = blockIdx.x / b.num_kv_heads;
+    const int tile = blockIdx.x / SPLIT;
+    const int ch0 = blockIdx.x % SPLIT * CH;          // first of this workgroup's channels
+    const int slot = by_kv_heads.quotient(tile);
+    const int kvh = tile - slot * b.num_kv_heads;
 
     int lo = 0, hi = b.num_reqs;                      // the request of this slot: the last one that starts at or before it
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (first_slot(b, G, mid) <= slot) lo = mid; else hi = mid;
+        if (first_slot(b.cu_new_lens[mid], G, mid) <= slot) lo = mid; else hi = mid;
     }
     const int r = lo;
-    // the pages of this wave's first 64 chunks, one per lane, asked for before the lengths are known (entries past the
-    // request's pages are not used)
     const int pg_log2 = 4 + b.page_shift, ps = b.page_size;
-    const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
-    auto pages_from = [&](int i0) -> int {            // of chunks wave + NW * (i0 + lane)
-        const long long key = ((long long)wave + (long long)NW * (i0 + lane)) * KEYS;
-        return pt[min(key >> pg_log2, (long long)b.max_pages - 1)];
-    };
-    int pages = pages_from(0);
+    // The page of this wave's i-th chunk, wave + NW i, by a scalar load, which does not count among the loads of K and V.  (With the
+    // pages in a vector register every chunk waited for all loads on their way.)
+    const __attribute__((address_space(4))) int32_t* pt =
+        (const __attribute__((address_space(4))) int32_t*)(uintptr_t)(b.page_table + (long long)r * b.max_pages);
+    auto page_of = [&](int i) -> int { return pt[min((int)(((uint32_t)(wave + NW * i) * KEYS) >> pg_log2), b.max_pages - 1)]; };
+    // all lengths in one round trip, and with it every argument that is needed further down
+    const int new_len = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
+    int page = page_of(0);                            // (an entry past the request's pages is read and not used)
+    asm volatile("" ::"s"(page), "s"(new_len), "s"(prefix_len), "s"(cu_new), "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out), "s"(a.lse), "s"(a.causal));
+    __builtin_amdgcn_sched_barrier(0);
 
     // (lengths forced into what the page table and the packed tensors can hold: see safe_new_len)
-    const int N = safe_new_len(b, r, a.causal != 0);
+    const int N = clamp_new_len(b, new_len, a.causal != 0);
     const int n_rows = N * G;
-    const long long row0_wide = ((long long)slot - first_slot(b, G, r)) * ROWS;
+    const long long row0_wide = ((long long)slot - first_slot(cu_new, G, r)) * ROWS;
     if (row0_wide < 0 || row0_wide >= n_rows) return;                       // uniform over the workgroup
     const int row0 = (int)row0_wide;
-    const int P = safe_prefix_len(b, r, a.causal ? N : 0);
-    const int kv_len = a.causal ? P + min(row0 + ROWS - 1, n_rows - 1) / G + 1 : P;   // keys that some row here sees
+    const int P = clamp_prefix_len(b, prefix_len, a.causal ? N : 0);
+    const int kv_len = a.causal ? P + by_G.quotient(min(row0 + ROWS - 1, n_rows - 1)) + 1 : P;   // keys that some row here sees
     const int n_chunks = (kv_len + KEYS - 1) / KEYS;
-    const int min_limit = a.causal ? P + row0 / G : P - 1;                  // last key that every row here sees
+    const int min_limit = a.causal ? P + by_G.quotient(row0) : P - 1;               // last key that every row here sees
     const int row = min(row0 + l16, n_rows - 1);
-    const int tok = row / G;
+    const int tok = by_G.quotient(row);
     const int limit = a.causal ? P + tok : P - 1;                           // last key of this lane's row
-    const long long first_row = safe_first_row(b, r, N);
+    const long long first_row = clamp_first_row(b, cu_new, N);
 
     const float* __restrict__ qp = (const float*)a.q + ((first_row + tok) * b.num_q_heads + kvh * G + (row - tok * G)) * D + 4 * g;
     f32x4 q[QK];
@@ -115,32 +121,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
     for (int j = 0; j < QK; ++j) q[j] = *(const f32x4*)(qp + 16 * j);
 
     float m = -INFINITY, l = 0.f;                     // l: this lane's keys only, until the end
-    f32x4 o[4 * NB];
+    f32x4 o[VE * NB];
 #pragma unroll
-    for (int i = 0; i < 4 * NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < VE * NB; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    int page_i0 = 0;
-    auto chunk_base = [&](int i) -> long long {       // element offset of the KV head's 16 rows of chunk wave + NW i
-        if (i - page_i0 >= 64) {
-            page_i0 = i;
-            pages = pages_from(i);
-        }
-        const int page = min(max(__builtin_amdgcn_readlane(pages, i - page_i0), 0), b.num_pages - 1);
+    auto chunk_base = [&](int i, int pg) -> long long {       // element offset of the KV head's 16 rows of chunk wave + NW i
         const int off = ((wave + NW * i) * KEYS) & (ps - 1);
-        return (((long long)page * b.num_kv_heads + kvh) * ps + off) * D;
+        return (((long long)min(max(pg, 0), b.num_pages - 1) * b.num_kv_heads + kvh) * ps + off) * D;
     };
-    f32x4 k[2][QK], v[4][NB];
+    f32x4 k[2][QK];
+    vec v[4][NB];
     auto load_k = [&](long long at, f32x4 (&kk)[QK]) {
         const float* kp = (const float*)a.k_cache + at + l16 * D + 4 * g;
 #pragma unroll
         for (int j = 0; j < QK; ++j) kk[j] = *(const f32x4*)(kp + 16 * j);
     };
     auto load_v = [&](long long at) {
-        const float* vp = (const float*)a.v_cache + at + 4 * g * D + 4 * l16;
+        const float* vp = (const float*)a.v_cache + at + 4 * g * D + ch0 + VE * l16;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int n = 0; n < NB; ++n) v[u][n] = *(const f32x4*)(vp + u * D + 64 * n);
+            for (int n = 0; n < NB; ++n) v[u][n] = *(const vec*)(vp + u * D + 64 * n);
     };
     auto compute = [&](int c, long long at, const f32x4 (&kk)[QK]) {
         f32x4 s = {0.f, 0.f, 0.f, 0.f};
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
         for (int u = 0; u < 4; ++u) p[u] = expf(x[u] - ref);
         l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
-        for (int i = 0; i < 4 * NB; ++i) o[i] *= alpha;
+        for (int i = 0; i < VE * NB; ++i) o[i] *= alpha;
         if (masked) {
             // keys past the tile's last are no tokens: whatever their slots hold must not count.  A key that some rows
             // see and others do not may hold an infinity or NaN, which a weight of 0 would not remove: such a chunk
@@ -173,24 +174,24 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
             for (int u = 0; u < 4; ++u)
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
-                    if (c * KEYS + 4 * g + u >= kv_len) v[u][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (c * KEYS + 4 * g + u >= kv_len) v[u][n] = vec(0.f);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) odd = odd || !is_finite(v[u][n][e]);
+                    for (int e = 0; e < VE; ++e) odd = odd || !is_finite(v[u][n][e]);
                 }
             if (__builtin_amdgcn_ballot_w64(odd) != 0) {
                 for (int kk2 = 0; kk2 < KEYS && c * KEYS + kk2 < kv_len; ++kk2) {
                     const int u = kk2 & 3;
                     const float mine = u == 0 ? p[0] : u == 1 ? p[1] : u == 2 ? p[2] : p[3];
                     const float pk = __shfl(mine, l16 + 16 * (kk2 >> 2));
-                    const float* vp = (const float*)a.v_cache + at + (long long)kk2 * D + 16 * g;
+                    const float* vp = (const float*)a.v_cache + at + (long long)kk2 * D + ch0 + 4 * VE * g;
                     if (c * KEYS + kk2 <= limit)
 #pragma unroll
                         for (int n = 0; n < NB; ++n)
 #pragma unroll
                             for (int t = 0; t < 4; ++t) {
-                                const f32x4 w = *(const f32x4*)(vp + 64 * n + 4 * t);
+                                const vec w = *(const vec*)(vp + 64 * n + VE * t);
 #pragma unroll
-                                for (int e = 0; e < 4; ++e) o[4 * n + e][t] = fmaf(pk, w[e], o[4 * n + e][t]);
+                                for (int e = 0; e < VE; ++e) o[VE * n + e][t] = fmaf(pk, w[e], o[VE * n + e][t]);
                             }
                 }
                 return;
@@ -201,41 +202,50 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[4 * n + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][n][e], p[u], o[4 * n + e], 0, 0, 0);
+                for (int e = 0; e < VE; ++e) o[VE * n + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[u][n][e], p[u], o[VE * n + e], 0, 0, 0);
     };
     const int n_mine = n_chunks > wave ? (n_chunks - wave + NW - 1) / NW : 0;    // chunks wave, wave + NW, ...
     if (n_mine > 0) {
-        // this chunk's V and the next one's K are on their way while this chunk's scores are computed
-        long long at = chunk_base(0);
+        // this chunk's V, the next one's K and the page of the one after it are on their way while this chunk's scores are computed
+        // (past the last chunk the last one's again: with loads that depend on there being one the waits would have to allow for both)
+        const int end = n_mine - 1;
+        long long at = chunk_base(0, page);
         load_k(at, k[0]);
-        for (int i = 0; i < n_mine; i += 2) {
+        page = page_of(min(1, end));
+        for (int i = 0; i <= end; i += 2) {
             load_v(at);
-            const long long at1 = i + 1 < n_mine ? chunk_base(i + 1) : at;
-            load_k(at1, k[1]);
+            const long long next = chunk_base(min(i + 1, end), page);
+            load_k(next, k[1]);
+            page = page_of(min(i + 2, end));
             compute(wave + NW * i, at, k[0]);
-            if (i + 1 >= n_mine) break;
-            load_v(at1);
-            at = i + 2 < n_mine ? chunk_base(i + 2) : at1;
+            if (i + 1 > end) break;
+            load_v(next);
+            at = chunk_base(min(i + 2, end), page);
             load_k(at, k[0]);
-            compute(wave + NW * (i + 1), at1, k[1]);
+            page = page_of(min(i + 3, end));
+            compute(wave + NW * (i + 1), next, k[1]);
         }
     }
 
-    // ---- the waves' results: o[4 n + e][t] is channel 64 n + 16 g + 4 t + e of row l16
+    // ---- the waves' results: o[VE n + e][t] is channel ch0 + 64 n + VE (4 g + t) + e of row l16
     l = group_sum(l);
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-            *(f32x4*)&o_s[wave][l16][64 * n + 16 * g + 4 * t] = f32x4{o[4 * n][t], o[4 * n + 1][t], o[4 * n + 2][t], o[4 * n + 3][t]};
+        for (int x = 0; x < VE; ++x) {                // 4 VE channels, four at a time
+            f32x4 w;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) w[y] = o[VE * n + (4 * x + y) % VE][(4 * x + y) / VE];
+            *(f32x4*)&o_s[wave][l16][64 * n + 4 * VE * g + 4 * x] = w;
+        }
     if (g == 0) {
         m_s[wave][l16] = m;
         l_s[wave][l16] = l;
     }
     __syncthreads();
-    // 16 rows x D / 4 pieces of 16 bytes
-    for (int idx = tid; idx < ROWS * (D / 4); idx += 64 * NW) {
-        const int my = idx / (D / 4), c4 = idx % (D / 4) * 4;
+    // 16 rows x CH / 4 pieces of 16 bytes
+    for (int idx = tid; idx < ROWS * (CH / 4); idx += 64 * NW) {
+        const int my = idx / (CH / 4), c4 = idx % (CH / 4) * 4;
         if (row0 + my >= n_rows) break;
         float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
@@ -248,10 +258,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a)
             acc += wgt * *(const f32x4*)&o_s[w][my][c4];
         }
         const float inv = (l_all > 0.f) ? 1.f / l_all : 0.f;                // no keys (cross, empty cache): zero row
-        const int o_row = row0 + my, o_tok = o_row / G;
+        const int o_row = row0 + my, o_tok = by_G.quotient(o_row);
         const long long at = (first_row + o_tok) * b.num_q_heads + kvh * G + (o_row - o_tok * G);
-        *(f32x4*)((float*)a.out + at * D + c4) = acc * inv;
-        if (a.lse != nullptr && c4 == 0) a.lse[at] = (l_all > 0.f) ? m_all + logf(l_all) : -INFINITY;
+        *(f32x4*)((float*)a.out + at * D + ch0 + c4) = acc * inv;
+        if (a.lse != nullptr && ch0 + c4 == 0) a.lse[at] = (l_all > 0.f) ? m_all + logf(l_all) : -INFINITY;
     }
 }
 
@@ -273,6 +283,15 @@ int waves_of(long long workgroups, bool single, long long keys)
     return waves;
 }
 
+
+// Few workgroups with many keys are bound by their compute unit's matrix pipes and by what it fetches while the others idle: up to
+// SPLIT_WORKGROUPS of them become four each, which make a quarter of the channels (the scores again, a quarter of V).  4 heads on 1 of 64,
+// 256 cached + 64 new tokens (17 workgroups), both kernels, 10.3 -> 9.3 us, 1024 + 64 20.3 -> 15.7; from 80 workgroups on it is slower
+// (88: 10.8 and 13.9).
+// Decode steps have more workgroups than rows (a slot for every request's last tile): where all that have rows find a compute unit of their
+// own they get it, ALONE; two on one keep each other's loads out of its cache (32 contexts of 1000 tokens, 32 / 8 heads of 64: 35.0 and 26.8 us).
+constexpr int SPLIT_WORKGROUPS = 64, COMPUTE_UNITS = 256;
+
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream)
@@ -282,15 +301,23 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream)
     const int G = b.num_q_heads / b.num_kv_heads;
     const long long grid = ((long long)b.total_new_tokens * G / ROWS + b.num_reqs) * b.num_kv_heads;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    auto go = [&](auto d, auto nw) {
-        hipLaunchKernelGGL((attn_f32_kernel<decltype(d)::value, decltype(nw)::value>), dim3((unsigned)grid), dim3(64 * decltype(nw)::value), 0, stream, a);
+    auto go = [&](auto d, auto nw, auto split, auto alone) {
+        constexpr int D = decltype(d)::value, NW = decltype(nw)::value, SPLIT = decltype(split)::value;
+        hipLaunchKernelGGL((attn_f32_kernel<D, NW, SPLIT, decltype(alone)::value>), dim3((unsigned)(grid * SPLIT)), dim3(64 * NW), 0, stream, a, G, divisor_of(G), divisor_of(b.num_kv_heads));
     };
-    const int waves = waves_of(grid, (long long)b.max_new_len * G <= ROWS, (long long)b.max_pages * b.page_size);
+    const bool single = (long long)b.max_new_len * G <= ROWS;              // at most one row tile for a (request, KV head)
+    const int waves = waves_of(grid, single, (long long)b.max_pages * b.page_size);
+    const bool alone = single && grid > COMPUTE_UNITS && (long long)b.num_reqs * b.num_kv_heads <= COMPUTE_UNITS;
     auto of_dim = [&](auto d) {
-        if (waves == 8) go(d, std::integral_constant<int, 8>{});
-        else if (waves == 4) go(d, std::integral_constant<int, 4>{});
-        else if (waves == 2) go(d, std::integral_constant<int, 2>{});
-        else go(d, std::integral_constant<int, 1>{});
+        using one = std::integral_constant<int, 1>;
+        using eight = std::integral_constant<int, 8>;
+        constexpr bool small = decltype(d)::value == 64;
+        if (waves == 8 && grid <= SPLIT_WORKGROUPS) go(d, eight{}, std::integral_constant<int, 4>{}, std::false_type{});
+        else if (waves == 8 && small && alone) go(d, eight{}, one{}, std::integral_constant<bool, small>{});
+        else if (waves == 8) go(d, eight{}, one{}, std::false_type{});
+        else if (waves == 4) go(d, std::integral_constant<int, 4>{}, one{}, std::false_type{});
+        else if (waves == 2) go(d, std::integral_constant<int, 2>{}, one{}, std::false_type{});
+        else go(d, one{}, one{}, std::false_type{});
     };
     if (b.head_dim == 64) of_dim(std::integral_constant<int, 64>{});
     else of_dim(std::integral_constant<int, 128>{});

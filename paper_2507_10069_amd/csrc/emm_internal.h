@@ -24,12 +24,13 @@ struct BatchView {
 // inside the caller's buffers.  A consistent batch passes through unchanged.
 //   new tokens of request r: 0 .. max_new_len, at most T, and (causal: they have slots) at most what a row of
 //   the page table can hold
-__device__ inline int safe_new_len(const BatchView& b, int r, bool causal)
+__device__ inline int clamp_new_len(const BatchView& b, int new_len, bool causal)
 {
-    int n = min(max(b.new_lens[r], 0), min(b.max_new_len, b.total_new_tokens));
+    int n = min(max(new_len, 0), min(b.max_new_len, b.total_new_tokens));
     if (causal) n = (int)min((long long)n, (long long)b.max_pages * b.page_size);
     return n;
 }
+__device__ inline int safe_new_len(const BatchView& b, int r, bool causal) { return clamp_new_len(b, b.new_lens[r], causal); }
 //   cached tokens: what fits the page-table row next to n_slots more tokens (the new ones if causal, else 0)
 __device__ inline int clamp_prefix_len(const BatchView& b, int prefix_len, int n_slots)
 {
@@ -69,6 +70,21 @@ struct SharedPrefixView {
     int32_t max_own_tiles;           // bound on a request's own part in tiles, 0 = the page table's width
     int32_t max_unit_tiles;          // bound on a unit's shared part in tiles, 0 = the page table's width
 };
+
+// Division of 0 .. 2^31 - 1 by a number that the host knows (in a kernel a division is a chain of 25 instructions).
+// With 2^(shift - 1) < d <= 2^shift it is n * ceil(2^(31 + shift) / d) / 2^(31 + shift),
+// exact because d times the multiplier passes 2^(31 + shift) by less than d and n < 2^31, so the quotient grows by less than 1 / d.
+struct Divisor {
+    uint32_t mul;
+    int32_t shift;
+    __device__ int quotient(int n) const { return (int)((uint32_t)(((uint64_t)(2u * (uint32_t)n) * mul) >> 32) >> shift); }
+};
+inline Divisor divisor_of(int d)                                    // d >= 1
+{
+    int shift = 0;
+    while ((1ll << shift) < d) ++shift;
+    return {(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
+}
 
 // Each launcher enqueues on `stream` and returns the launch status.
 hipError_t launch_kv_scatter(const BatchView& b, const void* k_new, const void* v_new, void* k_cache,

@@ -879,6 +879,19 @@ def test_fp32_waves_per_workgroup(reqs, H, Hkv, d, new, longest):
     _compare(wl, dw)
 
 
+# the channels of a row tile are split among four workgroups up to 64 of them; decode steps whose (request, KV head) pairs, not their
+# workgroups, find a compute unit each (256 pairs in 320 workgroups, 264 in 330); contexts of fewer keys than the waves take at once
+@pytest.mark.parametrize("reqs,H,Hkv,d,new,longest", [(1, 4, 1, 64, 252, 70), (1, 4, 1, 128, 252, 70), (1, 4, 1, 64, 256, 200), (1, 4, 1, 128, 256, 200),
+                                                      (5, 5, 1, 128, 7, 900), (32, 32, 8, 64, 1, 143), (33, 32, 8, 64, 1, 143), (32, 32, 8, 128, 1, 143)])
+def test_fp32_split_channels_and_lone_workgroups(reqs, H, Hkv, d, new, longest):
+    print("case fp32 split", reqs, H, Hkv, d, new, longest, flush=True)
+    ctx = [longest, 0, 1, 15, 16, 17, 63, 64, 65]
+    wl = W.build_workload("f32_split", "causal", "f32", 990 + reqs, num_q_heads=H, num_kv_heads=Hkv, head_dim=d, page_size=16,
+                          prefix_lens=[ctx[i % len(ctx)] for i in range(reqs)], new_lens=[new - i % 2 if new > 1 else 1 for i in range(reqs)])
+    dw = _gpu_run(wl)
+    _compare(wl, dw)
+
+
 def test_kv_page_checksum_of_the_largest_page():
     """Pages of 1 MiB per pool (the largest admitted: e.g. 16 KV heads x 256 tokens x 128 channels in bf16) filled
     with large byte values: the position-weighted sum of a 16-byte chunk alone passes 2^32 there.  Bytes and
@@ -979,15 +992,18 @@ def test_f32_tile_edges(name, kind, H, Hkv, d, ps, prefix, new):
     _compare(wl, _gpu_run(wl))
 
 
-@pytest.mark.parametrize("d,bad", [(64, np.nan), (64, np.inf), (128, np.nan)])
-def test_f32_rows_do_not_see_what_later_tokens_hold(d, bad):
+# others: requests beside the one looked at, which make the batch too large for row tiles whose channels are split
+@pytest.mark.parametrize("d,bad,others", [(64, np.nan, 0), (64, np.inf, 0), (128, np.nan, 0), (64, np.inf, 70), (128, np.inf, 70)])
+def test_f32_rows_do_not_see_what_later_tokens_hold(d, bad, others):
     """A value row of a later token that is no number must not reach the rows before it, which share its row tile."""
     wl = W.build_workload("f32_later", "causal", "f32", 730, num_q_heads=4, num_kv_heads=1, head_dim=d, page_size=16,
-                          prefix_lens=[21], new_lens=[11])
+                          prefix_lens=[21] + [9] * others, new_lens=[11] + [1] * others)
     wl.v_new[7, 0, 3] = bad
     dw = _gpu_run(wl)
     _, _, ref, lse_ref = oracle.run_workload(wl)
     out = dw.out.cpu().numpy().astype(np.float64)
+    assert np.abs(out[11:] - ref[11:]).max(initial=0) <= F32_MAX_ABS
+    out, ref = out[:11], ref[:11]
     assert np.isfinite(ref[:7]).all() and np.abs(out[:7] - ref[:7]).max() <= F32_MAX_ABS
     seen = np.zeros(d, dtype=bool)
     seen[3] = True
