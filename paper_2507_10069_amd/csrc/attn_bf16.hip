@@ -171,6 +171,10 @@ struct LaunchShape {
     int fan;                // sub-pairs per (request, KV head) pair: 1, 2, 4 or 8
     int uneven;             // 1: 17 .. 30 units in an XCD's last round are cut unevenly (see uneven_of)
     int ws_pieces;          // piece records per XCD that the workspace holds
+    // for the kernels, which plan before they can ask for anything and have no time for divisions
+    int G;                  // query heads per KV head
+    int fan_log2;
+    Divisor by_G, by_kv_heads;
 };
 
 struct UnitPlan {
@@ -182,6 +186,8 @@ struct UnitPlan {
     bool rows_only;         // parts == 2 stands for a halving along the rows only (never a cut along the keys)
     int min_tiles;          // key tiles that a piece must have
     int uneven;             // > 0: parts == 2 and piece 0 gets uneven / (uneven + 1) of the key tiles (see uneven_of)
+    int req, kvh;           // the pair's request and KV head, and
+    int new_len, prefix_len, cu_new;     // the request's lengths as the arrays hold them
 };
 
 // pieces per tail unit when rem units are left over after full_rounds rounds of 32
@@ -190,9 +196,7 @@ __host__ __device__ inline int split_factor_of(int rem, int full_rounds)
     if (rem == 0) return 1;
     if (full_rounds == 0) {
         // the whole XCD is under-filled: as many pieces per unit as fill it (1 unit: 32, 2: 16, 3-4: 8, 5-8: 4, 9-16: 2)
-        int p = 1;
-        while (p < MAX_PARTS && 2 * p * rem <= CU_PER_XCD) p *= 2;
-        return p;
+        return rem == 1 ? MAX_PARTS : CU_PER_XCD >> (32 - __builtin_clz(rem - 1));
     }
     // With more leftover units the compute units that stay idle in the last round are few, and the busy
     // ones run at a higher clock for it (the chip is power limited): cutting then costs more than it gains.
@@ -210,7 +214,10 @@ __host__ __device__ inline bool rows_only_of(int rem, int full_rounds) { return 
 // after k / (k + 1) of a unit's time instead of 1 (24 units: k = 3, cut at 3/4).  Returns k, or 0 if rem is not in range.
 __host__ __device__ inline int uneven_of(int rem)
 {
-    return (rem > CU_PER_XCD / 2 && rem <= CU_PER_XCD - 2) ? (rem + (CU_PER_XCD - rem) - 1) / (CU_PER_XCD - rem) : 0;
+    // 31 / d for d = 2 .. 15, four bits each
+    static_assert(CU_PER_XCD == 32, "the table");
+    constexpr unsigned long long QUOTIENT = 0x222223334567af00ull;
+    return (rem > CU_PER_XCD / 2 && rem <= CU_PER_XCD - 2) ? (int)(QUOTIENT >> (4 * (CU_PER_XCD - rem)) & 15) : 0;
 }
 __host__ __device__ inline int split_factor(int rem, int full_rounds, int uneven_ok)
 {
@@ -230,7 +237,7 @@ __host__ __device__ inline int sub_pair_tiles(int new_len, int G, int fan, int s
 // running maximum starts finite.  (Rows only see more keys further down the tile.)
 __device__ inline bool cuttable(int n_tiles, int parts, int limit_min, int min_tiles)
 {
-    const int last_begin = (parts - 1) * n_tiles / parts;
+    const int last_begin = (parts - 1) * n_tiles >> __builtin_ctz(parts);       // (parts is a power of two)
     return n_tiles >= min_tiles * parts && (last_begin + 1) * BC - 1 <= limit_min;
 }
 // Into how many pieces a unit planned for `parts` pieces is really cut: the largest power of two up to `parts`
@@ -283,10 +290,10 @@ struct XcdPlan {
 __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int listed)
 {
     XcdPlan p;
-    const int turn = xcd % L.fan;                            // this XCD's place among those that share the list
+    const int turn = xcd & (L.fan - 1);                      // this XCD's place among those that share the list (fan is a power of two)
     const bool single = L.fan > 1 && listed == 1;
     p.halves = single && turn <= 1;
-    p.total = single ? (turn <= 1 ? 1 : 0) : (listed - turn + L.fan - 1) / L.fan;
+    p.total = single ? (turn <= 1 ? 1 : 0) : (listed - turn + L.fan - 1) >> L.fan_log2;
     p.rem = p.total % CU_PER_XCD;
     const int full = p.total / CU_PER_XCD;
     p.parts = split_factor(p.rem, full, L.uneven);
@@ -318,28 +325,42 @@ __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int l
 // cached and 76 to 304 new (42 and 36 units where 39 each are possible) 142 -> 136 us, one request of 16384 + 36 34.6 -> 32.9 us.
 // merge_idx >= 0 asks instead, whatever in_xcd is, for the plan of merge workgroup merge_idx of the XCD: the unit
 // in tail slot merge_idx / shares, with .part = merge_idx % shares, shares = parts (1 for an uneven cut).
-__device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShape& L, int xcd, int in_xcd, int merge_idx = -1)
+// The lanes look at all the lengths of their pairs' requests, so that those of the workgroup's own unit need no round trip of
+// their own, and nothing is divided: powers of two are shifted by, numbers that the host knows are multiplied by.  (With the lengths asked for
+// one after the other where they were needed, arguments likewise, and eight divisions, the way to the first tile was 1200 instructions and six
+// round trips long.  Without: one request of 16384 + 36 tokens 30.7 -> 28.9 us for both kernels, eight questions on two images 61.9 -> 60.2,
+// 32 ordinary requests 905 -> 898.)
+__device__ inline UnitPlan plan_unit(const BatchView& b, const LaunchShape& L, int xcd, int in_xcd, int merge_idx = -1)
 {
     UnitPlan u;
+    const int G = L.G;
     u.half = -1; u.xcd = xcd;
     u.pair = -1; u.tile = 0; u.parts = 1; u.part = 0; u.slot = 0; u.rows_only = false; u.min_tiles = MIN_TILES_PER_PART; u.uneven = 0;
+    u.req = u.kvh = u.new_len = u.prefix_len = u.cu_new = 0;
     if (!L.split) {
         if (merge_idx >= 0 || in_xcd >= L.pairs_per_xcd * L.n_row_tiles) return u;
-        const int sp = xcd + NUM_XCD * (in_xcd / L.n_row_tiles);
+        const int in_pair = in_xcd / L.n_row_tiles;
+        const int sp = xcd + NUM_XCD * in_pair;
         if (sp >= L.n_pairs) return u;
-        const int idx = L.n_row_tiles - 1 - in_xcd % L.n_row_tiles;      // position among the sub-pair's tiles
-        if (idx >= sub_pair_tiles(safe_new_len(b, sp / L.fan / b.num_kv_heads, false), G, L.fan, sp)) return u;
-        u.pair = sp / L.fan;
-        u.tile = sp % L.fan + L.fan * idx;
+        const int idx = L.n_row_tiles - 1 - (in_xcd - in_pair * L.n_row_tiles);          // position among the sub-pair's tiles
+        const int pair = sp >> L.fan_log2;
+        u.req = L.by_kv_heads.quotient(pair);
+        u.kvh = pair - u.req * b.num_kv_heads;
+        u.new_len = b.new_lens[u.req]; u.prefix_len = b.prefix_lens[u.req]; u.cu_new = b.cu_new_lens[u.req];
+        if (idx >= sub_pair_tiles(clamp_new_len(b, u.new_len, false), G, L.fan, sp)) return u;
+        u.pair = pair;
+        u.tile = (sp & (L.fan - 1)) + L.fan * idx;
         return u;
     }
-    const int turn = xcd % L.fan;                            // this XCD's place among those that share a list
+    const int turn = xcd & (L.fan - 1);                      // this XCD's place among those that share a list
     const int list_xcd = xcd - turn;
     // lane pi looks at the pi-th pair of the list, pair (list_xcd + 8 pi) / fan
     const int pi = threadIdx.x & 63;
     const int lane_sp = list_xcd + NUM_XCD * pi;
-    const int cnt = (pi < L.pairs_per_xcd && lane_sp < L.n_pairs)
-                        ? (safe_new_len(b, lane_sp / L.fan / b.num_kv_heads, false) * G + BR - 1) / BR : 0;
+    const bool listed_here = pi < L.pairs_per_xcd && lane_sp < L.n_pairs;
+    const int lane_req = L.by_kv_heads.quotient(listed_here ? lane_sp >> L.fan_log2 : 0);
+    const int new_lane = b.new_lens[lane_req], prefix_lane = b.prefix_lens[lane_req], cu_lane = b.cu_new_lens[lane_req];
+    const int cnt = listed_here ? (clamp_new_len(b, new_lane, false) * G + BR - 1) / BR : 0;
     const int incl = wave_scan64(cnt);
     const int listed = __builtin_amdgcn_readlane(incl, 63);
     const XcdPlan x = xcd_plan(L, xcd, listed);
@@ -356,21 +377,33 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, int G, const LaunchShap
         slot = ordinal - first_tail;
     } else {
         if (parts == 1) return u;
-        const int e = in_xcd - total;
-        const int shares = x.uneven > 0 ? 1 : parts;         // merge workgroups per unit
-        slot = merge_idx >= 0 ? merge_idx / shares : e / (parts - 1);
-        part = merge_idx >= 0 ? merge_idx % shares : 1 + e % (parts - 1);
-        if (slot >= rem) return u;
+        if (merge_idx >= 0) {
+            const int shares = x.uneven > 0 ? 1 : parts;     // merge workgroups per unit, a power of two
+            slot = merge_idx >> __builtin_ctz(shares);
+            part = merge_idx & (shares - 1);
+            if (slot >= rem) return u;
+        } else {
+            const int e = in_xcd - total;                    // of rem (parts - 1), fewer than 32
+            if (e >= rem * (parts - 1)) return u;
+            const int mul = parts == 2 ? 65537 : parts == 4 ? 21846 : parts == 8 ? 9363 : parts == 16 ? 4370 : 2115;     // 65536 / (parts - 1) + 1
+            slot = e * mul >> 16;
+            part = 1 + e - slot * (parts - 1);
+        }
         ordinal = first_tail + slot;
     }
     // the pair that holds this ordinal: the first one whose inclusive running count exceeds it
-    const int in_list = x.halves ? 0 : ordinal * L.fan + turn;
+    const int in_list = x.halves ? 0 : (ordinal << L.fan_log2) + turn;
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(incl > in_list);
     if (hit == 0) return u;
     const int hit_pi = __builtin_ctzll(hit);
     const int hit_incl = __builtin_amdgcn_readlane(incl, hit_pi);
     const int hit_sp = list_xcd + NUM_XCD * hit_pi;
-    u.pair = hit_sp / L.fan;
+    u.pair = hit_sp >> L.fan_log2;
+    u.req = __builtin_amdgcn_readlane(lane_req, hit_pi);
+    u.kvh = u.pair - u.req * b.num_kv_heads;
+    u.new_len = __builtin_amdgcn_readlane(new_lane, hit_pi);
+    u.prefix_len = __builtin_amdgcn_readlane(prefix_lane, hit_pi);
+    u.cu_new = __builtin_amdgcn_readlane(cu_lane, hit_pi);
     u.tile = hit_incl - 1 - in_list;                         // = cnt - 1 - (place in the list - exclusive count): the last tile first
     if (parts > 1 && ordinal >= first_tail) {                // a tail unit
         u.parts = parts;
@@ -417,32 +450,35 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     // the last (longest key range) to the first, so that the workgroups running together on an XCD mostly
     // stream the same pages through its L2.  plan_unit() says which unit, and which part of its key range,
     // this workgroup does.
-    const int G = b.num_q_heads / b.num_kv_heads;
+    const int G = L.G;
 #ifdef EMM_TIMELINE
     const long long tl_t0 = __builtin_amdgcn_s_memrealtime();            // 100 MHz, the same on every compute unit
     const long long tl_c0 = __builtin_readcyclecounter();                // shader clock of this compute unit
 #endif
-    const int pair = plan.pair, tile = plan.tile;
-    const int kvh = pair % b.num_kv_heads;
-    const int r = pair / b.num_kv_heads;
+    const int tile = plan.tile;
+    const int kvh = plan.kvh, r = plan.req;
 
-    // The page ids of the unit's first 64 key tiles are asked for right away, before the request's lengths are
-    // known (the load needs only the request): one memory latency less between launch and first MFMA.  Lane k
-    // will fetch 16-key block 4 k + wave / 2 of tile k; what entries past the context hold is never used.
+    // The page ids of this workgroup's first 64 key tiles are asked for as soon as it is known which tiles these are: at once
+    // for a whole unit and for the first piece of one that is cut.  Lane k will fetch 16-key block 4 k + wave / 2 behind the first tile; what
+    // entries past the context hold is never used.
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
-    const int blk_early = (threadIdx.x & 63) * 4 + (threadIdx.x >> 7);
-    const int pg_early = pt[min(blk_early >> b.page_shift, b.max_pages - 1)];
+    int blk_early = (threadIdx.x & 63) * 4 + (threadIdx.x >> 7), pg_early = 0;
+    auto ask_pages = [&]() { pg_early = pt[min(blk_early >> b.page_shift, b.max_pages - 1)]; };
+    const bool from_start = plan.part == 0;
+    if (from_start) ask_pages();
+    // (the arguments needed further down are asked for here: the compiler would where they are first used, a round trip each)
+    asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out));
 
     // (lengths forced into what the page table and the packed tensors can hold: see safe_new_len)
-    const int N = safe_new_len(b, r, CAUSAL);
+    const int N = clamp_new_len(b, plan.new_len, CAUSAL);
     const int n_rows = N * G;                                // rows of this (request, KV head)
     const int row0 = tile * BR;
     if (row0 >= n_rows) return;                              // uniform over the workgroup
-    const int P = safe_prefix_len(b, r, CAUSAL ? N : 0);
-    const int first_row = safe_first_row(b, r, N);           // of the request in the packed tensors
+    const int P = clamp_prefix_len(b, plan.prefix_len, CAUSAL ? N : 0);
+    const int first_row = clamp_first_row(b, plan.cu_new, N);            // of the request in the packed tensors
     const int ctx_len = CAUSAL ? P + N : P;                  // slots of this request that hold tokens
     const int last_row = min(row0 + BR - 1, n_rows - 1);
-    const int kv_len = CAUSAL ? P + last_row / G + 1 : P;    // keys this row tile can see
+    const int kv_len = CAUSAL ? P + L.by_G.quotient(last_row) + 1 : P;   // keys this row tile can see
     const int n_tiles_unit = (kv_len + BC - 1) / BC;
     // A tail unit that cannot be cut along the keys (too short) is halved along its ROWS instead: waves 0-3 of
     // the row tile work in the regular workgroup, waves 4-7 in the workgroup of piece 1, the other four only
@@ -455,7 +491,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     }
     // into how many pieces the unit is really cut along the keys: as planned for its XCD, fewer if it is too
     // short for that, 1 if it cannot be cut at all or is only to be halved
-    const int limit_first_row = CAUSAL ? P + row0 / G : P - 1;
+    const int limit_first_row = CAUSAL ? P + L.by_G.quotient(row0) : P - 1;
     const int cut = (plan.parts == 1 || plan.rows_only) ? 1
                     : plan.uneven > 0 ? (uneven_cuttable(n_tiles_unit, plan.uneven, limit_first_row) ? 2 : 1)
                                       : pieces_cut(n_tiles_unit, plan.parts, limit_first_row, plan.min_tiles);
@@ -470,10 +506,19 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         return;
     }
     // this workgroup's key tiles: t_begin .. t_begin + n_tiles - 1
-    const int t_split = uneven_split(n_tiles_unit, plan.uneven);          // meaningful for an uneven cut only
-    const int t_begin = (plan.uneven > 0 && cut == 2) ? (plan.part ? t_split : 0) : plan.part * n_tiles_unit / cut;
-    const int n_tiles = (plan.uneven > 0 && cut == 2) ? (plan.part ? n_tiles_unit - t_split : t_split)
-                                                      : (plan.part + 1) * n_tiles_unit / cut - t_begin;
+    int t_begin, n_tiles;
+    if (plan.uneven > 0 && cut == 2) {
+        const int t_split = uneven_split(n_tiles_unit, plan.uneven);
+        t_begin = plan.part ? t_split : 0;
+        n_tiles = plan.part ? n_tiles_unit - t_split : t_split;
+    } else {
+        t_begin = plan.part * n_tiles_unit >> __builtin_ctz(cut);        // (cut is a power of two)
+        n_tiles = ((plan.part + 1) * n_tiles_unit >> __builtin_ctz(cut)) - t_begin;
+    }
+    if (!from_start) {
+        blk_early += 4 * t_begin;
+        ask_pages();
+    }
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -485,9 +530,9 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     const bool active = wrow0 < n_rows && (row_half < 0 || (wave >> 2) == row_half);
     const int my_row = wrow0 + l32;
     const int row_c = min(my_row, n_rows - 1);
-    const int tok = row_c / G;                               // new-token index of this lane's row
+    const int tok = L.by_G.quotient(row_c);                  // new-token index of this lane's row
     const int limit = CAUSAL ? P + tok : P - 1;              // last visible key of this lane's row
-    const int wave_min_limit = CAUSAL ? P + min(wrow0, n_rows - 1) / G : P - 1;
+    const int wave_min_limit = CAUSAL ? P + L.by_G.quotient(min(wrow0, n_rows - 1)) : P - 1;
     // tiles 0 .. n_clear-1 lie entirely below every row's limit in this wave: no mask needed
     const int n_clear = (wave_min_limit + 1) / BC;
 
@@ -678,16 +723,16 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     if (n_tiles > 0) {
         // ---- prologue: the first tiles K(0), V(0), K(1), V(1), K(2) of this workgroup's range on their way
         //      to LDS (tile numbers in the comments below are relative to t_begin; ring slots follow them)
-        const int last_lane = (n_blocks_valid - 1 - (wave >> 1)) >> 2;      // last lane whose block of tile `lane` holds tokens
-        if (t_begin == 0 && last_lane >= 0) {
+        const int last_lane = ((n_blocks_valid - 1 - (wave >> 1)) >> 2) - t_begin;       // last lane whose block of tile t_begin + lane holds tokens
+        if (last_lane >= 0) {
             // the ids asked for at the start; lanes past the context take the wave's last block that holds tokens
             // (any block inside the context will do there: its keys are masked and its V rows zeroed)
             const int src_lane = min(last_lane, 63);
             const int id = min(max(pg_early, 0), b.num_pages - 1);
             const int page = lane <= src_lane ? id : __builtin_amdgcn_readlane(id, src_lane);
-            const int blk = min(blk_early, src_lane * 4 + (wave >> 1));
+            const int blk = min(blk_early, (t_begin + src_lane) * 4 + (wave >> 1));
             pg_vec = ((page * b.num_kv_heads + kvh) << b.page_shift) + (blk & ((1 << b.page_shift) - 1));
-            pg_base = 0;
+            pg_base = t_begin;
         } else {
             refill_pages(t_begin);
         }
@@ -994,7 +1039,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         rec[3] = n_tiles;
         rec[4] = __builtin_amdgcn_s_getreg(4 | (31 << 11));            // HW_REG_HW_ID, all 32 bits
         rec[5] = __builtin_amdgcn_s_getreg(20 | (3 << 11));            // HW_REG_XCC_ID, bits 3:0
-        rec[6] = ((long long)pair << 32) | (unsigned)(tile * 64 + plan.part);
+        rec[6] = ((long long)plan.pair << 32) | (unsigned)(tile * 64 + plan.part);
         rec[7] = cut;
     }
 #endif
@@ -1041,16 +1086,16 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
             }
         const int e_row = row0 + e_wave * 32 + e_l32;
         if (a.lse != nullptr && e_h32 == 0 && e_row < n_rows) {
-            const int e_tok = e_row / G;
+            const int e_tok = L.by_G.quotient(e_row);
             a.lse[((long long)first_row + e_tok) * b.num_q_heads + kvh * G + (e_row - e_tok * G)] =
                 (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
         }
         // the wave's own LDS writes are visible to its own reads once they have completed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         const long long q_row0 = first_row;
-        const int t_add = 4 / G, g_add = 4 - t_add * G;      // row + 4 is token + t_add, head + g_add (mod G)
+        const int t_add = L.by_G.quotient(4), g_add = 4 - t_add * G;      // row + 4 is token + t_add, head + g_add (mod G)
         const int first = row0 + e_wave * 32 + (e_lane >> 4);
-        int o_tok = first / G, o_g = first - o_tok * G;
+        int o_tok = L.by_G.quotient(first), o_g = first - o_tok * G;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int in_wave = (e_lane >> 4) + 4 * j;       // lanes 16k .. 16k+15 take row 4j + k
@@ -1083,7 +1128,7 @@ __device__ __attribute__((noinline)) void attend_unit_carefully(unsigned long lo
     const KernArgs* __restrict__ ka = (const KernArgs*)(const __attribute__((address_space(4))) KernArgs*)kernargs;
     const AttnArgs& a = ka->a;
     const LaunchShape& L = ka->L;
-    const UnitPlan plan = plan_unit(a.b, a.b.num_q_heads / a.b.num_kv_heads, L, xcd, in_xcd);
+    const UnitPlan plan = plan_unit(a.b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
     attend_unit<CAUSAL, true>(a, L, xcd, in_xcd, plan, (unsigned char*)lds);
 }
@@ -1098,7 +1143,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
     // Workgroups are dealt to the 8 XCDs round-robin by the dispatcher; plan_unit() says which unit, and which
     // part of its key range, this one does.
     const int xcd = blockIdx.x % NUM_XCD, in_xcd = blockIdx.x / NUM_XCD;
-    const UnitPlan plan = plan_unit(b, b.num_q_heads / b.num_kv_heads, L, xcd, in_xcd);
+    const UnitPlan plan = plan_unit(b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
     attend_unit<CAUSAL, false>(a, L, xcd, in_xcd, plan, smem);
 }
@@ -1109,7 +1154,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
 // all before the first use, and (m, l) of one column and piece, from which all weights are made in LDS meanwhile.  (With shares
 // by registers every share read all (m, l): as many bytes again for 32 pieces.)  Pieces past the last repeat it, with weight 0.
 template <int PARTS, int SHARES = PARTS>
-__device__ inline void merge_share(const float* __restrict__ ws0, float* lds, int cut, int sub, int row0, int n_rows, int G, int kvh,
+__device__ inline void merge_share(const float* __restrict__ ws0, float* lds, int cut, int sub, int row0, int n_rows, const LaunchShape& L, int kvh,
                                    long long first_row, const AttnArgs& a)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -1183,7 +1228,7 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
 #pragma unroll
             for (int j = 0; j < PARTS; ++j) l_tot += wl_s[j * COLS + c];
             const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-            const int tok = row / G, h32 = (col >> 5) & 1;
+            const int G = L.G, tok = L.by_G.quotient(row), h32 = (col >> 5) & 1;
             const long long at = (first_row + tok) * a.b.num_q_heads + kvh * G + (row - tok * G);
             // register 4 group + e of a column is channel 32 (group / 4) + 8 (group % 4) + 4 h32 + e
             bf16x4 o;
@@ -1204,38 +1249,37 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
 __global__ __launch_bounds__(NTHREADS) void attn_bf16_merge_kernel(AttnArgs a, LaunchShape L)
 {
     const BatchView& b = a.b;
-    const int G = b.num_q_heads / b.num_kv_heads;
+    const int G = L.G;
     const int xcd = blockIdx.x % NUM_XCD;
-    const UnitPlan plan = plan_unit(b, G, L, xcd, 0, blockIdx.x / NUM_XCD);   // .part is this workgroup's share
+    const UnitPlan plan = plan_unit(b, L, xcd, 0, blockIdx.x / NUM_XCD);      // .part is this workgroup's share
     if (plan.pair < 0) return;
-    const int kvh = plan.pair % b.num_kv_heads;
-    const int r = plan.pair / b.num_kv_heads;
-    const int N = safe_new_len(b, r, a.causal != 0);         // the same values as in the main kernel
+    const int kvh = plan.kvh;
+    const int N = clamp_new_len(b, plan.new_len, a.causal != 0);         // the same values as in the main kernel
     const int n_rows = N * G;
     const int row0 = plan.tile * BR;
     if (row0 >= n_rows) return;
-    const int P = safe_prefix_len(b, r, a.causal ? N : 0);
+    const int P = clamp_prefix_len(b, plan.prefix_len, a.causal ? N : 0);
     const int last_row = min(row0 + BR - 1, n_rows - 1);
-    const int kv_len = a.causal ? P + last_row / G + 1 : P;
-    const int limit_first_row = a.causal ? P + row0 / G : P - 1;
+    const int kv_len = a.causal ? P + L.by_G.quotient(last_row) + 1 : P;
+    const int limit_first_row = a.causal ? P + L.by_G.quotient(row0) : P - 1;
     const int cut = plan.rows_only ? 1
                     : plan.uneven > 0 ? (uneven_cuttable((kv_len + BC - 1) / BC, plan.uneven, limit_first_row) ? 2 : 1)
                                       : pieces_cut((kv_len + BC - 1) / BC, plan.parts, limit_first_row, plan.min_tiles);
     if (cut == 1) return;                                    // not cut along the keys
 
-    const long long first_row = safe_first_row(b, r, N);
+    const long long first_row = clamp_first_row(b, plan.cu_new, N);
     const float* __restrict__ ws0 = part_base(a.workspace, L.ws_pieces, xcd, plan.slot, plan.parts, 0);
     __shared__ __attribute__((aligned(16))) float lds[4 * NTHREADS + 4 * NTHREADS / 2];
     if (plan.uneven > 0) {
-        merge_share<2, 1>(ws0, lds, cut, 0, row0, n_rows, G, kvh, first_row, a);
+        merge_share<2, 1>(ws0, lds, cut, 0, row0, n_rows, L, kvh, first_row, a);
         return;
     }
     switch (plan.parts) {
-        case 2: merge_share<2>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
-        case 4: merge_share<4>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
-        case 8: merge_share<8>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
-        case 16: merge_share<16>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
-        default: merge_share<32>(ws0, lds, cut, plan.part, row0, n_rows, G, kvh, first_row, a); break;
+        case 2: merge_share<2>(ws0, lds, cut, plan.part, row0, n_rows, L, kvh, first_row, a); break;
+        case 4: merge_share<4>(ws0, lds, cut, plan.part, row0, n_rows, L, kvh, first_row, a); break;
+        case 8: merge_share<8>(ws0, lds, cut, plan.part, row0, n_rows, L, kvh, first_row, a); break;
+        case 16: merge_share<16>(ws0, lds, cut, plan.part, row0, n_rows, L, kvh, first_row, a); break;
+        default: merge_share<32>(ws0, lds, cut, plan.part, row0, n_rows, L, kvh, first_row, a); break;
     }
 }
 
@@ -1271,6 +1315,10 @@ static void launch_shape(const BatchView& b, bool has_workspace, LaunchShape& L,
     L.n_pairs = (int)n_pairs;
     L.pairs_per_xcd = (int)pairs_per_xcd;
     L.fan = fan;
+    L.fan_log2 = __builtin_ctz(fan);
+    L.G = G;
+    L.by_G = divisor_of(G);
+    L.by_kv_heads = divisor_of(b.num_kv_heads);
     L.split = (has_workspace && pairs_per_xcd <= SPLIT_MAX_PAIRS_PER_XCD) ? 1 : 0;
     L.uneven = 1;
     const bool uniform = L.split && (long long)b.num_reqs * b.max_new_len == b.total_new_tokens;

@@ -52,12 +52,14 @@ __global__ __launch_bounds__(THREADS) void attn_merge_parts_kernel(BatchView b, 
                                                                    const __bf16* __restrict__ out_shared,
                                                                    const float* __restrict__ lse_shared,
                                                                    const float* __restrict__ lse_own, __bf16* __restrict__ out,
-                                                                   float* __restrict__ lse)
+                                                                   float* __restrict__ lse, Divisor by_heads)
 {
+    // (every argument in one round trip: the compiler asks for some where they are first used)
+    asm volatile("" ::"s"(req_shared_len), "s"(out_shared), "s"(lse_shared), "s"(lse_own), "s"(out), "s"(lse), "s"(b.cu_new_lens), "s"(b.num_reqs));
     const long long n_rows = (long long)b.total_new_tokens * b.num_q_heads;
     const long long my_row = (long long)blockIdx.x * (THREADS / 16) + (threadIdx.x >> 4);
     const long long row = my_row < n_rows ? my_row : n_rows - 1;          // every lane stays for the ballots: left below
-    const int t = n_rows <= 0x7fffffff ? (int)row / b.num_q_heads : (int)(row / b.num_q_heads);   // (a 64-bit division is 150 instructions)
+    const int t = n_rows <= 0x7fffffff ? by_heads.quotient((int)row) : (int)(row / b.num_q_heads);   // (a 64-bit division is 150 instructions)
     const float lo = lse_own[row];
     const int r = request_of_token(b, t);
     float merged = lo;
@@ -69,6 +71,7 @@ __global__ __launch_bounds__(THREADS) void attn_merge_parts_kernel(BatchView b, 
         const float ls = lse_shared[row];
         const bf16x8 a = *(const bf16x8*)(out_shared + at);
         const bf16x8 c = *(const bf16x8*)(out + at);
+        asm volatile("" ::"v"(ls), "v"(a), "v"(c));          // all three at once (left to itself the compiler asks for two when it has looked at ls)
         const float m = fmaxf(ls, lo);
         if (m > -INFINITY) {
             const float ws = __expf(ls - m), wo = __expf(lo - m);
@@ -93,7 +96,7 @@ hipError_t launch_attn_merge_parts(const BatchView& b, const int32_t* req_shared
     const long long grid = (n_rows + THREADS / 16 - 1) / (THREADS / 16);
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(attn_merge_parts_kernel, dim3((unsigned)grid), dim3(THREADS), 0, stream, b, req_shared_len,
-                       (const __bf16*)out_shared, lse_shared, lse_own, (__bf16*)out, lse);
+                       (const __bf16*)out_shared, lse_shared, lse_own, (__bf16*)out, lse, divisor_of(b.num_q_heads));
     return hipGetLastError();
 }
 

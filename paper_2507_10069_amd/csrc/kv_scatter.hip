@@ -9,7 +9,8 @@
 // kernel arguments; the batch's offsets and lengths (64 of each at once, one per lane, the token's request found by a
 // ballot) together with the rows to be moved, whose place does not depend on them; the page id.
 // Measured against a binary search by scalar loads with the rows asked for last: 5.1 -> 3.9 us for 36 tokens, 48.4 ->
-// 46.2 us (6.4 TB/s) for 36336 tokens of 8 heads; a kernel that does nothing takes 1.7 us.
+// 46.2 us (6.4 TB/s) for 36336 tokens of 8 heads; a kernel that does nothing takes 1.7 us.  (The kernel arguments were three round
+// trips of their own until all were asked for at once: 5.2 -> 4.0 us behind a call that keeps the chip busy.)
 #include "emm_internal.h"
 
 namespace emm {
@@ -25,6 +26,12 @@ __global__ __launch_bounds__(64 * WAVES) void kv_scatter_kernel(BatchView b, con
                                                                 int row_shift)
 {
     const int t = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // packed token, wave-uniform
+    // every argument in one round trip: the compiler asks for some where they are first used.  (Behind the asm it takes scalar loads only
+    // from the constant address space.)
+    typedef const __attribute__((address_space(4))) int32_t* scalar_ints;
+    const scalar_ints cu_s = (scalar_ints)(uintptr_t)b.cu_new_lens, table_s = (scalar_ints)(uintptr_t)b.page_table;
+    asm volatile("" ::"s"(k_new), "s"(v_new), "s"(k_cache), "s"(v_cache), "s"(b.cu_new_lens), "s"(b.prefix_lens), "s"(b.page_table), "s"(row_shift),
+                 "s"(b.num_reqs), "s"(b.num_kv_heads), "s"(b.page_shift), "s"(b.max_pages));
     if (t >= b.total_new_tokens) return;
     const int lane = threadIdx.x & 63;
 
@@ -44,7 +51,7 @@ __global__ __launch_bounds__(64 * WAVES) void kv_scatter_kernel(BatchView b, con
     int lo = 0, hi = b.num_reqs;
     while (hi - lo > 64) {
         const int mid = (lo + hi) >> 1;
-        if (b.cu_new_lens[mid] <= t) lo = mid; else hi = mid;
+        if (cu_s[mid] <= t) lo = mid; else hi = mid;
     }
     const int mine = min(lo + lane, hi - 1);
     const int cu_mine = b.cu_new_lens[mine], prefix_mine = b.prefix_lens[mine];
@@ -54,7 +61,7 @@ __global__ __launch_bounds__(64 * WAVES) void kv_scatter_kernel(BatchView b, con
     const long long pos64 = (long long)__builtin_amdgcn_readlane(prefix_mine, at) + (t - __builtin_amdgcn_readlane(cu_mine, at));
     // inconsistent lengths or a corrupt table: drop the write, never stray
     const int pos = (int)min(max(pos64, 0ll), (long long)b.max_pages * b.page_size - 1);
-    const int page = b.page_table[(long long)r * b.max_pages + (pos >> (4 + b.page_shift))];
+    const int page = table_s[(long long)r * b.max_pages + (pos >> (4 + b.page_shift))];
     // (the rows are waited for here, with the page id: left to itself the compiler asks for them where they are stored)
 #pragma unroll
     for (int u = 0; u < HELD; ++u)

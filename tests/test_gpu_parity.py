@@ -973,6 +973,21 @@ def test_scores_that_jump_between_tiles(name, kind, H, Hkv, prefix, new, planted
     assert B.DeviceWorkload.to_numpy_bits(dw.out).tobytes() == first
 
 
+# every division by the heads of a group or by the KV heads is a multiplication by a number the host works out: groups and KV heads that are
+# no powers of two, rows of a token on both sides of a row tile of 256, whole units, pieces and row halves, fewer pairs than XCDs and more
+@pytest.mark.parametrize("G,Hkv", [(1, 1), (3, 1), (5, 3), (6, 7), (7, 5), (9, 2), (11, 1), (13, 6), (24, 1), (47, 2)])
+def test_group_sizes_and_kv_heads(G, Hkv):
+    print("case group sizes", G, Hkv, flush=True)
+    rows = -(-256 // G)                                      # tokens whose rows fill a row tile
+    wl = W.build_workload("group_sizes", "causal", "bf16", 740 + G, num_q_heads=G * Hkv, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=[2100, 0, 40, 700], new_lens=[rows - 1, rows, 2 * rows + 1, 1])
+    dw = _gpu_run(wl)
+    _compare(wl, dw, _sample_tokens(wl, 40, seed=G))
+    wl = W.build_workload("group_sizes_one", "causal", "bf16", 745 + G, num_q_heads=G * Hkv, num_kv_heads=Hkv, head_dim=128, page_size=32,
+                          prefix_lens=[5000], new_lens=[max(2, rows // 2)])
+    _compare(wl, _gpu_run(wl), _sample_tokens(wl, 20, seed=G))
+
+
 # 16 rows and 16 keys per step, 8 waves taking the chunks in turn, 64 chunks per wave (8192 keys) between page-table reads
 F32_CASES = [
     ("rows_and_keys_at_the_tile_edges", "causal", 4, 1, 64, 16, [0, 1, 15, 16, 17, 111, 112, 127, 128, 129], [1, 3, 4, 5, 8, 1, 16, 17, 33, 2]),
