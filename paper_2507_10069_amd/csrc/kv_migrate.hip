@@ -10,13 +10,17 @@
 // word at offset i of the n-byte page, sum(d) and sum(k * d[k]) (v_dot4_u32_u8 with constants), from which
 //   A = 1 + sum over the page of d            B = n + sum over the page of (n - position) * d,  both mod 65521.
 //
-// A large move (STREAM) goes past the caches, loads and stores with the non-temporal hint: neither side is read again
-// here, and lines that wait to be written back hold up the reads.  8 requests of 18432 tokens (302 MB each way, pack +
-// unpack) 239 -> 219 us = 5.5 TB/s read + write, where the runtime's own copy of 2 GiB reaches 4.9; loads alone 203 of 227, stores
-// alone 220.  What the last-level cache holds is left there, where the transport or the next kernel finds it: the line is drawn
-// where pages and staging together pass its 256 MiB (a staging buffer unpacked after it was packed: 134 MB of pages, 268 MB
-// in all, 94 us and 99 with the hint; 302 in all 114 and 110; 134 in all 42 and 49; 67 in all 23 and 25.  Pages and buffers
-// that nobody had touched before: 108 and 100, 121 and 111, 50 and 51, 31 and 28).
+// What goes past the caches (the non-temporal hint), so that it neither displaces what is needed nor waits in them to be written
+// back while reads queue behind it: unpack's loads, which are the last use of the staging buffer; unpack's stores, unless the move is
+// small enough for the next kernel to find the pages in the last-level cache; pack's loads of a large move.  Pack's stores do not: the
+// transport, or the unpack on the same GPU, reads the staging buffer next.  Measured, pack and unpack one after the other, MB of K and V pages:
+// us with nothing streamed / everything (the rule above 128 MB before) / this:
+//   32: 27.9 / 27.5 / 23.4   48: 42.8 / 38.6 / 32.9   64: 50.1 / 50.7 / 43.7   96: 80.4 / 75.6 / 66.5   128: 107.8 / 99.2 / 85.1
+//   192: 159.6 / 147.2 / 124.9   256: 211.7 / 196.7 / 166.5   302 (8 requests of 18432 tokens): 237 / 219 / 188 = 6.4 TB/s read + write   604: 469 / 439 / 421
+// (The same on buffers never moved before, 302 MB 221 / 194; but 223 / 232 where the buffers themselves have just been filled and the
+// last-level cache is full of lines to be written back.)
+// The lines lie where the sides cross: pack's loads streamed or not 45.4 and 43.7 at 64 MB, 66.5 and 66.7 at 96; unpack's stores 23.8 and
+// 23.4 at 32 MB, 32.9 and 35.8 at 48.
 #include "emm_internal.h"
 
 #include <type_traits>
@@ -27,7 +31,7 @@ namespace {
 
 constexpr int THREADS = 256;
 constexpr unsigned ADLER_MOD = 65521;
-constexpr long long STREAM_BYTES = 256ll << 20;
+constexpr long long STREAM_LOADS = 80ll << 20, STREAM_STORES = 40ll << 20;           // of K and V pages
 
 // wave sum of a 64-bit value
 __device__ inline unsigned long long wave_sum_u64(unsigned long long x)
@@ -55,7 +59,7 @@ __device__ inline void store16(unsigned char* p, u32x4 w)
 }
 
 // UNPACK = false: pools -> staging; true: staging -> pools.  page_bytes: one page of ONE pool.
-template <bool UNPACK, bool STREAM>
+template <bool UNPACK, bool LOADS, bool STORES>
 __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __restrict__ k_cache,
                                                            unsigned char* __restrict__ v_cache,
                                                            unsigned char* __restrict__ staging,
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __rest
             const long long off = off0 + (long long)u * THREADS * 16;
             if (off < n) {
                 const unsigned char* pool = off < page_bytes ? kp + off : vp + (off - page_bytes);
-                w[u] = load16<STREAM>(UNPACK ? sp + off : pool);
+                w[u] = load16<LOADS>(UNPACK ? sp + off : pool);
             }
         }
 #pragma unroll
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(THREADS) void kv_pages_kernel(unsigned char* __rest
             const long long off = off0 + (long long)u * THREADS * 16;
             if (off < n) {
                 unsigned char* pool = off < page_bytes ? kp + off : vp + (off - page_bytes);
-                store16<STREAM>(UNPACK ? pool : sp + off, w[u]);
+                store16<STORES>(UNPACK ? pool : sp + off, w[u]);
                 const unsigned words[4] = {w[u][0], w[u][1], w[u][2], w[u][3]};
                 unsigned s_all = 0;                                       // of the 16 bytes: at most 4080
 #pragma unroll
@@ -132,16 +136,18 @@ hipError_t launch_kv_pages(bool unpack, void* k_cache, void* v_cache, void* stag
                            uint32_t* mismatches, hipStream_t stream)
 {
     if (n == 0) return hipSuccess;
-    auto go = [&](auto unpack_c, auto stream_c) {
-        hipLaunchKernelGGL((kv_pages_kernel<decltype(unpack_c)::value, decltype(stream_c)::value>), dim3((unsigned)n), dim3(THREADS), 0, stream,
-                           (unsigned char*)k_cache, (unsigned char*)v_cache, (unsigned char*)staging, page_ids, num_pages, page_bytes,
-                           checksums, expected, mismatches);
+    auto go = [&](auto unpack_c, auto loads_c, auto stores_c) {
+        hipLaunchKernelGGL((kv_pages_kernel<decltype(unpack_c)::value, decltype(loads_c)::value, decltype(stores_c)::value>), dim3((unsigned)n),
+                           dim3(THREADS), 0, stream, (unsigned char*)k_cache, (unsigned char*)v_cache, (unsigned char*)staging, page_ids,
+                           num_pages, page_bytes, checksums, expected, mismatches);
     };
-    const bool streamed = 4 * page_bytes * n > STREAM_BYTES;            // K and V pages and their staging
-    if (unpack && streamed) go(std::true_type{}, std::true_type{});
-    else if (unpack) go(std::true_type{}, std::false_type{});
-    else if (streamed) go(std::false_type{}, std::true_type{});
-    else go(std::false_type{}, std::false_type{});
+    const std::true_type streamed;
+    const std::false_type cached;
+    const long long bytes = 2 * page_bytes * n;
+    if (unpack && bytes > STREAM_STORES) go(std::true_type{}, streamed, streamed);
+    else if (unpack) go(std::true_type{}, streamed, cached);
+    else if (bytes > STREAM_LOADS) go(std::false_type{}, streamed, cached);
+    else go(std::false_type{}, cached, cached);
     return hipGetLastError();
 }
 

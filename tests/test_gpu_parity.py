@@ -864,6 +864,12 @@ def test_kv_page_migration_past_the_caches(n, page_bytes):
         assert zlib.adler32(staging[p].cpu().numpy().tobytes()) == int(sums[p]) & 0xffffffff
 
 
+@pytest.mark.parametrize("n,page_bytes", [(1280, 16384), (1281, 16384), (2560, 16384), (2561, 16384), (40, 1 << 19), (41, 1 << 19), (81, 1 << 19)])
+def test_kv_page_migration_at_the_lines_of_the_hints(n, page_bytes):
+    """Either side of the sizes from which unpack's stores (40 MiB of K and V pages) and pack's loads (80 MiB) go past the caches."""
+    test_kv_page_migration_past_the_caches(n, page_bytes)
+
+
 # workgroups of 16 rows on either side of where they get fewer waves: tables of under 512 keys at 320, 1024, 2048 workgroups (one row
 # tile each) and 4096 (several), longer ones at 512; tables of one, two and four chunks of 16 keys
 @pytest.mark.parametrize("reqs,H,Hkv,d,new,longest", [(37, 8, 8, 64, 1, 143), (38, 8, 8, 128, 1, 143), (40, 8, 8, 64, 1, 143), (121, 8, 8, 128, 1, 143),
