@@ -465,6 +465,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     int blk_early = (threadIdx.x & 63) * 4 + (threadIdx.x >> 7), pg_early = 0;
     auto ask_pages = [&]() { pg_early = pt[min(blk_early >> b.page_shift, b.max_pages - 1)]; };
     const bool from_start = plan.part == 0;
+    __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0): the plan's loads are behind us, said so that no wait for them is put behind this one
     if (from_start) ask_pages();
     // (the arguments needed further down are asked for here: the compiler would where they are first used, a round trip each)
     asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out));
