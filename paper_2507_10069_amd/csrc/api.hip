@@ -92,7 +92,7 @@ emm_status check_decode_shared(const emm_batch* b, const emm::BatchView& v, cons
 emm_status attention(const emm_batch* b, const void* q, const void* k_cache, const void* v_cache, void* out,
                      float* lse, void* workspace, size_t workspace_bytes, void* hip_stream, int causal,
                      const emm_shared_prefix* sp = nullptr, const void* k_new = nullptr, const void* v_new = nullptr,
-                     bool fused = false, bool static_scratch = false)
+                     bool fused = false, bool static_scratch = false, bool own_pages = false)
 {
     emm_status st = check_scalars(b);
     if (st != EMM_OK) return st;
@@ -152,6 +152,7 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     args.workspace = need > 0 ? workspace : nullptr;
     args.k_new = k_new;
     args.v_new = v_new;
+    args.own_pages = own_pages ? 1 : 0;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t err;
     if (static_scratch) err = emm::launch_attn_bf16_decode_static(args, shape, stream);
@@ -418,7 +419,7 @@ extern "C" emm_status emm_prefill_attn_shared(const emm_batch* groups, const emm
     //    members packed into common row tiles
     if (groups->num_reqs > 0) {
         st = attention(groups, q, k_cache, v_cache, ws + w.out_shared, reinterpret_cast<float*>(ws + w.lse_shared), inner,
-                       w.inner_bytes, hip_stream, 0);
+                       w.inner_bytes, hip_stream, 0, nullptr, nullptr, nullptr, false, false, true);
         if (st != EMM_OK) return st;
     }
     // 2. every request over its own keys (what its page table holds behind the shared part), causal

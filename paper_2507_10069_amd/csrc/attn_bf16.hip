@@ -437,7 +437,7 @@ typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
 template <bool CAUSAL>
 __device__ void attend_unit_carefully(unsigned long long kernargs, int xcd, int in_xcd, lds_bytes lds);
 
-template <bool CAUSAL, bool CAREFUL>
+template <bool CAUSAL, bool CAREFUL, bool STREAM>
 __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, const int xcd, const int in_xcd, UnitPlan plan,
                                    unsigned char* smem)
 {
@@ -584,15 +584,19 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     auto slab_of = [&](int kt) -> long long {                // byte offset of this wave's block of tile kt
         return (long long)__builtin_amdgcn_readlane(pg_vec, kt - pg_base) * 4096;
     };
+    auto to_lds = [&](const unsigned char* src, int goff, uint32_t to) {
+        if constexpr (STREAM) lds_dma16_streamed(src, goff, to);
+        else lds_dma16(src, goff, to);
+    };
     auto load_k = [&](int kt, int kbuf) {
         const unsigned char* src = kcb + slab_of(kt);
-        lds_dma16(src, k_goff0, smem_base + kbuf * KV_BYTES + ld_lds);
-        lds_dma16(src, k_goff1, smem_base + kbuf * KV_BYTES + ld_lds + 1024);
+        to_lds(src, k_goff0, smem_base + kbuf * KV_BYTES + ld_lds);
+        to_lds(src, k_goff1, smem_base + kbuf * KV_BYTES + ld_lds + 1024);
     };
     auto load_v = [&](int kt, int vbuf) {
         const unsigned char* src = vcb + slab_of(kt);
-        lds_dma16(src, v_goff0, smem_base + V_SM + vbuf * KV_BYTES + ld_lds);
-        lds_dma16(src, v_goff1, smem_base + V_SM + vbuf * KV_BYTES + ld_lds + 1024);
+        to_lds(src, v_goff0, smem_base + V_SM + vbuf * KV_BYTES + ld_lds);
+        to_lds(src, v_goff1, smem_base + V_SM + vbuf * KV_BYTES + ld_lds + 1024);
     };
     // after this wave's loads of V tile kt have landed: zero the rows (keys) it fetched that lie past
     // the request's tokens.  Only the request's last tile can have such rows.
@@ -1131,10 +1135,10 @@ __device__ __attribute__((noinline)) void attend_unit_carefully(unsigned long lo
     const LaunchShape& L = ka->L;
     const UnitPlan plan = plan_unit(a.b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
-    attend_unit<CAUSAL, true>(a, L, xcd, in_xcd, plan, (unsigned char*)lds);
+    attend_unit<CAUSAL, true, false>(a, L, xcd, in_xcd, plan, (unsigned char*)lds);
 }
 
-template <bool CAUSAL>
+template <bool CAUSAL, bool STREAM>
 __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * KV_BYTES];   // K ring, then V ring
@@ -1146,7 +1150,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
     const int xcd = blockIdx.x % NUM_XCD, in_xcd = blockIdx.x / NUM_XCD;
     const UnitPlan plan = plan_unit(b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
-    attend_unit<CAUSAL, false>(a, L, xcd, in_xcd, plan, smem);
+    attend_unit<CAUSAL, false, STREAM>(a, L, xcd, in_xcd, plan, smem);
 }
 
 // One workgroup's share of the merge of a unit planned for PARTS pieces and cut into `cut` of them: the columns (threads of
@@ -1416,6 +1420,20 @@ void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool 
     }
 }
 
+// K and V that are read once, and more of them than the last-level cache keeps until the next call, are fetched past the caches, so that
+// they do not displace each other: every request has one row tile at most, which one workgroup does or its pieces do (enough pairs that
+// none is halved by rows on two XCDs), and the caller knows that the page tables are as narrow as the contexts and that few pages, if
+// any, are in two of them -- the groups' pass of a shared prefill.  64 questions of 4 tokens on 8 videos of 16384 (268 MB): 95.9 -> 86.5 us,
+// the groups' pass alone 76 -> 67; where the 8 groups hold two videos between them, which the caches could keep, 83.7 after 87.5.
+static bool read_once(const AttnArgs& a, const LaunchShape& L)
+{
+    constexpr long long STREAM_BYTES = 96ll << 20;
+    const BatchView& b = a.b;
+    const long long pairs = (long long)b.num_reqs * b.num_kv_heads;
+    return a.own_pages != 0 && pairs >= 2 * NUM_XCD && (long long)b.max_new_len * L.G <= BR &&
+           pairs * b.max_pages * b.page_size * (4 * D) > STREAM_BYTES;
+}
+
 hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream)
 {
     const BatchView& b = a.b;
@@ -1428,9 +1446,11 @@ hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream)
     const long long grid = NUM_XCD * per_xcd;
     if (grid > 0x3fffffff) return hipErrorInvalidValue;
     if (a.causal)
-        hipLaunchKernelGGL(attn_bf16_d128_kernel<true>, dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
+        hipLaunchKernelGGL((attn_bf16_d128_kernel<true, false>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
+    else if (read_once(a, L))
+        hipLaunchKernelGGL((attn_bf16_d128_kernel<false, true>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
     else
-        hipLaunchKernelGGL(attn_bf16_d128_kernel<false>, dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
+        hipLaunchKernelGGL((attn_bf16_d128_kernel<false, false>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || L.ws_pieces == 0) return err;              // nothing can have been cut along the keys
     hipLaunchKernelGGL(attn_bf16_merge_kernel, dim3(NUM_XCD * MERGE_PER_XCD), dim3(NTHREADS), 0, stream, a, L);

@@ -216,3 +216,20 @@ def test_error_codes():
     assert lib.emm_prefill_attn_shared(*args, B._ptr(ps["workspace"]), need, None) == B.EMM_OK
     torch.cuda.synchronize()
     _compare(wl, dw)
+
+
+# either side of the 96 MiB of shared K and V from which the groups' pass fetches past the caches (16 groups x 4 KV heads x 512 B a token: 3072
+# tokens); groups of unequal rows; in the last two a key whose scores overflow, so that its unit is done again by the careful pass
+@pytest.mark.parametrize("shared,new,planted", [(3008, 2, False), (3200, 2, False), (3200, 5, False), (3200, 2, True), (3008, 2, True)])
+def test_groups_large_enough_to_stream(shared, new, planted):
+    print("case streamed groups", shared, new, planted, flush=True)
+    reqs = 32
+    wl = _case([shared + 16 * (r % 3) for r in range(reqs)], [max(1, new - r % 2) for r in range(reqs)], [r // 2 for r in range(reqs)],
+               [shared] * reqs)
+    if planted:
+        wl.q[:] = W.to_bf16_bits(np.full(wl.q.shape, 4.0, np.float32))
+        _plant_key(wl, 0, 1700, 4.0)                         # (the group's pages: both members see it)
+        _plant_key(wl, 12, shared - 1, 4.0)
+    dw, plan = _run_shared(wl)
+    assert plan["num_groups"] == reqs // 2
+    print("   errors (max, mean, lse):", _compare(wl, dw, _sample_tokens(wl, 16, seed=shared)), flush=True)
