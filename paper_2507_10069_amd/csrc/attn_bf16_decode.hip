@@ -594,7 +594,7 @@ constexpr int LOADS = 8;                                     // pieces of a wave
 inline bool many_pieces(const DecodeShape& S) { return S.pieces_max + (S.n_unit_pairs > 0 ? S.pieces_unit : 0) > MANY_PIECES; }
 
 template <bool CAUSAL, bool SHARED, int WAVES, bool AHEAD>
-__global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv)
+__global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, Divisor by_piece)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     __shared__ f32x2 acc_s[WAVES][D / 2], ml_s[WAVES];
@@ -606,40 +606,57 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
     const float* __restrict__ rec_own = (const float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G + row) * REC_FLOATS;
 
     // pieces j0 + wave, j0 + wave + WAVES, ... of a list of records, `stride` floats apart, that holds `room` of them
-    f32x2 val[LOADS], ml[LOADS];
-    auto ask = [&](const float* __restrict__ rec, size_t stride, int j0, int room) {
+    struct Asked {
+        f32x2 val[LOADS], ml[LOADS];
+    } own, of_unit;
+    auto ask = [&](Asked& to, const float* __restrict__ rec, size_t stride, int j0, int room) {
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
             const float* __restrict__ src = rec + (size_t)min(j0 + wave + u * WAVES, room - 1) * stride;
-            val[u] = *(const f32x2*)(src + 2 * lane);
-            ml[u] = *(const f32x2*)(src + D);
+            to.val[u] = *(const f32x2*)(src + 2 * lane);
+            to.ml[u] = *(const f32x2*)(src + D);
         }
     };
     const int n_new = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
     const int req_unit = SHARED ? sv.req_unit[r] : -1, req_shared = SHARED ? sv.req_shared_len[r] : 0;
     if (AHEAD) {
-        ask(rec_own, MAX_G * REC_FLOATS, 0, S.pieces_max);
+        ask(own, rec_own, MAX_G * REC_FLOATS, 0, S.pieces_max);
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("" ::"s"(n_new), "s"(cu_new));          // needed at the end only, but asked for here
+        // needed further down only, but asked for here
+        asm volatile("" ::"s"(n_new), "s"(cu_new), "s"(by_piece.mul), "s"(a.out), "s"(a.lse));
+        if (SHARED) asm volatile("" ::"s"(sv.unit_shared_len), "s"(sv.unit_first_req), "s"(sv.num_units));
     }
 
     const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
     // the records of this row: n_own from the request's own workgroups, then n_unit from its unit's
     // (counts and positions forced into what the workspace holds, whatever the device arrays say)
     const int unit = SHARED ? min(max(req_unit, -1), sv.num_units - 1) : -1;
-    const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(req_shared, 0) / BK : 0, S.tiles_per_piece, unit >= 0),
+    const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(req_shared, 0) / BK : 0, by_piece, unit >= 0),
                           S.pieces_max);
     const bool nothing = n_new <= 0 || (unit < 0 && n_own == 1);          // no query token, or finished by the main kernel
     // (with the loads on their way left only where the result would be stored: a branch here would have them wait behind it)
     if (!AHEAD) {
         if (nothing) return;
-        ask(rec_own, MAX_G * REC_FLOATS, 0, max(n_own, 1));
+        ask(own, rec_own, MAX_G * REC_FLOATS, 0, max(n_own, 1));
+    }
+    // the unit's first records too, before the first use of any
+    int n_unit = 0;
+    const float* __restrict__ rec_unit = rec_own;
+    if (SHARED && unit >= 0) {
+        const int unit_len = sv.unit_shared_len[unit], unit_first = sv.unit_first_req[unit];
+        const int shared_len = (int)min((long long)max(unit_len, 0), (long long)b.max_pages * b.page_size) / BK * BK;
+        n_unit = shared_len > 0 ? min(up_to_pieces(shared_len / BK, by_piece), S.pieces_unit) : 0;
+        const int member = min(max(r - unit_first, 0), MAX_ROWS / G - 1);                  // position of the request in its unit
+        rec_unit = (const float*)a.workspace + unit_records_offset(S) +
+                   ((size_t)(unit * b.num_kv_heads + kvh) * S.pieces_unit * MAX_ROWS + member * G + row) * REC_FLOATS;
+        if (n_unit > 0) ask(of_unit, rec_unit, MAX_ROWS * REC_FLOATS, 0, S.pieces_unit);
     }
 
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
     float m = -INFINITY, l = 0.f;                            // of this wave's pieces (every piece has a visible key)
     f32x2 acc = {0.f, 0.f};
-    auto add = [&](int j0, int n) {                          // the pieces asked for, those below n
+    auto add = [&](Asked& from, int j0, int n) {             // the pieces asked for, those below n
+        f32x2 (&val)[LOADS] = from.val, (&ml)[LOADS] = from.ml;
         float m_new = m;
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
@@ -660,20 +677,16 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
             acc[1] += wgt * (in ? val[u][1] : 0.f);
         }
     };
-    add(0, n_own);
+    add(own, 0, n_own);
     for (int j0 = LOADS * WAVES; j0 < n_own; j0 += LOADS * WAVES) {
-        ask(rec_own, MAX_G * REC_FLOATS, j0, S.pieces_max);
-        add(j0, n_own);
+        ask(own, rec_own, MAX_G * REC_FLOATS, j0, S.pieces_max);
+        add(own, j0, n_own);
     }
-    if (SHARED && unit >= 0) {
-        const int shared_len = (int)min((long long)max(sv.unit_shared_len[unit], 0), (long long)b.max_pages * b.page_size) / BK * BK;
-        const int n_unit = min((shared_len / BK + S.tiles_per_piece - 1) / S.tiles_per_piece, S.pieces_unit);
-        const int member = min(max(r - sv.unit_first_req[unit], 0), MAX_ROWS / G - 1);       // position of the request in its unit
-        const float* __restrict__ rec_unit = (const float*)a.workspace + unit_records_offset(S) +
-                   ((size_t)(unit * b.num_kv_heads + kvh) * S.pieces_unit * MAX_ROWS + member * G + row) * REC_FLOATS;
-        for (int j0 = 0; j0 < n_unit; j0 += LOADS * WAVES) {
-            ask(rec_unit, MAX_ROWS * REC_FLOATS, j0, S.pieces_unit);
-            add(j0, n_unit);
+    if (SHARED && n_unit > 0) {
+        add(of_unit, 0, n_unit);
+        for (int j0 = LOADS * WAVES; j0 < n_unit; j0 += LOADS * WAVES) {
+            ask(of_unit, rec_unit, MAX_ROWS * REC_FLOATS, j0, S.pieces_unit);
+            add(of_unit, j0, n_unit);
         }
     }
     acc_s[wave][lane] = acc;
@@ -940,7 +953,7 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
     const dim3 mgrid((unsigned)b.num_reqs, (unsigned)b.num_kv_heads, (unsigned)(b.num_q_heads / b.num_kv_heads));
     auto merge = [&](auto causal, auto waves, auto ahead) {
         hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<decltype(causal)::value, SHARED, decltype(waves)::value, decltype(ahead)::value>), mgrid,
-                           dim3(64 * decltype(waves)::value), 0, stream, a, S, sv);
+                           dim3(64 * decltype(waves)::value), 0, stream, a, S, sv, info.by_piece);
     };
     auto merge_of = [&](auto causal) {
         using few = std::integral_constant<int, FEW_WAVES>;
