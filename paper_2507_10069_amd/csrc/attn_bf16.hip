@@ -1420,14 +1420,17 @@ void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool 
     }
 }
 
-// K and V that are read once, and more of them than the last-level cache keeps until the next call, are fetched past the caches, so that
+// K and V that are read once, and more of them than the last-level cache keeps for the next call on the same data, are fetched past the caches, so that
 // they do not displace each other: every request has one row tile at most, which one workgroup does or its pieces do (enough pairs that
 // none is halved by rows on two XCDs), and the caller knows that the page tables are as narrow as the contexts and that few pages, if
 // any, are in two of them -- the groups' pass of a shared prefill.  64 questions of 4 tokens on 8 videos of 16384 (268 MB): 95.9 -> 86.5 us,
 // the groups' pass alone 76 -> 67; where the 8 groups hold two videos between them, which the caches could keep, 83.7 after 87.5.
+// The line lies where a call repeated on the same data loses nothing either (groups of 4, MB of K and V: us repeated, and with three batches
+// in turn; before / streamed): 134: 46.5 / 54.2, 61.5 / 57.8; 201: 56.5 / 56.5, 69.0 / 57.5; 268: 84.8 / 78.8, 88.2 / 81.4; 536: 134.7 /
+// 120.5, 137.4 / 120.9.  (Groups of 8: 167: 67.0 / 74.7, 80.0 / 77.0; 201: 76.3 / 75.6, 83.0 / 75.6.)
 static bool read_once(const AttnArgs& a, const LaunchShape& L)
 {
-    constexpr long long STREAM_BYTES = 96ll << 20;
+    constexpr long long STREAM_BYTES = 176ll << 20;
     const BatchView& b = a.b;
     const long long pairs = (long long)b.num_reqs * b.num_kv_heads;
     return a.own_pages != 0 && pairs >= 2 * NUM_XCD && (long long)b.max_new_len * L.G <= BR &&

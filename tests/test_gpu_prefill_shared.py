@@ -218,9 +218,9 @@ def test_error_codes():
     _compare(wl, dw)
 
 
-# either side of the 96 MiB of shared K and V from which the groups' pass fetches past the caches (16 groups x 4 KV heads x 512 B a token: 3072
+# either side of the 176 MiB of shared K and V from which the groups' pass fetches past the caches (16 groups x 4 KV heads x 512 B a token: 5632
 # tokens); groups of unequal rows; in the last two a key whose scores overflow, so that its unit is done again by the careful pass
-@pytest.mark.parametrize("shared,new,planted", [(3008, 2, False), (3200, 2, False), (3200, 5, False), (3200, 2, True), (3008, 2, True)])
+@pytest.mark.parametrize("shared,new,planted", [(5568, 2, False), (5760, 2, False), (5760, 5, False), (5760, 2, True), (5568, 2, True)])
 def test_groups_large_enough_to_stream(shared, new, planted):
     print("case streamed groups", shared, new, planted, flush=True)
     reqs = 32
