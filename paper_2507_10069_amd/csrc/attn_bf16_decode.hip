@@ -6,7 +6,7 @@
 // exactly once, so the work is cut along the KEY axis, first into pieces of `tiles_per_piece` 32-key
 // tiles (one workgroup each), then, inside a workgroup, block by block of 16 keys over its 4 waves.
 //
-//   workgroup = one piece of one pair, 4 waves, 64 KB of LDS, two on a compute unit (or 8, 128 KB, one).  Wave w takes blocks w, w+4, ... of
+//   workgroup = one piece of one pair, 4 waves, 64 KB of LDS, two on a compute unit.  Wave w takes blocks w, w+4, ... of
 //               the piece and does everything for them by itself: it fetches them by LDS-DMA into a ring of its
 //               own (two blocks of K and V: one is computed while the other is on its way), waits for its own
 //               fetches only, and keeps its own online softmax.  There is no barrier before the end.  (With
@@ -53,11 +53,8 @@ using namespace bf16attn;
 constexpr int MAX_G = 16;                        // query heads per KV head this kernel takes
 constexpr int REC_FLOATS = D + 2;                // per row of a record: 128 accumulator values, m, l (folded: the rows' values, then their m, l)
 constexpr int RED_FLOATS = D + 4;                // per row in LDS: 128 accumulator values, m, l, and the next row 16 bytes aligned
-// Waves per workgroup.  Eight, and all of a compute unit's LDS, where a piece is no more than a block for each and a compute unit has one
-// piece anyway: a wave's two blocks in turn become one (32 / 8 heads, one context of 1500 tokens 7.2 -> 6.8 us, two of 2000 7.9 -> 7.3).  With
-// longer pieces eight are slower than four (one of 6000 10.2 and 9.8, 16 of 1000 on 28 / 4 heads 10.8 and 10.3).
-constexpr int FEW = 4, MANY = 8;
-constexpr int MANY_TILES = 4;                    // of a piece: 8 blocks
+constexpr int NW = 4;                            // waves per workgroup
+constexpr int NT = NW * 64;
 constexpr int BK = 32;                           // keys per tile, the unit in which pieces are measured
 constexpr int BLK = 16;                          // keys per block, what a wave fetches and computes at a time (a page holds 1 to 16)
 constexpr int BLOCKS_PER_TILE = BK / BLK;
@@ -69,7 +66,7 @@ constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 25
 constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see attn_bf16_decode_shape
 constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
 static_assert(MAX_G * RED_FLOATS * 4 <= RING_BYTES, "the merge across waves reuses the rings");
-static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= FEW * 64, "a wave's page ids sit in one register");
+static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
 
 // What a launch adds to its arguments: the ticket of a folded merge (0: none) and quotients that every workgroup would have to work out
 // (with every argument asked for at the start a call is 0.3 us shorter than with divisions).
@@ -106,25 +103,10 @@ __device__ inline float quad_sum(float x)
     const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
-// max or sum over the 16 lanes of a row of lanes, in every one of them
-template <int CTRL> __device__ inline float from_lane(float x)
+// what the lane N places further on holds, of the 16 of a row of lanes, which go round
+template <int N> __device__ inline float from_lane(float x)
 {
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, false));
-}
-constexpr int ROR1 = 0x121, ROR2 = 0x122, ROR4 = 0x124, ROR8 = 0x128;       // rotate within a row of 16
-__device__ inline float max_of_16(float x)
-{
-    x = fmaxf(x, from_lane<ROR8>(x));
-    x = fmaxf(x, from_lane<ROR4>(x));
-    x = fmaxf(x, from_lane<ROR2>(x));
-    return fmaxf(x, from_lane<ROR1>(x));
-}
-__device__ inline float sum_of_16(float x)
-{
-    x += from_lane<ROR8>(x);
-    x += from_lane<ROR4>(x);
-    x += from_lane<ROR2>(x);
-    return x + from_lane<ROR1>(x);
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + 16 - N, 0xf, 0xf, false));
 }
 // workspace: the requests' own records first, [pair][piece][MAX_G rows], then the units', [unit][KV head][piece][MAX_ROWS]
 __device__ __host__ inline size_t unit_records_offset(const DecodeShape& S)
@@ -171,6 +153,9 @@ __device__ inline void wait_fetches()
     asm volatile("s_waitcnt vmcnt(%0)" ::"i"(PENDING) : "memory");
 }
 
+// waves of the merge kernel by the pieces of a context (see there)
+constexpr int MANY_PIECES = 32, MANY_WAVES = 16, FEW_WAVES = 4;
+
 // ---- Folded merge: where a context has few pieces (fold_applies), the last of its workgroups to finish combines them and the second
 // kernel is not launched.  Nobody waits for anybody: a workgroup stores its record, counts itself in and leaves unless it is the one that
 // completes the count.  Records and counts are stored, counted and read with agent scope (past what the XCDs do not share), a wave's
@@ -196,11 +181,19 @@ __device__ inline f32x2_rec get_record(const float* at)
     return __builtin_bit_cast(f32x2_rec, __hip_atomic_load((const unsigned long long*)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-template <bool CAUSAL, bool SHARED, bool FUSED, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, LaunchInfo info)
+// A piece's two channels, weighted, in either merge.  What is fused is written out, so that both round alike: left to the compiler it is this
+// in the one and both channels in the other.
+__device__ inline void add_weighted(f32x2_rec& acc, float wgt, f32x2_rec x)
+{
+#pragma clang fp contract(off)
+    acc[0] = fmaf(wgt, x[0], acc[0]);
+    acc[1] += wgt * x[1];
+}
+
+template <bool CAUSAL, bool SHARED, bool FUSED>
+__global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, LaunchInfo info)
 {
     static_assert(CAUSAL || !FUSED, "only a causal step has a new token to store");
-    constexpr int NT = 64 * NW;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * RING_BYTES];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -531,49 +524,67 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_decode_kernel(AttnArgs a
     if (*(volatile int*)smem == 0) return;
     const float* rec0 = (const float*)a.workspace + (size_t)pair * S.pieces_max * MAX_G * REC_FLOATS;
     // 8 rows at a time: a wave takes ROWS of them, a lane two channels of each; the weights are made with a lane for each record,
-    // of the first row in lanes 0 .. 15, of the second in 16 .. 31
-    constexpr int ROWS = 8 / NW;
-    static_assert(ROWS * FOLD_PIECES <= 64, "a lane for every weight");
+    // of the first row in lanes 0 .. 15, of the second in 16 .. 31.  The sums are those of attn_bf16_decode_merge_kernel term by
+    // term, its FEW_WAVES partial ones of every fourth piece first: a context's result does not tell which of the two merged it.
+    constexpr int ROWS = 2, PARTS = FEW_WAVES;
+    static_assert(ROWS * FOLD_PIECES <= 64 && PARTS == 4, "a lane for every weight; the rotations by which partial sums are made");
     for (int row0 = wave; row0 < G; row0 += ROWS * NW) {
         const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(row0 + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
         const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
         f32x2 val[ROWS][FOLD_PIECES];
 #pragma unroll
-        for (int u0 = 0; u0 < FOLD_PIECES; u0 += 4)
+        for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
             if (u0 < n)
 #pragma unroll
-                for (int u = u0; u < u0 + 4; ++u)
+                for (int u = u0; u < u0 + PARTS; ++u)
 #pragma unroll
                     for (int h = 0; h < ROWS; ++h)
                         val[h][u] = get_record(rec0 + min(u, n - 1) * (MAX_G * REC_FLOATS) + min(row0 + h * NW, G - 1) * D + 2 * lane);
-        const float m = u_lane < n ? ml[0] : -INFINITY;
-        const float m_all = max_of_16(m);
-        const float wgt = u_lane < n ? __builtin_amdgcn_exp2f((m - (m_all == -INFINITY ? 0.f : m_all)) * c_log2) : 0.f;
-        const float l_tot = sum_of_16(u_lane < n ? wgt * ml[1] : 0.f);
-        f32x2 acc[ROWS] = {};
+        const float m = u_lane < n ? ml[0] : -INFINITY, l = u_lane < n ? ml[1] : 0.f;
+        float m_part = fmaxf(m, from_lane<4>(m));            // of the pieces that leave the same remainder by 4
+        m_part = fmaxf(m_part, from_lane<8>(m_part));
+        const float wgt = __builtin_amdgcn_exp2f((m - (m_part == -INFINITY ? 0.f : m_part)) * c_log2);
+        float l_part = wgt * l;                              // lanes 0 .. 3 of the row: from the first piece to the last
+        l_part = fmaf(from_lane<4>(wgt), from_lane<4>(l), l_part);
+        l_part = fmaf(from_lane<8>(wgt), from_lane<8>(l), l_part);
+        l_part = fmaf(from_lane<12>(wgt), from_lane<12>(l), l_part);
+        float m_all = fmaxf(m_part, from_lane<1>(m_part));
+        m_all = fmaxf(m_all, from_lane<2>(m_all));
+        const float w_part = m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_part - m_all) * c_log2);
+        float l_tot = w_part * l_part;                       // lane 0 of the row
+        l_tot = fmaf(from_lane<1>(w_part), from_lane<1>(l_part), l_tot);
+        l_tot = fmaf(from_lane<2>(w_part), from_lane<2>(l_part), l_tot);
+        l_tot = fmaf(from_lane<3>(w_part), from_lane<3>(l_part), l_tot);
+        f32x2 part[ROWS][PARTS] = {};
 #pragma unroll
-        for (int u0 = 0; u0 < FOLD_PIECES; u0 += 4)
+        for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
             if (u0 < n)
 #pragma unroll
-                for (int u = u0; u < u0 + 4; ++u)
+                for (int w = 0; w < PARTS; ++w)
 #pragma unroll
                     for (int h = 0; h < ROWS; ++h) {         // (past the last record its value again: 0, lest it be infinite)
-                        const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u + FOLD_PIECES * h));
-                        acc[h][0] += w_u * (u < n ? val[h][u][0] : 0.f);
-                        acc[h][1] += w_u * (u < n ? val[h][u][1] : 0.f);
+                        const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u0 + w + FOLD_PIECES * h));
+                        add_weighted(part[h][w], w_u, u0 + w < n ? val[h][u0 + w] : f32x2{0.f, 0.f});
                     }
 #pragma unroll
         for (int h = 0; h < ROWS; ++h) {
             const int row = row0 + NW * h;
             if (row >= G) break;
-            const float l = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
+            f32x2 acc = {0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < PARTS; ++w) {
+                const float w_w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_part), w + FOLD_PIECES * h));
+                acc[0] = fmaf(w_w, part[h][w][0], acc[0]);
+                acc[1] = fmaf(w_w, part[h][w][1], acc[1]);
+            }
+            const float l_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
             const float m_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_all), FOLD_PIECES * h));
             const long long at_out = first_row * b.num_q_heads + kvh * G + row;
             bf16x2 o;
-            o[0] = (__bf16)(l > 0.f ? acc[h][0] / l : 0.f);
-            o[1] = (__bf16)(l > 0.f ? acc[h][1] / l : 0.f);
+            o[0] = (__bf16)(l_row > 0.f ? acc[0] / l_row : 0.f);
+            o[1] = (__bf16)(l_row > 0.f ? acc[1] / l_row : 0.f);
             *(bf16x2*)((__bf16*)a.out + at_out * D + 2 * lane) = o;
-            if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l > 0.f) ? m_row * b.softmax_scale + logf(l) : -INFINITY;
+            if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l_row > 0.f) ? m_row * b.softmax_scale + logf(l_row) : -INFINITY;
         }
     }
 }
@@ -589,7 +600,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_decode_kernel(AttnArgs a
 // for them all costs more than the round trip: see AHEAD_BYTES.  The lengths come first then.
 // 16 waves when a row has many pieces (a single long context), 4 when it has few (a big batch, where 1024-thread
 // workgroups would only crowd the chip).
-constexpr int MANY_PIECES = 32, MANY_WAVES = 16, FEW_WAVES = 4;
 constexpr int LOADS = 8;                                     // pieces of a wave in flight at a time
 inline bool many_pieces(const DecodeShape& S) { return S.pieces_max + (S.n_unit_pairs > 0 ? S.pieces_unit : 0) > MANY_PIECES; }
 
@@ -673,8 +683,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
             const bool in = j0 + wave + u * WAVES < n;       // what is no piece may hold anything, infinities and NaN included
             const float wgt = __builtin_amdgcn_exp2f((ml[u][0] - ref) * c_log2);
             l += wgt * (in ? ml[u][1] : 0.f);
-            acc[0] += wgt * (in ? val[u][0] : 0.f);
-            acc[1] += wgt * (in ? val[u][1] : 0.f);
+            add_weighted(acc, wgt, in ? val[u] : f32x2{0.f, 0.f});
         }
     };
     add(own, 0, n_own);
@@ -939,15 +948,10 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
     const LaunchInfo info = {fold_applies(b, S) ? next_ticket() : 0, b.num_q_heads / b.num_kv_heads, (int32_t)dims.y, divisor_of(b.num_kv_heads), divisor_of(S.tiles_per_piece),
                              SHARED ? divisor_of(S.n_pairs) : Divisor{}, SHARED ? divisor_of(std::max(S.n_unit_pairs, 1)) : Divisor{}};
     if (!a.causal && FUSED) return hipErrorInvalidValue;
-    auto attend = [&](auto waves) {
-        constexpr int NW = decltype(waves)::value;
-        if (a.causal)
-            hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED, NW>), dims, dim3(64 * NW), 0, stream, a, S, sv, info);
-        else if constexpr (!FUSED)
-            hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false, NW>), dims, dim3(64 * NW), 0, stream, a, S, sv, info);
-    };
-    if (!SHARED && S.tiles_per_piece <= MANY_TILES && grid <= WORKGROUPS_PER_ROUND / 2) attend(std::integral_constant<int, SHARED ? FEW : MANY>{});
-    else attend(std::integral_constant<int, FEW>{});
+    if (a.causal)
+        hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED>), dims, dim3(NT), 0, stream, a, S, sv, info);
+    else if constexpr (!FUSED)
+        hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false>), dims, dim3(NT), 0, stream, a, S, sv, info);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || info.ticket != 0 || (!SHARED && S.pieces_max == 1)) return err;    // merged, or one piece each: already written
     const dim3 mgrid((unsigned)b.num_reqs, (unsigned)b.num_kv_heads, (unsigned)(b.num_q_heads / b.num_kv_heads));

@@ -587,6 +587,51 @@ def test_decode_merge_by_the_last_workgroup(H, Hkv, ctx, new):
         check(replay)
 
 
+# G query heads per KV head beside the 16 whose pieces the second kernel always merges; 3, 4, 9, 16 pieces (17: the second kernel for both),
+# a batch of contexts of fewer pieces than the longest
+@pytest.mark.parametrize("Hkv,ctx", [(1, [300]), (2, [500]), (1, [1100]), (2, [1999]), (1, [2050]), (2, [1500, 40, 0, 700, 130])])
+def test_decode_rows_do_not_tell_which_kernel_merged_them(Hkv, ctx):
+    """A query row's result has the same bits whether the last workgroup or the second kernel combines its pieces."""
+    print("case rows of either merge", Hkv, ctx, flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+
+    def run(G, like=None):
+        wl = W.build_workload("either_merge", "causal", "bf16", 767, num_q_heads=G * Hkv, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                              prefix_lens=ctx, new_lens=[1] * len(ctx))
+        if like is not None:
+            wl.page_table, wl.k_cache, wl.v_cache, wl.k_new, wl.v_new = like.page_table, like.k_cache, like.v_cache, like.k_new, like.v_new
+            wl.q = np.ascontiguousarray(like.q.reshape(len(ctx), Hkv, 16, 128)[:, :, :G]).reshape(len(ctx), Hkv * G, 128)
+        dw = _gpu_run(wl)
+        return wl, bits(dw.out).reshape(len(ctx), Hkv, G, 128), dw.lse.cpu().numpy().reshape(len(ctx), Hkv, G)
+
+    like, out, lse = run(16)
+    for G in (1, 4, 5, 8, 15):
+        _, out_g, lse_g = run(G, like)
+        assert out_g.tobytes() == np.ascontiguousarray(out[:, :, :G]).tobytes(), G
+        assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
+
+
+def test_decode_of_short_contexts_does_not_depend_on_the_batch():
+    """Contexts of one piece, which is cut among a workgroup's waves in one way only: alone and in a batch of more workgroups than compute units."""
+    print("case short contexts alone and together", flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+    ctx = [127, 112, 95, 80, 64, 63, 40, 17, 15, 0] * 4
+    wl = W.build_workload("alone", "causal", "bf16", 768, num_q_heads=32, num_kv_heads=8, head_dim=128, page_size=16,
+                          prefix_lens=ctx, new_lens=[1] * len(ctx))
+    dw = _gpu_run(wl)
+    _compare(wl, dw)
+    out, lse = bits(dw.out), dw.lse.cpu().numpy()
+    for r in range(len(ctx)):
+        one = dict(num_q_heads=32, num_kv_heads=8, head_dim=128, page_size=16, num_pages=wl.num_pages, max_pages_per_req=wl.max_pages_per_req,
+                   dtype="bf16", softmax_scale=wl.softmax_scale)
+        batch = B.make_batch(num_reqs=1, total_new_tokens=1, max_new_len=1, page_table=dw.page_table[r:r + 1], prefix_lens=dw.prefix_lens[r:r + 1],
+                             new_lens=dw.new_lens[r:r + 1], cu_new_lens=torch.tensor([0, 1], dtype=torch.int32, device="cuda"), **one)
+        alone, alone_lse = torch.zeros_like(dw.out[:1]), torch.zeros_like(dw.lse[:1])
+        B.emm_decode_attn(batch, dw.q[r:r + 1], dw.k_cache, dw.v_cache, alone, alone_lse, dw.workspace)
+        torch.cuda.synchronize()
+        assert bits(alone).tobytes() == out[r:r + 1].tobytes() and alone_lse.cpu().numpy().tobytes() == lse[r:r + 1].tobytes(), r
+
+
 def test_decode_merge_of_an_infinite_value():
     """An infinity in V makes its channel infinite and no other, in whichever piece its key lies; of two pieces the last workgroup's
     merge reads the second one in the places of the third and fourth too."""
