@@ -160,12 +160,12 @@ constexpr int MANY_PIECES = 32, MANY_WAVES = 16, FEW_WAVES = 4;
 // kernel is not launched.  Nobody waits for anybody: a workgroup stores its record, counts itself in and leaves unless it is the one that
 // completes the count.  Records and counts are stored, counted and read with agent scope (past what the XCDs do not share), a wave's
 // stores are awaited before its workgroup counts, and pieces are combined in their order, so the result does not depend on who is last.
-// The count of a (request, KV head) lies in the last row of its first record, which G < MAX_G query heads leave unused, and needs no
+// The count of a (request, KV head) lies in the last row of its first record, which FOLD_ROWS query heads leave unused, and needs no
 // zero to start from: it is the launch's ticket (48 bits that no other launch of this process has) above the number of workgroups.
 // Each workgroup asks for it with the lengths and, unless the ticket is there, puts it there before its first fetch; whoever completes
 // the count takes the ticket away, so that a replay of a captured launch starts again.  Every workgroup that the grid has for a context
 // counts, whatever the device arrays hold, so the count is completed in every launch.
-constexpr int FOLD_PIECES = 16, FOLD_COUNT_BITS = 16;
+constexpr int FOLD_PIECES = 16, FOLD_ROWS = 8, FOLD_COUNT_BITS = 16;
 __device__ inline unsigned long long* fold_count(const AttnArgs& a, const DecodeShape& S, int pair)
 {
     return (unsigned long long*)((float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G) * REC_FLOATS + (MAX_G - 1) * D);
@@ -534,69 +534,66 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     __syncthreads();
     if (*(volatile int*)smem == 0) return;
     const float* rec0 = (const float*)a.workspace + (size_t)pair * S.pieces_max * MAX_G * REC_FLOATS;
-    // 8 rows at a time: a wave takes ROWS of them, a lane two channels of each; the weights are made with a lane for each record,
+    // A wave takes up to ROWS of the rows, a lane two channels of each; the weights are made with a lane for each record,
     // of the first row in lanes 0 .. 15, of the second in 16 .. 31.  The sums are those of attn_bf16_decode_merge_kernel term by
     // term, its FEW_WAVES partial ones of every fourth piece first: a context's result does not tell which of the two merged it.
-    constexpr int ROWS = 2, PARTS = FEW_WAVES;
+    constexpr int ROWS = FOLD_ROWS / NW, PARTS = FEW_WAVES;
     static_assert(ROWS * FOLD_PIECES <= 64 && PARTS == 4, "a lane for every weight; the rotations by which partial sums are made");
-    for (int row0 = wave; row0 < G; row0 += ROWS * NW) {
-        const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(row0 + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
-        const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
-        f32x2 val[ROWS][FOLD_PIECES];
+    if (wave >= G) return;
+    const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(wave + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
+    const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
+    f32x2 val[ROWS][FOLD_PIECES];
+#pragma unroll
+    for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
+        if (u0 < n)
+#pragma unroll
+            for (int h = 0; h < ROWS; ++h)
+                if (wave + h * NW < G)
+#pragma unroll
+                    for (int u = u0; u < u0 + PARTS; ++u)
+                        val[h][u] = get_record(rec0 + min(u, n - 1) * (MAX_G * REC_FLOATS) + (wave + h * NW) * D + 2 * lane);
+    const float m = u_lane < n ? ml[0] : -INFINITY, l = u_lane < n ? ml[1] : 0.f;
+    float m_part = fmaxf(m, from_lane<4>(m));                // of the pieces that leave the same remainder by 4
+    m_part = fmaxf(m_part, from_lane<8>(m_part));
+    const float wgt = __builtin_amdgcn_exp2f((m - (m_part == -INFINITY ? 0.f : m_part)) * c_log2);
+    float l_part = wgt * l;                                  // lanes 0 .. 3 of the row: from the first piece to the last
+    l_part = fmaf(from_lane<4>(wgt), from_lane<4>(l), l_part);
+    l_part = fmaf(from_lane<8>(wgt), from_lane<8>(l), l_part);
+    l_part = fmaf(from_lane<12>(wgt), from_lane<12>(l), l_part);
+    float m_all = fmaxf(m_part, from_lane<1>(m_part));
+    m_all = fmaxf(m_all, from_lane<2>(m_all));
+    const float w_part = m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_part - m_all) * c_log2);
+    float l_tot = w_part * l_part;                           // lane 0 of the row
+    l_tot = fmaf(from_lane<1>(w_part), from_lane<1>(l_part), l_tot);
+    l_tot = fmaf(from_lane<2>(w_part), from_lane<2>(l_part), l_tot);
+    l_tot = fmaf(from_lane<3>(w_part), from_lane<3>(l_part), l_tot);
+#pragma unroll
+    for (int h = 0; h < ROWS; ++h) {
+        const int row = wave + NW * h;
+        if (row >= G) break;
+        f32x2 part[PARTS] = {}, acc = {0.f, 0.f};
 #pragma unroll
         for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
             if (u0 < n)
 #pragma unroll
-                for (int u = u0; u < u0 + PARTS; ++u)
+                for (int w = 0; w < PARTS; ++w) {            // (past the last record its value again: 0, lest it be infinite)
+                    const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u0 + w + FOLD_PIECES * h));
+                    add_weighted(part[w], w_u, u0 + w < n ? val[h][u0 + w] : f32x2{0.f, 0.f});
+                }
 #pragma unroll
-                    for (int h = 0; h < ROWS; ++h)
-                        val[h][u] = get_record(rec0 + min(u, n - 1) * (MAX_G * REC_FLOATS) + min(row0 + h * NW, G - 1) * D + 2 * lane);
-        const float m = u_lane < n ? ml[0] : -INFINITY, l = u_lane < n ? ml[1] : 0.f;
-        float m_part = fmaxf(m, from_lane<4>(m));            // of the pieces that leave the same remainder by 4
-        m_part = fmaxf(m_part, from_lane<8>(m_part));
-        const float wgt = __builtin_amdgcn_exp2f((m - (m_part == -INFINITY ? 0.f : m_part)) * c_log2);
-        float l_part = wgt * l;                              // lanes 0 .. 3 of the row: from the first piece to the last
-        l_part = fmaf(from_lane<4>(wgt), from_lane<4>(l), l_part);
-        l_part = fmaf(from_lane<8>(wgt), from_lane<8>(l), l_part);
-        l_part = fmaf(from_lane<12>(wgt), from_lane<12>(l), l_part);
-        float m_all = fmaxf(m_part, from_lane<1>(m_part));
-        m_all = fmaxf(m_all, from_lane<2>(m_all));
-        const float w_part = m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_part - m_all) * c_log2);
-        float l_tot = w_part * l_part;                       // lane 0 of the row
-        l_tot = fmaf(from_lane<1>(w_part), from_lane<1>(l_part), l_tot);
-        l_tot = fmaf(from_lane<2>(w_part), from_lane<2>(l_part), l_tot);
-        l_tot = fmaf(from_lane<3>(w_part), from_lane<3>(l_part), l_tot);
-        f32x2 part[ROWS][PARTS] = {};
-#pragma unroll
-        for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
-            if (u0 < n)
-#pragma unroll
-                for (int w = 0; w < PARTS; ++w)
-#pragma unroll
-                    for (int h = 0; h < ROWS; ++h) {         // (past the last record its value again: 0, lest it be infinite)
-                        const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u0 + w + FOLD_PIECES * h));
-                        add_weighted(part[h][w], w_u, u0 + w < n ? val[h][u0 + w] : f32x2{0.f, 0.f});
-                    }
-#pragma unroll
-        for (int h = 0; h < ROWS; ++h) {
-            const int row = row0 + NW * h;
-            if (row >= G) break;
-            f32x2 acc = {0.f, 0.f};
-#pragma unroll
-            for (int w = 0; w < PARTS; ++w) {
-                const float w_w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_part), w + FOLD_PIECES * h));
-                acc[0] = fmaf(w_w, part[h][w][0], acc[0]);
-                acc[1] = fmaf(w_w, part[h][w][1], acc[1]);
-            }
-            const float l_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
-            const float m_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_all), FOLD_PIECES * h));
-            const long long at_out = first_row * b.num_q_heads + kvh * G + row;
-            bf16x2 o;
-            o[0] = (__bf16)(l_row > 0.f ? acc[0] / l_row : 0.f);
-            o[1] = (__bf16)(l_row > 0.f ? acc[1] / l_row : 0.f);
-            *(bf16x2*)((__bf16*)a.out + at_out * D + 2 * lane) = o;
-            if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l_row > 0.f) ? m_row * b.softmax_scale + logf(l_row) : -INFINITY;
+        for (int w = 0; w < PARTS; ++w) {
+            const float w_w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_part), w + FOLD_PIECES * h));
+            acc[0] = fmaf(w_w, part[w][0], acc[0]);
+            acc[1] = fmaf(w_w, part[w][1], acc[1]);
         }
+        const float l_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
+        const float m_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_all), FOLD_PIECES * h));
+        const long long at_out = first_row * b.num_q_heads + kvh * G + row;
+        bf16x2 o;
+        o[0] = (__bf16)(l_row > 0.f ? acc[0] / l_row : 0.f);
+        o[1] = (__bf16)(l_row > 0.f ? acc[1] / l_row : 0.f);
+        *(bf16x2*)((__bf16*)a.out + at_out * D + 2 * lane) = o;
+        if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l_row > 0.f) ? m_row * b.softmax_scale + logf(l_row) : -INFINITY;
     }
 }
 
@@ -914,18 +911,24 @@ size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView
 
 namespace {
 
-// Folded where the batch fits the chip at once (grid of at most 512) and its pieces are short, so that the second launch is a good part
-// of the call: up to 8 pieces of 16 tiles, or 16 of FOLD_SHORT.  Of these the GPU needs the same time or less (28 / 4 heads, us, two
-// kernels and one: 32 contexts of 1000 tokens 17.0 and 15.5, 16 of 500 8.6 and 7.6, one of 1500 7.2 and 7.2), and the host a
-// launch less, which is what bounds the smallest (one of 1500, a call after the other: 9.0 and 7.1).  Not folded: more than 512
-// workgroups (32 of 2000 to 8000, 32 / 8 heads: 119.6 and 121.2) and 16 longer pieces (4 of 1500 to 6000: 13.4 and 13.9), where the round
-// trips of whoever comes last end the call.
-constexpr int FOLD_SHORT = 6;
+// Folded where the batch fits the chip at once (grid of at most 512), its pieces are short, so that the second launch is a good part
+// of the call, and what the last workgroup has to read is little: it reads all records of its context, through one compute unit, while
+// the second kernel has a workgroup for each row.  us of the GPU for two kernels and one:
+//   4 pieces    28 / 4 heads, one context of 500 tokens 6.7 and 6.6, 16 of 500 9.0 and 8.6, 32 / 8 heads, 4 of 500 7.0 and 6.5
+//   8           32 / 8 heads, 4 of 1500 9.4 and 9.0
+//   12          28 / 4, one of 1500 6.7 and 7.2, 4 7.9 and 8.2; 32 / 8, one 6.6 and 6.8; 8 / 8, one 6.4 and 6.4
+//   16          28 / 4, one of 2000 6.8 and 7.5, 4 8.7 and 9.3; 32 / 8, one 6.7 and 7.0, 2 of 2000 8.6 and 8.7
+//   15 heads on 1: 3 pieces 6.9 and 7.8, 16 7.2 and 9.9
+// The host is a launch quicker, and it bounds such calls where they are not replayed from a graph (28 / 4, one of 1500, a call after the
+// other: 8.7 and 7.3), so the line lies where one launch takes the GPU half a microsecond more.  Not folded: more than 512
+// workgroups (32 of 2000 to 8000, 32 / 8 heads: 119.6 and 121.2) and more than 8 longer pieces (4 of 1500 to 6000: 13.4 and 13.9).
+constexpr int FOLD_SHORT = 6, FOLD_READS = 24;               // pieces x rows of a wave
 bool fold_applies(const BatchView& b, const DecodeShape& S)
 {
-    const int most = S.tiles_per_piece <= FOLD_SHORT ? FOLD_PIECES : S.tiles_per_piece <= 16 ? FOLD_PIECES / 2 : 0;
+    const int G = b.num_q_heads / b.num_kv_heads;
+    const int most = S.tiles_per_piece <= FOLD_SHORT ? std::min(FOLD_PIECES, FOLD_READS / ((G + NW - 1) / NW)) : S.tiles_per_piece <= 16 ? FOLD_PIECES / 2 : 0;
     return S.n_unit_pairs == 0 && S.pieces_max > 1 && S.pieces_max <= most && (long long)S.n_pairs * S.pieces_max <= WORKGROUPS_PER_ROUND &&
-           b.num_q_heads / b.num_kv_heads < MAX_G;
+           G <= FOLD_ROWS;
 }
 
 // 48 bits that no other launch of this process has, above FOLD_COUNT_BITS bits of count.  They start from a number that is another in

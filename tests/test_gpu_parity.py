@@ -534,8 +534,8 @@ def test_decode_merge_piece_counts(kind, H, Hkv, ctx):
     _compare(wl, dw)
 
 
-# Batches whose last workgroup merges: 1, 2, 3, 5, 16 pieces (17: the second kernel), of 4 tiles and more, 1 to 15 of a record's 16 rows
-# (16: the second kernel), grids of 256 and 512 workgroups, contexts of fewer pieces than the longest, requests without a token
+# Batches whose last workgroup merges: 1, 2, 3, 5, 16 pieces (17: the second kernel), of 4 tiles and more, 1 to 8 of a record's 16 rows
+# (15 and 16: the second kernel), grids of 256 and 512 workgroups, contexts of fewer pieces than the longest, requests without a token
 @pytest.mark.parametrize("H,Hkv,ctx,new", [(28, 4, [127], [1]), (28, 4, [128], [1]), (8, 1, [300], [1]), (15, 1, [600], [1]), (16, 1, [600], [1]),
                                            (4, 1, [2047], [1]), (4, 1, [2048], [1]), (3, 3, [1500, 40, 0, 700], [1, 0, 1, 1]), (28, 4, [500] * 16, [1] * 16),
                                            (28, 4, [1000, 900, 10] * 10 + [1000, 129], [1] * 32), (32, 8, [1999, 2000], [1, 1])])
@@ -587,9 +587,9 @@ def test_decode_merge_by_the_last_workgroup(H, Hkv, ctx, new):
         check(replay)
 
 
-# G query heads per KV head beside the 16 whose pieces the second kernel always merges; 3, 4, 9, 16 pieces (17: the second kernel for both),
-# a batch of contexts of fewer pieces than the longest
-@pytest.mark.parametrize("Hkv,ctx", [(1, [300]), (2, [500]), (1, [1100]), (2, [1999]), (1, [2050]), (2, [1500, 40, 0, 700, 130])])
+# G query heads per KV head beside the 16 whose pieces the second kernel always merges; 3, 4, 9, 12, 13, 16 pieces (more than 8 rows or, with
+# 5 and more, than 12 pieces, and 17 pieces: the second kernel for both), a batch of contexts of fewer pieces than the longest
+@pytest.mark.parametrize("Hkv,ctx", [(1, [300]), (2, [500]), (1, [1100]), (1, [1530]), (1, [1600]), (2, [1999]), (1, [2050]), (2, [1500, 40, 0, 700, 130])])
 def test_decode_rows_do_not_tell_which_kernel_merged_them(Hkv, ctx):
     """A query row's result has the same bits whether the last workgroup or the second kernel combines its pieces."""
     print("case rows of either merge", Hkv, ctx, flush=True)
@@ -605,7 +605,7 @@ def test_decode_rows_do_not_tell_which_kernel_merged_them(Hkv, ctx):
         return wl, bits(dw.out).reshape(len(ctx), Hkv, G, 128), dw.lse.cpu().numpy().reshape(len(ctx), Hkv, G)
 
     like, out, lse = run(16)
-    for G in (1, 4, 5, 8, 15):
+    for G in (1, 4, 5, 8, 9, 15):
         _, out_g, lse_g = run(G, like)
         assert out_g.tobytes() == np.ascontiguousarray(out[:, :, :G]).tobytes(), G
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
