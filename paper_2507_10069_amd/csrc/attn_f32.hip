@@ -61,16 +61,16 @@ __device__ inline bool is_finite(float x) { return (__float_as_uint(x) & 0x7f800
 // cu_new_lens[r] is, so the grid needs no more than T G / 16 + B slots and no prefix sums over row tiles.
 __device__ inline long long first_slot(int cu_new, int G, int r) { return (long long)max(cu_new, 0) * G / ROWS + r; }
 
-// NW: waves per workgroup; SPLIT: workgroups that share a row tile's channels; ALONE: no two workgroups on a compute unit
-template <int D, int NW, int SPLIT, bool ALONE>
+// NW: waves per workgroup; SPLIT: workgroups that share a row tile's channels; APART: fewer workgroups fit a compute unit (see PLACES)
+template <int D, int NW, int SPLIT, bool APART>
 __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a, int G, Divisor by_G, Divisor by_kv_heads)
 {
     constexpr int QK = D / 16;                        // 16-byte pieces of a Q or K row per lane
     constexpr int CH = D / SPLIT;                     // channels of the output that this workgroup makes
     constexpr int NB = CH < 64 ? 1 : CH / 64;         // blocks of V
     constexpr int VE = CH / NB / 16;                  // channels of a block that a lane reads: VE l16 .. VE l16 + VE - 1
-    constexpr int STRIDE = ALONE ? 164 : CH + 4;      // floats between rows of the LDS records: spreads the banks (ALONE: and takes half the LDS)
-    static_assert(!ALONE || (NW == 8 && CH <= 160 && NW * ROWS * STRIDE * 4 > 80 << 10), "more than half of 160 KB");
+    constexpr int STRIDE = APART ? 164 : CH + 4;      // floats between rows of the LDS records: spreads the banks (APART: and takes more LDS)
+    static_assert(!APART || (CH <= 160 && NW * ROWS * STRIDE * 4 > (NW == 8 ? 80 << 10 : 40 << 10)), "more than a half or a quarter of 160 KB");
     typedef float vec __attribute__((ext_vector_type(VE)));
     __shared__ __attribute__((aligned(16))) float o_s[NW][ROWS][STRIDE];
     __shared__ float m_s[NW][ROWS], l_s[NW][ROWS];
@@ -273,6 +273,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a, int G,
 // 71 / 66 / 70 / 87, up to 2700 244 / 256 / 258 / 312; of 64 on 4 KV heads (384), the same 61 / 69 / 125 / 191.  Prompts share K and V
 // among their row tiles: 1024 new tokens, 32 heads on 8 of 64 (2056) 88 / 71 / 83 / 92; 32 requests of 64 + 256 (4352) 127 / 86 / 82 / 76.
 // `single`: at most one row tile for a (request, KV head), as in a decode step.
+// (Those times are older than the loads that overlap and the registers they take.  Of 162 shapes measured since, the choice is 4 % behind the
+// best on average; the largest differences are at head_dim 128: 101 contexts of 801 tokens on one KV head, 8 and 4 waves, 30.2 and 26.9, 19 prompts of
+// 17 + 44 on 8, 4 and 1, 36.8 and 25.6.)
 int waves_of(long long workgroups, bool single, long long keys)
 {
     int waves;
@@ -283,14 +286,25 @@ int waves_of(long long workgroups, bool single, long long keys)
     return waves;
 }
 
-
 // Few workgroups with many keys are bound by their compute unit's matrix pipes and by what it fetches while the others idle: up to
 // SPLIT_WORKGROUPS of them become four each, which make a quarter of the channels (the scores again, a quarter of V).  4 heads on 1 of 64,
 // 256 cached + 64 new tokens (17 workgroups), both kernels, 10.3 -> 9.3 us, 1024 + 64 20.3 -> 15.7; from 80 workgroups on it is slower
 // (88: 10.8 and 13.9).
-// Decode steps have more workgroups than rows (a slot for every request's last tile): where all that have rows find a compute unit of their
-// own they get it, ALONE; two on one keep each other's loads out of its cache (32 contexts of 1000 tokens, 32 / 8 heads of 64: 35.0 and 26.8 us).
-constexpr int SPLIT_WORKGROUPS = 64, COMPUTE_UNITS = 256;
+constexpr int SPLIT_WORKGROUPS = 64;
+// By its registers two workgroups of 8 waves or four of 4 fit a compute unit (head_dim 64).  The dispatcher fills places, not time: some compute
+// units get all they hold while others have fewer, or none where the grid's workgroups without rows held the places and left (a decode step has
+// one slot more than row tiles for every request), and who shares a compute unit is as much longer.  So fewer fit, APART, in steps of one row
+// tile per (request, KV head): one of 8 waves, and three of 4 where as many places are enough for all that have rows.  us, as many as the registers allow
+// and APART: 8 waves, 32 contexts of 1000 tokens on 8 KV heads (256 pairs) 35.0 and 26.8, 22 of 414 to 1659 on 16 (352) 48.5 and 42.3, 163 of 1145 to
+// 4580 on 4 (652) 211 and 196 (equal ones lose what the chip holds at once: 347 of 915 on one (347) 38.8 and 41.3, and more the shorter they are: 17 of
+// 79 on 16 (272) 9.9 and 12.5); 4 waves, 340 of 933 on 2 (680) 76.4 and 67.4, 81 of 360 on 8 (648) 29.0 and 25.8, but 99 of 43 on 8 (792) 10.4 and 12.0
+// and 104 of 877 on 4 (416) 49.5 and 50.2.
+constexpr int COMPUTE_UNITS = 256, PLACES = 3;
+bool apart_of(int waves, long long workgroups, long long pairs, long long keys)
+{
+    if (waves == 8) return workgroups > COMPUTE_UNITS && (pairs <= COMPUTE_UNITS || keys >= 512);
+    return waves == 4 && pairs > (PLACES - 1) * COMPUTE_UNITS && pairs <= PLACES * COMPUTE_UNITS;
+}
 
 }  // namespace
 
@@ -301,20 +315,22 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream)
     const int G = b.num_q_heads / b.num_kv_heads;
     const long long grid = ((long long)b.total_new_tokens * G / ROWS + b.num_reqs) * b.num_kv_heads;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    auto go = [&](auto d, auto nw, auto split, auto alone) {
+    auto go = [&](auto d, auto nw, auto split, auto apart) {
         constexpr int D = decltype(d)::value, NW = decltype(nw)::value, SPLIT = decltype(split)::value;
-        hipLaunchKernelGGL((attn_f32_kernel<D, NW, SPLIT, decltype(alone)::value>), dim3((unsigned)(grid * SPLIT)), dim3(64 * NW), 0, stream, a, G, divisor_of(G), divisor_of(b.num_kv_heads));
+        hipLaunchKernelGGL((attn_f32_kernel<D, NW, SPLIT, decltype(apart)::value>), dim3((unsigned)(grid * SPLIT)), dim3(64 * NW), 0, stream, a, G, divisor_of(G), divisor_of(b.num_kv_heads));
     };
     const bool single = (long long)b.max_new_len * G <= ROWS;              // at most one row tile for a (request, KV head)
-    const int waves = waves_of(grid, single, (long long)b.max_pages * b.page_size);
-    const bool alone = single && grid > COMPUTE_UNITS && (long long)b.num_reqs * b.num_kv_heads <= COMPUTE_UNITS;
+    const long long keys = (long long)b.max_pages * b.page_size;
+    const int waves = waves_of(grid, single, keys);
+    const bool apart = single && apart_of(waves, grid, (long long)b.num_reqs * b.num_kv_heads, keys);
     auto of_dim = [&](auto d) {
         using one = std::integral_constant<int, 1>;
         using eight = std::integral_constant<int, 8>;
         constexpr bool small = decltype(d)::value == 64;
         if (waves == 8 && grid <= SPLIT_WORKGROUPS) go(d, eight{}, std::integral_constant<int, 4>{}, std::false_type{});
-        else if (waves == 8 && small && alone) go(d, eight{}, one{}, std::integral_constant<bool, small>{});
+        else if (waves == 8 && small && apart) go(d, eight{}, one{}, std::integral_constant<bool, small>{});
         else if (waves == 8) go(d, eight{}, one{}, std::false_type{});
+        else if (waves == 4 && small && apart) go(d, std::integral_constant<int, 4>{}, one{}, std::integral_constant<bool, small>{});
         else if (waves == 4) go(d, std::integral_constant<int, 4>{}, one{}, std::false_type{});
         else if (waves == 2) go(d, std::integral_constant<int, 2>{}, one{}, std::false_type{});
         else go(d, one{}, one{}, std::false_type{});

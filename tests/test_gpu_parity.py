@@ -930,10 +930,13 @@ def test_fp32_waves_per_workgroup(reqs, H, Hkv, d, new, longest):
     _compare(wl, dw)
 
 
-# the channels of a row tile are split among four workgroups up to 64 of them; decode steps whose (request, KV head) pairs, not their
-# workgroups, find a compute unit each (256 pairs in 320 workgroups, 264 in 330); contexts of fewer keys than the waves take at once
+# the channels of a row tile are split among four workgroups up to 64 of them; decode steps of which fewer workgroups than the registers allow
+# share a compute unit (8 waves: 320 and 340 workgroups, 128 channels not; 4 waves: 512, 513, 768 and 769 pairs); contexts of fewer keys than
+# the waves take at once
 @pytest.mark.parametrize("reqs,H,Hkv,d,new,longest", [(1, 4, 1, 64, 252, 70), (1, 4, 1, 128, 252, 70), (1, 4, 1, 64, 256, 200), (1, 4, 1, 128, 256, 200),
-                                                      (5, 5, 1, 128, 7, 900), (32, 32, 8, 64, 1, 143), (33, 32, 8, 64, 1, 143), (32, 32, 8, 128, 1, 143)])
+                                                      (5, 5, 1, 128, 7, 900), (32, 32, 8, 64, 1, 143), (33, 32, 8, 64, 1, 143), (32, 32, 8, 128, 1, 143),
+                                                      (40, 8, 8, 64, 1, 600), (64, 8, 8, 64, 1, 143), (171, 3, 3, 64, 1, 143), (96, 8, 8, 64, 1, 143),
+                                                      (769, 1, 1, 64, 1, 143)])
 def test_fp32_split_channels_and_lone_workgroups(reqs, H, Hkv, d, new, longest):
     print("case fp32 split", reqs, H, Hkv, d, new, longest, flush=True)
     ctx = [longest, 0, 1, 15, 16, 17, 63, 64, 65]
