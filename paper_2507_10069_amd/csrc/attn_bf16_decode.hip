@@ -264,7 +264,8 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         n_rows = min(max(sv.unit_num_reqs[unit], 1) * G, MAX_ROWS);
         direct = false;
     }
-    if (piece >= n_pieces) return;
+    // (a grid of several z may have workgroups past the last piece that the workspace has room for)
+    if (piece >= (SHARED ? n_pieces : min(n_pieces, S.pieces_max))) return;
     if (S.late) ask_pages();
     const bool folded = FOLD && !direct;                     // see FOLD_PIECES
     unsigned long long* const count = fold_count(a, S, pair);

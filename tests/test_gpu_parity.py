@@ -632,6 +632,40 @@ def test_decode_of_short_contexts_does_not_depend_on_the_batch():
         assert bits(alone).tobytes() == out[r:r + 1].tobytes() and alone_lse.cpu().numpy().tobytes() == lse[r:r + 1].tobytes(), r
 
 
+@pytest.mark.parametrize("too_short", [False, True])
+def test_decode_grid_of_more_pieces_than_one_dimension_holds(too_short):
+    """One context of 130 million keys, 32770 pieces of 124 tiles, in 2 x 16385 workgroups.  Its page table names one page throughout, so the
+    result is that page's.  With a bound that is one piece too short the workspace holds 32769 records, and nothing is stored behind them."""
+    print("case pieces in two grid dimensions", too_short, flush=True)
+    H, page, piece, pieces = 4, 256, 124 * 32, 32770
+    keys = pieces * piece
+    width = keys // page
+    assert width * page == keys
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((1, H, 128), (8, 1, page, 128), (8, 1, page, 128)))
+    out, lse = torch.zeros_like(q), torch.zeros((1, H), device="cuda")
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    batch = B.make_batch(num_reqs=1, num_q_heads=H, num_kv_heads=1, head_dim=128, page_size=page, num_pages=8, max_pages_per_req=width,
+                         total_new_tokens=1, max_new_len=1, dtype="bf16", softmax_scale=128 ** -0.5,
+                         page_table=torch.full((1, width), 3, dtype=torch.int32, device="cuda"), prefix_lens=ints(keys), new_lens=ints(1),
+                         cu_new_lens=ints(0, 1))
+    shared = B.make_shared_prefix(0, max_own_tiles=(pieces - too_short) * 124)
+    need = B.emm_decode_attn_shared_workspace_size(batch, shared)
+    assert need == (pieces - too_short) * 8320
+    guard = 2 * 8320
+    workspace = torch.full((need + guard,), 0x5a, dtype=torch.uint8, device="cuda")
+    B.emm_cross_attn_shared(batch, shared, q, k, v, out, lse, workspace[:need])
+    torch.cuda.synchronize()
+    assert (workspace[need:] == 0x5a).all(), "stored behind the records"
+    if too_short:
+        return
+    scores = (q[0].double() @ k[3, 0].double().t()) * 128 ** -0.5
+    want, want_lse = torch.softmax(scores, 1) @ v[3, 0].double(), torch.logsumexp(scores, 1) + np.log(width)
+    assert (out[0].double() - want).abs().max() <= BF16_MAX_ABS
+    assert (lse[0].double() - want_lse).abs().max() <= LSE_ABS
+
+
 def test_decode_merge_of_an_infinite_value():
     """An infinity in V makes its channel infinite and no other, in whichever piece its key lies; of two pieces the last workgroup's
     merge reads the second one in the places of the third and fourth too."""
