@@ -4,6 +4,8 @@ Bars: the KV scatter is bit-exact over the whole pool; bf16 attention outputs ar
 and mean-abs 2e-3 of the oracle (bf16 inputs, fp32 accumulation); the fp32 configuration is held to
 max-abs 1e-4.  Every workload is compared element by element, the three large ones at full size too (the
 oracle takes 15 to 30 s for each); a quick variant compares them on sampled query tokens."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -574,16 +576,22 @@ def test_decode_merge_by_the_last_workgroup(H, Hkv, ctx, new):
         torch.cuda.synchronize()
         with torch.cuda.graph(graph, stream=side):
             dw.decode_step()
-    dw.out.zero_()
     lens = dw.prefix_lens.clone()
-    for replay in range(4):
-        dw.prefix_lens.copy_(lens // (replay + 1))           # other contexts, other piece counts, the same captured launch
+
+    def replay_with(new_lens):
+        """The same captured launch on other contexts, whose new rows go into other slots of pools that hold none yet."""
+        for tensor, source in ((dw.k_cache, wl.k_cache), (dw.v_cache, wl.v_cache)):
+            tensor.copy_(torch.from_numpy(source.view(np.int16)).view(torch.bfloat16))
+        dw.prefix_lens.copy_(new_lens)
+        dw.out.zero_()
+        dw.lse.zero_()
         graph.replay()
         torch.cuda.synchronize()
-        dw.prefix_lens.copy_(lens)
-        for tensor, source in ((dw.k_cache, wl.k_cache), (dw.v_cache, wl.v_cache)):
-            tensor.copy_(torch.from_numpy(source.view(np.int16)).view(torch.bfloat16))       # the shorter contexts' new rows went into other slots
-        graph.replay()
+    for replay in range(4):
+        short = dataclasses.replace(wl, prefix_lens=wl.prefix_lens // (replay + 1))      # 0: as captured; then other piece counts
+        replay_with(lens // (replay + 1))
+        _compare(short, dw)
+        replay_with(lens)
         check(replay)
 
 
