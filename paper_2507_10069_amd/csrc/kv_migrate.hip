@@ -10,17 +10,22 @@
 // word at offset i of the n-byte page, sum(d) and sum(k * d[k]) (v_dot4_u32_u8 with constants), from which
 //   A = 1 + sum over the page of d            B = n + sum over the page of (n - position) * d,  both mod 65521.
 //
-// What goes past the caches (the non-temporal hint), so that it neither displaces what is needed nor waits in them to be written
-// back while reads queue behind it: unpack's loads, which are the last use of the staging buffer; unpack's stores, unless the move is
-// small enough for the next kernel to find the pages in the last-level cache; pack's loads of a large move.  Pack's stores do not: the
-// transport, or the unpack on the same GPU, reads the staging buffer next.  Measured, pack and unpack one after the other, MB of K and V pages:
-// us with nothing streamed / everything (the rule above 128 MB before) / this:
-//   32: 27.9 / 27.5 / 23.4   48: 42.8 / 38.6 / 32.9   64: 50.1 / 50.7 / 43.7   96: 80.4 / 75.6 / 66.5   128: 107.8 / 99.2 / 85.1
-//   192: 159.6 / 147.2 / 124.9   256: 211.7 / 196.7 / 166.5   302 (8 requests of 18432 tokens): 237 / 219 / 188 = 6.4 TB/s read + write   604: 469 / 439 / 421
-// (The same on buffers never moved before, 302 MB 221 / 194; but 223 / 232 where the buffers themselves have just been filled and the
-// last-level cache is full of lines to be written back.)
-// The lines lie where the sides cross: pack's loads streamed or not 45.4 and 43.7 at 64 MB, 66.5 and 66.7 at 96; unpack's stores 23.8 and
-// 23.4 at 32 MB, 32.9 and 35.8 at 48.
+// What goes past the caches (the non-temporal hint): unpack's loads, which are the last use of the staging buffer; unpack's stores, unless the
+// move is small enough for the next kernel to find the pages in the last-level cache; pack's loads of a large move.  Pack's stores do not.
+// What a hint gains depends on what the caches hold; us on one GPU, MB of K and V pages, nothing streamed / everything / this:
+//   pack, caches full of what was read last        67: 26.6 / 27.6 / 26.6   101: 36.8 / 39.6 / 37.0   302: 99.7 / 107.0 / 91.4   604: 211 / 208 / 185
+//   pack of pages just written                     101: 33.7 / 33.4 / 34.0   302: 112.6 / 105.7 / 94.3   604: 243 / 216 / 211
+//   unpack of a buffer just received, otherwise the same   67: 24.3 / 24.4 / 24.6   101: 34.2 / 33.9 / 34.3   134: 48.7 / 43.4 / 43.8
+//   and the pages read after that                  67: 56.0 / 61.6 / 56.0   101: 70.0 / 78.9 / 70.1   134: 89.8 / 95.8 / 83.8
+//   pack and unpack in turn on three sets          34: 27.3 / 28 / 23.2   67: 49.8 / 53 / 48.6   101: 79.3 / 75 / 71.1   134: 107.4 / 99 / 93.3
+//                                                  201: 159 / 146.2 / 124.9   302: 237 / 218.8 / 189.2 (6.4 TB/s read + write)   604: 469 / 437.5 / 420.7
+// It costs where the caches are full of lines to be written back: pack after a fill of 768 MB, everything streamed and this, 302: 107.5 and 116.6,
+// 604: 208.9 and 223.9, and so packs in turn, which leave their own staging buffers (302: 103.3 and 109.5); and where the same buffer is unpacked again
+// out of the caches (34: nothing streamed 11.7, this 13.8).  A copy to another buffer between the two, in place of a transport, takes away what the unpack
+// gained (302: 319 and 326 for the three, 201: 206 and 234; 134: 168 with nothing streamed, 136); a transport to another GPU was not measured.
+// The lines: pack's loads in turn, streamed or not, 45.4 and 43.7 at 64 MB, 66.5 and 66.7 at 96.  Unpack's stores streamed from 40 MB on were a gain in
+// turn (67: 44.0 and 48.6, 134: 85.0 and 93.3) and a loss on pages that nothing had touched (67: 28.3 and 26.6, 101: 41.8 and 36.9), and leave the pages
+// to be fetched again; above 128 MB they are as the move in turn has them (302: 189 and 212; on untouched pages 117 and 92).
 #include "emm_internal.h"
 
 #include <type_traits>
@@ -31,7 +36,7 @@ namespace {
 
 constexpr int THREADS = 256;
 constexpr unsigned ADLER_MOD = 65521;
-constexpr long long STREAM_LOADS = 80ll << 20, STREAM_STORES = 40ll << 20;           // of K and V pages
+constexpr long long STREAM_LOADS = 80ll << 20, STREAM_STORES = 128ll << 20;          // pack's loads, unpack's stores: of K and V pages
 
 // wave sum of a 64-bit value
 __device__ inline unsigned long long wave_sum_u64(unsigned long long x)

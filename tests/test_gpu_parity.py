@@ -951,9 +951,10 @@ def test_kv_page_migration_past_the_caches(n, page_bytes):
         assert zlib.adler32(staging[p].cpu().numpy().tobytes()) == int(sums[p]) & 0xffffffff
 
 
-@pytest.mark.parametrize("n,page_bytes", [(1280, 16384), (1281, 16384), (2560, 16384), (2561, 16384), (40, 1 << 19), (41, 1 << 19), (81, 1 << 19)])
+@pytest.mark.parametrize("n,page_bytes", [(1280, 16384), (1281, 16384), (2560, 16384), (2561, 16384), (40, 1 << 19), (41, 1 << 19), (81, 1 << 19),
+                                           (4096, 16384), (4097, 16384)])
 def test_kv_page_migration_at_the_lines_of_the_hints(n, page_bytes):
-    """Either side of the sizes from which unpack's stores (40 MiB of K and V pages) and pack's loads (80 MiB) go past the caches."""
+    """Either side of the sizes from which pack's loads (80 MiB of K and V pages) and unpack's stores (128 MiB) go past the caches."""
     test_kv_page_migration_past_the_caches(n, page_bytes)
 
 
