@@ -190,7 +190,9 @@ emm_status emm_decode_attn_static(const emm_batch *batch, const void *q, const v
  *   own_prefix_lens   [B]                        prefix_lens[r] - req_shared_len[r]
  * (*) the sizes are what the caller provides; the rows are written packed, as narrow as what they hold allows, with
  * the row stride that the descriptor states (groups.max_pages_per_req, own.max_pages_per_req <= the batch's): the
- * launches size their grids, and decide whether anything is cut along the keys, from that width.
+ * launches size their grids, and decide whether anything is cut along the keys, from that width; and the groups' pass
+ * takes it for the groups' length, and their pages for different ones, when it decides whether K and V are too many to be
+ * worth keeping in the caches.  Wider tables give the same results, later (short groups behind wide tables: up to a quarter).
  * and fills the scalar fields of two descriptors, `groups` (one "request" per group) and `own` (the batch itself
  * with the moved page table), whose four array pointers it leaves NULL: the caller copies the arrays to the
  * device and sets them (own.new_lens and own.cu_new_lens are the batch's).  num_groups == 0: nothing to gain, use

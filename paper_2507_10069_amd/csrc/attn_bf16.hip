@@ -1422,12 +1422,16 @@ void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool 
 
 // K and V that are read once, and more of them than the last-level cache keeps for the next call on the same data, are fetched past the caches, so that
 // they do not displace each other: every request has one row tile at most, which one workgroup does or its pieces do (enough pairs that
-// none is halved by rows on two XCDs), and the caller knows that the page tables are as narrow as the contexts and that few pages, if
-// any, are in two of them -- the groups' pass of a shared prefill.  64 questions of 4 tokens on 8 videos of 16384 (268 MB): 95.9 -> 86.5 us,
-// the groups' pass alone 76 -> 67; where the 8 groups hold two videos between them, which the caches could keep, 83.7 after 87.5.
-// The line lies where a call repeated on the same data loses nothing either (groups of 4, MB of K and V: us repeated, and with three batches
-// in turn; before / streamed): 134: 46.5 / 54.2, 61.5 / 57.8; 201: 56.5 / 56.5, 69.0 / 57.5; 268: 84.8 / 78.8, 88.2 / 81.4; 536: 134.7 /
-// 120.5, 137.4 / 120.9.  (Groups of 8: 167: 67.0 / 74.7, 80.0 / 77.0; 201: 76.3 / 75.6, 83.0 / 75.6.)
+// none is halved by rows on two XCDs), and the caller says that it is the groups' pass of a shared prefill, whose tables are as narrow as the contexts
+// and name few pages, if any, twice.  64 questions of 4 tokens on 8 videos of 16384 (268 MB): 95.9 -> 86.5 us, the groups' pass alone 76 -> 67.
+// Neither is looked at.  Groups that hold the same videos are counted as if they did not, which costs nothing that was seen (cached / streamed): 64 of 4096
+// tokens on two videos 69.3 / 69.2 us, on four 69.7 / 69.3, 32 of 16384 on two 119.8 / 119.4, 8 of 16384 on two 87.5 / 83.7.  Tables that are wider than what the
+// groups hold, which the planner does not make, ask for it too early: 32 groups of 2048 tokens behind 2048 pages, the same data again, 48.3 / 60.6,
+// 16 of 4096 45.7 / 52.7, with three batches in turn 59.7 / 55.2 and 56.4 / 52.2.  (Both ways in one kernel, by the lengths, cost the others up to 5 %.)
+// The line, cached / streamed, for groups of 4 (MB of K and V: us repeated on the same data, which the cache may hold, and with three batches in
+// turn): 134: 46.5 / 54.2, 61.5 / 57.8; 201: 54.9 / 56.0, 65.7 / 56.7; 235: 62.2 / 67.1, 72.4 / 66.6; 268: 73.8 / 72.4, 81.1 / 74.1; 537: 128.0 /
+// 114.4, 129.3 / 113.2.  (Groups of 8: 167: 67.0 / 74.7, 80.0 / 77.0; 201: 76.3 / 75.6, 83.0 / 75.6.)  So just above the line up to 8 % is lost by a
+// call that is repeated on the same data, and as much is gained where other data come in between.
 static bool read_once(const AttnArgs& a, const LaunchShape& L)
 {
     constexpr long long STREAM_BYTES = 176ll << 20;

@@ -56,7 +56,7 @@ struct AttnArgs {
     void* workspace;      // scratch for the bf16 kernel's cut units, or nullptr
     const void* k_new = nullptr;   // fused decode step only: the query tokens' own K/V rows [T][Hkv][d], which
     const void* v_new = nullptr;   // the kernel reads from here and stores in the (then writable) pools
-    int32_t own_pages = 0;         // 1: few pages, if any, are in the tables of two requests, and the tables are no wider than the contexts
+    int32_t own_pages = 0;         // 1: the caller says that few pages, if any, are in the tables of two requests, and the tables no wider than the contexts (speed only)
 };
 
 // Shared-prefix units of a decode batch (device arrays; see emm_shared_prefix in emm.h)

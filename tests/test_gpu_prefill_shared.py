@@ -233,3 +233,31 @@ def test_groups_large_enough_to_stream(shared, new, planted):
     dw, plan = _run_shared(wl)
     assert plan["num_groups"] == reqs // 2
     print("   errors (max, mean, lse):", _compare(wl, dw, _sample_tokens(wl, 16, seed=shared)), flush=True)
+
+
+@pytest.mark.parametrize("shared,new,planted", [(512, 2, False), (576, 5, True), (5632, 2, False), (5760, 2, True)])
+def test_group_tables_wider_than_their_contexts(shared, new, planted):
+    """A caller's group tables as wide as those the groups were found in: the width alone asks for the streaming kernel, whatever the groups hold."""
+    print("case wide group tables", shared, new, planted, flush=True)
+    reqs = 32
+    wl = _case([shared + 16 * (r % 3) for r in range(reqs)], [max(1, new - r % 2) for r in range(reqs)], [r // 2 for r in range(reqs)],
+               [shared] * reqs)
+    if planted:
+        wl.q[:] = W.to_bf16_bits(np.full(wl.q.shape, 4.0, np.float32))
+        _plant_key(wl, 0, 300, 4.0)
+        _plant_key(wl, 12, shared - 1, 4.0)
+    dw = B.DeviceWorkload(wl)
+    plan = dw.plan_prefill_shared(min_saved_key_tiles=0)
+    assert plan["num_groups"] == reqs // 2
+    ps, width = dw.prefill_shared, 400
+    groups, table = ps["groups"], ps["dev"]["group_page_table"]
+    assert groups.max_pages_per_req <= width
+    wide = torch.full((table.shape[0], width), -1, dtype=torch.int32, device="cuda")
+    wide[:, :table.shape[1]] = table
+    groups.page_table, groups.max_pages_per_req = wide.data_ptr(), width
+    ps["workspace"] = torch.empty(B.emm_prefill_attn_shared_workspace_size(groups, ps["own"]), dtype=torch.uint8, device="cuda")
+    dw.out.zero_()
+    dw.scatter()
+    dw.attention_prefill_shared()
+    torch.cuda.synchronize()
+    print("   errors (max, mean, lse):", _compare(wl, dw, _sample_tokens(wl, 16, seed=shared)), flush=True)
