@@ -470,7 +470,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     // (the arguments needed further down are asked for here: the compiler would where they are first used, a round trip each)
     asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out));
 
-    // (lengths forced into what the page table and the packed tensors can hold: see safe_new_len)
+    // (lengths forced into what the page table and the packed tensors can hold: see clamp_new_len)
     const int N = clamp_new_len(b, plan.new_len, CAUSAL);
     const int n_rows = N * G;                                // rows of this (request, KV head)
     const int row0 = tile * BR;

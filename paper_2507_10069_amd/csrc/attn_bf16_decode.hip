@@ -214,7 +214,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int pair = SHARED ? blk - piece * n_items : blk;                // unit mode: (unit, KV head)
     const int unit = info.by_kv_heads.quotient(pair);                     // own part: this is the request itself
     const int kvh = pair - unit * b.num_kv_heads;
-    // (what the device arrays hold is forced into range wherever an address depends on it: see safe_new_len)
+    // (what the device arrays hold is forced into range wherever an address depends on it: see clamp_new_len)
     const int r = unit_mode ? min(max(sv.unit_first_req[unit], 0), b.num_reqs - 1) : unit;   // the request whose page table is read
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         for (int q = 0; q < NR; ++q) {
             const int my_row = min(16 * q + l16, n_rows - 1);
             const int hq = kvh * G + (unit_mode ? my_row % G : my_row);
-            const long long q_row = unit_mode ? safe_first_row(b, min(r + my_row / G, b.num_reqs - 1), 1) : first_row;
+            const long long q_row = unit_mode ? clamp_first_row(b, b.cu_new_lens[min(r + my_row / G, b.num_reqs - 1)], 1) : first_row;
             const __bf16* __restrict__ qp = (const __bf16*)a.q + (q_row * b.num_q_heads + hq) * D + 8 * g;
 #pragma unroll
             for (int st = 0; st < 4; ++st) qf[q][st] = *(const bf16x8*)(qp + 32 * st);
@@ -747,7 +747,8 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
 //   place of a workgroup with work (64 contexts of 2048 to 8191 tokens behind a table of 256 tiles: 85 + 85 + 85 + 1 133 us, 64 four
 //   times 125; where all have 8192 tokens both take 176)
 //   MERGE           the second kernel, which a batch cut in single pieces does without (128 contexts of 1000 tokens: 15.7 us
-//                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds
+//                   in single pieces, 18.3 in four each), and WORKGROUP what every further piece adds.  (Where the last workgroup merges there is
+//                   no second kernel, but the pieces are chosen as if there were: the constants are fitted to two.)
 // What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
 // longest own part / shared part and with it the pieces per context that the grid must provide; `planned_tiles` is the
 // amount of work there is (32-key tiles per KV head, summed over contexts), by which contexts are known to DIFFER: half a piece

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnArgs a, int G,
     asm volatile("" ::"s"(page), "s"(new_len), "s"(prefix_len), "s"(cu_new), "s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out), "s"(a.lse), "s"(a.causal));
     __builtin_amdgcn_sched_barrier(0);
 
-    // (lengths forced into what the page table and the packed tensors can hold: see safe_new_len)
+    // (lengths forced into what the page table and the packed tensors can hold: see clamp_new_len)
     const int N = clamp_new_len(b, new_len, a.causal != 0);
     const int n_rows = N * G;
     const long long row0_wide = ((long long)slot - first_slot(cu_new, G, r)) * ROWS;

@@ -30,20 +30,17 @@ __device__ inline int clamp_new_len(const BatchView& b, int new_len, bool causal
     if (causal) n = (int)min((long long)n, (long long)b.max_pages * b.page_size);
     return n;
 }
-__device__ inline int safe_new_len(const BatchView& b, int r, bool causal) { return clamp_new_len(b, b.new_lens[r], causal); }
 //   cached tokens: what fits the page-table row next to n_slots more tokens (the new ones if causal, else 0)
 __device__ inline int clamp_prefix_len(const BatchView& b, int prefix_len, int n_slots)
 {
     const long long room = (long long)b.max_pages * b.page_size - n_slots;
     return (int)min((long long)max(prefix_len, 0), max(room, 0ll));
 }
-__device__ inline int safe_prefix_len(const BatchView& b, int r, int n_slots) { return clamp_prefix_len(b, b.prefix_lens[r], n_slots); }
 //   first packed row: such that n_new rows from it on lie inside [0, T)
 __device__ inline int clamp_first_row(const BatchView& b, int first_row, int n_new)
 {
     return min(max(first_row, 0), max(b.total_new_tokens - n_new, 0));
 }
-__device__ inline int safe_first_row(const BatchView& b, int r, int n_new) { return clamp_first_row(b, b.cu_new_lens[r], n_new); }
 
 struct AttnArgs {
     BatchView b;

@@ -1085,7 +1085,7 @@ def test_group_sizes_and_kv_heads(G, Hkv):
     _compare(wl, _gpu_run(wl), _sample_tokens(wl, 20, seed=G))
 
 
-# 16 rows and 16 keys per step, 8 waves taking the chunks in turn, 64 chunks per wave (8192 keys) between page-table reads
+# 16 rows and 16 keys per step, 8 waves taking the chunks in turn, a page id read for each chunk two ahead; more than 64 chunks per wave (8192 keys)
 F32_CASES = [
     ("rows_and_keys_at_the_tile_edges", "causal", 4, 1, 64, 16, [0, 1, 15, 16, 17, 111, 112, 127, 128, 129], [1, 3, 4, 5, 8, 1, 16, 17, 33, 2]),
     ("odd_group_wide_head", "causal", 6, 2, 128, 32, [33, 0, 70, 5], [17, 0, 5, 44]),
