@@ -328,8 +328,8 @@ __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int l
 // The lanes look at all the lengths of their pairs' requests, so that those of the workgroup's own unit need no round trip of
 // their own, and nothing is divided: powers of two are shifted by, numbers that the host knows are multiplied by.  (With the lengths asked for
 // one after the other where they were needed, arguments likewise, and eight divisions, the way to the first tile was 1200 instructions and six
-// round trips long.  Without: one request of 16384 + 36 tokens 30.7 -> 28.9 us for both kernels, eight questions on two images 61.9 -> 60.2,
-// 32 ordinary requests 905 -> 898.)
+// round trips long.  Without: scatter and both kernels for one request of 16384 + 36 tokens 30.1 -> 28.2 us, for eight questions on two images 61.0 -> 58.6,
+// 32 ordinary requests 890 -> 883.)
 __device__ inline UnitPlan plan_unit(const BatchView& b, const LaunchShape& L, int xcd, int in_xcd, int merge_idx = -1)
 {
     UnitPlan u;

@@ -922,7 +922,7 @@ namespace {
 //   16          28 / 4, one of 2000 6.8 and 7.5, 4 8.7 and 9.3; 32 / 8, one 6.7 and 7.0, 2 of 2000 8.6 and 8.7
 //   15 heads on 1: 3 pieces 6.9 and 7.8, 16 7.2 and 9.9
 // The host is a launch quicker, and it bounds such calls where they are not replayed from a graph (28 / 4, one of 1500, a call after the
-// other: 8.7 and 7.3), so the line lies where one launch takes the GPU half a microsecond more.  Not folded: more than 512
+// other: 9.0 and 7.3), so the line lies where one launch takes the GPU half a microsecond more.  Not folded: more than 512
 // workgroups (32 of 2000 to 8000, 32 / 8 heads: 119.6 and 121.2) and more than 8 longer pieces (4 of 1500 to 6000: 13.4 and 13.9).
 constexpr int FOLD_SHORT = 6, FOLD_READS = 24;               // pieces x rows of a wave
 bool fold_applies(const BatchView& b, const DecodeShape& S)

@@ -21,7 +21,7 @@
 //                 operand lane i stands for channels 4 i .. 4 i + 3 of the four products of a 64-channel block, so V
 //                 rows are read whole, 16 bytes per lane, and a lane ends up with 16 consecutive channels of its row.
 // Measured, scatter and attention per step, against one wave per row with lanes owning keys (no matrix instruction):
-// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 9.3 us (11.1 before the loads overlapped, the lengths came in one
+// 4 heads on 1 KV head of 64, 256 cached + 64 new tokens 38.8 -> 9.5 us (11.1 before the loads overlapped, the lengths came in one
 // round trip and the channels were split: see SPLIT_WORKGROUPS); the same
 // heads, 4 x (1024 + 256) tokens 254 -> 26 us; 8 heads on 2 of 128, 4096 new tokens 5.59 -> 0.44 ms (78 TFLOP/s of the
 // 154 that a large fp32 matrix product reaches).  Relative error against 64 bits 4.2e-7 -> 3.0e-7 on the first.
@@ -288,7 +288,7 @@ int waves_of(long long workgroups, bool single, long long keys)
 
 // Few workgroups with many keys are bound by their compute unit's matrix pipes and by what it fetches while the others idle: up to
 // SPLIT_WORKGROUPS of them become four each, which make a quarter of the channels (the scores again, a quarter of V).  4 heads on 1 of 64,
-// 256 cached + 64 new tokens (17 workgroups), both kernels, 10.3 -> 9.3 us, 1024 + 64 20.3 -> 15.7; from 80 workgroups on it is slower
+// 256 cached + 64 new tokens (17 workgroups), 10.3 -> 9.3 us of the GPU with the scatter, 1024 + 64 20.3 -> 15.7; from 80 workgroups on it is slower
 // (88: 10.8 and 13.9).
 constexpr int SPLIT_WORKGROUPS = 64;
 // By its registers two workgroups of 8 waves or four of 4 fit a compute unit (head_dim 64).  The dispatcher fills places, not time: some compute
