@@ -919,7 +919,7 @@ namespace {
 //   4 pieces    28 / 4 heads, one context of 500 tokens 6.7 and 6.6, 16 of 500 9.0 and 8.6, 32 / 8 heads, 4 of 500 7.0 and 6.5
 //   8           32 / 8 heads, 4 of 1500 9.4 and 9.0
 //   12          28 / 4, one of 1500 6.7 and 7.2, 4 7.9 and 8.2; 32 / 8, one 6.6 and 6.8; 8 / 8, one 6.4 and 6.4
-//   16          28 / 4, one of 2000 6.8 and 7.5, 4 8.7 and 9.3; 32 / 8, one 6.7 and 7.0, 2 of 2000 8.6 and 8.7
+//   16          28 / 4, one of 2000 6.8 and 7.5, 4 8.7 and 9.3; 32 / 8, one 6.7 and 7.0
 //   15 heads on 1: 3 pieces 6.9 and 7.8, 16 7.2 and 9.9
 // The host is a launch quicker, and it bounds such calls where they are not replayed from a graph (28 / 4, one of 1500, a call after the
 // other: 9.0 and 7.3), so the line lies where one launch takes the GPU half a microsecond more.  Not folded: more than 512
