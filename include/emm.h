@@ -364,7 +364,7 @@ emm_status emm_validate_batch_host(const emm_batch *batch, const int32_t *host_p
  *   slots_per_xcd   workgroups per XCD that may hold a unit; grid = 8 * (slots_per_xcd + 31 if cutting)
  *   units[x]        work units of XCD x.  With cutting, the fan XCDs that share pairs take the row tiles of all of them in
  *                   turns, so that their numbers differ by at most one; a single one, listed for the first of them, is
- *                   done by two of these XCDs, a half of its rows each.  Without, XCD j of the fan has tiles j, j + fan, ...
+ *                   done by two of these XCDs, a half of it each.  Without, XCD j of the fan has tiles j, j + fan, ...
  *   pieces[x]       pieces planned for each of its left-over units (1: none are cut)
  *   uneven_k[x]     > 0: those pieces are a long and a short one, the cut at k / (k + 1) of the keys
  *   rows_only[x]    1: the left-over units are halved along their rows, never cut along the keys

@@ -180,7 +180,7 @@ struct LaunchShape {
 struct UnitPlan {
     int pair, tile;         // pair < 0: this workgroup has nothing to do
     int xcd;                // where the records of its pieces lie
-    int half;               // 0, 1: rows of the first or second half only, where the unit has both; -1: all rows
+    int half;               // 0, 1: the first or second of the two XCDs that do this unit (`part` then counts its workgroups); -1: one XCD does it
     int parts, part;        // the unit's key tiles are cut into `parts` ranges; this workgroup does range `part`
     int slot;               // tail slot of the unit within its XCD (meaningful when parts > 1)
     bool rows_only;         // parts == 2 stands for a halving along the rows only (never a cut along the keys)
@@ -281,7 +281,7 @@ __device__ inline int wave_scan64(int x)
 // lengths contradict its scalar fields may need more than those let the host provide) halves the rows instead.
 struct XcdPlan {
     int total;              // units
-    bool halves;            // it does one half of the rows of the only unit of its list
+    bool halves;            // it does a half of the only unit of its list: see plan_unit
     int rem, parts;         // units left over after full rounds of 32, and the pieces planned for each
     bool rows_only;         // those are never cut along the keys
     int uneven;             // see uneven_of
@@ -291,7 +291,7 @@ __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int l
 {
     XcdPlan p;
     const int turn = xcd & (L.fan - 1);                      // this XCD's place among those that share the list (fan is a power of two)
-    const bool single = L.fan > 1 && listed == 1;
+    const bool single = L.fan > 1 && listed == 1;            // (planned for MAX_PARTS pieces: see split_factor_of)
     p.halves = single && turn <= 1;
     p.total = single ? (turn <= 1 ? 1 : 0) : (listed - turn + L.fan - 1) >> L.fan_log2;
     p.rem = p.total % CU_PER_XCD;
@@ -318,8 +318,11 @@ __host__ __device__ inline XcdPlan xcd_plan(const LaunchShape& L, int xcd, int l
 // Where a pair is dealt to several XCDs (L.fan > 1) the fan XCDs that share pairs have one list between them, all row tiles
 // of those pairs, and take its units in turns: their numbers differ by at most one, which a deal of each pair's row
 // tiles by itself does not achieve (the first XCD gets the odd tile of every pair, and all there are when no request has
-// more than one).  A single unit goes to two of the XCDs by row halves, the first rows 0 .. 127 of it and of all its pieces, the
-// second rows 128 .. 255: four of a workgroup's waves then work, one per SIMD, and a tile takes 60 % of the time.
+// more than one).  A single unit goes to two of the XCDs, half of its pieces each, and each piece to two workgroups of that XCD, rows
+// 0 .. 127 and rows 128 .. 255: four of a workgroup's waves then work, one per SIMD, and a tile takes 60 % of the time.  What the two
+// workgroups fetch comes out of their L2 the second time.  (With rows 0 .. 127 of all pieces on one XCD and the others on the other both
+// brought in the whole context, 68 MB for the 34 of 16384 tokens on 4 KV heads, and one XCD merged: one request of 16384 + 36, scatter and
+// both kernels, 28.1 -> 24.6 us, the merge 7.2 -> 5.6.)  A unit that is not cut is done by row halves on the two XCDs.
 // Measured (28 / 4 heads): 16 requests of 4000 to 8000 cached and 2 to 30 new tokens 96 -> 67 us, 30 of 2000 to 4000 and 2
 // to 36 92 -> 68 us (half of the XCDs had nothing to do), 13 of 2851
 // cached and 76 to 304 new (42 and 36 units where 39 each are possible) 142 -> 136 us, one request of 16384 + 36 34.6 -> 32.9 us.
@@ -365,7 +368,6 @@ __device__ inline UnitPlan plan_unit(const BatchView& b, const LaunchShape& L, i
     const int listed = __builtin_amdgcn_readlane(incl, 63);
     const XcdPlan x = xcd_plan(L, xcd, listed);
     if (x.halves) {
-        if (merge_idx >= 0 && turn == 1) return u;           // (merged once, by the first of the two)
         u.half = turn;
         u.xcd = list_xcd;
     }
@@ -464,7 +466,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     const int32_t* __restrict__ pt = b.page_table + (long long)r * b.max_pages;
     int blk_early = (threadIdx.x & 63) * 4 + (threadIdx.x >> 7), pg_early = 0;
     auto ask_pages = [&]() { pg_early = pt[min(blk_early >> b.page_shift, b.max_pages - 1)]; };
-    const bool from_start = plan.part == 0;
+    const bool from_start = plan.part == 0 && plan.half <= 0;
     __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0): the plan's loads are behind us, said so that no wait for them is put behind this one
     if (from_start) ask_pages();
     // (the arguments needed further down are asked for here: the compiler would where they are first used, a round trip each)
@@ -486,19 +488,23 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
     // fetch.  Rows are independent, so nothing has to be merged, and with one working wave per SIMD a tile
     // takes about 60 % of the time.  (With at most half a tile of rows there is nothing to halve.)
     int row_half = plan.half;                                // -1: all eight waves work on their rows
-    if (row_half >= 0 && n_rows - row0 <= BR / 2) {          // no rows in the second half: the first one's XCD does it all
-        if (row_half == 1) return;
-        row_half = -1;
-    }
+    if (row_half >= 0 && n_rows - row0 <= BR / 2) row_half = -1;         // no rows in the second half
     // into how many pieces the unit is really cut along the keys: as planned for its XCD, fewer if it is too
     // short for that, 1 if it cannot be cut at all or is only to be halved
     const int limit_first_row = CAUSAL ? P + L.by_G.quotient(row0) : P - 1;
     const int cut = (plan.parts == 1 || plan.rows_only) ? 1
                     : plan.uneven > 0 ? (uneven_cuttable(n_tiles_unit, plan.uneven, limit_first_row) ? 2 : 1)
                                       : pieces_cut(n_tiles_unit, plan.parts, limit_first_row, plan.min_tiles);
-    if (plan.uneven > 0 && cut == 1) {
+    if (plan.half >= 0 && cut > 1) {
+        // two XCDs do this unit: each takes half of the pieces, all rows of them (see plan_unit)
+        const int by_rows = row_half >= 0 ? 2 : 1;
+        if (plan.part >= (cut >> 1) * by_rows) return;
+        if (row_half >= 0) row_half = plan.part & 1;
+        plan.part = plan.half * (cut >> 1) + (by_rows == 2 ? plan.part >> 1 : plan.part);
+    } else if (plan.uneven > 0 && cut == 1) {
         if (plan.part > 0) return;                           // too short to cut: the regular workgroup does it all
     } else if (plan.parts > 1 && cut == 1) {
+        if (plan.half == 1 && row_half < 0) return;          // (the other XCD does it all)
         const bool halve = row_half < 0 && n_rows - row0 > BR / 2;       // (not where another XCD does the other half)
         if (plan.part > (halve ? 1 : 0)) return;
         if (halve) row_half = plan.part;
@@ -1158,18 +1164,19 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
 // bytes, which are read once: a thread takes the 16 bytes of one column and register group from each piece, 16 loads in
 // all before the first use, and (m, l) of one column and piece, from which all weights are made in LDS meanwhile.  (With shares
 // by registers every share read all (m, l): as many bytes again for 32 pieces.)  Pieces past the last repeat it, with weight 0.
-template <int PARTS, int SHARES = PARTS>
+template <int PARTS, int SHARES = PARTS, int PER = (PARTS > 16 ? 16 : PARTS)>
 __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, int cut, int sub, int row0, int n_rows, const LaunchShape& L, int kvh,
                                    long long first_row, const AttnArgs& a)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     constexpr int COLS = NTHREADS / SHARES;                  // columns of this share
-    constexpr int PER = PARTS > 16 ? 16 : PARTS;             // pieces a thread reads of one (column, group)
-    constexpr int SPLIT = PARTS / PER;                       // threads that share a (column, group)
+    constexpr int SPLIT = PARTS / PER;                       // threads that share a (column, group): PER pieces each
     constexpr int ITEMS = COLS * 16 * SPLIT / NTHREADS;      // (column, group)s of a thread
-    constexpr int MLS = PARTS * COLS / NTHREADS;             // (m, l)s of a thread: 1, or 2 for an uneven cut
+    constexpr int ML = PARTS * COLS;                         // (m, l)s of the share
+    constexpr int MLS = (ML + NTHREADS - 1) / NTHREADS;      // of a thread: 1 (of some threads none), or 2 for an uneven cut
     static_assert(ITEMS * PER <= 32 && NTHREADS % (16 * SPLIT) == 0, "loads in flight per thread");
     const int tid = threadIdx.x;
+    static_assert(MLS == 1 || ML % NTHREADS == 0, "(m, l)s of the last turn");
     // column `col` of the unit's 512: does it hold a row?
     auto row_of = [&](int col) { return row0 + (col >> 6) * 32 + (col & 31); };
     float* m_s = lds;                                        // [PARTS][COLS], then the weights
@@ -1177,7 +1184,7 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
     f32x2 ml[MLS];
 #pragma unroll
     for (int u = 0; u < MLS; ++u) {
-        const int idx = tid + u * NTHREADS, j = idx / COLS, col = sub * COLS + idx % COLS;
+        const int idx = ML < NTHREADS ? tid % ML : tid + u * NTHREADS, j = idx / COLS, col = sub * COLS + idx % COLS;
         ml[u] = *(const f32x2*)(ws0 + (size_t)min(j, cut - 1) * PART_FLOATS + 64 * NTHREADS + 2 * col);
     }
     f32x4 val[ITEMS][PER];
@@ -1190,7 +1197,8 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
                 val[it][u] = *(const f32x4*)(ws0 + (size_t)min(half * PER + u, cut - 1) * PART_FLOATS + (group * NTHREADS + col) * 4);
     }
 #pragma unroll
-    for (int u = 0; u < MLS; ++u) m_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? ml[u][0] : -INFINITY;
+    for (int u = 0; u < MLS; ++u)
+        if (ML >= NTHREADS || tid < ML) m_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? ml[u][0] : -INFINITY;
     __syncthreads();
     float w[MLS];
 #pragma unroll
@@ -1204,12 +1212,13 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
     }
     __syncthreads();                                         // all maxima have been taken
 #pragma unroll
-    for (int u = 0; u < MLS; ++u) {
-        m_s[tid + u * NTHREADS] = w[u];
-        wl_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? w[u] * ml[u][1] : 0.f;
-    }
+    for (int u = 0; u < MLS; ++u)
+        if (ML >= NTHREADS || tid < ML) {
+            m_s[tid + u * NTHREADS] = w[u];
+            wl_s[tid + u * NTHREADS] = (tid + u * NTHREADS) / COLS < cut ? w[u] * ml[u][1] : 0.f;
+        }
     __syncthreads();
-    float* half_s = wl_s + PARTS * COLS;                     // [COLS * 16][4]: sums of the second half of 32 pieces
+    float* further_s = wl_s + PARTS * COLS;                  // [SPLIT - 1][COLS * 16][4]: sums of the pieces behind the first PER
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const int idx = tid + it * NTHREADS, c = idx % COLS, col = sub * COLS + c, rest = idx / COLS, group = rest & 15, half = rest >> 4;
@@ -1221,11 +1230,12 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
             for (int e = 0; e < 4; ++e) acc[e] += wj * val[it][u][e];
         }
         if constexpr (SPLIT > 1) {
-            static_assert(SPLIT <= 2 && ITEMS == 1, "two halves, one item");
-            if (half == 1) *(f32x4*)(half_s + (idx - COLS * 16) * 4) = acc;
+            static_assert(ITEMS == 1, "a thread comes here once");
+            if (half > 0) *(f32x4*)(further_s + (idx - COLS * 16) * 4) = acc;
             __syncthreads();
-            if (half == 1) return;
-            acc += *(const f32x4*)(half_s + idx * 4);
+            if (half > 0) return;
+#pragma unroll
+            for (int h = 0; h < SPLIT - 1; ++h) acc += *(const f32x4*)(further_s + (h * COLS * 16 + idx) * 4);
         }
         const int row = row_of(col);
         if (row < n_rows) {
@@ -1250,7 +1260,7 @@ __device__ inline void merge_share(const float* __restrict__ ws0, float* lds, in
 // Merges the pieces of the cut units, column for column (thread for thread) the layout of the main kernel's epilogue.  An XCD
 // whose tail units are planned for p pieces each gets 32 workgroups: number k works on tail slot k / p and there on the
 // columns of share k % p, 512 / p of each piece's 512, so every workgroup reads as many bytes whatever p is (one
-// workgroup per unit for an uneven cut in two).  Workgroups whose slot holds no cut unit leave at once.
+// workgroup per unit for an uneven cut in two; of two XCDs that do one unit both have 32, of 64 shares).  Workgroups whose slot holds no cut unit leave at once.
 __global__ __launch_bounds__(NTHREADS) void attn_bf16_merge_kernel(AttnArgs a, LaunchShape L)
 {
     const BatchView& b = a.b;
@@ -1273,10 +1283,14 @@ __global__ __launch_bounds__(NTHREADS) void attn_bf16_merge_kernel(AttnArgs a, L
     if (cut == 1) return;                                    // not cut along the keys
 
     const long long first_row = clamp_first_row(b, plan.cu_new, N);
-    const float* __restrict__ ws0 = part_base(a.workspace, L.ws_pieces, xcd, plan.slot, plan.parts, 0);
+    const float* __restrict__ ws0 = part_base(a.workspace, L.ws_pieces, plan.xcd, plan.slot, plan.parts, 0);
     __shared__ __attribute__((aligned(16))) float lds[4 * NTHREADS + 4 * NTHREADS / 2];
     if (plan.uneven > 0) {
         merge_share<2, 1>(ws0, lds, cut, 0, row0, n_rows, L, kvh, first_row, a);
+        return;
+    }
+    if (plan.half >= 0) {                                    // the merge workgroups of two XCDs share the unit
+        merge_share<MAX_PARTS, 2 * MAX_PARTS, 8>(ws0, lds, cut, plan.half * MAX_PARTS + plan.part, row0, n_rows, L, kvh, first_row, a);
         return;
     }
     switch (plan.parts) {

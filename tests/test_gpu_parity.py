@@ -246,6 +246,23 @@ def test_single_row_tiles_shared_among_xcds(name, kind, H, Hkv, prefix, new):
     _compare(wl, dw)
 
 
+# the only unit of two XCDs, half of its pieces and of their merge each: 32, 16, 8 pieces, 4 and none, with rows in both halves of its row
+# tile (129 and more) and in one, where a KV head has 2, 4 or 8 XCDs
+@pytest.mark.parametrize("H,Hkv,new", [(28, 4, 36), (43, 1, 3), (128, 1, 1), (14, 2, 18)])
+@pytest.mark.parametrize("tokens", [2200, 2047, 1100, 1000, 96])
+def test_only_unit_of_two_xcds(H, Hkv, new, tokens):
+    print("case only unit", H, Hkv, new, tokens, flush=True)
+    wl = W.build_workload("only_unit", "causal", "bf16", 795, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                          prefix_lens=[tokens * 2], new_lens=[new])
+    dw = B.DeviceWorkload(wl)
+    if dw.workspace is not None:
+        dw.workspace.fill_(0xff)                             # NaN wherever no record is written
+    dw.out.zero_()
+    dw.step()
+    torch.cuda.synchronize()
+    _compare(wl, dw)
+
+
 # units left over after one full round on an XCD, cut in four however short the pieces (16 key tiles and more), and contexts under
 # 24 key tiles, for which there is no room for records and nothing may be cut
 TAIL_CASES = [
