@@ -153,6 +153,9 @@ __device__ inline void wait_fetches()
     asm volatile("s_waitcnt vmcnt(%0)" ::"i"(PENDING) : "memory");
 }
 
+// Where a context and a unit have at most ROW_PIECES pieces and there are rows for every compute unit, a wave of its own merges each row: see
+// attn_bf16_decode_merge_rows_kernel.
+constexpr int ROW_PIECES = 8, ROW_ROWS = 256;
 // waves of the merge kernel by the pieces of a context (see there)
 constexpr int MANY_PIECES = 32, MANY_WAVES = 16, FEW_WAVES = 4;
 
@@ -733,6 +736,121 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
         a.lse[q_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
 }
 
+// The same where a row has few pieces: a wave takes a row, all its pieces, of the request and of its unit, asked for at once, without LDS and barriers and
+// with a quarter of the waves, which is what bounds the kernel above where there are many rows of few pieces.  The sums are those of the four waves above,
+// term by term.  Both kernels, four waves for a row and one, us: units of 4 contexts, 40 of 1758 to 2414 tokens in 10 units, 28 / 4 heads, 25.6 and 23.2,
+// 36 of 2974 to 3573 in 6, 32 / 8, 32.8 and 29.6, 32 of 18432 in 8 75.3 and 73.8; no units, 64 of 8192 174.5 and 173.4, 32 of 350 to 4600, 32 / 8, 46.3 and 45.8.
+// With 16 pieces at once 4 contexts of 1822 to 3574 in one unit take 12.9 instead of 11.2, and 7 of 2078 to 3794 in two (196 rows) with 8 13.5
+// instead of 13.3: hence ROW_PIECES and ROW_ROWS.
+template <bool CAUSAL, bool SHARED, int PIECES, bool AHEAD>
+__global__ __launch_bounds__(64 * FEW_WAVES) void attn_bf16_decode_merge_rows_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, Divisor by_piece, Divisor by_heads,
+                                                                                     Divisor by_G, int G)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr int PARTS = FEW_WAVES;
+    static_assert(PIECES % PARTS == 0, "every fourth piece");
+    const BatchView& b = a.b;
+    const int lane = threadIdx.x & 63;
+    const int head_row = blockIdx.x * FEW_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // request * query heads + query head
+    const int r = by_heads.quotient(head_row);
+    if (r >= b.num_reqs) return;
+    const int head = head_row - r * b.num_q_heads;
+    const int kvh = by_G.quotient(head), row = head - kvh * G;
+    const int pair = r * b.num_kv_heads + kvh;
+    const float* __restrict__ rec_own = (const float*)a.workspace + ((size_t)pair * S.pieces_max * MAX_G + row) * REC_FLOATS;
+    struct Asked {
+        f32x2 val[PIECES], ml[PIECES];
+    } own, of_unit;
+    auto ask = [&](Asked& to, const float* __restrict__ rec, size_t stride, int room) {
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) {
+            const float* __restrict__ src = rec + (size_t)min(u, room - 1) * stride;
+            to.val[u] = *(const f32x2*)(src + 2 * lane);
+            to.ml[u] = *(const f32x2*)(src + D);
+        }
+    };
+    const int n_new = b.new_lens[r], prefix_len = b.prefix_lens[r], cu_new = b.cu_new_lens[r];
+    const int req_unit = SHARED ? sv.req_unit[r] : -1, req_shared = SHARED ? sv.req_shared_len[r] : 0;
+    if (AHEAD) {
+        ask(own, rec_own, MAX_G * REC_FLOATS, S.pieces_max);
+        __builtin_amdgcn_sched_barrier(0);
+        // needed further down only, but asked for here
+        asm volatile("" ::"s"(n_new), "s"(cu_new), "s"(by_piece.mul), "s"(a.out), "s"(a.lse));
+        if (SHARED) asm volatile("" ::"s"(sv.unit_shared_len), "s"(sv.unit_first_req), "s"(sv.num_units));
+    }
+    // the counts, forced into what the workspace holds: as in the kernel above
+    const int P = clamp_prefix_len(b, prefix_len, CAUSAL ? 1 : 0);
+    const int unit = SHARED ? min(max(req_unit, -1), sv.num_units - 1) : -1;
+    const int n_own = min(own_pieces_of(CAUSAL ? P + 1 : P, SHARED ? max(req_shared, 0) / BK : 0, by_piece, unit >= 0),
+                          S.pieces_max);
+    const bool nothing = n_new <= 0 || (unit < 0 && n_own == 1);          // no query token, or finished by the main kernel
+    if (!AHEAD) {
+        if (nothing) return;
+        ask(own, rec_own, MAX_G * REC_FLOATS, max(n_own, 1));
+    }
+    int n_unit = 0;
+    if (SHARED && unit >= 0) {
+        const int unit_len = sv.unit_shared_len[unit], unit_first = sv.unit_first_req[unit];
+        const int shared_len = (int)min((long long)max(unit_len, 0), (long long)b.max_pages * b.page_size) / BK * BK;
+        n_unit = shared_len > 0 ? min(up_to_pieces(shared_len / BK, by_piece), S.pieces_unit) : 0;
+        const int member = min(max(r - unit_first, 0), MAX_ROWS / G - 1);                  // position of the request in its unit
+        const float* __restrict__ rec_unit = (const float*)a.workspace + unit_records_offset(S) +
+                                             ((size_t)(unit * b.num_kv_heads + kvh) * S.pieces_unit * MAX_ROWS + member * G + row) * REC_FLOATS;
+        if (n_unit > 0) ask(of_unit, rec_unit, MAX_ROWS * REC_FLOATS, S.pieces_unit);
+    }
+    if (nothing) return;
+
+    const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
+    float m[PARTS], l[PARTS];                                // of the pieces that leave the same remainder by 4 (every piece has a visible key)
+    f32x2 acc[PARTS];
+#pragma unroll
+    for (int w = 0; w < PARTS; ++w) {
+        m[w] = -INFINITY;
+        l[w] = 0.f;
+        acc[w] = f32x2{0.f, 0.f};
+    }
+    auto add = [&](const Asked& from, int n) {
+#pragma unroll
+        for (int w = 0; w < PARTS; ++w) {
+            float m_new = m[w];
+#pragma unroll
+            for (int u = w; u < PIECES; u += PARTS) m_new = fmaxf(m_new, u < n ? from.ml[u][0] : -INFINITY);
+            const float ref = m_new == -INFINITY ? 0.f : m_new;          // no piece so far: all weights are 0
+            const float alpha = __builtin_amdgcn_exp2f((m[w] - ref) * c_log2);
+            l[w] *= alpha;
+            acc[w] *= alpha;
+            m[w] = m_new;
+#pragma unroll
+            for (int u = w; u < PIECES; u += PARTS) {
+                const bool in = u < n;                       // what is no piece may hold anything, infinities and NaN included
+                const float wgt = __builtin_amdgcn_exp2f(((in ? from.ml[u][0] : -INFINITY) - ref) * c_log2);
+                l[w] = fmaf(wgt, in ? from.ml[u][1] : 0.f, l[w]);
+                add_weighted(acc[w], wgt, in ? from.val[u] : f32x2{0.f, 0.f});
+            }
+        }
+    };
+    add(own, n_own);
+    if (SHARED && n_unit > 0) add(of_unit, n_unit);
+    float m_all = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < PARTS; ++w) m_all = fmaxf(m_all, m[w]);
+    float l_tot = 0.f;
+    f32x2 sum = {0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < PARTS; ++w) {
+        const float wgt = m[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m[w] - m_all) * c_log2);
+        l_tot = fmaf(wgt, l[w], l_tot);
+        sum[0] = fmaf(wgt, acc[w][0], sum[0]);
+        sum[1] = fmaf(wgt, acc[w][1], sum[1]);
+    }
+    const long long at = clamp_first_row(b, cu_new, 1) * (long long)b.num_q_heads + head;
+    bf16x2 o;
+    o[0] = (__bf16)(l_tot > 0.f ? sum[0] / l_tot : 0.f);
+    o[1] = (__bf16)(l_tot > 0.f ? sum[1] / l_tot : 0.f);
+    *(bf16x2*)((__bf16*)a.out + at * D + 2 * lane) = o;
+    if (lane == 0 && a.lse != nullptr) a.lse[at] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
+}
+
 // How a decode batch is cut: the piece length with the least time by a model of the main kernel (times in us, measured).
 //   START           from the launch to the first block and from the last block to the end
 //   TILE_HBM        one 32-key tile of one KV head (16 KB) at the rate at which the whole chip streams, 6.6 TB/s
@@ -980,6 +1098,27 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
         hipLaunchKernelGGL((attn_bf16_decode_merge_kernel<decltype(causal)::value, SHARED, decltype(waves)::value, decltype(ahead)::value>), mgrid,
                            dim3(64 * decltype(waves)::value), 0, stream, a, S, sv, info.by_piece);
     };
+    // a wave for each row where one can ask for all its pieces at once
+    const int most = std::max(S.pieces_max, S.n_unit_pairs > 0 ? S.pieces_unit : 0);
+    auto rows = [&](auto causal, auto pieces, auto ahead) {
+        const long long waves = (long long)b.num_reqs * b.num_q_heads;
+        hipLaunchKernelGGL((attn_bf16_decode_merge_rows_kernel<decltype(causal)::value, SHARED, decltype(pieces)::value, decltype(ahead)::value>),
+                           dim3((unsigned)((waves + FEW_WAVES - 1) / FEW_WAVES)), dim3(64 * FEW_WAVES), 0, stream, a, S, sv, info.by_piece,
+                           divisor_of(b.num_q_heads), divisor_of(info.G), info.G);
+    };
+    auto rows_of = [&](auto causal) {
+        auto of = [&](auto pieces) {
+            if (S.ahead) rows(causal, pieces, std::true_type{});
+            else rows(causal, pieces, std::false_type{});
+        };
+        if (most <= ROW_PIECES / 2) of(std::integral_constant<int, ROW_PIECES / 2>{});
+        else of(std::integral_constant<int, ROW_PIECES>{});
+    };
+    if (most <= ROW_PIECES && (long long)b.num_reqs * b.num_q_heads >= ROW_ROWS) {
+        if (a.causal) rows_of(std::true_type{});
+        else rows_of(std::false_type{});
+        return hipGetLastError();
+    }
     auto merge_of = [&](auto causal) {
         using few = std::integral_constant<int, FEW_WAVES>;
         using many = std::integral_constant<int, MANY_WAVES>;

@@ -636,6 +636,35 @@ def test_decode_rows_do_not_tell_which_kernel_merged_them(Hkv, ctx):
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
 
 
+# rows enough for a wave each in the second kernel (16 query heads per KV head: 320 and 256 rows; 255: four waves for a row), up to 4 pieces and up to 8,
+# beside the folded merge and four waves for a row (G of them)
+@pytest.mark.parametrize("Hkv,ctx,G_of", [(2, [501, 40, 0, 130, 127, 128, 500, 300, 260, 17], (1, 4, 8, 9)), (2, [800, 700, 40, 0, 130, 127, 128, 500, 1020, 640], (1, 4, 8, 12)),
+                                          (1, [1000] * 16, (5, 15))])
+def test_decode_rows_merged_by_a_wave_each(Hkv, ctx, G_of):
+    print("case a wave each", Hkv, ctx, flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+
+    def run(G, like=None):
+        wl = W.build_workload("wave_each", "causal", "bf16", 769, num_q_heads=G * Hkv, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                              prefix_lens=ctx, new_lens=[1] * len(ctx))
+        if like is not None:
+            wl.page_table, wl.k_cache, wl.v_cache, wl.k_new, wl.v_new = like.page_table, like.k_cache, like.v_cache, like.k_new, like.v_new
+            wl.q = np.ascontiguousarray(like.q.reshape(len(ctx), Hkv, 16, 128)[:, :, :G]).reshape(len(ctx), Hkv * G, 128)
+        dw = B.DeviceWorkload(wl)
+        dw.workspace.fill_(0xff)                             # NaN wherever no record is written
+        dw.out.zero_()
+        dw.step()
+        torch.cuda.synchronize()
+        _compare(wl, dw)
+        return wl, bits(dw.out).reshape(len(ctx), Hkv, G, 128), dw.lse.cpu().numpy().reshape(len(ctx), Hkv, G)
+
+    like, out, lse = run(16)
+    for G in G_of:
+        _, out_g, lse_g = run(G, like)
+        assert out_g.tobytes() == np.ascontiguousarray(out[:, :, :G]).tobytes(), G
+        assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
+
+
 def test_decode_of_short_contexts_does_not_depend_on_the_batch():
     """Contexts of one piece, which is cut among a workgroup's waves in one way only: alone and in a batch of more workgroups than compute units."""
     print("case short contexts alone and together", flush=True)
