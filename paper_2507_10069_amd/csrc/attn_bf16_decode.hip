@@ -65,7 +65,7 @@ constexpr int MIN_TILES_PER_PIECE = 4, MAX_TILES_PER_PIECE = 124;  // a wave's b
 constexpr int WORKGROUPS_PER_ROUND = 2 * 256;    // two workgroups on each of 256 CUs
 constexpr int WORKGROUPS_PER_ROUND_ONE_REQUEST = 384;    // see attn_bf16_decode_shape
 constexpr int MAX_ROWS = 32;                     // query rows of a shared-prefix unit
-static_assert(MAX_G * RED_FLOATS * 4 <= RING_BYTES, "the merge across waves reuses the rings");
+static_assert(MAX_G * RED_FLOATS * 4 <= RING_BYTES, "the merge across waves reuses the rings, each wave its own");
 static_assert(MAX_TILES_PER_PIECE * BLOCKS_PER_TILE <= NW * 64, "a wave's page ids sit in one register");
 
 // What a launch adds to its arguments: the ticket of a folded merge (0: none) and quotients that every workgroup would have to work out
@@ -184,6 +184,16 @@ __device__ inline f32x2_rec get_record(const float* at)
     return __builtin_bit_cast(f32x2_rec, __hip_atomic_load((const unsigned long long*)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// The same, 16 bytes of a record at a time (buffer instructions, whose cache policy can be stated; `record` is the same in all lanes).
+typedef uint32_t u32x4_rec __attribute__((ext_vector_type(4)));
+typedef float f32x4_rec __attribute__((ext_vector_type(4)));
+constexpr int AGENT_SCOPE = 16, RAW_BUFFER = 0x00020000;     // cache policy sc1; a buffer without a format
+__device__ inline void put_record4(float* record, int at, f32x4_rec x)
+{
+    const auto all = __builtin_amdgcn_make_buffer_rsrc(record, 0, MAX_G * REC_FLOATS * 4, RAW_BUFFER);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_rec, x), all, at * 4, 0, AGENT_SCOPE);
+}
+
 // A piece's two channels, weighted, in either merge.  What is fused is written out, so that both round alike: left to the compiler it is this
 // in the one and both channels in the other.
 __device__ inline void add_weighted(f32x2_rec& acc, float wgt, f32x2_rec x)
@@ -193,16 +203,22 @@ __device__ inline void add_weighted(f32x2_rec& acc, float wgt, f32x2_rec x)
     acc[1] += wgt * x[1];
 }
 
+// a launch without units passes none: arguments that lie closer together arrive sooner (16 contexts of 500 tokens, 28 / 4 heads, 8.46 and 8.25 us)
+struct NoUnits {};
+template <bool SHARED> using UnitsOf = std::conditional_t<SHARED, SharedPrefixView, NoUnits>;
+
 // FOLD: the launch has a ticket.  (With the folded merge in one kernel for all, calls that do not use it were 0.3 us longer: 32 / 8 heads,
 // one context of 60 tokens 3.65 us and 3.34.)
 template <bool CAUSAL, bool SHARED, bool FUSED, bool FOLD>
-__global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, SharedPrefixView sv, LaunchInfo info)
+__global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, DecodeShape S, LaunchInfo info, UnitsOf<SHARED> units)
 {
     static_assert(CAUSAL || !FUSED, "only a causal step has a new token to store");
     static_assert(!SHARED || !FOLD, "units have the second kernel");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * RING_BYTES];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
+    SharedPrefixView sv = {};
+    if constexpr (SHARED) sv = units;
 
     const BatchView& b = a.b;
     const int G = info.G;
@@ -249,6 +265,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     // and every argument that is needed further down, which the compiler would ask for where it is first used
     asm volatile("" ::"s"(a.q), "s"(a.k_cache), "s"(a.v_cache), "s"(a.out), "s"(a.lse), "s"(a.workspace), "s"(info.by_piece.mul), "s"(S.n_pairs));
     if (FUSED) asm volatile("" ::"s"(a.k_new), "s"(a.v_new));
+    if (FOLD) asm volatile("" ::"s"(info.ticket));
     __builtin_amdgcn_sched_barrier(0);
     int kv_len, n_pieces, n_rows;
     bool direct;                                             // one piece and no unit: this workgroup writes the output
@@ -349,7 +366,8 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
     const int v_rd0 = BLOCK_BYTES + (4 * g + (l16 >> 2)) * 256 + ((((l16 >> 1) & 1) ^ ((l16 >> 2) << 2)) << 4) + (l16 & 1) * 8;
     const float c_log2 = b.softmax_scale * 1.44269504088896340736f;
 
-    float* __restrict__ red = (float*)smem;                  // [NW waves][16 rows][132], after the loop
+    // after the loop: each wave's results in its own ring, [16 rows][132], so that no wave has to wait until the others are past theirs
+    auto partial = [&](int w, int row) { return (float*)(smem + w * RING_BYTES) + row * RED_FLOATS; };
     // The piece with NR groups of 16 query rows: the G heads of the request or, in unit mode, the G heads of each of
     // the unit's requests; columns of the MFMA past them repeat the last row and are discarded.
     auto attend = [&](auto nr_c) {
@@ -448,8 +466,6 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
                 if (i + NSLOT < n_mine) fetch(i + NSLOT, slot);
             }
         }
-        __syncthreads();                                     // every wave is past its rings
-
         // ---- merge 1: the waves' partial results, 16 rows at a time, through LDS
         float* __restrict__ rec =
             unit_mode ? (float*)a.workspace + unit_records_offset(S) + (size_t)(pair * S.pieces_unit + piece) * MAX_ROWS * REC_FLOATS
@@ -460,7 +476,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
             const int row0 = 16 * q, rows_here = min(MAX_G, n_rows - row0);
             const float l_row = quad_sum(l_run[q]);
             if (l16 < rows_here) {
-                float* dst = red + (wave * MAX_G + l16) * RED_FLOATS;
+                float* dst = partial(wave, l16);
 #pragma unroll
                 for (int nb = 0; nb < 8; ++nb) *(f32x4*)(dst + 16 * nb + 4 * g) = o_acc[q][nb];
                 if (g == 0) *(f32x2*)(dst + D) = f32x2{m_run[q], l_row};
@@ -479,7 +495,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
                     vec x[NW];
 #pragma unroll
                     for (int w = 0; w < NW; ++w) {
-                        const float* src = red + (w * MAX_G + lrow) * RED_FLOATS;
+                        const float* src = partial(w, lrow);
                         ml[w] = *(const f32x2*)(src + D);
                         x[w] = *(const vec*)(src + ch);
                     }
@@ -505,7 +521,9 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
                             a.lse[first_row * b.num_q_heads + head] = (l_tot > 0.f) ? m_all * b.softmax_scale + logf(l_tot) : -INFINITY;
                     } else if (folded) {
 #pragma unroll
-                        for (int v = 0; v < W; v += 2) put_record(rec + row * D + ch + v, f32x2{acc[v], acc[v + 1]});
+                        for (int v = 0; v < W; v += 2)
+                            if constexpr (W == 2) put_record(rec + row * D + ch + v, f32x2{acc[v], acc[v + 1]});
+                        if constexpr (W == 4) put_record4(rec, row * D + ch, acc);
                         if (ch == 0) put_record(rec + MAX_G * D + row * 2, f32x2{m_all, l_tot});
                     } else {
 #pragma unroll
@@ -536,69 +554,94 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_decode_kernel(AttnArgs a, Dec
         if (last) __hip_atomic_store(count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (*(volatile int*)smem == 0) return;
+    if (*(volatile __attribute__((address_space(3))) int*)smem == 0) return;
     const float* rec0 = (const float*)a.workspace + (size_t)pair * S.pieces_max * MAX_G * REC_FLOATS;
-    // A wave takes up to ROWS of the rows, a lane two channels of each; the weights are made with a lane for each record,
-    // of the first row in lanes 0 .. 15, of the second in 16 .. 31.  The sums are those of attn_bf16_decode_merge_kernel term by
+    // A wave takes a row and a lane two channels of it, or, with more rows than waves, two rows, half of the lanes each, and a lane four; the weights are made
+    // with a lane for each record, of the first row in lanes 0 .. 15, of the second in 16 .. 31, and go to all lanes through LDS.  (A wave has a SIMD to
+    // itself here and is bound by the instructions that it issues: with two rows in turn, 7 heads, it was 1.0 us from the count to the records and 1.1 to the
+    // result, of 7.2; now 0.85 and 0.75.)  The sums are those of attn_bf16_decode_merge_kernel term by
     // term, its FEW_WAVES partial ones of every fourth piece first: a context's result does not tell which of the two merged it.
     constexpr int ROWS = FOLD_ROWS / NW, PARTS = FEW_WAVES;
-    static_assert(ROWS * FOLD_PIECES <= 64 && PARTS == 4, "a lane for every weight; the rotations by which partial sums are made");
+    static_assert(ROWS == 2 && ROWS * FOLD_PIECES == 32 && PARTS == 4, "a lane for every weight; the rotations by which partial sums are made");
     if (wave >= G) return;
-    const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(wave + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
-    const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
-    f32x2 val[ROWS][FOLD_PIECES];
-#pragma unroll
-    for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
-        if (u0 < n)
-#pragma unroll
-            for (int h = 0; h < ROWS; ++h)
-                if (wave + h * NW < G)
-#pragma unroll
-                    for (int u = u0; u < u0 + PARTS; ++u)
-                        val[h][u] = get_record(rec0 + min(u, n - 1) * (MAX_G * REC_FLOATS) + (wave + h * NW) * D + 2 * lane);
-    const float m = u_lane < n ? ml[0] : -INFINITY, l = u_lane < n ? ml[1] : 0.f;
-    float m_part = fmaxf(m, from_lane<4>(m));                // of the pieces that leave the same remainder by 4
-    m_part = fmaxf(m_part, from_lane<8>(m_part));
-    const float wgt = __builtin_amdgcn_exp2f((m - (m_part == -INFINITY ? 0.f : m_part)) * c_log2);
-    float l_part = wgt * l;                                  // lanes 0 .. 3 of the row: from the first piece to the last
-    l_part = fmaf(from_lane<4>(wgt), from_lane<4>(l), l_part);
-    l_part = fmaf(from_lane<8>(wgt), from_lane<8>(l), l_part);
-    l_part = fmaf(from_lane<12>(wgt), from_lane<12>(l), l_part);
-    float m_all = fmaxf(m_part, from_lane<1>(m_part));
-    m_all = fmaxf(m_all, from_lane<2>(m_all));
-    const float w_part = m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_part - m_all) * c_log2);
-    float l_tot = w_part * l_part;                           // lane 0 of the row
-    l_tot = fmaf(from_lane<1>(w_part), from_lane<1>(l_part), l_tot);
-    l_tot = fmaf(from_lane<2>(w_part), from_lane<2>(l_part), l_tot);
-    l_tot = fmaf(from_lane<3>(w_part), from_lane<3>(l_part), l_tot);
-#pragma unroll
-    for (int h = 0; h < ROWS; ++h) {
-        const int row = wave + NW * h;
-        if (row >= G) break;
-        f32x2 part[PARTS] = {}, acc = {0.f, 0.f};
+    auto merge = [&](auto width_c) {
+        constexpr int W = decltype(width_c)::value;          // channels of a lane
+        typedef float vec __attribute__((ext_vector_type(W)));
+        typedef __bf16 out_vec __attribute__((ext_vector_type(W)));
+        const int u_lane = lane & (FOLD_PIECES - 1), row_lane = min(wave + (lane / FOLD_PIECES & (ROWS - 1)) * NW, G - 1);
+        const f32x2 ml = get_record(rec0 + min(u_lane, n - 1) * (MAX_G * REC_FLOATS) + MAX_G * D + 2 * row_lane);
+        const int half = W == 4 ? lane >> 5 : 0, row = wave + NW * half, ch = W * (lane & (D / W - 1));
+        const auto records = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(rec0), 0, n * (MAX_G * REC_FLOATS * 4), RAW_BUFFER);
+        const int at_row = (min(row, G - 1) * D + ch) * 4;
+        vec val[FOLD_PIECES];
 #pragma unroll
         for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
             if (u0 < n)
 #pragma unroll
-                for (int w = 0; w < PARTS; ++w) {            // (past the last record its value again: 0, lest it be infinite)
-                    const float w_u = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), u0 + w + FOLD_PIECES * h));
-                    add_weighted(part[w], w_u, u0 + w < n ? val[h][u0 + w] : f32x2{0.f, 0.f});
+                for (int u = u0; u < u0 + PARTS; ++u) {
+                    const int at_piece = min(u, n - 1) * (MAX_G * REC_FLOATS * 4);
+                    if constexpr (W == 4) val[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(records, at_row, at_piece, AGENT_SCOPE));
+                    else val[u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(records, at_row, at_piece, AGENT_SCOPE));
                 }
-#pragma unroll
-        for (int w = 0; w < PARTS; ++w) {
-            const float w_w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_part), w + FOLD_PIECES * h));
-            acc[0] = fmaf(w_w, part[w][0], acc[0]);
-            acc[1] = fmaf(w_w, part[w][1], acc[1]);
+        const float m = u_lane < n ? ml[0] : -INFINITY, l = u_lane < n ? ml[1] : 0.f;
+        float m_part = fmaxf(m, from_lane<4>(m));            // of the pieces that leave the same remainder by 4
+        m_part = fmaxf(m_part, from_lane<8>(m_part));
+        const float wgt = __builtin_amdgcn_exp2f((m - (m_part == -INFINITY ? 0.f : m_part)) * c_log2);
+        float l_part = wgt * l;                              // lanes 0 .. 3 of the row: from the first piece to the last
+        l_part = fmaf(from_lane<4>(wgt), from_lane<4>(l), l_part);
+        l_part = fmaf(from_lane<8>(wgt), from_lane<8>(l), l_part);
+        l_part = fmaf(from_lane<12>(wgt), from_lane<12>(l), l_part);
+        float m_all = fmaxf(m_part, from_lane<1>(m_part));
+        m_all = fmaxf(m_all, from_lane<2>(m_all));
+        const float w_part = m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_part - m_all) * c_log2);
+        float l_tot = w_part * l_part;                       // lane 0 of the row
+        l_tot = fmaf(from_lane<1>(w_part), from_lane<1>(l_part), l_tot);
+        l_tot = fmaf(from_lane<2>(w_part), from_lane<2>(l_part), l_tot);
+        l_tot = fmaf(from_lane<3>(w_part), from_lane<3>(l_part), l_tot);
+        // to every lane what is its row's: the pieces' weights, the partial sums', l and m
+        float* own = (float*)smem + 256 + wave * 128;        // (clear of the word that says who is last)
+        if (lane < ROWS * FOLD_PIECES) {
+            own[lane] = wgt;
+            own[32 + lane] = w_part;
+            own[64 + lane] = l_tot;
+            own[96 + lane] = m_all;
         }
-        const float l_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(l_tot), FOLD_PIECES * h));
-        const float m_row = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_all), FOLD_PIECES * h));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own LDS writes are visible to its own reads
+        const f32x4 w_parts = *(const f32x4*)(own + 32 + FOLD_PIECES * half);
+        const float l_row = own[64 + FOLD_PIECES * half], m_row = own[96 + FOLD_PIECES * half];
+        vec part[PARTS] = {}, acc = vec(0.f);
+#pragma unroll
+        for (int u0 = 0; u0 < FOLD_PIECES; u0 += PARTS)
+            if (u0 < n) {
+                const f32x4 w_u = *(const f32x4*)(own + FOLD_PIECES * half + u0);
+                if (u0 + PARTS > n)                          // (past the last record its value again: 0, lest it be infinite)
+#pragma unroll
+                    for (int w = 1; w < PARTS; ++w)
+                        if (u0 + w >= n) val[u0 + w] = vec(0.f);
+#pragma unroll
+                for (int w = 0; w < PARTS; ++w)
+#pragma unroll
+                    for (int v = 0; v < W; v += 2) {
+                        f32x2 p = {part[w][v], part[w][v + 1]};
+                        add_weighted(p, w_u[w], f32x2{val[u0 + w][v], val[u0 + w][v + 1]});
+                        part[w][v] = p[0];
+                        part[w][v + 1] = p[1];
+                    }
+            }
+#pragma unroll
+        for (int w = 0; w < PARTS; ++w)
+#pragma unroll
+            for (int v = 0; v < W; ++v) acc[v] = fmaf(w_parts[w], part[w][v], acc[v]);
+        if (row >= G) return;
         const long long at_out = first_row * b.num_q_heads + kvh * G + row;
-        bf16x2 o;
-        o[0] = (__bf16)(l_row > 0.f ? acc[0] / l_row : 0.f);
-        o[1] = (__bf16)(l_row > 0.f ? acc[1] / l_row : 0.f);
-        *(bf16x2*)((__bf16*)a.out + at_out * D + 2 * lane) = o;
-        if (lane == 0 && a.lse != nullptr) a.lse[at_out] = (l_row > 0.f) ? m_row * b.softmax_scale + logf(l_row) : -INFINITY;
-    }
+        out_vec o;
+#pragma unroll
+        for (int v = 0; v < W; ++v) o[v] = (__bf16)(l_row > 0.f ? acc[v] / l_row : 0.f);
+        *(out_vec*)((__bf16*)a.out + at_out * D + ch) = o;
+        if (ch == 0 && a.lse != nullptr) a.lse[at_out] = (l_row > 0.f) ? m_row * b.softmax_scale + logf(l_row) : -INFINITY;
+    };
+    if (G <= NW) merge(std::integral_constant<int, 2>{});
+    else merge(std::integral_constant<int, 4>{});
 }
 
 // merge 2: one workgroup per (pair, query row); wave w takes pieces w, w + WAVES, ..., a lane two channels of each.
@@ -1034,6 +1077,8 @@ namespace {
 // Folded where the batch fits the chip at once (grid of at most 512), its pieces are short, so that the second launch is a good part
 // of the call, and what the last workgroup has to read is little: it reads all records of its context, through one compute unit, while
 // the second kernel has a workgroup for each row.  us of the GPU for two kernels and one:
+//   (one: before its last workgroup read 16 bytes a lane; since then 7 heads are .3 to .5 us quicker: one context of 1500 6.7, 4 of 1000 7.0 -> 6.6,
+//   8 of 900 8.7 -> 8.1, 16 of 500 8.8 -> 8.3; up to 4 heads as they were or .1)
 //   4 pieces    28 / 4 heads, one context of 500 tokens 6.7 and 6.6, 16 of 500 9.0 and 8.6, 32 / 8 heads, 4 of 500 7.0 and 6.5
 //   8           32 / 8 heads, 4 of 1500 9.4 and 9.0
 //   12          28 / 4, one of 1500 6.7 and 7.2, 4 7.9 and 8.2; 32 / 8, one 6.6 and 6.8; 8 / 8, one 6.4 and 6.4
@@ -1082,12 +1127,14 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
     const LaunchInfo info = {fold_applies(b, S) ? next_ticket() : 0, b.num_q_heads / b.num_kv_heads, (int32_t)dims.y, divisor_of(b.num_kv_heads), divisor_of(S.tiles_per_piece),
                              SHARED ? divisor_of(S.n_pairs) : Divisor{}, SHARED ? divisor_of(std::max(S.n_unit_pairs, 1)) : Divisor{}};
     if (!a.causal && FUSED) return hipErrorInvalidValue;
+    UnitsOf<SHARED> units = {};
+    if constexpr (SHARED) units = sv;
     auto attend = [&](auto fold) {
         constexpr bool FOLD = decltype(fold)::value;
         if (a.causal)
-            hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED, FOLD>), dims, dim3(NT), 0, stream, a, S, sv, info);
+            hipLaunchKernelGGL((attn_bf16_decode_kernel<true, SHARED, FUSED, FOLD>), dims, dim3(NT), 0, stream, a, S, info, units);
         else if constexpr (!FUSED)
-            hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false, FOLD>), dims, dim3(NT), 0, stream, a, S, sv, info);
+            hipLaunchKernelGGL((attn_bf16_decode_kernel<false, SHARED, false, FOLD>), dims, dim3(NT), 0, stream, a, S, info, units);
     };
     if (!SHARED && info.ticket != 0) attend(std::integral_constant<bool, !SHARED>{});
     else attend(std::false_type{});
