@@ -665,6 +665,28 @@ def test_decode_rows_merged_by_a_wave_each(Hkv, ctx, G_of):
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
 
 
+# pieces of four tiles: waves with no block of 16 keys, one, and two, which are done side by side; the new token's row in each wave's first and
+# second block, at their edges; whole pieces before the last
+@pytest.mark.parametrize("H,Hkv,ctx", [(28, 4, [0, 15, 16, 47, 48, 62, 63, 64, 65, 79, 80, 81, 95, 96, 111, 112, 113, 126, 127]), (8, 8, [128, 191, 192, 207, 240, 255, 256, 383]),
+                                       (16, 1, [64, 100, 127, 300])])
+def test_decode_two_blocks_of_a_wave(H, Hkv, ctx):
+    print("case two blocks", H, Hkv, len(ctx), flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+
+    def build(kind):
+        return W.build_workload("two_blocks", kind, "bf16", 771, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16,
+                                prefix_lens=ctx, new_lens=[1] * len(ctx))
+    dw = _gpu_run(build("causal"))
+    _compare(dw.wl, dw)
+    fused = B.DeviceWorkload(build("causal"))
+    fused.decode_step()
+    torch.cuda.synchronize()
+    for name in ("out", "k_cache", "v_cache"):
+        assert bits(getattr(fused, name)).tobytes() == bits(getattr(dw, name)).tobytes(), name
+    cross = _gpu_run(build("cross"))
+    _compare(cross.wl, cross)
+
+
 def test_decode_of_short_contexts_does_not_depend_on_the_batch():
     """Contexts of one piece, which is cut among a workgroup's waves in one way only: alone and in a batch of more workgroups than compute units."""
     print("case short contexts alone and together", flush=True)
