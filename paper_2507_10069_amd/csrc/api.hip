@@ -92,7 +92,7 @@ emm_status check_decode_shared(const emm_batch* b, const emm::BatchView& v, cons
 emm_status attention(const emm_batch* b, const void* q, const void* k_cache, const void* v_cache, void* out,
                      float* lse, void* workspace, size_t workspace_bytes, void* hip_stream, int causal,
                      const emm_shared_prefix* sp = nullptr, const void* k_new = nullptr, const void* v_new = nullptr,
-                     bool fused = false, bool static_scratch = false, bool own_pages = false)
+                     bool fused = false, bool static_scratch = false, bool own_pages = false, const emm::AttnParts& parts = emm::AttnParts{})
 {
     emm_status st = check_scalars(b);
     if (st != EMM_OK) return st;
@@ -159,7 +159,7 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     else if (sp != nullptr) err = emm::launch_attn_bf16_decode(args, shared_view_of(sp), shape, fused, stream);
     else if (b->dtype != EMM_BF16) err = emm::launch_attn_f32(args, stream);
     else if (decode) err = emm::launch_attn_bf16_decode(args, emm::SharedPrefixView{}, shape, false, stream);
-    else err = emm::launch_attn_bf16_d128(args, stream);
+    else err = emm::launch_attn_bf16_d128(args, stream, parts);
     return err == hipSuccess ? EMM_OK : EMM_ERR_LAUNCH;
 }
 
@@ -422,11 +422,16 @@ extern "C" emm_status emm_prefill_attn_shared(const emm_batch* groups, const emm
                        w.inner_bytes, hip_stream, 0, nullptr, nullptr, nullptr, false, false, true);
         if (st != EMM_OK) return st;
     }
-    // 2. every request over its own keys (what its page table holds behind the shared part), causal
+    // 2. every request over its own keys (what its page table holds behind the shared part), causal; the members' rows merged with their other part on the
+    //    way out where nothing of this pass is cut
+    const emm::BatchView own_view = view_of(own);
+    if (groups->num_reqs > 0 && !emm::attn_bf16_decode_applies(own_view) && emm::attn_bf16_d128_takes_parts(own_view))
+        return attention(own, q, k_cache, v_cache, out, lse, inner, w.inner_bytes, hip_stream, 1, nullptr, nullptr, nullptr, false, false, false,
+                         emm::AttnParts{ws + w.out_shared, reinterpret_cast<const float*>(ws + w.lse_shared), req_shared_len});
     st = attention(own, q, k_cache, v_cache, out, lse_own, inner, w.inner_bytes, hip_stream, 1);
     if (st != EMM_OK) return st;
     // 3. the members' rows: both parts into one
-    const hipError_t err = emm::launch_attn_merge_parts(view_of(own), req_shared_len, ws + w.out_shared,
+    const hipError_t err = emm::launch_attn_merge_parts(own_view, req_shared_len, ws + w.out_shared,
                                                         reinterpret_cast<const float*>(ws + w.lse_shared), lse_own, out, lse,
                                                         static_cast<hipStream_t>(hip_stream));
     return err == hipSuccess ? EMM_OK : EMM_ERR_LAUNCH;

@@ -429,6 +429,7 @@ __device__ inline float* part_base(void* workspace, int ws_pieces, int xcd, int 
 struct KernArgs {
     AttnArgs a;
     LaunchShape L;
+    AttnParts parts;        // the PARTS instantiation's
 };
 typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
 
@@ -436,11 +437,12 @@ typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
 // workspace), by the whole workgroup.  CAREFUL = false is the fast way described at the top; if some row's weights
 // overflowed on the way (see OVERFLOW_LIMIT) it writes nothing and hands the item to the CAREFUL = true
 // instantiation, which takes the true running maximum before every tile's exponentials and cannot overflow.  `smem`: the 128 KB of LDS of the workgroup, K ring, then V ring.
-template <bool CAUSAL>
+// PARTS: the rows' attention over other keys is there already and is merged with this one before it is stored.
+template <bool CAUSAL, bool PARTS>
 __device__ void attend_unit_carefully(unsigned long long kernargs, int xcd, int in_xcd, lds_bytes lds);
 
-template <bool CAUSAL, bool CAREFUL, bool STREAM>
-__device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, const int xcd, const int in_xcd, UnitPlan plan,
+template <bool CAUSAL, bool CAREFUL, bool STREAM, bool PARTS>
+__device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, const AttnParts& parts, const int xcd, const int in_xcd, UnitPlan plan,
                                    unsigned char* smem)
 {
     constexpr int V_SM = NBUF * KV_BYTES;                    // byte offset of the V buffers
@@ -1031,7 +1033,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         const int any = v0[0] | v0[1] | v0[2] | v0[3] | v1[0] | v1[1] | v1[2] | v1[3];
         if (__builtin_amdgcn_readfirstlane(any) != 0) {
             __syncthreads();                                 // all have read the votes before the second pass refills the rings
-            attend_unit_carefully<CAUSAL>((unsigned long long)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), xcd, in_xcd,
+            attend_unit_carefully<CAUSAL, PARTS>((unsigned long long)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), xcd, in_xcd,
                                           (lds_bytes)smem);
             // the wave ends here: said in so many words, because otherwise the accumulators count as live across
             // the call and are kept in private memory from here to the epilogue on the fast path too
@@ -1083,8 +1085,41 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         const int e_wave = t2 >> 6, e_lane = t2 & 63;
         const int e_l32 = e_lane & 31, e_h32 = e_lane >> 5;
         const float l_tot = pair_sum(l_run);                 // partner lane is in the same state
-        const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
+        float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         unsigned char* stage = smem + e_wave * (32 * OUT_STRIDE);        // this wave's 32 rows, OUT_STRIDE bytes apart
+        const int e_row = row0 + e_wave * 32 + e_l32;
+        const int e_tok = L.by_G.quotient(min(e_row, n_rows - 1));
+        const long long e_head = ((long long)first_row + e_tok) * b.num_q_heads + kvh * G + (min(e_row, n_rows - 1) - e_tok * G);
+        float e_lse = (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
+        // The other part's rows: the convex combination of both by their softmax denominators.  This part's weight goes into its normalisation, the other's
+        // to the lanes that store the row, behind it in LDS.  (A kernel of its own for it, attn_merge.hip, was the fifth of a shared prefill: 64 questions of 4
+        // tokens on 8 videos of 16384 83.8 -> 82.9 us, 64 of 2 to 20 over 8192 shared and up to 508 own tokens 140.0 -> 134.5, 40 of up to 30 on 32 / 8 heads
+        // over 16000 232.5 -> 229.3; with the other part's rows asked for where they are stored 84.0, 138.1 and 231.7.)
+        const bool other = PARTS && parts.req_len[r] > 0;
+        const long long q_row0 = first_row;
+        const int t_add = L.by_G.quotient(4), g_add = 4 - t_add * G;      // row + 4 is token + t_add, head + g_add (mod G)
+        const int first = row0 + e_wave * 32 + (e_lane >> 4);
+        int o_tok = L.by_G.quotient(first), o_g = first - o_tok * G;
+        bf16x8 theirs[PARTS ? 8 : 1];                        // of the rows that this lane stores, asked for at once
+        if constexpr (PARTS) {
+            if (other) {
+                const float ls = parts.lse[e_head];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int row = min(first + 4 * j, n_rows - 1), tok = L.by_G.quotient(row);
+                    theirs[j] = *(const bf16x8*)((const __bf16*)parts.out + ((q_row0 + tok) * b.num_q_heads + kvh * G + (row - tok * G)) * D + (e_lane & 15) * 8);
+                }
+                const float m = fmaxf(ls, e_lse);
+                float w_other = 0.f;
+                if (m > -INFINITY) {
+                    const float ws = __expf(ls - m), wo = __expf(e_lse - m), norm = 1.f / (ws + wo);
+                    inv *= wo * norm;
+                    w_other = ws * norm;
+                    e_lse = m + __logf(ws + wo);
+                }
+                if (e_h32 == 0) *(float*)(stage + e_l32 * OUT_STRIDE + 256) = w_other;
+            }
+        }
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
@@ -1095,24 +1130,26 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
                 for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o_acc[nb][4 * v4 + e] * inv);
                 *(bf16x4*)(stage + e_l32 * OUT_STRIDE + 2 * (32 * nb + 8 * v4 + 4 * e_h32)) = w;
             }
-        const int e_row = row0 + e_wave * 32 + e_l32;
-        if (a.lse != nullptr && e_h32 == 0 && e_row < n_rows) {
-            const int e_tok = L.by_G.quotient(e_row);
-            a.lse[((long long)first_row + e_tok) * b.num_q_heads + kvh * G + (e_row - e_tok * G)] =
-                (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
-        }
+        if (a.lse != nullptr && e_h32 == 0 && e_row < n_rows) a.lse[e_head] = e_lse;
         // the wave's own LDS writes are visible to its own reads once they have completed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const long long q_row0 = first_row;
-        const int t_add = L.by_G.quotient(4), g_add = 4 - t_add * G;      // row + 4 is token + t_add, head + g_add (mod G)
-        const int first = row0 + e_wave * 32 + (e_lane >> 4);
-        int o_tok = L.by_G.quotient(first), o_g = first - o_tok * G;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int in_wave = (e_lane >> 4) + 4 * j;       // lanes 16k .. 16k+15 take row 4j + k
             if (first + 4 * j < n_rows) {
-                const uint4 v = *(const uint4*)(stage + in_wave * OUT_STRIDE + (e_lane & 15) * 16);
-                *(uint4*)((__bf16*)a.out + ((q_row0 + o_tok) * b.num_q_heads + kvh * G + o_g) * D + (e_lane & 15) * 8) = v;
+                uint4 v = *(const uint4*)(stage + in_wave * OUT_STRIDE + (e_lane & 15) * 16);
+                const long long at = ((q_row0 + o_tok) * b.num_q_heads + kvh * G + o_g) * D + (e_lane & 15) * 8;
+                if constexpr (PARTS) {
+                    if (other) {
+                        const float w = *(const float*)(stage + in_wave * OUT_STRIDE + 256);
+                        const bf16x8 mine = __builtin_bit_cast(bf16x8, v);
+                        bf16x8 o;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)mine[e] + (float)theirs[j][e] * w);
+                        v = __builtin_bit_cast(uint4, o);
+                    }
+                }
+                *(uint4*)((__bf16*)a.out + at) = v;
             }
             o_tok += t_add;
             o_g += g_add;
@@ -1126,7 +1163,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
 // survive the call.  It reads the kernel's arguments from the kernel argument segment, whose address the kernel
 // hands over (asked for in here, in a function that is not a kernel, that address comes out as null), rather than
 // through a copy in private memory, and works the item's plan out again.
-template <bool CAUSAL>
+template <bool CAUSAL, bool PARTS>
 __device__ __attribute__((noinline)) void attend_unit_carefully(unsigned long long kernargs_v, int xcd_v, int in_xcd_v, lds_bytes lds_v)
 {
     // arguments arrive in vector registers; everything here is the same in all lanes, and the tile loads want their
@@ -1141,10 +1178,10 @@ __device__ __attribute__((noinline)) void attend_unit_carefully(unsigned long lo
     const LaunchShape& L = ka->L;
     const UnitPlan plan = plan_unit(a.b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
-    attend_unit<CAUSAL, true, false>(a, L, xcd, in_xcd, plan, (unsigned char*)lds);
+    attend_unit<CAUSAL, true, false, PARTS>(a, L, ka->parts, xcd, in_xcd, plan, (unsigned char*)lds);
 }
 
-template <bool CAUSAL, bool STREAM>
+template <bool CAUSAL, bool STREAM, bool PARTS>
 __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * KV_BYTES];   // K ring, then V ring
@@ -1156,7 +1193,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_bf16_d128_kernel(KernArgs ka
     const int xcd = blockIdx.x % NUM_XCD, in_xcd = blockIdx.x / NUM_XCD;
     const UnitPlan plan = plan_unit(b, L, xcd, in_xcd);
     if (plan.pair < 0) return;
-    attend_unit<CAUSAL, false, STREAM>(a, L, xcd, in_xcd, plan, smem);
+    attend_unit<CAUSAL, false, STREAM, PARTS>(a, L, ka.parts, xcd, in_xcd, plan, smem);
 }
 
 // One workgroup's share of the merge of a unit planned for PARTS pieces and cut into `cut` of them: the columns (threads of
@@ -1455,7 +1492,16 @@ static bool read_once(const AttnArgs& a, const LaunchShape& L)
            pairs * b.max_pages * b.page_size * (4 * D) > STREAM_BYTES;
 }
 
-hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream)
+// Does a pass over this batch merge with another part of its rows as it goes?  Where no unit can be cut along the keys: pieces are merged by a kernel of their own.
+bool attn_bf16_d128_takes_parts(const BatchView& b)
+{
+    LaunchShape L;
+    long long slots = 0;
+    launch_shape(b, true, L, slots);
+    return L.ws_pieces == 0;
+}
+
+hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream, const AttnParts& parts)
 {
     const BatchView& b = a.b;
     if (b.total_new_tokens == 0 || b.num_reqs == 0) return hipSuccess;
@@ -1466,12 +1512,17 @@ hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream)
     const long long per_xcd = slots + (L.split ? EXTRA_PER_XCD : 0);
     const long long grid = NUM_XCD * per_xcd;
     if (grid > 0x3fffffff) return hipErrorInvalidValue;
-    if (a.causal)
-        hipLaunchKernelGGL((attn_bf16_d128_kernel<true, false>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
-    else if (read_once(a, L))
-        hipLaunchKernelGGL((attn_bf16_d128_kernel<false, true>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
-    else
-        hipLaunchKernelGGL((attn_bf16_d128_kernel<false, false>), dim3((unsigned)grid), dim3(NTHREADS), 0, stream, KernArgs{a, L});
+    if (parts.req_len != nullptr && (!a.causal || L.ws_pieces > 0)) return hipErrorInvalidValue;
+    auto go = [&](auto causal, auto streamed, auto with_parts) {
+        hipLaunchKernelGGL((attn_bf16_d128_kernel<decltype(causal)::value, decltype(streamed)::value, decltype(with_parts)::value>), dim3((unsigned)grid),
+                           dim3(NTHREADS), 0, stream, KernArgs{a, L, parts});
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    if (parts.req_len != nullptr) go(yes{}, no{}, yes{});
+    else if (a.causal) go(yes{}, no{}, no{});
+    else if (read_once(a, L)) go(no{}, yes{}, no{});
+    else go(no{}, no{}, no{});
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || L.ws_pieces == 0) return err;              // nothing can have been cut along the keys
     hipLaunchKernelGGL(attn_bf16_merge_kernel, dim3(NUM_XCD * MERGE_PER_XCD), dim3(NTHREADS), 0, stream, a, L);

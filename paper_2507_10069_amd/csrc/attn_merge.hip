@@ -7,7 +7,8 @@
 // of key sets is the convex combination of the parts' results with weights exp(lse_part - lse_all), which this
 // kernel forms, row by row:
 //     out = (e^{lse_a} out_a + e^{lse_b} out_b) / (e^{lse_a} + e^{lse_b}),   lse = log(e^{lse_a} + e^{lse_b}).
-// Rows of requests that are in no sharing group have no first part and stay as they are.
+// Rows of requests that are in no sharing group have no first part and stay as they are.  This kernel is for own passes whose units may be cut along the
+// keys (attn_bf16_d128_takes_parts); the others merge in the attention kernel.
 //
 // Pure data movement, HBM bound: per row two 256-byte reads, one 256-byte write and three floats.  A row is done
 // by 16 lanes (8 channels, 16 bytes each), a workgroup does 16 rows.

@@ -56,6 +56,13 @@ struct AttnArgs {
     int32_t own_pages = 0;         // 1: the caller says that few pages, if any, are in the tables of two requests, and the tables no wider than the contexts (speed only)
 };
 
+// What a prefill pass adds to its result: attention of the same rows over other keys (own pass of a prefill with shared prefixes)
+struct AttnParts {
+    const void* out = nullptr;            // [T][H][d]
+    const float* lse = nullptr;           // [T][H]
+    const int32_t* req_len = nullptr;     // [B]: keys that the other part of a request's rows is over; none where <= 0
+};
+
 // Shared-prefix units of a decode batch (device arrays; see emm_shared_prefix in emm.h)
 struct SharedPrefixView {
     const int32_t* unit_first_req;   // [U]
@@ -88,7 +95,9 @@ inline Divisor divisor_of(int d)                                    // d >= 1
 hipError_t launch_kv_scatter(const BatchView& b, const void* k_new, const void* v_new, void* k_cache,
                              void* v_cache, int elt_bytes, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream);
-hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream);
+// (parts: only of a batch that is causal and nothing of which is cut along the keys, see attn_bf16_d128_takes_parts)
+hipError_t launch_attn_bf16_d128(const AttnArgs& a, hipStream_t stream, const AttnParts& parts = AttnParts{});
+bool attn_bf16_d128_takes_parts(const BatchView& b);
 size_t attn_bf16_d128_workspace_bytes(const BatchView& b);   // what launch_attn_bf16_d128 wants behind AttnArgs::workspace
 // host only: how launch_attn_bf16_d128 would lay the batch out (new_lens: host copy); arrays of 8 are per XCD
 void attn_bf16_d128_plan_host(const BatchView& b, const int32_t* new_lens, bool has_workspace, int32_t* shape6, long long* grid,

@@ -150,6 +150,30 @@ def test_one_part_far_above_the_other(where):
     print("   errors (max, mean, lse):", _compare(wl, dw), flush=True)
 
 
+# own tables of 23 key tiles, whose pass merges both parts on its way out, and of 24, behind which a kernel does; whole row tiles, row halves and several
+# row tiles of a request; requests in no group; planted: a key of the own part whose scores overflow, so that its unit is done again by the careful pass
+@pytest.mark.parametrize("H,Hkv", [(28, 4), (16, 2)])
+@pytest.mark.parametrize("own,new,planted", [(1472 - 40, 40, False), (1536 - 40, 41, False), (0, 1, False), (300, 12, True), (1600, 12, True)])
+def test_own_parts_at_the_line_of_the_separate_merge(H, Hkv, own, new, planted):
+    print("case own parts", H, Hkv, own, new, planted, flush=True)
+    wl = _case([1024 + own, 1024 + own // 2, 1024, 90, 1024 + own // 3], [new, max(1, new - 7), 1 + new // 2, 30, new], [0, 0, 0, 1, 0], [1024] * 3 + [0, 1024], H=H, Hkv=Hkv,
+               seed=57)
+    if planted:
+        wl.q[:] = W.to_bf16_bits(np.full(wl.q.shape, 4.0, np.float32))
+        _plant_key(wl, 0, 1024 + 150, 4.0)
+        _plant_key(wl, 3, 80, 4.0)
+    dw, plan = _run_shared(wl)
+    assert plan["num_groups"] == 1
+    print("   errors (max, mean, lse):", _compare(wl, dw), flush=True)
+    first = B.DeviceWorkload.to_numpy_bits(dw.out).tobytes()
+    ps = dw.prefill_shared
+    ps["workspace"].fill_(0xA5)
+    dw.out.zero_()
+    B.emm_prefill_attn_shared(ps["groups"], ps["own"], ps["dev"]["req_shared_len"], dw.q, dw.k_cache, dw.v_cache, dw.out, None, ps["workspace"])
+    torch.cuda.synchronize()
+    assert first == B.DeviceWorkload.to_numpy_bits(dw.out).tobytes()
+
+
 def test_without_lse_and_repeated_calls_are_deterministic():
     wl = W.prefill_shared_config("prefill_shared_image_b32", 8)
     dw, plan = _run_shared(wl)
