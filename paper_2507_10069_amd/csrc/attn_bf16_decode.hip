@@ -1105,6 +1105,18 @@ bool has_hints(const BatchView& b, const SharedPrefixView& sv)
     return sv.planned_tiles > 0 || (sv.max_own_tiles > 0 && sv.max_own_tiles < table_tiles_of(b));
 }
 
+// Units save reading the shared keys again, but a unit's pieces are longer to compute (two groups of rows), its rows have more records to merge and a
+// small batch with units has no folded merge.  Where all there is to read, shared keys once, fits the L2s (8 of 4 MiB), the members after the first find it
+// there, and every context by itself is quicker: of 160 batches of 2 to 56 contexts in groups of 2 to 8, 28 / 4 and 32 / 8 heads, all 21 below 27 MB, by 4 to 54 %
+// (3 of 2432 shared tokens in one unit 10.9 and 7.9 us, 8 of 1856 in two 13.3 and 9.1, 10 of 1856 in two 15.4 and 10.0, 8 of 1792 in four 12.1 and 11.6); from there to
+// 60 MB it is .68 to 1.53, above the units are mostly quicker.  Only where the caller says how much there is and how long the longest parts are.
+constexpr long long ALONE_BYTES = 26ll << 20;
+bool better_alone(const BatchView& b, const SharedPrefixView& sv)
+{
+    return sv.planned_tiles > 0 && sv.max_own_tiles > 0 && sv.max_unit_tiles > 0 &&
+           (long long)sv.planned_tiles * b.num_kv_heads * (BK * D * 4) <= ALONE_BYTES;
+}
+
 // pieces of a context that the workspace of the batch without units and hints has room for at least
 long long pieces_reserved(const BatchView& b)
 {
@@ -1117,6 +1129,14 @@ long long pieces_reserved(const BatchView& b)
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
 {
     const DecodeShape S = plan(b, sv, LLONG_MAX);
+    if (sv.num_units > 0 && better_alone(b, sv)) {
+        // contexts up to the longest own part behind the longest shared one, within the records that the units would take
+        SharedPrefixView alone = {};
+        alone.max_own_tiles = (int32_t)std::min<long long>(INT32_MAX, (long long)sv.max_own_tiles + sv.max_unit_tiles);
+        const long long room = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit * (MAX_ROWS / MAX_G);
+        const DecodeShape A = plan(b, alone, room);
+        if ((long long)A.n_pairs * A.pieces_max <= room) return A;
+    }
     if (sv.num_units > 0 || !has_hints(b, sv) || S.pieces_max <= pieces_reserved(b)) return S;
     const long long room = std::max<long long>(pieces_reserved(b), plan(b, SharedPrefixView{}, LLONG_MAX).pieces_max);
     return S.pieces_max <= room ? S : plan(b, sv, room * S.n_pairs);
@@ -1134,7 +1154,7 @@ size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S)
 
 size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView& sv)
 {
-    DecodeShape S = attn_bf16_decode_shape(b, sv);
+    DecodeShape S = sv.num_units > 0 ? plan(b, sv, LLONG_MAX) : attn_bf16_decode_shape(b, sv);         // (units that are not used: never more)
     if (sv.num_units == 0 && !has_hints(b, sv)) S.pieces_max = (int)std::max<long long>(S.pieces_max, pieces_reserved(b));
     return attn_bf16_decode_workspace_bytes(S);
 }
@@ -1251,7 +1271,8 @@ hipError_t launch_decode(const AttnArgs& a, const SharedPrefixView& sv, const De
 hipError_t launch_attn_bf16_decode(const AttnArgs& a, const SharedPrefixView& sv, const DecodeShape& S, bool fused, hipStream_t stream)
 {
     // without units only the bounds matter: the plain kernels, cut by the sharper plan
-    if (sv.num_units > 0) return fused ? launch_decode<true, true>(a, sv, S, stream) : launch_decode<true, false>(a, sv, S, stream);
+    // (a shape without unit pairs: the contexts by themselves, see better_alone)
+    if (sv.num_units > 0 && S.n_unit_pairs > 0) return fused ? launch_decode<true, true>(a, sv, S, stream) : launch_decode<true, false>(a, sv, S, stream);
     return fused ? launch_decode<false, true>(a, sv, S, stream) : launch_decode<false, false>(a, sv, S, stream);
 }
 

@@ -419,6 +419,35 @@ def test_decode_shared_prefix_parity(name, H, Hkv, ctx, new, group, shared, n_un
     _compare(wl, dw)
 
 
+# below the 26 MiB of K and V from which planned units are used (each context by itself, into a workspace of the units' size) and above; 32-key tiles
+@pytest.mark.parametrize("H,Hkv,ctx,group,shared", [(28, 4, [1700, 1500, 1501, 1600], [0] * 4, [1472] * 4), (28, 4, [4096 + 40 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4096] * 6),
+                                                    (28, 4, [4352 + 150 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4352] * 6), (32, 8, [1024, 1055, 1056, 1500, 90], [0, 0, 0, 0, 1], [1024] * 4 + [0]),
+                                                    (16, 1, [9000, 9001, 8992 + 31], [0, 0, 0], [8992] * 3)])
+def test_units_that_are_not_worth_it(H, Hkv, ctx, group, shared):
+    print("case alone", H, Hkv, ctx, flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+    wl = W.build_workload("alone_or_units", "causal", "bf16", 1501, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16, prefix_lens=ctx,
+                          new_lens=[1] * len(ctx), share_group=group, shared_len=shared)
+    dw = _gpu_run(wl)
+    plan = dw.plan_shared()
+    assert plan["num_units"] >= 1
+    room = dw.shared_workspace.numel()
+    guarded = torch.full((room + 4096,), 0xff, dtype=torch.uint8, device="cuda")
+    dw.shared_workspace = guarded[:room]
+    for call in (dw.attention_shared, lambda: dw.decode_step(shared=True)):
+        dw.out.zero_()
+        dw.lse.zero_()
+        call()
+        torch.cuda.synchronize()
+        _compare(wl, dw)
+    assert bool((guarded[room:] == 0xff).all())
+    first = bits(dw.out).tobytes()
+    dw.out.zero_()
+    dw.attention_shared()
+    torch.cuda.synchronize()
+    assert bits(dw.out).tobytes() == first
+
+
 FUSED_CASES = [(c[0], c[2], c[3], c[4], c[5], None, None) for c in DECODE_CASES if c[1] == "causal" and c[0] != "decode_g17"] + \
               [(c[0], c[1], c[2], c[3], c[4], c[5], c[6]) for c in SHARED_CASES]
 
