@@ -1088,9 +1088,12 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         unsigned char* stage = smem + e_wave * (32 * OUT_STRIDE);        // this wave's 32 rows, OUT_STRIDE bytes apart
         const int e_row = row0 + e_wave * 32 + e_l32;
-        const int e_tok = L.by_G.quotient(min(e_row, n_rows - 1));
-        const long long e_head = ((long long)first_row + e_tok) * b.num_q_heads + kvh * G + (min(e_row, n_rows - 1) - e_tok * G);
-        float e_lse = (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY;
+        auto head_of = [&]() -> long long {                  // of this lane's row, in [T][H]
+            const int row = PARTS ? min(e_row, n_rows - 1) : e_row, tok = L.by_G.quotient(row);
+            return ((long long)first_row + tok) * b.num_q_heads + kvh * G + (row - tok * G);
+        };
+        auto own_lse = [&]() -> float { return (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY; };
+        float both_lse = 0.f;
         // The other part's rows: the convex combination of both by their softmax denominators.  This part's weight goes into its normalisation, the other's
         // to the lanes that store the row, behind it in LDS.  (A kernel of its own for it, attn_merge.hip, was the fifth of a shared prefill: 64 questions of 4
         // tokens on 8 videos of 16384 83.8 -> 82.9 us, 64 of 2 to 20 over 8192 shared and up to 508 own tokens 140.0 -> 134.5, 40 of up to 30 on 32 / 8 heads
@@ -1103,19 +1106,20 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         bf16x8 theirs[PARTS ? 8 : 1];                        // of the rows that this lane stores, asked for at once
         if constexpr (PARTS) {
             if (other) {
-                const float ls = parts.lse[e_head];
+                const float ls = parts.lse[head_of()];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int row = min(first + 4 * j, n_rows - 1), tok = L.by_G.quotient(row);
                     theirs[j] = *(const bf16x8*)((const __bf16*)parts.out + ((q_row0 + tok) * b.num_q_heads + kvh * G + (row - tok * G)) * D + (e_lane & 15) * 8);
                 }
-                const float m = fmaxf(ls, e_lse);
+                const float lo = own_lse(), m = fmaxf(ls, lo);
+                both_lse = lo;
                 float w_other = 0.f;
                 if (m > -INFINITY) {
-                    const float ws = __expf(ls - m), wo = __expf(e_lse - m), norm = 1.f / (ws + wo);
+                    const float ws = __expf(ls - m), wo = __expf(lo - m), norm = 1.f / (ws + wo);
                     inv *= wo * norm;
                     w_other = ws * norm;
-                    e_lse = m + __logf(ws + wo);
+                    both_lse = m + __logf(ws + wo);
                 }
                 if (e_h32 == 0) *(float*)(stage + e_l32 * OUT_STRIDE + 256) = w_other;
             }
@@ -1130,7 +1134,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
                 for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o_acc[nb][4 * v4 + e] * inv);
                 *(bf16x4*)(stage + e_l32 * OUT_STRIDE + 2 * (32 * nb + 8 * v4 + 4 * e_h32)) = w;
             }
-        if (a.lse != nullptr && e_h32 == 0 && e_row < n_rows) a.lse[e_head] = e_lse;
+        if (a.lse != nullptr && e_h32 == 0 && e_row < n_rows) a.lse[head_of()] = other ? both_lse : own_lse();
         // the wave's own LDS writes are visible to its own reads once they have completed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
