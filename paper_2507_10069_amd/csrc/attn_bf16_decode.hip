@@ -19,8 +19,9 @@
 //               idle; the kernel is bound by the rate at which blocks arrive from HBM.
 //   merge 1   = the 4 waves' (maximum, row sum, accumulator) are combined through LDS;
 //   merge 2   = a pair with several pieces leaves one record per piece in the workspace, and the last of its workgroups
-//               (small batches: see FOLD_PIECES) or attn_bf16_decode_merge_kernel combines them; a pair with one piece writes
-//               its output directly.  Both kernels derive the piece count from the lengths.
+//               (small batches: see FOLD_PIECES), attn_bf16_decode_merge_kernel or, where rows have few pieces,
+//               attn_bf16_decode_merge_rows_kernel combines them; a pair with one piece writes its output directly.  All derive
+//               the piece count from the lengths.
 //
 // Shared prefixes (Section 3.3: requests repeat system prompts and images).  Requests whose leading pages
 // are the same physical pages can be given as a UNIT: up to 32 / G consecutive requests and the length they
@@ -28,7 +29,7 @@
 // end of the grid take the shared part, with the query rows of all the unit's requests side by side in the
 // two groups of 16 rows, while the requests' own workgroups start behind the shared part; the merge
 // kernel adds the records of both.  Built as a second instantiation (SHARED) so that the plain path pays
-// nothing for it.
+// nothing for it.  Units of a batch that the L2s can hold are left aside: see better_alone.
 //
 // Fused step (FUSED instantiation, emm_decode_step): the query token's own K/V row need not be in the pool
 // beforehand.  The wave whose block holds the token's slot asks for the row in k_new / v_new before its first fetch and
