@@ -171,12 +171,12 @@ emm_status emm_decode_attn_static(const emm_batch *batch, const void *q, const v
  * packed into common row tiles for the shared keys, which are then streamed once per group and row tile; each
  * request's remaining keys (the rest of its cached prefix and its new tokens, causal) are done per request; and the
  * two partial results of every row are merged by their softmax denominators -- the same attention as
- * emm_prefill_attn up to rounding (both partial outputs pass through bf16).
+ * emm_prefill_attn up to rounding (partial outputs pass through bf16).
  *
  * emm_prefill_shared_plan_host finds the groups from HOST copies of the batch arrays (runs of consecutive requests
  * whose page tables agree on their leading pages; shared length a multiple of 64 tokens, at least
  * max(min_shared_tokens, 64); a group is formed only if its packed rows need fewer 256-row tiles than its members
- * apart).  The three steps cost two more kernel launches and a second pass over every output row than the one plain
+ * apart).  The steps cost one or two more kernel launches and a second pass over output rows than the one plain
  * call, so groups are only worth having when they save enough streaming: with key_tiles_plain / key_tiles_shared
  * the 64-key tiles that all 256-row work units together stream without and with the groups, the plan keeps its
  * groups only if key_tiles_plain - key_tiles_shared >= min_saved_key_tiles (0: always; negative: the library's
