@@ -294,6 +294,15 @@ def test_decode_plan_of_contexts_known_to_differ(n_req, H, Hkv, lo, hi, shortest
     assert S.pieces_max == -(-max(tiles) // S.tiles_per_piece)
 
 
+@pytest.mark.parametrize("n_req,H,Hkv,tokens,pairs", [(8, 28, 4, 900, True), (16, 28, 4, 400, True), (8, 28, 4, 1024, True), (8, 28, 4, 1025, False),
+                                                      (5, 32, 8, 720, True), (1, 32, 8, 3889, True), (1, 32, 8, 4097, False)])
+def test_decode_plan_takes_pieces_of_two_blocks_a_wave_while_each_has_a_compute_unit(n_req, H, Hkv, tokens, pairs):
+    """Pieces of four tiles are the quickest as long as there are at most 256 of them in all; from 257 on longer ones are."""
+    tiles = -(-tokens // 32)
+    S = _decode_plan(n_req, H, Hkv, 32 * tiles, planned_tiles=n_req * tiles, max_own_tiles=tiles)
+    assert (S.tiles_per_piece == 4) == pairs, S.tiles_per_piece
+
+
 @pytest.mark.parametrize("seed", range(20))
 def test_decode_plan_of_equal_contexts_is_cut_evenly(seed):
     """Pieces of equal contexts are as short as their number allows: no last piece that is a sliver beside the others."""
