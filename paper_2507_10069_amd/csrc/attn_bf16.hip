@@ -1085,7 +1085,7 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         const int e_wave = t2 >> 6, e_lane = t2 & 63;
         const int e_l32 = e_lane & 31, e_h32 = e_lane >> 5;
         const float l_tot = pair_sum(l_run);                 // partner lane is in the same state
-        float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
+        const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         unsigned char* stage = smem + e_wave * (32 * OUT_STRIDE);        // this wave's 32 rows, OUT_STRIDE bytes apart
         const int e_row = row0 + e_wave * 32 + e_l32;
         auto head_of = [&]() -> long long {                  // of this lane's row, in [T][H]
@@ -1094,10 +1094,10 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
         };
         auto own_lse = [&]() -> float { return (l_tot > 0.f) ? mc_run * 0.69314718055994530942f + logf(l_tot) : -INFINITY; };
         float both_lse = 0.f;
-        // The other part's rows: the convex combination of both by their softmax denominators.  This part's weight goes into its normalisation, the other's
-        // to the lanes that store the row, behind it in LDS.  (A kernel of its own for it, attn_merge.hip, was the fifth of a shared prefill: 64 questions of 4
-        // tokens on 8 videos of 16384 83.8 -> 82.9 us, 64 of 2 to 20 over 8192 shared and up to 508 own tokens 140.0 -> 134.5, 40 of up to 30 on 32 / 8 heads
-        // over 16000 232.5 -> 229.3; with the other part's rows asked for where they are stored 84.0, 138.1 and 231.7.)
+        // The other part's rows: the convex combination of both by their softmax denominators, in the steps of the kernel that does it where units are cut
+        // (attn_merge.hip), so that a row has the same bits whichever of the two merged it.  The row's weights go behind it in LDS.  (With that kernel as the fifth of a
+        // shared prefill: 64 questions of 4 tokens on 8 videos of 16384 83.8 -> 82.9 us, 64 of 2 to 20 over 8192 shared and up to 508 own tokens 140.0 -> 134.5, 40 of up to 30 on
+        // 32 / 8 heads over 16000 232.5 -> 229.3; with the other part's rows asked for where they are stored 84.0, 138.1 and 231.7.)
         const bool other = PARTS && parts.req_len[r] > 0;
         const long long q_row0 = first_row;
         const int t_add = L.by_G.quotient(4), g_add = 4 - t_add * G;      // row + 4 is token + t_add, head + g_add (mod G)
@@ -1114,14 +1114,13 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
                 }
                 const float lo = own_lse(), m = fmaxf(ls, lo);
                 both_lse = lo;
-                float w_other = 0.f;
+                f32x4 weights = {0.f, 0.f, 0.f, 0.f};        // theirs, this part's, what norms them; all 0: the row stays as it is
                 if (m > -INFINITY) {
-                    const float ws = __expf(ls - m), wo = __expf(lo - m), norm = 1.f / (ws + wo);
-                    inv *= wo * norm;
-                    w_other = ws * norm;
+                    const float ws = __expf(ls - m), wo = __expf(lo - m);
+                    weights = f32x4{ws, wo, 1.f / (ws + wo), 0.f};
                     both_lse = m + __logf(ws + wo);
                 }
-                if (e_h32 == 0) *(float*)(stage + e_l32 * OUT_STRIDE + 256) = w_other;
+                if (e_h32 == 0) *(f32x4*)(stage + e_l32 * OUT_STRIDE + 256) = weights;
             }
         }
 #pragma unroll
@@ -1145,12 +1144,12 @@ __device__ inline void attend_unit(const AttnArgs& a, const LaunchShape& L, cons
                 const long long at = ((q_row0 + o_tok) * b.num_q_heads + kvh * G + o_g) * D + (e_lane & 15) * 8;
                 if constexpr (PARTS) {
                     if (other) {
-                        const float w = *(const float*)(stage + in_wave * OUT_STRIDE + 256);
+                        const f32x4 w = *(const f32x4*)(stage + in_wave * OUT_STRIDE + 256);
                         const bf16x8 mine = __builtin_bit_cast(bf16x8, v);
                         bf16x8 o;
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)mine[e] + (float)theirs[j][e] * w);
-                        v = __builtin_bit_cast(uint4, o);
+                        for (int e = 0; e < 8; ++e) o[e] = (__bf16)merged_channel((float)theirs[j][e], w[0], (float)mine[e], w[1], w[2]);
+                        if (w[2] != 0.f) v = __builtin_bit_cast(uint4, o);
                     }
                 }
                 *(uint4*)((__bf16*)a.out + at) = v;

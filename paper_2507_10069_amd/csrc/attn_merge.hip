@@ -79,7 +79,7 @@ __global__ __launch_bounds__(THREADS) void attn_merge_parts_kernel(BatchView b, 
             const float inv = 1.f / (ws + wo);
             bf16x8 o;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = (__bf16)(((float)a[i] * ws + (float)c[i] * wo) * inv);
+            for (int i = 0; i < 8; ++i) o[i] = (__bf16)merged_channel((float)a[i], ws, (float)c[i], wo, inv);
             *(bf16x8*)(out + at) = o;
             merged = m + __logf(ws + wo);
         }

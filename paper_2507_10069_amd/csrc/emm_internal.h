@@ -63,6 +63,9 @@ struct AttnParts {
     const int32_t* req_len = nullptr;     // [B]: keys that the other part of a request's rows is over; none where <= 0
 };
 
+// A channel of two parts of a row, with their weights and 1 / (sum of the weights).  What is fused is written out, so that all that merge parts round alike.
+__device__ inline float merged_channel(float a, float wa, float c, float wc, float inv) { return fmaf(a, wa, c * wc) * inv; }
+
 // Shared-prefix units of a decode batch (device arrays; see emm_shared_prefix in emm.h)
 struct SharedPrefixView {
     const int32_t* unit_first_req;   // [U]

@@ -285,3 +285,43 @@ def test_group_tables_wider_than_their_contexts(shared, new, planted):
     dw.attention_prefill_shared()
     torch.cuda.synchronize()
     print("   errors (max, mean, lse):", _compare(wl, dw, _sample_tokens(wl, 16, seed=shared)), flush=True)
+
+
+def _own_behind_wider_tables(dw, tokens):
+    """The own pass's descriptor with rows of the page table that hold `tokens` tokens (what is behind a request's pages is never read)."""
+    ps = dw.prefill_shared
+    own = B.emm_batch.from_buffer_copy(ps["own"])
+    narrow = ps["dev"]["own_page_table"]
+    table = torch.zeros((narrow.shape[0], tokens // own.page_size), dtype=torch.int32, device="cuda")
+    table[:, :narrow.shape[1]] = narrow
+    own.max_pages_per_req, own.page_table = table.shape[1], table.data_ptr()
+    return own, table
+
+
+# Tables of 24 key tiles and more leave room for pieces, so a kernel of its own merges the two parts; contexts of up to 23 tiles are not cut behind them either (up to
+# 15 where a row tile is one of several rounds).  Same rows, same two parts: the result must not tell which of the two merged them.
+@pytest.mark.parametrize("H,Hkv,own,new", [(28, 4, 1472 - 40, 40), (28, 4, 0, 1), (28, 4, 300, 12), (16, 2, 700, 33), (32, 8, 200, 4), (8, 8, 900, 70)])
+@pytest.mark.parametrize("planted", [False, True])
+def test_parts_merged_on_the_way_out_have_the_bits_of_the_separate_merge(H, Hkv, own, new, planted):
+    print("case bits of both merges", H, Hkv, own, new, planted, flush=True)
+    wl = _case([1024 + own, 1024 + own // 2, 1024, 90, 1024 + min(own // 3, 400)], [new, max(1, new - 7), 1 + new // 2, 30, new], [0, 0, 0, 1, 0], [1024] * 3 + [0, 1024], H=H, Hkv=Hkv,
+               seed=59)
+    if planted:                                              # scores that overflow: the careful pass merges
+        wl.q[:] = W.to_bf16_bits(np.full(wl.q.shape, 4.0, np.float32))
+        _plant_key(wl, 0, 1024 + own // 2, 4.0)
+        _plant_key(wl, 3, 80, 4.0)
+    dw, plan = _run_shared(wl)
+    assert plan["num_groups"] == 1
+    bits = B.DeviceWorkload.to_numpy_bits
+    out, lse = bits(dw.out).tobytes(), dw.lse.cpu().numpy().tobytes()
+    ps = dw.prefill_shared
+    wide, table = _own_behind_wider_tables(dw, 2048)
+    # room for pieces in the wide pass and none in the narrow one: the two routes
+    assert B.emm_prefill_attn_workspace_size(wide) > 0 and B.emm_prefill_attn_workspace_size(ps["own"]) == 0
+    workspace = torch.full((B.emm_prefill_attn_shared_workspace_size(ps["groups"], wide),), 0xA5, dtype=torch.uint8, device="cuda")
+    dw.out.zero_()
+    dw.lse.zero_()
+    B.emm_prefill_attn_shared(ps["groups"], wide, ps["dev"]["req_shared_len"], dw.q, dw.k_cache, dw.v_cache, dw.out, dw.lse, workspace)
+    torch.cuda.synchronize()
+    assert bits(dw.out).tobytes() == out
+    assert dw.lse.cpu().numpy().tobytes() == lse
