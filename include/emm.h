@@ -238,7 +238,7 @@ emm_status emm_prefill_attn_shared(const emm_batch *groups, const emm_batch *own
  *   - req_unit[r] is the unit of request r or -1, req_shared_len[r] the shared_len of that unit or 0; units
  *     do not overlap.
  * emm_shared_prefix_plan_host derives such units from host copies of the batch arrays.  Where the hint and both bounds are given
- * and say that there is little to read, the contexts are attended one by one instead, which is then quicker.
+ * and say that there is little to read, with units and without them, the contexts are attended one by one instead, which is then mostly quicker.
  */
 typedef struct {
     int32_t num_units;                 /* U >= 0; with 0 the call is emm_decode_attn with a planning hint    */

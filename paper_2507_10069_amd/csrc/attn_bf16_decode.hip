@@ -1116,14 +1116,22 @@ bool has_hints(const BatchView& b, const SharedPrefixView& sv)
 
 // Units save reading the shared keys again, but a unit's pieces are longer to compute (two groups of rows), its rows have more records to merge and a
 // small batch with units has no folded merge.  Where all there is to read, shared keys once, fits the L2s (8 of 4 MiB), the members after the first find it
-// there, and every context by itself is quicker: of 160 batches of 2 to 56 contexts in groups of 2 to 8, 28 / 4 and 32 / 8 heads, all 21 below 27 MB, by 4 to 54 %
-// (3 of 2432 shared tokens in one unit 10.9 and 7.9 us, 8 of 1856 in two 13.3 and 9.1, 10 of 1856 in two 15.4 and 10.0, 8 of 1792 in four 12.1 and 11.6); from there to
-// 60 MB it is .68 to 1.53, above the units are mostly quicker.  Only where the caller says how much there is and how long the longest parts are.
-constexpr long long ALONE_BYTES = 26ll << 20;
+// there, and every context by itself is mostly quicker, unless that reads shared keys too often or cuts pieces for contexts that are not there: it is planned with nothing
+// known but the two bounds, every context as long as the longest could be, so what bounds both is the amount that this would be.  Up to 64 MiB of it alone takes
+// .53 to 1.06 of the time with units, K and V in the caches or not (144 batches of 2 to 44 contexts, 1 to 16 query heads on 1 to 8 KV heads: median .75; 3 of 2432 shared
+// tokens in one unit, 28 / 4 heads, 10.5 and 7.7 us, 8 of 1856 in two 11.2 and 7.7).  Up to 88 it is .64 to 1.02 from three query heads per KV head on and up to 1.23 with one
+// or two, whose units are one group of rows; up to 140 .52 to 1.51.  Far above: two contexts of 6016 shared tokens beside 40 of 100, 28 / 4 heads, 504 MiB, 11.6 and 27.3 us,
+// 32 of 2048 shared on 8 / 8 heads, 264 MiB, 12.7 and 18.7.  Only where the caller says how much there is and how long the longest parts are.
+constexpr long long ALONE_BYTES = 26ll << 20, ALONE_READ_BYTES = 88ll << 20, ALONE_READ_FEW_BYTES = 64ll << 20;
+constexpr int ALONE_FEW_HEADS = 2;
 bool better_alone(const BatchView& b, const SharedPrefixView& sv)
 {
+    constexpr long long TILE_BYTES = BK * D * 4;
+    const long long read = ((long long)sv.max_own_tiles + sv.max_unit_tiles) * TILE_BYTES;           // of one context and KV head, at most
+    const long long most = b.num_q_heads / b.num_kv_heads <= ALONE_FEW_HEADS ? ALONE_READ_FEW_BYTES : ALONE_READ_BYTES;
     return sv.planned_tiles > 0 && sv.max_own_tiles > 0 && sv.max_unit_tiles > 0 &&
-           (long long)sv.planned_tiles * b.num_kv_heads * (BK * D * 4) <= ALONE_BYTES;
+           (long long)sv.planned_tiles * b.num_kv_heads * TILE_BYTES <= ALONE_BYTES &&
+           read <= most / std::max(1ll, (long long)b.num_reqs * b.num_kv_heads);
 }
 
 // pieces of a context that the workspace of the batch without units and hints has room for at least
@@ -1143,8 +1151,12 @@ DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& s
         SharedPrefixView alone = {};
         alone.max_own_tiles = (int32_t)std::min<long long>(INT32_MAX, (long long)sv.max_own_tiles + sv.max_unit_tiles);
         const long long room = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit * (MAX_ROWS / MAX_G);
-        const DecodeShape A = plan(b, alone, room);
-        if ((long long)A.n_pairs * A.pieces_max <= room) return A;
+        DecodeShape A = plan(b, alone, room);
+        if ((long long)A.n_pairs * A.pieces_max <= room) {
+            A.late = S.late;                                 // (by the amount of work, which the plan of its own was not told)
+            A.stream = S.stream;
+            return A;
+        }
     }
     if (sv.num_units > 0 || !has_hints(b, sv) || S.pieces_max <= pieces_reserved(b)) return S;
     const long long room = std::max<long long>(pieces_reserved(b), plan(b, SharedPrefixView{}, LLONG_MAX).pieces_max);

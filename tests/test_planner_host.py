@@ -303,6 +303,33 @@ def test_decode_plan_takes_pieces_of_two_blocks_a_wave_while_each_has_a_compute_
     assert (S.tiles_per_piece == 4) == pairs, S.tiles_per_piece
 
 
+def _plan_of_units(H, Hkv, units, private):
+    """The plan of a batch of units (members, shared tokens, own tokens of each) and private contexts (requests, tokens), told all there is to tell."""
+    tiles = lambda tokens: -(-tokens // 32)
+    planned = sum(shared // 32 + n * tiles(own) for n, shared, own in units) + sum(n * tiles(tokens) for n, tokens in private)
+    return _decode_plan(sum(n for n, _, _ in units) + sum(n for n, _ in private), H, Hkv, max([s + o for _, s, o in units] + [t for _, t in private]), planned_tiles=planned,
+                        max_own_tiles=max([tiles(o) for _, _, o in units] + [tiles(t) for _, t in private]), num_units=len(units),
+                        max_unit_tiles=max(s // 32 for _, s, _ in units))
+
+
+# groups beside private chats, which one by one would all be planned as long as the longest; large groups of one query head per KV head, whose members
+# would read the shared keys 32 times
+@pytest.mark.parametrize("H,Hkv,units,private", [(28, 4, [(2, 6016, 60)], [(40, 100)]), (28, 4, [(2, 3008, 60)], [(30, 200)]), (32, 8, [(2, 2048, 60)], [(60, 60)]),
+                                                 (8, 8, [(32, 2048, 60)], []), (8, 8, [(32, 1984, 20)] * 2, []), (2, 2, [(32, 6400, 20)] * 2, []), (16, 8, [(7, 2048, 90), (4, 128, 90)], [])])
+def test_decode_plan_keeps_units_that_save_reading(H, Hkv, units, private):
+    S = _plan_of_units(H, Hkv, units, private)
+    assert S.n_unit_pairs == len(units) * Hkv
+    assert S.tiles_per_piece <= 10
+
+
+@pytest.mark.parametrize("H,Hkv,units,private", [(28, 4, [(3, 2432, 100)], []), (28, 4, [(4, 1856, 100)] * 2, []), (32, 8, [(5, 1856, 60)] * 2, []), (32, 8, [(4, 1024, 60)], [(1, 90)]),
+                                                 (2, 2, [(16, 1536, 100), (3, 704, 100)], [(1, 100)])])
+def test_decode_plan_leaves_units_aside_where_there_is_little_to_read(H, Hkv, units, private):
+    S = _plan_of_units(H, Hkv, units, private)
+    assert S.n_unit_pairs == 0 and S.pieces_unit <= 1
+    assert S.stream == 0 and S.late == 0                     # as the amount of work has it: all fits the caches
+
+
 @pytest.mark.parametrize("seed", range(20))
 def test_decode_plan_of_equal_contexts_is_cut_evenly(seed):
     """Pieces of equal contexts are as short as their number allows: no last piece that is a sliver beside the others."""
