@@ -14,6 +14,7 @@ import oracle
 from helpers import as_f64, err_stats
 from paper_2507_10069_amd import binding as B
 from paper_2507_10069_amd import workloads as W
+from test_planner_host import _decode_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -50,6 +51,18 @@ def _compare(wl, dw, tokens=None):
         assert mx <= F32_MAX_ABS, mx
     assert lse_err <= LSE_ABS, lse_err
     return mx, mean, lse_err
+
+
+def _plan_run(dw, units=True):
+    """The plan by which the library does dw's decode step, with the units and hints that it has or as the plain call."""
+    told = {k: getattr(dw.shared, k) for k in ("num_units", "planned_tiles", "max_own_tiles", "max_unit_tiles")} if units else {}
+    b = dw.batch
+    return _decode_plan(b.num_reqs, b.num_q_heads, b.num_kv_heads, b.max_pages_per_req * b.page_size, **told)
+
+
+def _units_run(dw):
+    """Units that the step with shared prefixes takes as such: all that were planned, or none where there is little to read."""
+    return _plan_run(dw).n_unit_pairs // dw.batch.num_kv_heads
 
 
 def _sample_tokens(wl, n, seed=0):
@@ -381,12 +394,15 @@ def test_cross_decode_shared_prefix_parity(name, H, Hkv, ctx, new, group, shared
     plan = dw.plan_shared()
     print("   units:", plan["num_units"], plan["unit_num_reqs"].tolist(), plan["unit_shared_len"].tolist(), flush=True)
     assert plan["num_units"] >= 1
-    dw.out.zero_()
-    dw.lse.zero_()
-    dw.attention_shared()
-    torch.cuda.synchronize()
-    print("   errors (max, mean, lse):", _compare(wl, dw), flush=True)
-    assert np.abs(as_f64(B.DeviceWorkload.to_numpy_bits(dw.out)) - plain).max() <= BF16_MAX_ABS
+    for hint in (True, False):                          # with it most of these units are left aside
+        dw.plan_shared(use_hint=hint)
+        assert hint or _units_run(dw) == plan["num_units"]
+        dw.out.zero_()
+        dw.lse.zero_()
+        dw.attention_shared()
+        torch.cuda.synchronize()
+        print("   units run", _units_run(dw), "errors (max, mean, lse):", _compare(wl, dw), flush=True)
+        assert np.abs(as_f64(B.DeviceWorkload.to_numpy_bits(dw.out)) - plain).max() <= BF16_MAX_ABS
 
 
 @pytest.mark.parametrize("name,H,Hkv,ctx,new,group,shared,n_units", SHARED_CASES)
@@ -413,24 +429,26 @@ def test_decode_shared_prefix_parity(name, H, Hkv, ctx, new, group, shared, n_un
     torch.cuda.synchronize()
     assert B.DeviceWorkload.to_numpy_bits(dw.out).tobytes() == first
     dw.plan_shared(use_hint=False)                      # without the hint and the bounds: the page table's width rules
+    assert _units_run(dw) == n_units
     dw.out.zero_()
     dw.attention_shared()
     torch.cuda.synchronize()
     _compare(wl, dw)
 
 
-# below the 26 MiB of K and V from which planned units are used (each context by itself, into a workspace of the units' size) and above; 32-key tiles
-@pytest.mark.parametrize("H,Hkv,ctx,group,shared", [(28, 4, [1700, 1500, 1501, 1600], [0] * 4, [1472] * 4), (28, 4, [4096 + 40 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4096] * 6),
-                                                    (28, 4, [4352 + 150 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4352] * 6), (32, 8, [1024, 1055, 1056, 1500, 90], [0, 0, 0, 0, 1], [1024] * 4 + [0]),
-                                                    (16, 1, [9000, 9001, 8992 + 31], [0, 0, 0], [8992] * 3)])
-def test_units_that_are_not_worth_it(H, Hkv, ctx, group, shared):
+# batches with little to read (each context by itself, into a workspace of the units' size), and one that reads too much that way; 32-key tiles
+@pytest.mark.parametrize("H,Hkv,ctx,group,shared,used", [
+    (28, 4, [1700, 1500, 1501, 1600], [0] * 4, [1472] * 4, False), (28, 4, [4096 + 40 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4096] * 6, False),
+    (28, 4, [4352 + 150 * i for i in range(6)], [0, 0, 0, 1, 1, 1], [4352] * 6, False), (32, 8, [1024, 1055, 1056, 1500, 90], [0, 0, 0, 0, 1], [1024] * 4 + [0], False),
+    (16, 1, [9000, 9001, 8992 + 31], [0, 0, 0], [8992] * 3, False), (28, 4, [3008 + 60] * 2 + [200 + i for i in range(30)], [0] * 2 + list(range(1, 31)), [3008] * 2 + [0] * 30, True)])
+def test_units_that_are_not_worth_it(H, Hkv, ctx, group, shared, used):
     print("case alone", H, Hkv, ctx, flush=True)
     bits = B.DeviceWorkload.to_numpy_bits
     wl = W.build_workload("alone_or_units", "causal", "bf16", 1501, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16, prefix_lens=ctx,
                           new_lens=[1] * len(ctx), share_group=group, shared_len=shared)
     dw = _gpu_run(wl)
     plan = dw.plan_shared()
-    assert plan["num_units"] >= 1
+    assert plan["num_units"] >= 1 and _units_run(dw) == (plan["num_units"] if used else 0)
     room = dw.shared_workspace.numel()
     guarded = torch.full((room + 4096,), 0xff, dtype=torch.uint8, device="cuda")
     dw.shared_workspace = guarded[:room]
@@ -471,15 +489,17 @@ def test_fused_decode_step_equals_scatter_then_attention(name, H, Hkv, ctx, new,
     assert bits(dw.out).tobytes() == bits(ref.out).tobytes()
     assert bits(dw.k_cache).tobytes() == bits(ref.k_cache).tobytes() and bits(dw.v_cache).tobytes() == bits(ref.v_cache).tobytes()
     assert np.array_equal(dw.lse.cpu().numpy(), ref.lse.cpu().numpy())
-    if group is not None:
-        ref.plan_shared()
+    for hint in (True, False) if group is not None else ():              # with the hint most of these units are left aside
+        plan = ref.plan_shared(use_hint=hint)
+        assert hint or _units_run(ref) == plan["num_units"]
         ref.out.zero_()
         ref.attention_shared()                          # pools already hold the new rows
         dw2 = B.DeviceWorkload(build())
-        dw2.plan_shared()
+        dw2.plan_shared(use_hint=hint)
         dw2.out.zero_()
         dw2.decode_step(shared=True)
         torch.cuda.synchronize()
+        _compare(dw2.wl, dw2)
         assert bits(dw2.out).tobytes() == bits(ref.out).tobytes()
         assert bits(dw2.k_cache).tobytes() == bits(ref.k_cache).tobytes() and bits(dw2.v_cache).tobytes() == bits(ref.v_cache).tobytes()
 
@@ -517,14 +537,18 @@ def test_random_decode_batches(seed):
     plain_out = bits(ref.out).copy()
     plan = ref.plan_shared()
     print("   units:", plan["num_units"], plan["unit_num_reqs"].tolist(), plan["unit_shared_len"].tolist(), flush=True)
-    ref.out.zero_()
-    ref.attention_shared()
-    torch.cuda.synchronize()
-    _compare(ref.wl, ref)
-    shared_out = bits(ref.out).copy()
-    for use_units, want in ((False, plain_out), (True, shared_out)):
+    shared_out = {}
+    for hint in (True, False):                              # with the hint most of these units are left aside
+        ref.plan_shared(use_hint=hint)
+        assert hint or _units_run(ref) == plan["num_units"]
+        ref.out.zero_()
+        ref.attention_shared()
+        torch.cuda.synchronize()
+        _compare(ref.wl, ref)
+        shared_out[hint] = bits(ref.out).copy()
+    for use_units, hint, want in ((False, True, plain_out), (True, True, shared_out[True]), (True, False, shared_out[False])):
         dw = B.DeviceWorkload(build())
-        dw.plan_shared()
+        dw.plan_shared(use_hint=hint)
         dw.out.zero_()
         dw.decode_step(use_units)
         torch.cuda.synchronize()
@@ -819,8 +843,9 @@ def test_decode_block_of_scores_that_are_minus_infinity(blocks):
         wl.k_cache[wl.page_table[:, blk], :, :, 0] = 0xFF7F  # the lowest bf16
     dw = _gpu_run(wl)
     _compare(wl, dw)
-    dw.plan_shared()
-    for fused in (False, True):
+    for hint, fused in ((True, False), (True, True), (False, False), (False, True)):
+        dw.plan_shared(use_hint=hint)                        # with the hint: each context by itself
+        assert _units_run(dw) == (0 if hint else 1)
         dw.out.zero_()
         if fused:
             dw.decode_step(True)
@@ -903,6 +928,7 @@ def test_page_sizes_decode(ps):
     plan = ref.plan_shared()
     print("   units:", plan["num_units"], plan["unit_num_reqs"].tolist(), plan["unit_shared_len"].tolist(), flush=True)
     assert plan["num_units"] == 2 and plan["unit_shared_len"].tolist() == [512, 256]
+    assert _units_run(ref) == 2
     ref.out.zero_()
     ref.attention_shared()
     torch.cuda.synchronize()
@@ -930,18 +956,19 @@ def test_calls_can_be_captured_in_a_hip_graph_and_replayed():
     decode = W.build_workload("graph_decode", "causal", "bf16", 1701, num_q_heads=28, num_kv_heads=4, head_dim=128,
                               page_size=16, prefix_lens=[2100, 2200, 900, 40], new_lens=[1, 1, 1, 1],
                               share_group=[0, 0, 1, 2], shared_len=[2048, 2048, 0, 0])
-    for wl, step in ((prefill, lambda d: d.step()), (decode, lambda d: (d.scatter(), d.attention_shared())),
-                     (decode, lambda d: d.decode_step(True))):
+    for wl, hint, step in ((prefill, True, lambda d: d.step()), (decode, True, lambda d: (d.scatter(), d.attention_shared())), (decode, True, lambda d: d.decode_step(True)),
+                           (decode, False, lambda d: (d.scatter(), d.attention_shared())), (decode, False, lambda d: d.decode_step(True))):
         eager = _gpu_run(wl)
         if wl is decode:
-            eager.plan_shared()
+            eager.plan_shared(use_hint=hint)
+            assert _units_run(eager) == (0 if hint else 1)   # with the hint: each context by itself
             eager.out.zero_()
             step(eager)
             torch.cuda.synchronize()
         want_out, want_k = bits(eager.out).tobytes(), bits(eager.k_cache).tobytes()
         dw = B.DeviceWorkload(wl)
         if wl is decode:
-            dw.plan_shared()
+            dw.plan_shared(use_hint=hint)
         side = torch.cuda.Stream()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.stream(side):
@@ -951,8 +978,9 @@ def test_calls_can_be_captured_in_a_hip_graph_and_replayed():
                 step(dw)
         for replay in range(3):
             dw.out.zero_()                              # eager work and a synchronisation between the replays
-            if dw.workspace is not None:
-                dw.workspace.fill_(0x5A)                # stale workspace contents must not matter
+            for workspace in (dw.workspace, getattr(dw, "shared_workspace", None)):
+                if workspace is not None:
+                    workspace.fill_(0x5A)               # stale workspace contents must not matter
             torch.cuda.synchronize()
             graph.replay()
             torch.cuda.synchronize()
