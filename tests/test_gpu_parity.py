@@ -689,7 +689,7 @@ def test_decode_rows_do_not_tell_which_kernel_merged_them(Hkv, ctx):
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
 
 
-# rows enough for a wave each in the second kernel (16 query heads per KV head: 320 and 256 rows; 255: four waves for a row), up to 4 pieces and up to 8,
+# rows enough for a wave each in the second kernel (16 query heads per KV head: 320 and 256 rows; 240: four waves for a row), up to 4 pieces and up to 8,
 # beside the folded merge and four waves for a row (G of them)
 @pytest.mark.parametrize("Hkv,ctx,G_of", [(2, [501, 40, 0, 130, 127, 128, 500, 300, 260, 17], (1, 4, 8, 9)), (2, [800, 700, 40, 0, 130, 127, 128, 500, 1020, 640], (1, 4, 8, 12)),
                                           (1, [1000] * 16, (5, 15))])
@@ -716,6 +716,51 @@ def test_decode_rows_merged_by_a_wave_each(Hkv, ctx, G_of):
         _, out_g, lse_g = run(G, like)
         assert out_g.tobytes() == np.ascontiguousarray(out[:, :, :G]).tobytes(), G
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
+
+
+def _ragged(n, longest):
+    """One long context, the others short: empty, one key, pieces of their own."""
+    return [longest] + [(37 * i * i + 11 * i) % 400 for i in range(1, n)]
+
+
+# every form of the kernel that has a wave for each row: up to 4 pieces and up to 8, in the context or in its unit; records asked for before the lengths are
+# known (ahead) and behind them; with units and without, masked and not; requests without a query token, contexts of one piece, of nothing (cross)
+@pytest.mark.parametrize("kind", ["causal", "cross"])
+@pytest.mark.parametrize("H,Hkv,ctx,members,shared,hint,pieces,ahead", [
+    (16, 1, _ragged(96, 1500), 0, 0, False, 8, 0), (16, 1, _ragged(128, 1200), 0, 0, False, 4, 0), (16, 1, _ragged(36, 640), 0, 0, False, 8, 1), (16, 1, _ragged(36, 400), 0, 0, False, 4, 1),
+    (28, 4, [2049 + 17 * i % 200 for i in range(24)], 4, 2048, True, 8, 1), (16, 1, [3201 + 17 * i % 60 for i in range(20)], 2, 3200, False, 8, 1),
+    (32, 8, [2100 + 37 * i for i in range(19)], 8, 2048, True, 8, 0), (32, 8, [1025 + 17 * i % 100 for i in range(16)], 8, 1024, False, 4, 1),
+    (16, 1, [321 + 17 * i % 50 for i in range(80)] + [3000], 2, 320, False, 4, 0)])
+def test_every_form_of_the_merge_with_a_wave_for_each_row(kind, H, Hkv, ctx, members, shared, hint, pieces, ahead):
+    print("case forms of the row merge", kind, H, Hkv, len(ctx), members, shared, flush=True)
+    n = len(ctx)
+    in_unit = n // members * members if members else 0
+    wl = W.build_workload("row_merge", kind, "bf16", 773, num_q_heads=H, num_kv_heads=Hkv, head_dim=128, page_size=16, prefix_lens=ctx,
+                          new_lens=[0 if i % 11 == 7 and i >= in_unit or i == n - 2 and not members else 1 for i in range(n)],
+                          share_group=[r // members if r < in_unit else r for r in range(n)] if members else None, shared_len=[shared if r < in_unit else 0 for r in range(n)] if members else None)
+    dw = B.DeviceWorkload(wl)
+    if members:
+        dw.plan_shared(use_hint=hint)
+        assert _units_run(dw) == in_unit // members
+    S = _plan_run(dw, units=bool(members))
+    most = max(S.pieces_max, S.pieces_unit if members else 0)
+    assert n * H >= 256 and S.ahead == ahead and (1 < most <= 4 if pieces == 4 else 4 < most <= 8), (most, S.ahead)
+    if not members:
+        assert n * Hkv * S.pieces_max > 512 or H // Hkv > 8                # not merged by the last workgroup
+    bits = B.DeviceWorkload.to_numpy_bits
+    workspace = dw.shared_workspace if members else dw.workspace
+    if kind == "causal":
+        dw.scatter()
+    attend = dw.attention_shared if members else dw.attention
+    first = None
+    for fill in (0xff, 0x5a):                                # NaN and other values wherever no record is written
+        workspace.fill_(fill)
+        dw.out.zero_()
+        attend()
+        torch.cuda.synchronize()
+        _compare(wl, dw)
+        assert first in (None, bits(dw.out).tobytes())
+        first = bits(dw.out).tobytes()
 
 
 # pieces of four tiles: waves with no block of 16 keys, one, and two, which are done side by side; the new token's row in each wave's first and
