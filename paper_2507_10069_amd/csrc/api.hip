@@ -110,12 +110,11 @@ emm_status attention(const emm_batch* b, const void* q, const void* k_cache, con
     if (sp != nullptr) {
         st = check_decode_shared(b, view, sp);
         if (st != EMM_OK) return st;
-        shape = emm::attn_bf16_decode_shape(view, shared_view_of(sp));
+        shape = emm::attn_bf16_decode_shape(view, shared_view_of(sp), &need);
     } else if (decode) {
-        shape = emm::attn_bf16_decode_shape(view, emm::SharedPrefixView{});
+        shape = emm::attn_bf16_decode_shape(view, emm::SharedPrefixView{}, &need);
     }
-    if (sp != nullptr || decode) need = emm::attn_bf16_decode_workspace_bytes(shape);
-    else if (b->dtype == EMM_BF16) need = emm::attn_bf16_d128_workspace_bytes(view);
+    if (sp == nullptr && !decode && b->dtype == EMM_BF16) need = emm::attn_bf16_d128_workspace_bytes(view);
     if (static_scratch) {
         // the decode kernels with the library's own fixed array in place of a workspace
         if (!decode) return EMM_ERR_UNSUPPORTED;

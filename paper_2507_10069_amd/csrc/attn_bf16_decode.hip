@@ -1143,24 +1143,33 @@ long long pieces_reserved(const BatchView& b)
 
 }  // namespace
 
-DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv, size_t* bytes)
 {
     const DecodeShape S = plan(b, sv, LLONG_MAX);
-    if (sv.num_units > 0 && better_alone(b, sv)) {
+    if (sv.num_units > 0) {
+        *bytes = attn_bf16_decode_workspace_bytes(S);
+        if (!better_alone(b, sv)) return S;
         // contexts up to the longest own part behind the longest shared one, within the records that the units would take
         SharedPrefixView alone = {};
         alone.max_own_tiles = (int32_t)std::min<long long>(INT32_MAX, (long long)sv.max_own_tiles + sv.max_unit_tiles);
         const long long room = (long long)S.n_pairs * S.pieces_max + (long long)S.n_unit_pairs * S.pieces_unit * (MAX_ROWS / MAX_G);
         DecodeShape A = plan(b, alone, room);
-        if ((long long)A.n_pairs * A.pieces_max <= room) {
-            A.late = S.late;                                 // (by the amount of work, which the plan of its own was not told)
-            A.stream = S.stream;
-            return A;
-        }
+        if ((long long)A.n_pairs * A.pieces_max > room) return S;
+        A.late = S.late;                                     // (by the amount of work, which the plan of its own was not told)
+        A.stream = S.stream;
+        return A;
     }
-    if (sv.num_units > 0 || !has_hints(b, sv) || S.pieces_max <= pieces_reserved(b)) return S;
-    const long long room = std::max<long long>(pieces_reserved(b), plan(b, SharedPrefixView{}, LLONG_MAX).pieces_max);
-    return S.pieces_max <= room ? S : plan(b, sv, room * S.n_pairs);
+    const long long room = !has_hints(b, sv) || S.pieces_max <= pieces_reserved(b) ? LLONG_MAX
+                           : std::max<long long>(pieces_reserved(b), plan(b, SharedPrefixView{}, LLONG_MAX).pieces_max);
+    const DecodeShape within = S.pieces_max <= room ? S : plan(b, sv, room * S.n_pairs);
+    *bytes = attn_bf16_decode_workspace_bytes(within);
+    return within;
+}
+
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv)
+{
+    size_t bytes = 0;
+    return attn_bf16_decode_shape(b, sv, &bytes);
 }
 
 bool attn_bf16_decode_applies(const BatchView& b)
@@ -1175,8 +1184,10 @@ size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S)
 
 size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView& sv)
 {
-    DecodeShape S = sv.num_units > 0 ? plan(b, sv, LLONG_MAX) : attn_bf16_decode_shape(b, sv);         // (units that are not used: never more)
-    if (sv.num_units == 0 && !has_hints(b, sv)) S.pieces_max = (int)std::max<long long>(S.pieces_max, pieces_reserved(b));
+    size_t bytes = 0;
+    DecodeShape S = attn_bf16_decode_shape(b, sv, &bytes);
+    if (sv.num_units > 0 || has_hints(b, sv)) return bytes;
+    S.pieces_max = (int)std::max<long long>(S.pieces_max, pieces_reserved(b));
     return attn_bf16_decode_workspace_bytes(S);
 }
 

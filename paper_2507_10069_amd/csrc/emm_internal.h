@@ -121,6 +121,9 @@ struct DecodeShape {
     enum { STREAM_NEVER, STREAM_PRIVATE /* those that no other request holds */, STREAM_BY_LENGTHS /* the same, of contexts that are long enough */ };
 };
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv);
+// bytes: what the call asks of its workspace.  With units it is what they take, used or left aside, so that which of the two a batch is
+// does not decide what is refused
+DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv, size_t* bytes);
 size_t attn_bf16_decode_workspace_bytes(const DecodeShape& S);
 // what a caller is told to bring: of a batch without units and hints enough for the same batch with any hints
 size_t attn_bf16_decode_reserve_bytes(const BatchView& b, const SharedPrefixView& sv);

@@ -227,6 +227,27 @@ def test_decode_shared_argument_checks():
     assert n.value == plain
 
 
+# units that are used, and those of batches with little to read, whose contexts are attended one by one, in one piece and in several
+@pytest.mark.parametrize("H,Hkv,reqs,own,unit,planned,used", [(32, 8, 10, 4, 576, 624, True), (28, 4, 3, 4, 76, 88, False), (128, 16, 20, 2, 4, 44, False)])
+def test_units_left_aside_need_the_workspace_of_units(H, Hkv, reqs, own, unit, planned, used):
+    from types import SimpleNamespace
+    from test_planner_host import _decode_plan
+    lib = B.load()
+    ok = SimpleNamespace(data_ptr=lambda: 4096)              # stands in for a device tensor; never dereferenced
+    ok_ptr = ctypes.c_void_p(4096)
+    hints = dict(num_units=1, planned_tiles=planned, max_own_tiles=own, max_unit_tiles=unit)
+    assert (_decode_plan(reqs, H, Hkv, 32 * (own + unit), **hints).n_unit_pairs > 0) == used
+    b = _batch(num_reqs=reqs, num_q_heads=H, num_kv_heads=Hkv, num_pages=4096, max_pages_per_req=2 * (own + unit), total_new_tokens=reqs, max_new_len=1,
+               page_table=ok, prefix_lens=ok, new_lens=ok, cu_new_lens=ok)
+    sp = B.make_shared_prefix(**hints, unit_first_req=ok, unit_num_reqs=ok, unit_shared_len=ok, req_unit=ok, req_shared_len=ok)
+    need = B.emm_decode_attn_shared_workspace_size(b, sp)
+
+    def call(workspace, given):
+        return lib.emm_decode_attn_shared(ctypes.byref(b), ctypes.byref(sp), ok_ptr, ok_ptr, ok_ptr, ok_ptr, None, workspace, given, None)
+    assert need > 0 and call(ok_ptr, need - 1) == B.EMM_ERR_WORKSPACE
+    assert call(None, need) == B.EMM_ERR_NULL
+
+
 def test_kv_pages_argument_checks():
     lib = B.load()
     ok_ptr = ctypes.c_void_p(4096)                       # never dereferenced: n == 0 or the checks fail first
