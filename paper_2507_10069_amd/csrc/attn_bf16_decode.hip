@@ -205,6 +205,13 @@ __device__ inline void add_weighted(f32x2_rec& acc, float wgt, f32x2_rec x)
     acc[1] += wgt * x[1];
 }
 
+// The same for a sum of weights: the first of some pieces, which scales what there is already, and the others.
+__device__ inline float add_weight(bool first, float l, float alpha, float wgt, float x)
+{
+#pragma clang fp contract(off)
+    return first ? fmaf(l, alpha, wgt * x) : fmaf(wgt, x, l);
+}
+
 // a launch without units passes none: arguments that lie closer together arrive sooner (16 contexts of 500 tokens, 28 / 4 heads, 8.46 and 8.25 us)
 struct NoUnits {};
 template <bool SHARED> using UnitsOf = std::conditional_t<SHARED, SharedPrefixView, NoUnits>;
@@ -799,14 +806,13 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_decode_merge_kernel(Attn
         }
         const float ref = m_new == -INFINITY ? 0.f : m_new;  // no piece of this wave so far: all weights are 0
         const float alpha = __builtin_amdgcn_exp2f((m - ref) * c_log2);
-        l *= alpha;
         acc *= alpha;
         m = m_new;
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
             const bool in = j0 + wave + u * WAVES < n;       // what is no piece may hold anything, infinities and NaN included
             const float wgt = __builtin_amdgcn_exp2f((ml[u][0] - ref) * c_log2);
-            l += wgt * (in ? ml[u][1] : 0.f);
+            l = add_weight(u == 0, l, alpha, wgt, in ? ml[u][1] : 0.f);
             add_weighted(acc, wgt, in ? val[u] : f32x2{0.f, 0.f});
         }
     };
@@ -929,14 +935,13 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void attn_bf16_decode_merge_rows_ke
             for (int u = w; u < PIECES; u += PARTS) m_new = fmaxf(m_new, u < n ? from.ml[u][0] : -INFINITY);
             const float ref = m_new == -INFINITY ? 0.f : m_new;          // no piece so far: all weights are 0
             const float alpha = __builtin_amdgcn_exp2f((m[w] - ref) * c_log2);
-            l[w] *= alpha;
             acc[w] *= alpha;
             m[w] = m_new;
 #pragma unroll
             for (int u = w; u < PIECES; u += PARTS) {
                 const bool in = u < n;                       // what is no piece may hold anything, infinities and NaN included
                 const float wgt = __builtin_amdgcn_exp2f(((in ? from.ml[u][0] : -INFINITY) - ref) * c_log2);
-                l[w] = fmaf(wgt, in ? from.ml[u][1] : 0.f, l[w]);
+                l[w] = add_weight(u == w, l[w], alpha, wgt, in ? from.ml[u][1] : 0.f);
                 add_weighted(acc[w], wgt, in ? from.val[u] : f32x2{0.f, 0.f});
             }
         }

@@ -718,6 +718,38 @@ def test_decode_rows_merged_by_a_wave_each(Hkv, ctx, G_of):
         assert lse_g.tobytes() == np.ascontiguousarray(lse[:, :, :G]).tobytes(), G
 
 
+# the same with units of two: records of the request and of its unit (256 rows; 240: four waves for a row), up to 4 pieces and up to 8
+@pytest.mark.parametrize("shared,own,pieces", [(640, 300, 8), (320, 150, 4), (512, 450, 8), (32, 900, 8), (960, 40, 8), (320, 640, 8)])
+def test_decode_rows_of_units_merged_by_a_wave_each(shared, own, pieces):
+    print("case a wave each, units", shared, own, flush=True)
+    bits = B.DeviceWorkload.to_numpy_bits
+    ctx = [shared + 1 + 97 * i % own for i in range(16)]
+
+    def run(G, like=None):
+        wl = W.build_workload("wave_each_units", "causal", "bf16", 775, num_q_heads=G, num_kv_heads=1, head_dim=128, page_size=16, prefix_lens=ctx,
+                              new_lens=[1] * 16, share_group=[i // 2 for i in range(16)], shared_len=[shared] * 16)
+        if like is not None:
+            wl.page_table, wl.k_cache, wl.v_cache, wl.k_new, wl.v_new = like.page_table, like.k_cache, like.v_cache, like.k_new, like.v_new
+            wl.q = np.ascontiguousarray(like.q[:, :G])
+        dw = B.DeviceWorkload(wl)
+        dw.plan_shared(use_hint=False)
+        S = _plan_run(dw)
+        most = max(S.pieces_max, S.pieces_unit)
+        assert _units_run(dw) == 8 and (1 < most <= 4 if pieces == 4 else 4 < most <= 8), most
+        dw.shared_workspace.fill_(0xff)                      # NaN wherever no record is written
+        dw.out.zero_()
+        dw.decode_step(True)
+        torch.cuda.synchronize()
+        _compare(wl, dw)
+        return wl, S.tiles_per_piece, bits(dw.out).reshape(16, G, 128), dw.lse.cpu().numpy().reshape(16, G)
+
+    like, tiles, out, lse = run(16)
+    _, tiles_15, out_15, lse_15 = run(15, like)
+    assert tiles_15 == tiles
+    assert out_15.tobytes() == np.ascontiguousarray(out[:, :15]).tobytes()
+    assert lse_15.tobytes() == np.ascontiguousarray(lse[:, :15]).tobytes()
+
+
 def _ragged(n, longest):
     """One long context, the others short: empty, one key, pieces of their own."""
     return [longest] + [(37 * i * i + 11 * i) % 400 for i in range(1, n)]
