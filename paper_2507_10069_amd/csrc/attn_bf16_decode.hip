@@ -988,7 +988,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void attn_bf16_decode_merge_rows_ke
 //                   done side by side.  (Contexts told to be equal, plan before and after, us: 28 / 4 heads, 8 of 900 tokens 7.37 and 6.83, with K and V not
 //                   in the caches 8.41 and 7.99, 16 of 400 7.07 and 6.32, 8.16 and 7.65, 2 of 3500 7.71 and 7.08; 32 / 8, 5 of 720 7.06 and 6.23, one of
 //                   3889 7.46 and 6.85.  A figure of its own for a chip that is half empty, .34 a tile, gained 3 to 10 % on single
-//                   pieces of 100 contexts of 500 to 1000 tokens and lost as much on 130 of 3400: not used)
+//                   pieces of 100 contexts of 500 to 1000 tokens and lost as much on 130 of 3400: not used.)  Contexts of up to 10 tiles are
+//                   in one piece or several as without it: 300 tokens in one piece and in three, 32 / 4 heads 5.3 and 5.7, 8 on 40 / 8 5.4 and 5.8, 16 / 8 5.1 and 5.4
 // What the host is told (SharedPrefixView) sharpens the plan: `max_own_tiles` / `max_unit_tiles` bound the
 // longest own part / shared part and with it the pieces per context that the grid must provide; `planned_tiles` is the
 // amount of work there is (32-key tiles per KV head, summed over contexts), by which contexts are known to DIFFER: half a piece
@@ -1012,6 +1013,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void attn_bf16_decode_merge_rows_ke
 constexpr double START_US = 6.0, TILE_HBM_US = 0.00248, TILE_CU_US = 0.45, MERGE_US = 3.0, WORKGROUP_US = 0.003;
 constexpr double TILE_CU_DIFFER_US = 0.42, WORKGROUP_DIFFER_US = 0.004;
 constexpr double PAIR_US = 0.5;
+constexpr int PAIR_FROM_TILES = 11;
 constexpr long long STATIC_RECORDS = (16ll << 20) / (MAX_G * REC_FLOATS * 4);
 
 // The merge kernel asks for records before it knows which of them there are when they are few in all, or when the amount of
@@ -1077,7 +1079,7 @@ DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_
             cost += START_US * 0.25 * (busy / WORKGROUPS_PER_ROUND) +
                     (last_round ? 0.5 * piece * (1.0 - (double)last_round / WORKGROUPS_PER_ROUND) : 0.0);
         if (S.n_unit_pairs > 0 || c.own > 1) cost += MERGE_US;
-        if (c.tpp <= PAIR_TILES && S.n_unit_pairs == 0 && c.grid <= WORKGROUPS_PER_ROUND / 2) cost -= PAIR_US;
+        if (c.tpp <= PAIR_TILES && own_tiles >= PAIR_FROM_TILES && S.n_unit_pairs == 0 && c.grid <= WORKGROUPS_PER_ROUND / 2) cost -= PAIR_US;
         return cost + (known ? WORKGROUP_DIFFER_US : WORKGROUP_US) * c.grid;
     };
     const int longest_piece = (int)std::max<long long>(MIN_TILES_PER_PIECE, std::min<long long>(MAX_TILES_PER_PIECE, longest));

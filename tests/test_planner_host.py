@@ -303,6 +303,14 @@ def test_decode_plan_takes_pieces_of_two_blocks_a_wave_while_each_has_a_compute_
     assert (S.tiles_per_piece == 4) == pairs, S.tiles_per_piece
 
 
+@pytest.mark.parametrize("n_req,H,Hkv,tokens,hint", [(1, 28, 4, 300, False), (1, 32, 4, 320, False), (8, 40, 8, 300, False), (1, 64, 8, 320, True), (8, 28, 4, 320, True), (64, 8, 1, 317, False)])
+def test_decode_plan_of_ten_tiles_is_one_piece(n_req, H, Hkv, tokens, hint):
+    """What pieces of two blocks a wave save does not make up for the merge of so short a context."""
+    tiles = -(-tokens // 32)
+    S = _decode_plan(n_req, H, Hkv, 32 * tiles, **(dict(planned_tiles=n_req * tiles, max_own_tiles=tiles) if hint else {}))
+    assert S.pieces_max == 1, S.tiles_per_piece
+
+
 def _plan_of_units(H, Hkv, units, private):
     """The plan of a batch of units (members, shared tokens, own tokens of each) and private contexts (requests, tokens), told all there is to tell."""
     tiles = lambda tokens: -(-tokens // 32)
