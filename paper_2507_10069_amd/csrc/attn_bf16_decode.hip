@@ -1033,8 +1033,8 @@ constexpr int RESERVED_PIECES = 96;
 
 long long table_tiles_of(const BatchView& b) { return ((long long)b.max_pages * b.page_size + BK - 1) / BK; }
 
-// most_allowed: records (own pieces, without units) that the plan may need, unless even the longest pieces need more
-DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_allowed)
+// most_allowed: records (own pieces, without units) that the plan may need, unless even the longest pieces need more; us: the plan's time by the model
+DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_allowed, double* us = nullptr)
 {
     DecodeShape S;
     S.n_pairs = b.num_reqs * b.num_kv_heads;
@@ -1103,6 +1103,7 @@ DecodeShape plan(const BatchView& b, const SharedPrefixView& sv, long long most_
         }
         if (least < 0 || cost < least) least = cost;
     }
+    if (us != nullptr) *us = cost_of(cut_of(best));
     S.tiles_per_piece = best;
     S.pieces_max = (int)pieces(own_tiles, best);
     S.pieces_unit = (int)pieces(unit_tiles, best);
@@ -1124,21 +1125,23 @@ bool has_hints(const BatchView& b, const SharedPrefixView& sv)
 // Units save reading the shared keys again, but a unit's pieces are longer to compute (two groups of rows), its rows have more records to merge and a
 // small batch with units has no folded merge.  Where all there is to read, shared keys once, fits the L2s (8 of 4 MiB), the members after the first find it
 // there, and every context by itself is mostly quicker, unless that reads shared keys too often or cuts pieces for contexts that are not there: it is planned with nothing
-// known but the two bounds, every context as long as the longest could be, so what bounds both is the amount that this would be.  Up to 64 MiB of it alone takes
-// .53 to 1.06 of the time with units, K and V in the caches or not (144 batches of 2 to 44 contexts, 1 to 16 query heads on 1 to 8 KV heads: median .75; 3 of 2432 shared
-// tokens in one unit, 28 / 4 heads, 10.5 and 7.7 us, 8 of 1856 in two 11.2 and 7.7).  Up to 88 it is .64 to 1.02 from three query heads per KV head on and up to 1.23 with one
-// or two, whose units are one group of rows; up to 140 .52 to 1.51.  Far above: two contexts of 6016 shared tokens beside 40 of 100, 28 / 4 heads, 504 MiB, 11.6 and 27.3 us,
-// 32 of 2048 shared on 8 / 8 heads, 264 MiB, 12.7 and 18.7.  Only where the caller says how much there is and how long the longest parts are.
-constexpr long long ALONE_BYTES = 26ll << 20, ALONE_READ_BYTES = 88ll << 20, ALONE_READ_FEW_BYTES = 64ll << 20;
-constexpr int ALONE_FEW_HEADS = 2;
-bool better_alone(const BatchView& b, const SharedPrefixView& sv)
+// known but the two bounds, every context as long as the longest could be, and taken where even that amount is done in less time than the plan of the units.
+//   ALONE           from the launch to the end, with the folded merge
+//   REREAD          a tile of one KV head out of the caches, by the whole chip; FEW with one or two query heads per KV head, whose units are one group of
+//                   rows and quicker than the model has them
+// 380 batches of 2 to 65 contexts, 1 to 16 query heads on 1 to 8 KV heads, groups beside private contexts and alone, up to 400 MiB of that amount, both ways, K and V in the
+// caches and not: .83 of the time with units in the mean (always one by one .83, the better of both .82), 1.09 at most (1.80).  One by one and units: 3 of 2432 shared tokens, 28 / 4
+// heads, 7.7 and 10.5 us, 8 of 1856 in two 7.7 and 11.2; two of 6016 beside 40 of 100 27.3 and 11.6, 32 of 2048 on 8 / 8 heads 18.7 and 12.7.  190 others, with which nothing was
+// fitted: .83, 1.07 at most.  By a line on the amount (88 MiB, 64 with one or two heads) .86 and 1.09.  Only where the caller says how much there is and how long the longest parts are.
+constexpr long long ALONE_BYTES = 26ll << 20;
+constexpr double ALONE_US = 7.0, REREAD_US = 0.0010, REREAD_FEW_US = 0.0013;
+constexpr int REREAD_FEW_HEADS = 2;
+// us_of_units: of the plan with the units
+bool better_alone(const BatchView& b, const SharedPrefixView& sv, double us_of_units)
 {
-    constexpr long long TILE_BYTES = BK * D * 4;
-    const long long read = ((long long)sv.max_own_tiles + sv.max_unit_tiles) * TILE_BYTES;           // of one context and KV head, at most
-    const long long most = b.num_q_heads / b.num_kv_heads <= ALONE_FEW_HEADS ? ALONE_READ_FEW_BYTES : ALONE_READ_BYTES;
-    return sv.planned_tiles > 0 && sv.max_own_tiles > 0 && sv.max_unit_tiles > 0 &&
-           (long long)sv.planned_tiles * b.num_kv_heads * TILE_BYTES <= ALONE_BYTES &&
-           read <= most / std::max(1ll, (long long)b.num_reqs * b.num_kv_heads);
+    if (sv.planned_tiles <= 0 || sv.max_own_tiles <= 0 || sv.max_unit_tiles <= 0 || (long long)sv.planned_tiles * b.num_kv_heads * (BK * D * 4) > ALONE_BYTES) return false;
+    const double most = ((double)sv.max_own_tiles + sv.max_unit_tiles) * b.num_reqs * b.num_kv_heads;
+    return ALONE_US + most * (b.num_q_heads / b.num_kv_heads <= REREAD_FEW_HEADS ? REREAD_FEW_US : REREAD_US) < us_of_units;
 }
 
 // pieces of a context that the workspace of the batch without units and hints has room for at least
@@ -1152,10 +1155,11 @@ long long pieces_reserved(const BatchView& b)
 
 DecodeShape attn_bf16_decode_shape(const BatchView& b, const SharedPrefixView& sv, size_t* bytes)
 {
-    const DecodeShape S = plan(b, sv, LLONG_MAX);
+    double us = 0;
+    const DecodeShape S = plan(b, sv, LLONG_MAX, &us);
     if (sv.num_units > 0) {
         *bytes = attn_bf16_decode_workspace_bytes(S);
-        if (!better_alone(b, sv)) return S;
+        if (!better_alone(b, sv, us)) return S;
         // contexts up to the longest own part behind the longest shared one, within the records that the units would take
         SharedPrefixView alone = {};
         alone.max_own_tiles = (int32_t)std::min<long long>(INT32_MAX, (long long)sv.max_own_tiles + sv.max_unit_tiles);

@@ -331,7 +331,8 @@ def test_decode_plan_keeps_units_that_save_reading(H, Hkv, units, private):
 
 
 @pytest.mark.parametrize("H,Hkv,units,private", [(28, 4, [(3, 2432, 100)], []), (28, 4, [(4, 1856, 100)] * 2, []), (32, 8, [(5, 1856, 60)] * 2, []), (32, 8, [(4, 1024, 60)], [(1, 90)]),
-                                                 (2, 2, [(16, 1536, 100), (3, 704, 100)], [(1, 100)])])
+                                                 (2, 2, [(16, 1536, 100), (3, 704, 100)], [(1, 100)]), (28, 4, [(3, 2816, 100), (4, 96, 100), (2, 1216, 100), (3, 672, 100)], [(4, 500)]),
+                                                 (32, 8, [(8, 992, 60)], [(8, 500)])])
 def test_decode_plan_leaves_units_aside_where_there_is_little_to_read(H, Hkv, units, private):
     S = _plan_of_units(H, Hkv, units, private)
     assert S.n_unit_pairs == 0 and S.pieces_unit <= 1
